@@ -131,8 +131,6 @@ k_densify(const uint16_t* __restrict__ feat, const uint32_t* __restrict__ offs, 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int BM = 128, BN = 128, BK = 32, LDK = BK + 8;   // LDS rows padded by 16 bytes
-
 struct GemmEpi {
   const float* bias;     // [N] or null
   int relu;              // 1: max(x, 0)
@@ -144,206 +142,177 @@ struct GemmEpi {
   int ldcb;
 };
 
-template <int TA, int TB>
+// One operand's share of a k-tile, T rows (m or n) by BK k's, staged by 128
+// threads: 8 chunks of 8 values each.  TR = 0, the matrix is [row][k]: a chunk
+// is 8 k's of one row and goes to LDS as it is.  TR = 1, the matrix is
+// [k][row]: a thread holds 8 k's by 8 rows, transposed in registers (pairs of
+// values, one byte permute each) on the way to LDS, so both layouts use 16-byte
+// global loads and 16-byte LDS stores.  Addresses are clamped into the matrix
+// (no branch around a load); k's past K are zeroed on the way to LDS, rows past
+// the edge only reach outputs that are not stored.  LDS rows are padded by 16
+// bytes: an odd number of 16-byte units, so neither the stores nor the
+// fragments' loads meet in a bank.
+template <int TR, int T, int BK>
+struct Stage {
+  static constexpr int KC = BK / 8;
+  static_assert(T * BK == 128 * 64, "128 threads x 8 chunks of 8");
+  __device__ static __forceinline__ void load(const __bf16* __restrict__ P, int ld, int row0, int rows, int K,
+                                              int k0, int t, bf16x8 (&r)[8]) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if constexpr (TR == 0) {
+        const int c = t + 128 * i, row = min(row0 + c / KC, rows - 1), k = k0 + (c % KC) * 8;
+        r[i] = *reinterpret_cast<const bf16x8*>(P + (size_t)row * ld + (k < K ? k : 0));
+      } else {
+        const int k = k0 + (t % KC) * 8 + i, row = min(row0 + (t / KC) * 8, rows - 8);
+        r[i] = *reinterpret_cast<const bf16x8*>(P + (size_t)(k < K ? k : 0) * ld + row);
+      }
+    }
+  }
+  __device__ static __forceinline__ void store(__bf16 (*L)[BK + 8], int K, int k0, int t, bf16x8 (&r)[8]) {
+    bf16x8 z;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) z[i] = (__bf16)0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if constexpr (TR == 0) {
+        const int c = t + 128 * i, kk = (c % KC) * 8;
+        *reinterpret_cast<bf16x8*>(&L[c / KC][kk]) = k0 + kk < K ? r[i] : z;
+      } else {
+        if (k0 + (t % KC) * 8 + i >= K) r[i] = z;
+      }
+    }
+    if constexpr (TR == 1) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        bf16x8 v;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = r[i][j];
+        *reinterpret_cast<bf16x8*>(&L[(t / KC) * 8 + j][(t % KC) * 8]) = v;
+      }
+    }
+  }
+};
+
+// One T x T tile of C per block, 4 waves, each a quarter as products of 32 x 32
+// on v_mfma_f32_32x32x16_bf16; k in rising steps of 16 into one accumulator, so
+// every tile size gives the same bits.  Two k-tiles of global loads are in
+// flight in registers while the MFMAs work on a third in LDS (two buffers, one
+// barrier a k-tile): a 1,024-row batch has few blocks a CU, so the loads'
+// latency is what has to be covered.  Waves 0 and 1 stage A, 2 and 3 stage B.
+// Bound by the LDS reads and the barrier of a k-tile.  Against one 128 x 128 x 64
+// tile per block with one k-tile of loads ahead (forward) and 128 x 128 x 32
+// with the transpose as 2-byte LDS stores (weight gradients): 1024 x 1024 x 4096
+// forward 25.6 us (was 54), 4096 x 1024 x 1024 gradient 27.8 us (was 82),
+// 1024 x 256 x 1024 gradient 12.3 us (was 77).
+template <int TA, int TB, int T, int BK>
 __global__ void __launch_bounds__(256)
-k_gemm_bf16(int M, int N, int K, const __bf16* __restrict__ A, int lda, const __bf16* __restrict__ B,
-            int ldb, GemmEpi ep) {
-  __shared__ __bf16 As[BM][LDK];
-  __shared__ __bf16 Bs[BN][LDK];
+k_gemm(int M, int N, int K, const __bf16* __restrict__ A, int lda, const __bf16* __restrict__ B, int ldb,
+       GemmEpi ep) {
+  __shared__ __bf16 As[2][T][BK + 8];
+  __shared__ __bf16 Bs[2][T][BK + 8];
+  constexpr int F = T / 64;                       // 32 x 32 products per wave and side
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int wm = wv >> 1, wn = wv & 1;            // 2 x 2 waves, 64 x 64 each
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  f32x16 acc[2][2];
+  const int wm = wv >> 1, wn = wv & 1, t = tid & 127;
+  const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
+  using SA = Stage<TA, T, BK>;
+  using SB = Stage<1 - TB, T, BK>;
+  f32x16 acc[F][F];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < F; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < F; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  for (int k0 = 0; k0 < K; k0 += BK) {
-    // ---- stage A tile as As[m][k]
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const int chunk = tid + 256 * c;            // 512 chunks of 8 elements
-      if (TA == 0) {
-        const int m = chunk >> 2, kk = (chunk & 3) * 8;
-        const int gm = m0 + m, gk = k0 + kk;
-        bf16x8 v;
-        if (gm < M && gk < K) v = *reinterpret_cast<const bf16x8*>(A + (size_t)gm * lda + gk);
-        else
-#pragma unroll
-          for (int i = 0; i < 8; ++i) v[i] = (__bf16)0.f;
-        *reinterpret_cast<bf16x8*>(&As[m][kk]) = v;
-      } else {
-        const int kk = chunk >> 4, m = (chunk & 15) * 8;
-        const int gm = m0 + m, gk = k0 + kk;
-        bf16x8 v;
-        if (gm < M && gk < K) v = *reinterpret_cast<const bf16x8*>(A + (size_t)gk * lda + gm);
-        else
-#pragma unroll
-          for (int i = 0; i < 8; ++i) v[i] = (__bf16)0.f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) As[m + i][kk] = v[i];
-      }
-    }
-    // ---- stage B tile as Bs[n][k]
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const int chunk = tid + 256 * c;
-      if (TB == 1) {
-        const int n = chunk >> 2, kk = (chunk & 3) * 8;
-        const int gn = n0 + n, gk = k0 + kk;
-        bf16x8 v;
-        if (gn < N && gk < K) v = *reinterpret_cast<const bf16x8*>(B + (size_t)gn * ldb + gk);
-        else
-#pragma unroll
-          for (int i = 0; i < 8; ++i) v[i] = (__bf16)0.f;
-        *reinterpret_cast<bf16x8*>(&Bs[n][kk]) = v;
-      } else {
-        const int kk = chunk >> 4, n = (chunk & 15) * 8;
-        const int gn = n0 + n, gk = k0 + kk;
-        bf16x8 v;
-        if (gn < N && gk < K) v = *reinterpret_cast<const bf16x8*>(B + (size_t)gk * ldb + gn);
-        else
-#pragma unroll
-          for (int i = 0; i < 8; ++i) v[i] = (__bf16)0.f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) Bs[n + i][kk] = v[i];
-      }
-    }
-    __syncthreads();
-    // ---- 2 x 2 tiles of 32 x 32, two k-steps of 16
+  auto load = [&](int k0, bf16x8 (&r)[8]) {
+    if (tid < 128) SA::load(A, lda, m0, M, K, k0, t, r);
+    else SB::load(B, ldb, n0, N, K, k0, t, r);
+  };
+  auto store = [&](int buf, int k0, bf16x8 (&r)[8]) {
+    if (tid < 128) SA::store(As[buf], K, k0, t, r);
+    else SB::store(Bs[buf], K, k0, t, r);
+  };
+  auto multiply = [&](int buf) {
 #pragma unroll
     for (int ks = 0; ks < BK; ks += 16) {
-      bf16x8 a[2], b[2];
+      bf16x8 a[F], b[F];
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-        a[i] = *reinterpret_cast<const bf16x8*>(&As[wm * 64 + i * 32 + (lane & 31)][ks + 8 * (lane >> 5)]);
+      for (int i = 0; i < F; ++i)
+        a[i] = *reinterpret_cast<const bf16x8*>(&As[buf][wm * (T / 2) + i * 32 + (lane & 31)][ks + 8 * (lane >> 5)]);
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-        b[j] = *reinterpret_cast<const bf16x8*>(&Bs[wn * 64 + j * 32 + (lane & 31)][ks + 8 * (lane >> 5)]);
+      for (int j = 0; j < F; ++j)
+        b[j] = *reinterpret_cast<const bf16x8*>(&Bs[buf][wn * (T / 2) + j * 32 + (lane & 31)][ks + 8 * (lane >> 5)]);
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < F; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < F; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
     }
+  };
+  bf16x8 r0[8], r1[8];
+  load(0, r0);
+  load(BK, r1);
+  store(0, 0, r0);
+  __syncthreads();
+  // two k-tiles a turn, the second one all zeros where their number is odd;
+  // the scheduling barriers keep the loads above the products
+  for (int k0 = 0; k0 < K; k0 += 2 * BK) {
+    load(k0 + 2 * BK, r0);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(0);
+    store(1, k0 + BK, r1);
+    __syncthreads();
+    load(k0 + 3 * BK, r1);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(1);
+    store(0, k0 + 2 * BK, r0);
     __syncthreads();
   }
-  // ---- epilogue: register r of lane l holds row 8(r/4) + 4(l/32) + r%4, column l%32
+  // epilogue: register r of lane l holds row 8(r/4) + 4(l/32) + r%4, column l%32;
+  // the bias and the mask values are loaded before the first store
+  float bias[F];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int j = 0; j < F; ++j)
+    bias[j] = ep.bias ? ep.bias[min(n0 + wn * (T / 2) + j * 32 + (lane & 31), N - 1)] : 0.f;
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+  for (int i = 0; i < F; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int gm = m0 + wm * 64 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const int gn = n0 + wn * 64 + j * 32 + (lane & 31);
-        if (gm >= M || gn >= N) continue;
-        float v = acc[i][j][r];
-        if (ep.bias) v += ep.bias[gn];
-        if (ep.relu) v = fmaxf(v, 0.f);
-        if (ep.mask && !((float)ep.mask[(size_t)gm * ep.ldm + gn] > 0.f)) v = 0.f;
-        if (ep.c32) ep.c32[(size_t)gm * ep.ldc + gn] = v;
-        if (ep.cbf) ep.cbf[(size_t)gm * ep.ldcb + gn] = (__bf16)v;
+    for (int j = 0; j < F; ++j) {
+      const int gm0 = m0 + wm * (T / 2) + i * 32 + 4 * (lane >> 5), gn = n0 + wn * (T / 2) + j * 32 + (lane & 31);
+      __bf16 mk[16];
+      if (ep.mask) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          mk[r] = ep.mask[(size_t)min(gm0 + 8 * (r >> 2) + (r & 3), M - 1) * ep.ldm + min(gn, N - 1)];
       }
+      if (gn < N) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int gm = gm0 + 8 * (r >> 2) + (r & 3);
+          float v = acc[i][j][r];
+          if (ep.bias) v += bias[j];
+          if (ep.relu) v = fmaxf(v, 0.f);
+          if (ep.mask && !((float)mk[r] > 0.f)) v = 0.f;
+          if (gm < M && ep.c32) ep.c32[(size_t)gm * ep.ldc + gn] = v;
+          if (gm < M && ep.cbf) ep.cbf[(size_t)gm * ep.ldcb + gn] = (__bf16)v;
+        }
+      }
+    }
 }
 
-// ---------------------------------------------------------------------------
-// The same product for A [M][K] and B given as [N][K] (both operands
-// contiguous along K), the forward layers' layout: every tile is staged with
-// 16-byte loads and stores.  Tiles of 128 x 128 x 64; while the MFMAs work
-// on the k-tile in LDS, the next k-tile's global loads are already in flight
-// into registers.  4 waves, each a 64 x 64 quarter of the tile as 2 x 2
-// products of 32 x 32 on v_mfma_f32_32x32x16_bf16.
-// ---------------------------------------------------------------------------
-constexpr int NBK = 64, NLDK = NBK + 8;   // LDS rows padded by 16 bytes
-__global__ void __launch_bounds__(256)
-k_gemm_nt(int M, int N, int K, const __bf16* __restrict__ A, int lda, const __bf16* __restrict__ B, int ldb,
-          GemmEpi ep) {
-  __shared__ __bf16 As[BM][NLDK];
-  __shared__ __bf16 Bs[BN][NLDK];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int wm = wv >> 1, wn = wv & 1;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  // a tile row holds 64 k = 8 chunks of 8; thread t stages chunks t + 256 c
-  bf16x8 ra[4], rb[4];
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int chunk = tid + 256 * c, row = chunk >> 3, kk = (chunk & 7) * 8;
-      const int gk = k0 + kk;
-      const int gm = m0 + row, gn = n0 + row;
-      if (gm < M && gk < K) ra[c] = *reinterpret_cast<const bf16x8*>(A + (size_t)gm * lda + gk);
-      else
-#pragma unroll
-        for (int i = 0; i < 8; ++i) ra[c][i] = (__bf16)0.f;
-      if (gn < N && gk < K) rb[c] = *reinterpret_cast<const bf16x8*>(B + (size_t)gn * ldb + gk);
-      else
-#pragma unroll
-        for (int i = 0; i < 8; ++i) rb[c][i] = (__bf16)0.f;
-    }
-  };
-  auto stage = [&]() {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int chunk = tid + 256 * c, row = chunk >> 3, kk = (chunk & 7) * 8;
-      *reinterpret_cast<bf16x8*>(&As[row][kk]) = ra[c];
-      *reinterpret_cast<bf16x8*>(&Bs[row][kk]) = rb[c];
-    }
-  };
-  load(0);
-  stage();
-  __syncthreads();
-  for (int k0 = 0; k0 < K; k0 += NBK) {
-    const bool more = k0 + NBK < K;
-    if (more) load(k0 + NBK);                     // in flight during the MFMAs below
-#pragma unroll
-    for (int ks = 0; ks < NBK; ks += 16) {
-      bf16x8 a[2], b[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-        a[i] = *reinterpret_cast<const bf16x8*>(&As[wm * 64 + i * 32 + (lane & 31)][ks + 8 * (lane >> 5)]);
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        b[j] = *reinterpret_cast<const bf16x8*>(&Bs[wn * 64 + j * 32 + (lane & 31)][ks + 8 * (lane >> 5)]);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    __syncthreads();
-    if (more) {
-      stage();
-      __syncthreads();
-    }
-  }
-  // epilogue: register r of lane l holds row 8(r/4) + 4(l/32) + r%4, column l%32
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int gm = m0 + wm * 64 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const int gn = n0 + wn * 64 + j * 32 + (lane & 31);
-        if (gm >= M || gn >= N) continue;
-        float v = acc[i][j][r];
-        if (ep.bias) v += ep.bias[gn];
-        if (ep.relu) v = fmaxf(v, 0.f);
-        if (ep.mask && !((float)ep.mask[(size_t)gm * ep.ldm + gn] > 0.f)) v = 0.f;
-        if (ep.c32) ep.c32[(size_t)gm * ep.ldc + gn] = v;
-        if (ep.cbf) ep.cbf[(size_t)gm * ep.ldcb + gn] = (__bf16)v;
-      }
+constexpr size_t kGemmFill = 256;   // blocks: one a CU
+
+// The tile: 128 x 128 (a fragment feeds two MFMAs, half the LDS reads a flop)
+// where those tiles give every CU a block, 64 x 64 below that.
+template <int TA, int TB>
+static void launch_gemm(int M, int N, int K, const __bf16* a, int lda, const __bf16* b, int ldb, const GemmEpi& ep,
+                        hipStream_t st) {
+  auto tiles = [&](int t) { return dim3((N + t - 1) / t, (M + t - 1) / t); };
+  const dim3 big = tiles(128);
+  if ((size_t)big.x * big.y >= kGemmFill)
+    hipLaunchKernelGGL((k_gemm<TA, TB, 128, 64>), big, dim3(256), 0, st, M, N, K, a, lda, b, ldb, ep);
+  else
+    hipLaunchKernelGGL((k_gemm<TA, TB, 64, 128>), tiles(64), dim3(256), 0, st, M, N, K, a, lda, b, ldb, ep);
 }
 
 // dst[c][r] = src[r][c] for a rows x cols bf16 matrix (32 x 32 tiles through LDS)
@@ -604,16 +573,12 @@ extern "C" hth_status hth_gemm_bf16(int trans_a, int trans_b, int M, int N, int 
   if (trans_a == 1 && trans_b == 1) return fail(HTH_E_UNSUPPORTED, "A^T B^T is not provided");
   GemmEpi ep{bias, relu, reinterpret_cast<const __bf16*>(mask), ldm, c32, ldc,
              reinterpret_cast<__bf16*>(cbf), ldcb};
-  const dim3 grid((N + BN - 1) / BN, (M + BM - 1) / BM), block(256);
   hipStream_t st = static_cast<hipStream_t>(stream);
   const __bf16* a = reinterpret_cast<const __bf16*>(A);
   const __bf16* b = reinterpret_cast<const __bf16*>(B);
-  if (trans_a == 0 && trans_b == 0)
-    hipLaunchKernelGGL((k_gemm_bf16<0, 0>), grid, block, 0, st, M, N, K, a, lda, b, ldb, ep);
-  else if (trans_a == 0)
-    hipLaunchKernelGGL(k_gemm_nt, grid, block, 0, st, M, N, K, a, lda, b, ldb, ep);
-  else
-    hipLaunchKernelGGL((k_gemm_bf16<1, 0>), grid, block, 0, st, M, N, K, a, lda, b, ldb, ep);
+  if (trans_a == 0 && trans_b == 0) launch_gemm<0, 0>(M, N, K, a, lda, b, ldb, ep, st);
+  else if (trans_a == 0) launch_gemm<0, 1>(M, N, K, a, lda, b, ldb, ep, st);
+  else launch_gemm<1, 0>(M, N, K, a, lda, b, ldb, ep, st);
   HTH_HIP(hipGetLastError());
   return HTH_OK;
 }
