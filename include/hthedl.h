@@ -579,6 +579,25 @@ hth_status hth_head_forward(const uint16_t* h, int Bn, int Kd, const float* w, c
 hth_status hth_head_score(const float* z, int Bn, float n_pos, float n_neg, const uint32_t* base, int kind,
                           float* score, void* stream);
 
+/* Screening scores of hypotheses row0 .. row0 + n_rows - 1 straight from their
+ * features: what hth_densify (d_parent_index NULL) or hth_densify_delta, the
+ * forward products of an MLP 4096 -> 1024 -> 256 -> 2 (ReLU, activations in
+ * bf16) and hth_head_score give, without the dense rows.  w1: bf16
+ * [4096][1024]; w2t: bf16 [256][1024], the transpose of W2; b1, b2, w3 [256][2]
+ * and b3 fp32.  base (uint32 [n_rows][2]) and score (fp32 [n_rows]) start at
+ * row0's entry; kind and base as for hth_head_score.  scratch: at least
+ * HTH_SCORE_SCRATCH_BYTES of device memory (W2 in the kernel's order, written
+ * by each call).  Asynchronous on `stream`.  Errors: HTH_E_INVALID (NULL, w1,
+ * w2t or scratch not 16-byte aligned, kind 1 without base), HTH_E_RANGE (kind,
+ * parent_context), HTH_E_NOMEM (scratch). */
+#define HTH_SCORE_SCRATCH_BYTES (512u << 10)
+hth_status hth_score_rows(const uint16_t* d_feat, const uint32_t* d_hyp_node_offsets, uint32_t row0,
+                          uint32_t n_rows, const uint16_t* d_parent_feat, const uint32_t* d_parent_offsets,
+                          const uint32_t* d_parent_index, uint32_t parent_context, const uint16_t* w1,
+                          const float* b1, const uint16_t* w2t, const float* b2, const float* w3,
+                          const float* b3, float n_pos, float n_neg, const uint32_t* base, int kind,
+                          float* score, void* scratch, size_t scratch_bytes, void* stream);
+
 /* Backward of the output layer: dw[k][o] = sum_b h[b][k] dz[b][o];
  * dh[b][k] = (dz[b] . w[k]) where h[b][k] > 0, else 0 (ReLU of the layer below). */
 hth_status hth_head_backward(const uint16_t* h, int Bn, int Kd, const float* w, const float* dz,
@@ -594,6 +613,32 @@ hth_status hth_colsum(const void* d, int is_bf16, int M, int N, float* out, void
 hth_status hth_adamw(float* p, const float* g, float* m, float* v, uint16_t* pbf, size_t n, float lr,
                      float beta1, float beta2, float eps, float wd, int step, void* stream);
 
+/* One training step of the screener's MLP (d_in -> d_h1 -> d_h2 -> 2, ReLU) in
+ * one call: the forward products, the output layer with its loss, every
+ * gradient and the AdamW updates, as the calls above compute them one by one.
+ * Tensors w1 [d_in][d_h1], b1, w2 [d_h1][d_h2], b2, w3 [d_h2][2], b3 in this
+ * order: fp32 masters p, gradients g (written), moments m and v (updated).
+ * w1b, w2b are the bf16 weights and w1t, w2t their transposes (read, then
+ * rewritten after the update).  h1, h2, dh1, dh2 (bf16 [n][width]), z and dz
+ * (fp32 [n][2]) are written.  x: bf16 [n][d_in]; y: fp32 [n][2] targets, or
+ * NULL: dz is read as the caller left it and no loss is added.  loss: NULL or
+ * the summed loss is added to *loss; dz is scaled by 1 / (2 n).  wd applies to
+ * the weights, not the biases.  Errors: HTH_E_INVALID (NULL or misaligned:
+ * 16 bytes), HTH_E_RANGE (n or step not positive, loss_kind),
+ * HTH_E_UNSUPPORTED (widths not multiples of 64, d_h2 above 256). */
+typedef struct {
+  int n, d_in, d_h1, d_h2;
+  const uint16_t* x;
+  const float* y;
+  float *p[6], *g[6], *m[6], *v[6];
+  uint16_t *w1b, *w2b, *w1t, *w2t;
+  uint16_t *h1, *h2, *dh1, *dh2;
+  float *z, *dz, *loss;
+  int loss_kind, step;
+  float lr, beta1, beta2, eps, wd;
+} hth_train;
+hth_status hth_train_step(const hth_train* t, void* stream);
+
 /* d[i] = bf16(s[i]) (round to nearest even). */
 hth_status hth_to_bf16(const float* s, uint16_t* d, size_t n, void* stream);
 
@@ -605,7 +650,7 @@ hth_status hth_transpose_bf16(const uint16_t* src, int rows, int cols, uint16_t*
 
 /* Indices of the k largest scores (d_idx [k], in no particular order; among
  * equal scores at the threshold, which ones are taken is unspecified; NaN
- * ranks last).  d_work: uint32 [65538].  Synchronous on `stream`. */
+ * ranks last).  d_work: uint32 [65538].  Asynchronous on `stream`. */
 hth_status hth_topk(const float* d_scores, uint32_t n, uint32_t k, uint32_t* d_idx, uint32_t* d_work,
                     void* stream);
 

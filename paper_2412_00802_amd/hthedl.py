@@ -47,7 +47,8 @@ EXPORTED = ["hth_kb_derived_bytes", "hth_kb_create", "hth_kb_set_examples", "hth
             "hth_kb_set_numeric", "hth_string_derived_bytes", "hth_kb_set_strings", "hth_kb_set_patterns",
             "hth_dplan_scratch_bytes", "hth_dplan_create", "hth_dplan_launch", "hth_dplan_destroy",
             "hth_draw_conjuncts", "hth_conjoin", "hth_dplan_stats", "hth_eval_one_noalloc",
-            "hth_cache_create", "hth_eval_batch_cached", "hth_cache_stats", "hth_cache_destroy"]
+            "hth_cache_create", "hth_eval_batch_cached", "hth_cache_stats", "hth_cache_destroy", "hth_train_step",
+            "hth_score_rows"]
 
 
 class HthError(RuntimeError):
@@ -85,6 +86,17 @@ class CacheInfo(ctypes.Structure):
 class DplanInfo(ctypes.Structure):
     _fields_ = [(f, ctypes.c_uint32) for f in ("levels", "role_nodes", "shared_passes", "thresholds",
                                                  "materialised", "rows")]
+
+
+class Train(ctypes.Structure):
+    """hth_train: the buffers and settings of one training step."""
+    _fields_ = ([(f, ctypes.c_int) for f in ("n", "d_in", "d_h1", "d_h2")] +
+                [("x", ctypes.c_void_p), ("y", ctypes.c_void_p)] +
+                [(f, ctypes.c_void_p * 6) for f in ("p", "g", "m", "v")] +
+                [(f, ctypes.c_void_p) for f in ("w1b", "w2b", "w1t", "w2t", "h1", "h2", "dh1", "dh2", "z", "dz",
+                                                "loss")] +
+                [("loss_kind", ctypes.c_int), ("step", ctypes.c_int)] +
+                [(f, ctypes.c_float) for f in ("lr", "beta1", "beta2", "eps", "wd")])
 
 
 class ProfEntry(ctypes.Structure):
@@ -153,6 +165,8 @@ def lib() -> ctypes.CDLL:
             "hth_colsum": [P, I, I, I, P, P],
             "hth_adamw": [P, P, P, P, P, S, F, F, F, F, F, I, P],
             "hth_to_bf16": [P, P, S, P],
+            "hth_score_rows": [P, P, U32, U32, P, P, P, U32, P, P, P, P, P, P, F, F, P, I, P, P, S, P],
+            "hth_train_step": [ctypes.POINTER(Train), P],
             "hth_transpose_bf16": [P, ctypes.c_int, ctypes.c_int, P, P],
             "hth_topk": [P, U32, U32, P, P, P],
         }
@@ -539,6 +553,23 @@ def hth_adamw(p, g, m, v, pbf, n: int, lr: float, beta1: float, beta2: float, ep
               step: int, stream=None) -> None:
     _check(lib().hth_adamw(_ptr(p), _ptr(g), _ptr(m), _ptr(v), _ptr(pbf), n, lr, beta1, beta2, eps, wd,
                            step, _stream(stream)))
+
+
+# bytes of the scratch of hth_score_rows (HTH_SCORE_SCRATCH_BYTES)
+SCORE_SCRATCH_BYTES = 512 << 10
+
+
+def hth_score_rows(d_feat, d_offsets, row0: int, n_rows: int, d_parent_feat, d_parent_offsets, d_parent_index, w1, b1,
+                   w2t, b2, w3, b3, n_pos: float, n_neg: float, score, scratch, base=None, kind: int = 0,
+                   parent_context: int = 0, stream=None) -> None:
+    _check(lib().hth_score_rows(_ptr(d_feat), _ptr(d_offsets), row0, n_rows, _ptr(d_parent_feat),
+                                _ptr(d_parent_offsets), _ptr(d_parent_index), parent_context, _ptr(w1), _ptr(b1),
+                                _ptr(w2t), _ptr(b2), _ptr(w3), _ptr(b3), n_pos, n_neg, _ptr(base), kind, _ptr(score),
+                                _ptr(scratch), scratch.numel() * scratch.element_size(), _stream(stream)))
+
+
+def hth_train_step(t: Train, stream=None) -> None:
+    _check(lib().hth_train_step(ctypes.byref(t), _stream(stream)))
 
 
 def hth_to_bf16(s, d, n: int, stream=None) -> None:

@@ -92,13 +92,11 @@ def score(scr: Screener, fb: FeatureBatch, n: int, n_pos: int, n_neg: int, out, 
     """Predicted F1 of candidates [0, n); base (device uint32 [n][2]): the
     parents' coverage (kept shares, kind 0, or removed counts, kind 1);
     parents: features relative to the parents."""
-    B = scr.batch
-    for r0 in range(0, n, B):
-        m = min(B, n - r0)
-        fb.densify(r0, m, scr.x, parents, parent_index, context)
-        z = scr.logits(m)
-        hthedl.hth_head_score(z, m, float(n_pos), float(n_neg), out[r0:r0 + m],
-                              base=None if base is None else base[r0:r0 + m], kind=kind)
+    rel = parents is not None
+    hthedl.hth_score_rows(fb.feat, fb.offsets, 0, n, parents.feat if rel else None, parents.offsets if rel else None,
+                          parent_index if rel else None, scr.w1b, scr.p["b1"], scr.w2t, scr.p["b2"], scr.p["w3"],
+                          scr.p["b3"], float(n_pos), float(n_neg), out, scr.score_scratch, base=base, kind=kind,
+                          parent_context=context if rel else 0)
 
 
 def run(kb, eng, pairs: int = 200_000, candidates_beam: int = 4096, refinements: int = 256, epochs: int = 10,

@@ -11,6 +11,7 @@ friends); this module only sequences the calls and owns the device buffers.
 """
 from __future__ import annotations
 
+import ctypes
 from typing import Dict, Optional, Sequence
 
 import numpy as np
@@ -72,6 +73,7 @@ class Screener:
         self.dz = torch.empty((B, D_OUT), dtype=torch.float32, device=self.dev)
         self.dh2 = torch.empty((B, D_H2), dtype=bf, device=self.dev)
         self.dh1 = torch.empty((B, D_H1), dtype=bf, device=self.dev)
+        self.score_scratch = torch.empty(hthedl.SCORE_SCRATCH_BYTES, dtype=torch.uint8, device=self.dev)
         self.loss = torch.zeros(1, dtype=torch.float32, device=self.dev)
 
     def _transpose(self) -> None:
@@ -92,25 +94,17 @@ class Screener:
         """One AdamW step on rows [0, n) of x (default self.x) with targets y
         (device float32 [n][2]).  The summed loss accumulates in self.loss."""
         x = self.x if x is None else x
-        G = hthedl.hth_gemm_bf16
-        self.forward(n, x)
-        hthedl.hth_head_forward(self.h2, n, D_H2, self.p["w3"], self.p["b3"], self.z, y, self.dz,
-                                1.0 / (2 * n), self.loss, loss_kind=self.loss_kind)
-        hthedl.hth_head_backward(self.h2, n, D_H2, self.p["w3"], self.dz, self.g["w3"], self.dh2)
-        hthedl.hth_colsum(self.dz, 0, n, D_OUT, self.g["b3"])
-        G(1, 0, D_H1, D_H2, n, self.h1, D_H1, self.dh2, D_H2, c32=self.g["w2"], ldc=D_H2)
-        hthedl.hth_colsum(self.dh2, 1, n, D_H2, self.g["b2"])
-        G(0, 1, n, D_H1, D_H2, self.dh2, D_H2, self.w2b, D_H2, mask=self.h1, ldm=D_H1, cbf=self.dh1,
-          ldcb=D_H1)
-        hthedl.hth_colsum(self.dh1, 1, n, D_H1, self.g["b1"])
-        G(1, 0, D_IN, D_H1, n, x, D_IN, self.dh1, D_H1, c32=self.g["w1"], ldc=D_H1)
+        names = ("w1", "b1", "w2", "b2", "w3", "b3")
+        t = hthedl.Train(n=n, d_in=D_IN, d_h1=D_H1, d_h2=D_H2, x=x.data_ptr(), y=None if y is None else y.data_ptr(),
+                         loss_kind=self.loss_kind, step=self.step_no + 1, lr=self.lr, beta1=self.b1, beta2=self.b2,
+                         eps=self.eps, wd=self.wd)
+        for f in ("p", "g", "m", "v"):
+            own = getattr(self, f)
+            setattr(t, f, (ctypes.c_void_p * 6)(*(own[k].data_ptr() for k in names)))
+        for f in ("w1b", "w2b", "w1t", "w2t", "h1", "h2", "dh1", "dh2", "z", "dz", "loss"):
+            setattr(t, f, getattr(self, f).data_ptr())
+        hthedl.hth_train_step(t)
         self.step_no += 1
-        for k in ("w1", "b1", "w2", "b2", "w3", "b3"):
-            pbf = self.w1b if k == "w1" else (self.w2b if k == "w2" else None)
-            hthedl.hth_adamw(self.p[k], self.g[k], self.m[k], self.v[k], pbf, self.p[k].numel(),
-                             self.lr, self.b1, self.b2, self.eps, self.wd if k[0] == "w" else 0.0,
-                             self.step_no)
-        self._transpose()
 
     def logits(self, n: int, x=None):
         self.forward(n, x)
