@@ -38,53 +38,12 @@ enum : uint32_t {
 };
 
 constexpr int kScanThreads = 1024;
-constexpr int kScanItems = 4;
-constexpr uint32_t kScanBlock = kScanThreads * kScanItems;
 
 __global__ void k_gather_bases(const int64_t* __restrict__ off, uint32_t R, uint32_t N,
                                uint64_t* __restrict__ base) {
   uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
   if (r < R) base[r] = (uint64_t)off[(size_t)r * (N + 1)];
   if (r == R - 1) base[R] = (uint64_t)off[(size_t)r * (N + 1) + N];
-}
-
-// One thread per (role, subject): check the row, write its relative offset,
-// count its assertions per object into inv_off[r][y + 1].  Rows with more
-// than hmin assertions (heavy rows) only get their offsets checked here; their
-// assertions are checked and counted chunk by chunk by k_validate_heavy.
-__global__ void k_validate_rows(const int64_t* __restrict__ off, const int32_t* __restrict__ tg,
-                                const uint64_t* __restrict__ base, uint32_t N, uint32_t hmin,
-                                uint32_t* __restrict__ fwd_off, uint32_t* __restrict__ inv_cnt,
-                                uint32_t* __restrict__ maxdeg, uint32_t* __restrict__ flags) {
-  uint32_t x = blockIdx.x * blockDim.x + threadIdx.x;
-  uint32_t r = blockIdx.y;
-  if (x >= N) return;
-  const int64_t* o = off + (size_t)r * (N + 1);
-  int64_t o0 = o[x], o1 = o[x + 1];
-  int64_t b0 = (int64_t)base[r], b1 = (int64_t)base[r + 1];
-  uint32_t* fo = fwd_off + (size_t)r * (N + 1);
-  if (o0 < b0 || o1 < o0 || o1 > b1) {
-    atomicOr(flags, F_NONMONO);
-    return;
-  }
-  fo[x] = (uint32_t)(o0 - b0);
-  if (x == N - 1) fo[N] = (uint32_t)(o1 - b0);
-  atomicMax(maxdeg + r, (uint32_t)(o1 - o0));
-  if (o1 - o0 > (int64_t)hmin) return;
-  uint32_t* cnt = inv_cnt + (size_t)r * (N + 1);
-  int32_t prev = -1;
-  uint32_t bad = 0;
-  for (int64_t e = o0; e < o1; ++e) {
-    int32_t t = tg[e];
-    if (t < 0 || (uint32_t)t >= N) {
-      bad |= F_TARGET;
-      continue;
-    }
-    if (t <= prev) bad |= F_ORDER;
-    prev = t;
-    atomicAdd(cnt + t + 1, 1u);
-  }
-  if (bad) atomicOr(flags, bad);
 }
 
 // Members of each row (one block per row): the plan's push/pull choice.
@@ -118,12 +77,6 @@ __global__ void k_fill_u32(uint32_t* __restrict__ p, size_t n, uint32_t v) {
   for (; i < n; i += step) p[i] = v;
 }
 
-__global__ void k_copy_u32(const uint32_t* __restrict__ s, uint32_t* __restrict__ d, size_t n) {
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  size_t step = (size_t)gridDim.x * blockDim.x;
-  for (; i < n; i += step) d[i] = s[i];
-}
-
 // Inclusive wave scan of one value per lane.
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
   const int lane = threadIdx.x & 63;
@@ -155,44 +108,7 @@ __device__ uint32_t block_excl_scan(uint32_t v, uint32_t* total) {
   return r;
 }
 
-// Phase 1: per-block sums (and maxima) of a[r][1 .. N] (the per-object counts).
-__global__ void __launch_bounds__(kScanThreads)
-k_scan_sums(const uint32_t* __restrict__ a, uint32_t N, uint32_t nb, uint32_t* __restrict__ bsum,
-            uint32_t* __restrict__ maxdeg) {
-  uint32_t r = blockIdx.y;
-  const uint32_t* p = a + (size_t)r * (N + 1) + 1;
-  uint32_t start = blockIdx.x * kScanBlock;
-  uint32_t s = 0, m = 0;
-  for (int k = 0; k < kScanItems; ++k) {
-    uint32_t i = start + k * kScanThreads + threadIdx.x;
-    if (i < N) {
-      uint32_t v = p[i];
-      s += v;
-      m = max(m, v);
-    }
-  }
-  __shared__ uint32_t ss[kScanThreads / 64], mm[kScanThreads / 64];
-  for (int d = 32; d >= 1; d >>= 1) {
-    s += __shfl_xor(s, d, 64);
-    m = max(m, __shfl_xor(m, d, 64));
-  }
-  if ((threadIdx.x & 63) == 0) {
-    ss[threadIdx.x >> 6] = s;
-    mm[threadIdx.x >> 6] = m;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t ts = 0, tm = 0;
-    for (int i = 0; i < kScanThreads / 64; ++i) {
-      ts += ss[i];
-      tm = max(tm, mm[i]);
-    }
-    bsum[(size_t)r * nb + blockIdx.x] = ts;
-    atomicMax(maxdeg + r, tm);
-  }
-}
-
-// Phase 2: exclusive scan of the block sums of each role (one block per role).
+// In place exclusive scan of each row of p[gridDim.x][nb] (one block per row).
 __global__ void __launch_bounds__(kScanThreads)
 k_scan_block_sums(uint32_t* __restrict__ bsum, uint32_t nb) {
   uint32_t* p = bsum + (size_t)blockIdx.x * nb;
@@ -212,86 +128,342 @@ k_scan_block_sums(uint32_t* __restrict__ bsum, uint32_t nb) {
   }
 }
 
-// Phase 3: inclusive scan inside each block plus its block offset.
-__global__ void __launch_bounds__(kScanThreads)
-k_scan_apply(uint32_t* __restrict__ a, uint32_t N, uint32_t nb, const uint32_t* __restrict__ bsum) {
-  uint32_t r = blockIdx.y;
-  uint32_t* p = a + (size_t)r * (N + 1) + 1;
-  uint32_t start = blockIdx.x * kScanBlock + threadIdx.x * kScanItems;
-  uint32_t v[kScanItems];
-  uint32_t s = 0;
-  for (int k = 0; k < kScanItems; ++k) {
-    uint32_t i = start + k;
-    v[k] = i < N ? p[i] : 0;
-    s += v[k];
-  }
-  __shared__ uint32_t tot;
-  uint32_t ex = block_excl_scan(s, &tot) + bsum[(size_t)r * nb + blockIdx.x];
-  for (int k = 0; k < kScanItems; ++k) {
-    uint32_t i = start + k;
-    ex += v[k];
-    if (i < N) p[i] = ex;
+// ---------------------------------------------------------------------------
+// building the derived layouts
+//
+// The inverse of a role is its exact transpose: a counting sort of the
+// assertions by object.  Counting and placing them with one global atomic per
+// assertion (two passes over random 4-byte addresses) took 16 of the 18 ms of
+// a load of 133M assertions.  Here the objects are cut into buckets of
+// 2^shift, and no pass touches random memory beyond an LDS area:
+//   k_load_rows    offsets checked, 32-bit offsets, subjects' bit rows;
+//   k_load_check   targets checked, assertions counted per bucket (LDS);
+//   k_load_part    each assertion's subject found from the offsets, the pairs
+//                  (subject, object) written bucket by bucket, in runs;
+//   k_load_bucket  one block per bucket: counts, scan and placement of its
+//                  pairs in LDS, the inverse rows written as one run.
+// The pairs lie in the object-rank area (8 bytes per assertion), which is
+// filled later.  Bound by HBM: about 30 bytes per assertion over the passes.
+// 133M assertions of 16 roles over 1M individuals: rows 99 us, check 197,
+// partition 805, buckets 676; a load 1.9 ms where it was 17.2.
+// An invalid knowledge base sets *flags; every kernel that would index with
+// unchecked data returns when it is set.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kPartEdges = 8192;       // assertions of one chunk
+constexpr int kPartThreads = 512;
+constexpr uint32_t kRowTiles = 8;           // 256-subject tiles of a block of k_load_rows
+constexpr uint32_t kBucketMost = 8192;      // objects whose counters fit a block's LDS
+constexpr uint32_t kBucketStage = 16384;    // inverse targets staged in LDS by one block
+constexpr uint32_t kBucketsMost = 8192;     // buckets a role (LDS counters of k_load_part)
+constexpr uint32_t kWordTile = 2048;        // words of a bit row per block
+constexpr uint64_t kLoadFill = 2048;        // bucket blocks that fill the chip
+
+struct HeavyOut {
+  uint32_t hmin, cap;
+  uint32_t* count;
+  uint32_t* out;        // (direction 2r + dir, subject, degree), any order
+};
+__device__ __forceinline__ void heavy_append(const HeavyOut& H, uint32_t rd, uint32_t x, uint32_t deg) {
+  const uint32_t slot = atomicAdd(H.count, 1u);
+  if (slot < H.cap) {
+    H.out[3 * (size_t)slot] = rd;
+    H.out[3 * (size_t)slot + 1] = x;
+    H.out[3 * (size_t)slot + 2] = deg;
   }
 }
 
-// Scatter: assertion (x, y) of role r becomes (y, x) of r^-.  Row order inside
-// an inverse row follows the atomics and is not fixed; evaluation results do
-// not depend on it.
-// Heavy rows (more than hmin assertions) are scattered by k_scatter_heavy.
-__global__ void k_scatter_inverse(const uint32_t* __restrict__ fwd_off, const int32_t* __restrict__ tg,
-                                  const uint64_t* __restrict__ base, uint32_t N, uint32_t hmin,
-                                  uint32_t* __restrict__ cursor, int32_t* __restrict__ inv_tg) {
-  uint32_t x = blockIdx.x * blockDim.x + threadIdx.x;
-  uint32_t r = blockIdx.y;
-  if (x >= N) return;
-  const uint32_t* fo = fwd_off + (size_t)r * (N + 1);
-  if (fo[x + 1] - fo[x] > hmin) return;
-  const int32_t* t = tg + base[r];
-  int32_t* it = inv_tg + base[r];
-  uint32_t* cur = cursor + (size_t)r * (N + 1);
-  for (uint32_t e = fo[x]; e < fo[x + 1]; ++e) {
-    uint32_t y = (uint32_t)t[e];
-    uint32_t pos = atomicAdd(cur + y, 1u);
-    it[pos] = (int32_t)x;
-  }
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, d, 64));
+  return v;
 }
 
-// The assertions of the forward heavy rows of one role, one block per chunk of
-// kHeavyChunk (tg and fo: the role's targets and relative offsets, inv_cnt and
-// cursor its inverse rows).  Validation: every target in [0, N), strictly
-// increasing inside the row; each assertion counted for its object.
+// One thread per (role, subject): the offsets' check, the 32-bit offset, the
+// subject's bit (the objects of the inverse direction), heavy rows, the
+// role's largest degree.
 __global__ void __launch_bounds__(256)
-k_validate_heavy(const int32_t* __restrict__ tg, const uint32_t* __restrict__ fo, const uint32_t* __restrict__ rows,
-                 const HeavyChunk* __restrict__ chunks, uint32_t N, uint32_t* __restrict__ inv_cnt,
-                 uint32_t* __restrict__ flags) {
-  const HeavyChunk c = chunks[blockIdx.x];
-  const uint32_t x = rows[c.hrow];
-  const uint32_t end = fo[x + 1];
-  const uint32_t e0 = fo[x] + c.k * kHeavyChunk, e1 = min(end, e0 + kHeavyChunk);
-  uint32_t bad = 0;
-  for (uint32_t e = e0 + threadIdx.x; e < e1; e += 256) {
-    const int32_t t = tg[e];
-    if (t < 0 || (uint32_t)t >= N) {
-      bad |= F_TARGET;
-      continue;
+k_load_rows(const int64_t* __restrict__ off, const uint64_t* __restrict__ base, uint32_t N, uint32_t W,
+            uint32_t* __restrict__ fwd_off, uint64_t* __restrict__ mask, uint32_t* __restrict__ maxdeg, HeavyOut H,
+            uint32_t* __restrict__ flags) {
+  __shared__ uint32_t s_most[4];
+  const uint32_t r = blockIdx.y, lane = threadIdx.x & 63;
+  const int64_t* o = off + (size_t)r * (N + 1);
+  const int64_t b0 = (int64_t)base[r], b1 = (int64_t)base[r + 1];
+  uint32_t* fo = fwd_off + (size_t)r * (N + 1);
+  uint32_t most = 0;
+  bool any_bad = false;
+#pragma unroll 4
+  for (uint32_t i = 0; i < kRowTiles; ++i) {
+    const uint64_t x = ((uint64_t)blockIdx.x * kRowTiles + i) * 256 + threadIdx.x;
+    uint32_t deg = 0;
+    if (x < N) {
+      const int64_t o0 = o[x], o1 = o[x + 1];
+      if (o0 < b0 || o1 < o0 || o1 > b1) {
+        any_bad = true;
+      } else {
+        fo[x] = (uint32_t)(o0 - b0);
+        if (x == N - 1) fo[N] = (uint32_t)(o1 - b0);
+        deg = (uint32_t)(o1 - o0);
+        if (deg > H.hmin) heavy_append(H, 2 * r, (uint32_t)x, deg);
+      }
     }
-    if (e + 1 < end && tg[e + 1] <= t) bad |= F_ORDER;
-    atomicAdd(inv_cnt + t + 1, 1u);
+    most = max(most, deg);
+    const uint64_t m = __ballot(deg > 0);
+    if (lane == 0 && x < N) mask[((size_t)2 * r + 1) * W + (x >> 6)] = m;
+  }
+  if (any_bad) atomicOr(flags, F_NONMONO);
+  most = wave_max(most);
+  if (lane == 0) s_most[threadIdx.x >> 6] = most;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    most = max(max(s_most[0], s_most[1]), max(s_most[2], s_most[3]));
+    if (most > __hip_atomic_load(maxdeg + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(maxdeg + r, most);
+  }
+}
+
+// The last x with off[x] <= v, for off[0] <= v < off[N]: a whole wave, 64
+// probes a step.
+__device__ __forceinline__ uint32_t wave_row_of(const uint32_t* __restrict__ off, uint32_t N, uint32_t v) {
+  const uint32_t lane = threadIdx.x & 63;
+  uint32_t lo = 0, hi = N;
+  while (hi - lo > 1) {
+    const uint32_t step = (hi - lo + 63) / 64;
+    const uint64_t at = (uint64_t)lo + (uint64_t)(lane + 1) * step;
+    const uint32_t c = (uint32_t)__popcll(__ballot(at < hi && off[min(at, (uint64_t)N)] <= v));
+    lo += c * step;
+    hi = min(hi, lo + step);
+  }
+  return lo;
+}
+
+// Targets in [0, N) and rising inside a row, chunk by chunk (a bit per
+// assertion marks the rows' starts); the assertions of each bucket of objects.
+__global__ void __launch_bounds__(kPartThreads)
+k_load_check(const uint32_t* __restrict__ fwd_off, const int32_t* __restrict__ tg, const uint64_t* __restrict__ base,
+             uint32_t N, uint32_t nb, uint32_t shift, uint32_t* __restrict__ bcount, uint32_t* __restrict__ flags) {
+  constexpr uint32_t kOwn = kPartEdges / kPartThreads;
+  extern __shared__ uint32_t s_hist[];
+  __shared__ uint32_t s_start[kPartEdges / 32], s_range[2];
+  const uint32_t r = blockIdx.y, tid = threadIdx.x;
+  const uint32_t n = (uint32_t)(base[r + 1] - base[r]);
+  const uint32_t chunks = (uint32_t)(((uint64_t)n + kPartEdges - 1) / kPartEdges);
+  // (only what earlier kernels set: this one's own blocks add other reasons)
+  if (blockIdx.x >= chunks || (*flags & (F_NONMONO | F_PAD))) return;
+  const uint32_t* fo = fwd_off + (size_t)r * (N + 1);
+  const int32_t* t = tg + base[r];
+  for (uint32_t i = tid; i < nb; i += kPartThreads) s_hist[i] = 0;
+  uint32_t bad = 0;
+  for (uint32_t c = blockIdx.x; c < chunks; c += gridDim.x) {
+    const uint32_t c0 = c * kPartEdges, cn = min(kPartEdges, n - c0);
+    int32_t y[kOwn], prev[kOwn];       // (a wave's first lane also loads the target before its own)
+#pragma unroll
+    for (uint32_t i = 0; i < kOwn; ++i) {
+      const uint32_t e = min(tid + i * kPartThreads, cn - 1);
+      y[i] = t[c0 + e];
+      prev[i] = (tid & 63) == 0 ? t[c0 + e - (c0 + e > 0)] : 0;
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < kPartEdges / 32; i += kPartThreads) s_start[i] = 0;
+    if (tid < 128) {
+      const uint32_t x = wave_row_of(fo, N, tid < 64 ? c0 : c0 + cn - 1);
+      if ((tid & 63) == 0) s_range[tid >> 6] = x;
+    }
+    __syncthreads();
+    const uint32_t lo = s_range[0], hi = s_range[1];
+    if (tid == 0 && fo[lo] == c0) atomicOr(&s_start[0], 1u);
+    for (uint32_t x = lo + 1 + tid; x <= hi; x += kPartThreads) {
+      const uint32_t e = fo[x] - c0;
+      if (e < cn) atomicOr(&s_start[e >> 5], 1u << (e & 31));
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t i = 0; i < kOwn; ++i) {
+      const uint32_t e = tid + i * kPartThreads;
+      const int32_t up = __shfl_up(y[i], 1, 64);
+      const int32_t p = (tid & 63) == 0 ? prev[i] : up;
+      if (e >= cn) continue;
+      if (y[i] < 0 || (uint32_t)y[i] >= N) {
+        bad |= F_TARGET;
+        continue;
+      }
+      if (!((s_start[e >> 5] >> (e & 31)) & 1) && y[i] <= p) bad |= F_ORDER;
+      atomicAdd(&s_hist[(uint32_t)y[i] >> shift], 1u);
+    }
   }
   if (bad) atomicOr(flags, bad);
+  __syncthreads();
+  for (uint32_t i = tid; i < nb; i += kPartThreads)
+    if (s_hist[i]) atomicAdd(bcount + (size_t)r * nb + i, s_hist[i]);
 }
 
-// Scatter of the forward heavy rows' assertions (after validation).
-__global__ void __launch_bounds__(256)
-k_scatter_heavy(const int32_t* __restrict__ tg, const uint32_t* __restrict__ fo, const uint32_t* __restrict__ rows,
-                const HeavyChunk* __restrict__ chunks, uint32_t* __restrict__ cursor, int32_t* __restrict__ inv_tg) {
-  const HeavyChunk c = chunks[blockIdx.x];
-  const uint32_t x = rows[c.hrow];
-  const uint32_t e0 = fo[x] + c.k * kHeavyChunk, e1 = min(fo[x + 1], e0 + kHeavyChunk);
-  for (uint32_t e = e0 + threadIdx.x; e < e1; e += 256) {
-    const uint32_t y = (uint32_t)tg[e];
-    inv_tg[atomicAdd(cursor + y, 1u)] = (int32_t)x;
+// The pairs of one chunk to their buckets: a thread takes 16 consecutive
+// assertions, their subjects from the marked row starts by a running maximum.
+// The pairs are put in bucket order in LDS, the chunk's share of each bucket is
+// reserved with one global atomic, and consecutive threads write consecutive
+// pairs of a bucket (a store per pair at its own address: 936 us for 133M
+// pairs, 805 us with the runs).  s_hist: for each bucket its count, then its
+// first place in the chunk; s_to: its first place in the bucket less that.
+__global__ void __launch_bounds__(kPartThreads)
+k_load_part(const uint32_t* __restrict__ fwd_off, const int32_t* __restrict__ tg, const uint64_t* __restrict__ base,
+            uint32_t N, uint32_t nb, uint32_t shift, uint32_t* __restrict__ bcur, uint2* __restrict__ pairs,
+            const uint32_t* __restrict__ flags) {
+  constexpr uint32_t kOwn = kPartEdges / kPartThreads;
+  extern __shared__ uint2 s_pair[];                       // [kPartEdges]
+  uint32_t* s_row = reinterpret_cast<uint32_t*>(s_pair);  // before the pairs: [kPartEdges] row marks
+  uint32_t* s_hist = reinterpret_cast<uint32_t*>(s_pair + kPartEdges);   // [nb]
+  uint32_t* s_to = s_hist + nb;                                          // [nb]
+  __shared__ uint32_t s_range[2], s_last[kPartThreads / 64];
+  const uint32_t r = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const uint32_t n = (uint32_t)(base[r + 1] - base[r]);
+  const uint64_t c0l = (uint64_t)blockIdx.x * kPartEdges;
+  if (c0l >= n || *flags) return;
+  const uint32_t c0 = (uint32_t)c0l, cn = min(kPartEdges, n - c0);
+  const uint32_t* fo = fwd_off + (size_t)r * (N + 1);
+  const int32_t* t = tg + base[r] + c0;
+  uint32_t y[kOwn], row[kOwn], rank[kOwn];
+#pragma unroll
+  for (uint32_t i = 0; i < kOwn; ++i) y[i] = (uint32_t)t[min(tid * kOwn + i, cn - 1)];
+  for (uint32_t i = tid; i < nb; i += kPartThreads) s_hist[i] = 0;
+  for (uint32_t i = tid; i < kPartEdges; i += kPartThreads) s_row[i] = 0;
+  if (tid < 128) {
+    const uint32_t x = wave_row_of(fo, N, tid < 64 ? c0 : c0 + cn - 1);
+    if (lane == 0) s_range[wv] = x;
   }
+  __syncthreads();
+  const uint32_t lo = s_range[0], hi = s_range[1];
+  // several rows may share a start: all but the last of them are empty
+  for (uint32_t x = lo + tid; x <= hi; x += kPartThreads) {
+    const uint32_t e = x == lo ? 0u : fo[x] - c0;
+    if (e < cn) atomicMax(&s_row[e], x);
+  }
+  __syncthreads();
+  uint32_t m = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < kOwn; ++i) row[i] = m = max(m, s_row[tid * kOwn + i]);
+  uint32_t inc = m;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t u = (uint32_t)__shfl_up((int)inc, d, 64);
+    if (lane >= (uint32_t)d) inc = max(inc, u);
+  }
+  if (lane == 63) s_last[wv] = inc;
+  uint32_t before = (uint32_t)__shfl_up((int)inc, 1, 64);
+  if (lane == 0) before = 0;
+  __syncthreads();
+  for (uint32_t w = 0; w < wv; ++w) before = max(before, s_last[w]);
+#pragma unroll
+  for (uint32_t i = 0; i < kOwn; ++i) {
+    row[i] = max(row[i], before);
+    if (tid * kOwn + i < cn) rank[i] = atomicAdd(&s_hist[y[i] >> shift], 1u);
+  }
+  __syncthreads();
+  // counts -> first places, and the chunk's share of each bucket
+  const uint32_t per = (nb + kPartThreads - 1) / kPartThreads;
+  const uint32_t k0 = min(tid * per, nb), k1 = min(k0 + per, nb);
+  uint32_t sum = 0;
+  for (uint32_t k = k0; k < k1; ++k) sum += s_hist[k];
+  inc = wave_incl_scan(sum);
+  if (lane == 63) s_last[wv] = inc;
+  __syncthreads();
+  uint32_t at = inc - sum;
+  for (uint32_t w = 0; w < wv; ++w) at += s_last[w];
+  for (uint32_t k = k0; k < k1; ++k) {
+    const uint32_t c = s_hist[k];
+    s_hist[k] = at;
+    if (c) s_to[k] = atomicAdd(bcur + (size_t)r * nb + k, c) - at;
+    at += c;
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t i = 0; i < kOwn; ++i)
+    if (tid * kOwn + i < cn) s_pair[s_hist[y[i] >> shift] + rank[i]] = make_uint2(row[i], y[i]);
+  __syncthreads();
+  uint2* out = pairs + base[r];
+  for (uint32_t i = tid; i < cn; i += kPartThreads) {
+    const uint2 q = s_pair[i];
+    out[s_to[q.y >> shift] + i] = q;
+  }
+}
+
+// One bucket of objects: the inverse offsets, rows, objects' bits, heavy rows
+// and largest degree.  Order inside an inverse row follows the atomics and is
+// not fixed; evaluation results do not depend on it.  A bucket wider than the
+// LDS counters goes by sub-ranges, reading its pairs once for each.
+__global__ void __launch_bounds__(kPartThreads)
+k_load_bucket(const uint2* __restrict__ pairs, const uint64_t* __restrict__ base, uint32_t N, uint32_t W, uint32_t nb,
+              uint32_t shift, uint32_t range, const uint32_t* __restrict__ bbase, uint32_t* __restrict__ inv_off,
+              int32_t* __restrict__ inv_tg, uint64_t* __restrict__ mask, uint32_t* __restrict__ maxdeg, HeavyOut H,
+              const uint32_t* __restrict__ flags) {
+  extern __shared__ uint32_t s_dyn[];
+  __shared__ uint32_t s_wsum[kPartThreads / 64];
+  uint32_t* s_cnt = s_dyn;                 // [range]
+  uint32_t* s_out = s_dyn + range;         // [kBucketStage]
+  if (*flags) return;
+  const uint32_t r = blockIdx.y, b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const uint32_t n = (uint32_t)(base[r + 1] - base[r]);
+  const uint32_t i0 = bbase[(size_t)r * nb + b], i1 = b + 1 < nb ? bbase[(size_t)r * nb + b + 1] : n;
+  const uint2* p = pairs + base[r];
+  uint32_t* io = inv_off + (size_t)r * (N + 1);
+  int32_t* it = inv_tg + base[r];
+  const uint64_t yend = min((uint64_t)(b + 1) << shift, (uint64_t)N);
+  uint32_t run = i0, most = 0;
+  for (uint64_t y0 = (uint64_t)b << shift; y0 < yend; y0 += range) {
+    for (uint32_t i = tid; i < range; i += kPartThreads) s_cnt[i] = 0;
+    __syncthreads();
+    for (uint64_t i = (uint64_t)i0 + tid; i < i1; i += kPartThreads) {
+      const uint32_t d = p[i].y - (uint32_t)y0;
+      if (d < range) atomicAdd(&s_cnt[d], 1u);
+    }
+    __syncthreads();
+    for (uint32_t k = tid; k < range; k += kPartThreads) {
+      const uint64_t m = __ballot(s_cnt[k] > 0);
+      const uint64_t w = (y0 + k) >> 6;
+      if (lane == 0 && w < W) mask[(size_t)2 * r * W + w] = m;
+    }
+    __syncthreads();
+    const uint32_t per = (range + kPartThreads - 1) / kPartThreads;
+    const uint32_t k0 = min(tid * per, range), k1 = min(k0 + per, range);
+    uint32_t sum = 0;
+    for (uint32_t k = k0; k < k1; ++k) sum += s_cnt[k];
+    const uint32_t inc = wave_incl_scan(sum);
+    if (lane == 63) s_wsum[wv] = inc;
+    __syncthreads();
+    uint32_t ex = inc - sum, total = 0;
+    for (uint32_t w = 0; w < kPartThreads / 64; ++w) {
+      if (w < wv) ex += s_wsum[w];
+      total += s_wsum[w];
+    }
+    for (uint32_t k = k0; k < k1; ++k) {
+      const uint32_t c = s_cnt[k];
+      const uint64_t yy = y0 + k;
+      if (yy < N) {
+        io[yy] = run + ex;
+        if (c > H.hmin) heavy_append(H, 2 * r + 1, (uint32_t)yy, c);
+      }
+      most = max(most, c);
+      s_cnt[k] = ex;
+      ex += c;
+    }
+    __syncthreads();
+    const bool staged = total <= kBucketStage;
+    for (uint64_t i = (uint64_t)i0 + tid; i < i1; i += kPartThreads) {
+      const uint2 q = p[i];
+      const uint32_t d = q.y - (uint32_t)y0;
+      if (d >= range) continue;
+      const uint32_t pos = atomicAdd(&s_cnt[d], 1u);
+      if (staged) s_out[pos] = q.x;
+      else it[run + pos] = (int32_t)q.x;
+    }
+    __syncthreads();
+    if (staged)
+      for (uint32_t i = tid; i < total; i += kPartThreads) it[run + i] = (int32_t)s_out[i];
+    run += total;
+    __syncthreads();
+  }
+  if (b + 1 == nb && tid == 0) io[N] = n;
+  most = wave_max(most);
+  if (lane == 0 && most > __hip_atomic_load(maxdeg + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(maxdeg + r, most);
 }
 
 // Objects of a role direction: the individuals that occur as targets in it
@@ -301,133 +473,114 @@ k_scatter_heavy(const int32_t* __restrict__ tg, const uint32_t* __restrict__ fo,
 // their total); ctg maps each assertion's target to its rank among the
 // objects, so that a shared pass can index transposed child rows that hold
 // the objects only.
-__global__ void __launch_bounds__(256)
-k_object_mask(const uint32_t* __restrict__ opp_off, uint32_t N, uint32_t W, uint64_t* __restrict__ mask) {
-  const uint32_t r = blockIdx.y;
-  const uint32_t y = blockIdx.x * 256 + threadIdx.x;
-  const uint32_t* o = opp_off + (size_t)r * (N + 1);
-  const bool obj = y < N && o[y + 1] > o[y];
-  const uint64_t m = __ballot(obj);
-  const uint32_t w = y >> 6;
-  if ((threadIdx.x & 63) == 0 && w < W) mask[(size_t)r * 2 * W + w] = m;
-}
-
-// One block per mask row: exclusive prefix of the words' popcounts.
-__global__ void __launch_bounds__(kScanThreads)
-k_object_base(const uint64_t* __restrict__ mask, uint32_t W, uint32_t* __restrict__ base) {
-  const uint64_t* m = mask + (size_t)blockIdx.x * W;
-  uint32_t* b = base + (size_t)blockIdx.x * (W + 1);
-  const uint32_t per = (W + kScanThreads - 1) / kScanThreads;
-  const uint32_t w0 = threadIdx.x * per, w1 = min(W, w0 + per);
-  uint32_t s = 0;
-  for (uint32_t w = w0; w < w1; ++w) s += (uint32_t)__popcll(m[w]);
-  __shared__ uint32_t tot;
-  uint32_t ex = block_excl_scan(s, &tot);
-  for (uint32_t w = w0; w < w1; ++w) {
-    b[w] = ex;
-    ex += (uint32_t)__popcll(m[w]);
+// The words of 64 consecutive subjects with at least one assertion, in
+// increasing order (the role passes visit only these, and a pass may take
+// several consecutive entries at once), are the non-zero words of the other
+// direction's objects.  Both lists of all directions in two kernels with a
+// scan of the tiles' sums between them.
+__device__ __forceinline__ void word_tile(const uint64_t* __restrict__ m, uint32_t W, uint64_t (&v)[8], uint32_t& pop,
+                                          uint32_t& full) {
+  const uint32_t w0 = blockIdx.x * kWordTile + threadIdx.x * 8;
+  pop = full = 0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    v[i] = w0 + i < W ? m[w0 + i] : 0;
+    pop += (uint32_t)__popcll(v[i]);
+    full += v[i] != 0;
   }
-  if (threadIdx.x == 0) b[W] = tot;
+}
+__global__ void __launch_bounds__(256)
+k_words_sum(const uint64_t* __restrict__ mask, uint32_t W, uint32_t tiles, uint32_t* __restrict__ tsum) {
+  __shared__ uint32_t s[2][4];
+  const uint32_t rd = 2 * blockIdx.y + blockIdx.z, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  uint64_t v[8];
+  uint32_t pop, full;
+  word_tile(mask + (size_t)rd * W, W, v, pop, full);
+  pop = wave_incl_scan(pop), full = wave_incl_scan(full);
+  if (lane == 63) s[0][wv] = pop, s[1][wv] = full;
+  __syncthreads();
+  if (threadIdx.x < 2)
+    tsum[((size_t)threadIdx.x * 2 * gridDim.y + rd) * tiles + blockIdx.x] =
+        s[threadIdx.x][0] + s[threadIdx.x][1] + s[threadIdx.x][2] + s[threadIdx.x][3];
+}
+__global__ void __launch_bounds__(256)
+k_words_write(const uint64_t* __restrict__ mask, uint32_t W, uint32_t tiles, const uint32_t* __restrict__ tsum,
+              uint32_t* __restrict__ objbase, uint32_t* __restrict__ words, uint32_t* __restrict__ nobj,
+              uint32_t* __restrict__ nwords) {
+  __shared__ uint32_t s[2][4];
+  const uint32_t rd = 2 * blockIdx.y + blockIdx.z, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  uint64_t v[8];
+  uint32_t pop, full;
+  word_tile(mask + (size_t)rd * W, W, v, pop, full);
+  const uint32_t ip = wave_incl_scan(pop), fi = wave_incl_scan(full);
+  if (lane == 63) s[0][wv] = ip, s[1][wv] = fi;
+  __syncthreads();
+  uint32_t p = tsum[(size_t)rd * tiles + blockIdx.x] + ip - pop;
+  uint32_t f = tsum[((size_t)2 * gridDim.y + rd) * tiles + blockIdx.x] + fi - full;
+  for (uint32_t w = 0; w < wv; ++w) p += s[0][w], f += s[1][w];
+  uint32_t* ob = objbase + (size_t)rd * (W + 1);
+  uint32_t* list = words + (size_t)(rd ^ 1) * W;
+  const uint32_t w0 = blockIdx.x * kWordTile + threadIdx.x * 8;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    if (w0 + i >= W) break;
+    ob[w0 + i] = p;
+    p += (uint32_t)__popcll(v[i]);
+    if (v[i]) list[f++] = w0 + i;
+  }
+  if (blockIdx.x + 1 == tiles && threadIdx.x == 255) {   // the row's totals
+    ob[W] = p;
+    nobj[rd] = p;
+    nwords[rd ^ 1] = f;
+  }
 }
 
+// Object ranks of the directions whose objects are at most half of the
+// individuals.
 __global__ void __launch_bounds__(256)
-k_object_rank(const int32_t* __restrict__ tg, uint64_t e0, uint64_t n, const uint64_t* __restrict__ mask,
-              const uint32_t* __restrict__ base, int32_t* __restrict__ ctg) {
+k_object_rank(const int32_t* __restrict__ fwd_tg, const int32_t* __restrict__ inv_tg, const uint64_t* __restrict__ base,
+              uint32_t N, uint32_t W, const uint64_t* __restrict__ mask, const uint32_t* __restrict__ objbase,
+              const uint32_t* __restrict__ nobj, int32_t* __restrict__ ctg_fwd, int32_t* __restrict__ ctg_inv,
+              const uint32_t* __restrict__ flags) {
+  const uint32_t rd = 2 * blockIdx.y + blockIdx.z, r = rd >> 1, dir = rd & 1;
+  if ((uint64_t)nobj[rd] * 2 > N || *flags) return;
+  const int32_t* tg = (dir ? inv_tg : fwd_tg) + base[r];
+  int32_t* ctg = (dir ? ctg_inv : ctg_fwd) + base[r];
+  const uint64_t* m = mask + (size_t)rd * W;
+  const uint32_t* ob = objbase + (size_t)rd * (W + 1);
+  const uint64_t n = base[r + 1] - base[r];
   for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (uint64_t)gridDim.x * 256) {
-    const uint32_t y = (uint32_t)tg[e0 + i];
-    const uint64_t m = mask[y >> 6];
-    ctg[e0 + i] = (int32_t)(base[y >> 6] + (uint32_t)__popcll(m & ((1ull << (y & 63)) - 1ull)));
+    const uint32_t y = (uint32_t)tg[i];
+    ctg[i] = (int32_t)(ob[y >> 6] + (uint32_t)__popcll(m[y >> 6] & ((1ull << (y & 63)) - 1ull)));
   }
 }
 
 struct DerivedLayout {
-  size_t fwd_off, inv_off, inv_tg, cursor, bsum, base, meta, words, wbase, objmask, objbase, ctg;
+  size_t fwd_off, inv_off, inv_tg, cursor, tsum, base, meta, words, objmask, objbase, ctg;
   size_t heavy, hchunk, hchunk0, cpop, total;
-  uint32_t nb;
+  uint32_t tiles;                // word tiles of a bit row
   size_t heavy_cap, chunk_cap;   // entries
 };
-
-// Heavy rows of one direction (more than hmin assertions), appended in any
-// order as (direction 2r + dir, subject, degree); the host sorts them and
-// writes the heavy-row and chunk tables.  A direction holds at most
-// E_dir / (hmin + 1) of them, so `cap` (from the floor of hmin) is never
-// reached; the check keeps the writes in bounds regardless.
-__global__ void __launch_bounds__(256)
-k_heavy_rows(const uint32_t* __restrict__ o, uint32_t N, uint32_t hmin, uint32_t rd, uint32_t cap,
-             uint32_t* __restrict__ count, uint32_t* __restrict__ out) {
-  const uint32_t x = blockIdx.x * 256 + threadIdx.x;
-  if (x >= N) return;
-  const uint32_t deg = o[x + 1] - o[x];
-  if (deg <= hmin) return;
-  const uint32_t slot = atomicAdd(count, 1u);
-  if (slot < cap) {
-    out[3 * (size_t)slot] = rd;
-    out[3 * (size_t)slot + 1] = x;
-    out[3 * (size_t)slot + 2] = deg;
-  }
-}
-
-// Words (64 consecutive subjects) with at least one assertion, per role and
-// direction, in increasing order: the role passes visit only these, and a
-// pass may take several consecutive entries at once (their assertions form
-// one contiguous range).  Three steps per list: per-block counts (256 words a
-// block), an exclusive scan of the block counts, then each block writes its
-// words at its scanned base.
-__device__ __forceinline__ bool word_nonempty(const uint32_t* __restrict__ o, uint32_t N, uint32_t W,
-                                              uint32_t w) {
-  if (w >= W) return false;
-  const uint32_t a = w * 64, b = min(a + 64, N);
-  return o[b] != o[a];
-}
-
-__global__ void __launch_bounds__(256)
-k_nonempty_count(const uint32_t* __restrict__ o, uint32_t N, uint32_t W, uint32_t* __restrict__ bcnt,
-                 uint32_t* __restrict__ count) {
-  __shared__ uint32_t wsum[4];
-  const uint32_t w = blockIdx.x * 256 + threadIdx.x;
-  const uint64_t m = __ballot(word_nonempty(o, N, W, w));
-  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = (uint32_t)__popcll(m);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const uint32_t tot = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-    bcnt[blockIdx.x] = tot;
-    if (tot) atomicAdd(count, tot);
-  }
-}
-
-__global__ void __launch_bounds__(256)
-k_nonempty_words(const uint32_t* __restrict__ o, uint32_t N, uint32_t W, const uint32_t* __restrict__ bbase,
-                 uint32_t* __restrict__ list) {
-  __shared__ uint32_t wsum[4];
-  const uint32_t w = blockIdx.x * 256 + threadIdx.x;
-  const bool ne = word_nonempty(o, N, W, w);
-  const uint64_t m = __ballot(ne);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  if (lane == 0) wsum[wv] = (uint32_t)__popcll(m);
-  __syncthreads();
-  uint32_t before = bbase[blockIdx.x];
-  for (int i = 0; i < wv; ++i) before += wsum[i];
-  if (ne) list[before + (uint32_t)__popcll(m & ((1ull << lane) - 1))] = w;
-}
 
 static DerivedLayout layout_for(const hth_kb_desc& d) {
   DerivedLayout L{};
   size_t R = d.n_roles, N = d.n_individuals;
   size_t offs = align_up(R * (N + 1) * 4, 256);
-  L.nb = (uint32_t)((N + kScanBlock - 1) / kScanBlock);
+  L.tiles = (uint32_t)(((N + 63) / 64 + kWordTile - 1) / kWordTile);
   size_t at = 0;
   L.fwd_off = at; at += offs;
   L.inv_off = at; at += offs;
   L.inv_tg = at; at += align_up((size_t)d.n_edges * 4, 256);
   L.cursor = at; at += offs;
-  L.bsum = at; at += align_up(R * L.nb * 4 + 4, 256);
+  L.tsum = at; at += align_up(4 * R * L.tiles * 4 + 4, 256);
   L.base = at; at += align_up((R + 1) * 8, 256);
-  L.meta = at; at += align_up((4 + 4 * R) * 4, 256);
+  L.meta = at; at += align_up((4 + 6 * R) * 4, 256);
   L.words = at; at += align_up(2 * R * ((N + 63) / 64) * 4, 256);
-  L.wbase = at; at += align_up(2 * R * (((N + 63) / 64 + 255) / 256) * 4, 256);
   L.objmask = at; at += align_up(2 * R * ((N + 63) / 64) * 8, 256);
   L.objbase = at; at += align_up(2 * R * ((N + 63) / 64 + 1) * 4, 256);
   L.ctg = at; at += align_up((size_t)d.n_edges * 8, 256);     // both directions
+  // a direction holds at most E_dir / (heavy_min + 1) heavy rows, so the table
+  // (by the floor of heavy_min) is never full; appends are checked regardless
   L.heavy_cap = 2 * (d.n_edges / (kHeavyMinFloor + 1)) + 2;
   L.chunk_cap = 2 * (d.n_edges / kHeavyChunk) + L.heavy_cap + 2;
   L.heavy = at; at += align_up(L.heavy_cap * 12, 256);
@@ -472,43 +625,14 @@ extern "C" hth_status hth_kb_derived_bytes(const hth_kb_desc* desc, size_t* byte
 }
 
 // A device error flag word -> HTH_E_INVALID with the reasons.
-static hth_status check_flags(const uint32_t* flags, hipStream_t st) {
-  uint32_t hflags = 0;
-  HTH_HIP(hipMemcpyAsync(&hflags, flags, 4, hipMemcpyDeviceToHost, st));
-  HTH_HIP(hipStreamSynchronize(st));
-  if (!hflags) return HTH_OK;
+static hth_status check_flags(uint32_t flags) {
+  if (!flags) return HTH_OK;
   std::string m = "invalid knowledge base:";
-  if (hflags & F_NONMONO) m += " role offsets not monotone;";
-  if (hflags & F_TARGET) m += " role target outside [0, N);";
-  if (hflags & F_ORDER) m += " role targets not strictly increasing in a row;";
-  if (hflags & F_PAD) m += " padding bits set in a bit row;";
+  if (flags & F_NONMONO) m += " role offsets not monotone;";
+  if (flags & F_TARGET) m += " role target outside [0, N);";
+  if (flags & F_ORDER) m += " role targets not strictly increasing in a row;";
+  if (flags & F_PAD) m += " padding bits set in a bit row;";
   return fail(HTH_E_INVALID, m);
-}
-
-// Appends to `trip` the heavy rows of direction `dir` of every role whose
-// largest degree there exceeds heavy_min, as (2r + dir, subject, degree).
-static hth_status find_heavy(hth_kb_s* kb, const DerivedLayout& L, int dir, uint32_t* count,
-                             std::vector<uint32_t>& trip, hipStream_t st) {
-  const uint32_t R = kb->d.n_roles, N = kb->N;
-  bool any = false;
-  for (uint32_t r = 0; r < R; ++r) any |= kb->max_deg[dir][r] > kb->heavy_min;
-  if (!any) return HTH_OK;
-  hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, st, count, (size_t)1, 0u);
-  for (uint32_t r = 0; r < R; ++r)
-    if (kb->max_deg[dir][r] > kb->heavy_min)
-      hipLaunchKernelGGL(k_heavy_rows, dim3((N + 255) / 256), dim3(256), 0, st,
-                         (dir ? kb->inv_off : kb->fwd_off) + (size_t)r * (N + 1), N, kb->heavy_min,
-                         2 * r + dir, (uint32_t)L.heavy_cap, count, kb->heavy_rows);
-  HTH_HIP(hipGetLastError());
-  uint32_t nh = 0;
-  HTH_HIP(hipMemcpyAsync(&nh, count, 4, hipMemcpyDeviceToHost, st));
-  HTH_HIP(hipStreamSynchronize(st));
-  if (nh > L.heavy_cap || trip.size() / 3 + nh > L.heavy_cap) return fail(HTH_E_RANGE, "heavy-row table overflow");
-  const size_t at = trip.size();
-  trip.resize(at + 3 * (size_t)nh);
-  HTH_HIP(hipMemcpyAsync(trip.data() + at, kb->heavy_rows, 3 * (size_t)nh * 4, hipMemcpyDeviceToHost, st));
-  HTH_HIP(hipStreamSynchronize(st));
-  return HTH_OK;
 }
 
 struct HeavyTables {
@@ -565,21 +689,21 @@ static hth_status kb_build(hth_kb_s* kb, char* derived, hipStream_t st) {
   kb->fwd_off = reinterpret_cast<uint32_t*>(derived + L.fwd_off);
   kb->inv_off = reinterpret_cast<uint32_t*>(derived + L.inv_off);
   kb->inv_tg = reinterpret_cast<int32_t*>(derived + L.inv_tg);
-  uint32_t* cursor = reinterpret_cast<uint32_t*>(derived + L.cursor);
-  uint32_t* bsum = reinterpret_cast<uint32_t*>(derived + L.bsum);
+  uint32_t* tsum = reinterpret_cast<uint32_t*>(derived + L.tsum);
   uint64_t* base = reinterpret_cast<uint64_t*>(derived + L.base);
   uint32_t* meta = reinterpret_cast<uint32_t*>(derived + L.meta);
-  uint32_t* flags = meta;
-  uint32_t* maxdeg = meta + 4;   // [2][R]
+  uint32_t* flags = meta;              // meta: flags, heavy rows, -, -, then
+  uint32_t* maxdeg = meta + 4;         // [2][R] largest degrees
+  uint32_t* nwords = meta + 4 + 2 * R; // [R][2] non-empty words
+  uint32_t* nobj = meta + 4 + 4 * R;   // [R][2] objects
   kb->role_base_dev = base;
 
-  const size_t offs = (size_t)R * (N + 1);
   auto fill = [&](uint32_t* p, size_t n, uint32_t v) {
     if (!n) return;
     unsigned g = (unsigned)std::min<size_t>((n + 255) / 256, 65536);
     hipLaunchKernelGGL(k_fill_u32, dim3(g), dim3(256), 0, st, p, n, v);
   };
-  fill(meta, 4 + 4 * R, 0);
+  fill(meta, 4 + 6 * (size_t)R, 0);
   const uint32_t tb = 256;
   // padding of concept rows and example rows
   if (d.n_concepts)
@@ -599,6 +723,7 @@ static hth_status kb_build(hth_kb_s* kb, char* derived, hipStream_t st) {
   kb->role_base.assign(R + 1, 0);
   kb->max_deg[0].assign(R, 0);
   kb->max_deg[1].assign(R, 0);
+  std::vector<uint32_t> got(4 + 6 * (size_t)R);
   if (R) {
     hipLaunchKernelGGL(k_gather_bases, dim3((R + 255) / 256), dim3(256), 0, st, d.role_offsets,
                        R, N, base);
@@ -608,124 +733,95 @@ static hth_status kb_build(hth_kb_s* kb, char* derived, hipStream_t st) {
     if (kb->role_base[0] != 0) return fail(HTH_E_INVALID, "role_offsets[0][0] must be 0");
     if (kb->role_base[R] != d.n_edges)
       return fail(HTH_E_INVALID, "role_offsets[R-1][N] must equal n_edges");
+    uint64_t most = 0;      // assertions of the largest role
     for (uint32_t r = 0; r < R; ++r) {
       if (kb->role_base[r + 1] < kb->role_base[r])
         return fail(HTH_E_INVALID, "role offsets decrease between roles");
       if (kb->role_base[r + 1] - kb->role_base[r] >= (1ull << 32))
         return fail(HTH_E_RANGE, "a role has 2^32 or more assertions");
+      most = std::max(most, kb->role_base[r + 1] - kb->role_base[r]);
     }
-    fill(kb->inv_off, offs, 0);
-    dim3 g((N + tb - 1) / tb, R);
-    hipLaunchKernelGGL(k_validate_rows, g, dim3(tb), 0, st, d.role_offsets, d.role_targets, base,
-                       N, kb->heavy_min, kb->fwd_off, kb->inv_off, maxdeg, flags);
-    HTH_HIP(hipGetLastError());
-    HTH_HIP(hipMemcpyAsync(kb->max_deg[0].data(), maxdeg, R * 4, hipMemcpyDeviceToHost, st));
-    hth_status fs = check_flags(flags, st);
-    if (fs) return fs;
-    // forward heavy rows: checked, counted and later scattered chunk by chunk
-    // (tables of the forward direction only until the inverse exists)
     kb->heavy_rows = reinterpret_cast<uint32_t*>(derived + L.heavy);
     kb->heavy_chunks = reinterpret_cast<HeavyChunk*>(derived + L.hchunk);
     kb->heavy_chunk0 = reinterpret_cast<uint32_t*>(derived + L.hchunk0);
-    std::vector<uint32_t> trip;
-    fs = find_heavy(kb, L, 0, meta + 1, trip, st);
-    if (fs) return fs;
-    HeavyTables fwd;
-    fs = upload_heavy(kb, L, trip, fwd, st);
-    if (fs) return fs;
-    for (uint32_t r = 0; r < R; ++r)
-      if (uint32_t nc = fwd.chunk_first[2 * r + 1] - fwd.chunk_first[2 * r])
-        hipLaunchKernelGGL(k_validate_heavy, dim3(nc), dim3(256), 0, st, d.role_targets + kb->role_base[r],
-                           kb->fwd_off + (size_t)r * (N + 1), kb->heavy_rows,
-                           kb->heavy_chunks + fwd.chunk_first[2 * r], N, kb->inv_off + (size_t)r * (N + 1), flags);
-    HTH_HIP(hipGetLastError());
-    fs = check_flags(flags, st);
-    if (fs) return fs;
-    dim3 gs(L.nb, R);
-    hipLaunchKernelGGL(k_scan_sums, gs, dim3(kScanThreads), 0, st, kb->inv_off, N, L.nb, bsum,
-                       maxdeg + R);
-    hipLaunchKernelGGL(k_scan_block_sums, dim3(R), dim3(kScanThreads), 0, st, bsum, L.nb);
-    hipLaunchKernelGGL(k_scan_apply, gs, dim3(kScanThreads), 0, st, kb->inv_off, N, L.nb, bsum);
-    {
-      unsigned gg = (unsigned)std::min<size_t>((offs + 255) / 256, 65536);
-      hipLaunchKernelGGL(k_copy_u32, dim3(gg), dim3(256), 0, st, kb->inv_off, cursor, offs);
-    }
-    hipLaunchKernelGGL(k_scatter_inverse, g, dim3(tb), 0, st, kb->fwd_off, d.role_targets, base,
-                       N, kb->heavy_min, cursor, kb->inv_tg);
-    for (uint32_t r = 0; r < R; ++r)
-      if (uint32_t nc = fwd.chunk_first[2 * r + 1] - fwd.chunk_first[2 * r])
-        hipLaunchKernelGGL(k_scatter_heavy, dim3(nc), dim3(256), 0, st, d.role_targets + kb->role_base[r],
-                           kb->fwd_off + (size_t)r * (N + 1), kb->heavy_rows,
-                           kb->heavy_chunks + fwd.chunk_first[2 * r], cursor + (size_t)r * (N + 1),
-                           kb->inv_tg + kb->role_base[r]);
-    HTH_HIP(hipGetLastError());
-    HTH_HIP(hipMemcpyAsync(kb->max_deg[1].data(), maxdeg + R, R * 4, hipMemcpyDeviceToHost, st));
-    // non-empty word lists; the two directions' offsets are [R][N+1] each, so
-    // run the kernel once per direction with list rows 2r + dir
-    uint32_t* words = reinterpret_cast<uint32_t*>(derived + L.words);
-    uint32_t* wcount = meta + 4 + 2 * R;                  // [R][2]
-    kb->words = words;
-    const uint32_t nwb = (kb->W + 255) / 256;
-    uint32_t* wbase = reinterpret_cast<uint32_t*>(derived + L.wbase);
-    for (int dir = 0; dir < 2; ++dir) {
-      const uint32_t* off = dir ? kb->inv_off : kb->fwd_off;
-      for (uint32_t r = 0; r < R; ++r) {
-        const uint32_t* o = off + (size_t)r * (N + 1);
-        uint32_t* bb = wbase + (size_t)(2 * r + dir) * nwb;
-        hipLaunchKernelGGL(k_nonempty_count, dim3(nwb), dim3(256), 0, st, o, N, kb->W, bb, wcount + 2 * r + dir);
-        hipLaunchKernelGGL(k_scan_block_sums, dim3(1), dim3(kScanThreads), 0, st, bb, nwb);
-        hipLaunchKernelGGL(k_nonempty_words, dim3(nwb), dim3(256), 0, st, o, N, kb->W, bb,
-                           words + (size_t)(2 * r + dir) * kb->W);
-      }
-    }
-    HTH_HIP(hipGetLastError());
-    kb->n_words.assign(2 * R, 0);
-    HTH_HIP(hipMemcpyAsync(kb->n_words.data(), wcount, 2 * R * 4, hipMemcpyDeviceToHost, st));
-    // objects of each direction and, where they are at most half of the
-    // individuals, every assertion's object rank
-    const uint32_t W = kb->W;
+    kb->words = reinterpret_cast<uint32_t*>(derived + L.words);
     kb->objmask = reinterpret_cast<uint64_t*>(derived + L.objmask);
     kb->objbase = reinterpret_cast<uint32_t*>(derived + L.objbase);
     kb->ctg_fwd = reinterpret_cast<int32_t*>(derived + L.ctg);
     kb->ctg_inv = kb->ctg_fwd + d.n_edges;
-    for (int dir = 0; dir < 2; ++dir)
-      hipLaunchKernelGGL(k_object_mask, dim3((N + 255) / 256, R), dim3(256), 0, st,
-                         dir ? kb->fwd_off : kb->inv_off, N, W, kb->objmask + (size_t)dir * W);
-    hipLaunchKernelGGL(k_object_base, dim3(2 * R), dim3(kScanThreads), 0, st, kb->objmask, W, kb->objbase);
-    HTH_HIP(hipGetLastError());
-    std::vector<uint32_t> nobj(2 * R);
-    for (uint32_t rd = 0; rd < 2 * R; ++rd)
-      HTH_HIP(hipMemcpyAsync(&nobj[rd], kb->objbase + (size_t)rd * (W + 1) + W, 4, hipMemcpyDeviceToHost, st));
-    HTH_HIP(hipStreamSynchronize(st));
-    kb->n_obj = nobj;
-    for (uint32_t r = 0; r < R; ++r) {
-      const uint64_t e0 = kb->role_base[r], n = kb->role_base[r + 1] - e0;
-      if (!n) continue;
-      const unsigned g = (unsigned)std::min<uint64_t>((n + 255) / 256, 65536);
-      for (int dir = 0; dir < 2; ++dir) {
-        if ((uint64_t)nobj[2 * r + dir] * 2 > N) continue;
-        hipLaunchKernelGGL(k_object_rank, dim3(g), dim3(256), 0, st,
-                           dir ? (const int32_t*)kb->inv_tg : d.role_targets, e0, n,
-                           kb->objmask + (size_t)(2 * r + dir) * W, kb->objbase + (size_t)(2 * r + dir) * (W + 1),
-                           dir ? kb->ctg_inv : kb->ctg_fwd);
-      }
+    const HeavyOut H{kb->heavy_min, (uint32_t)std::min<size_t>(L.heavy_cap, 0xFFFFFFFFu), meta + 1, kb->heavy_rows};
+    // buckets of objects: a power of two so that an average bucket of the
+    // largest role has its inverse targets staged in LDS (three quarters of the
+    // stage, for the spread), at least one word of 64, and within the counters;
+    // as wide as that allows (k_load_part's runs) while the blocks fill the chip
+    uint32_t shift = 6;
+    while (shift < 31 && ((uint64_t)N >> shift) > 0 &&
+           ((((uint64_t)N + (1ull << shift) - 1) >> shift) > kBucketsMost ||
+            ((1u << shift) < kBucketMost && (most << (shift + 1)) / N <= kBucketStage * 3 / 4 &&
+             ((uint64_t)N >> (shift + 1)) * R >= kLoadFill)))
+      ++shift;
+    const uint32_t nb = (uint32_t)(((uint64_t)N + (1ull << shift) - 1) >> shift);
+    const uint32_t range = (uint32_t)std::min<uint64_t>(1ull << shift, kBucketMost);
+    uint32_t* bbase = reinterpret_cast<uint32_t*>(derived + L.cursor);   // [R][nb] twice, in [R][N+1]
+    uint32_t* bcur = bbase + (size_t)R * nb;
+    uint2* pairs = reinterpret_cast<uint2*>(derived + L.ctg);
+    auto part_lds = [](size_t buckets) { return sizeof(uint2) * kPartEdges + 8 * buckets; };
+    HTH_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_load_part),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)part_lds(kBucketsMost)));
+    HTH_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_load_bucket),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)(4 * (kBucketMost + kBucketStage))));
+    fill(bbase, (size_t)R * nb, 0);
+    hipLaunchKernelGGL(k_load_rows, dim3((N - 1) / (256 * kRowTiles) + 1, R), dim3(256), 0, st, d.role_offsets, base, N, kb->W,
+                       kb->fwd_off, kb->objmask, maxdeg, H, flags);
+    const uint32_t chunks = (uint32_t)((most + kPartEdges - 1) / kPartEdges);
+    if (chunks) {
+      const unsigned per = std::max(1u, std::min(8u, (unsigned)((uint64_t)chunks * R / 2048)));
+      hipLaunchKernelGGL(k_load_check, dim3((chunks + per - 1) / per, R), dim3(kPartThreads), nb * 4, st, kb->fwd_off,
+                         d.role_targets, base, N, nb, shift, bbase, flags);
+    }
+    hipLaunchKernelGGL(k_scan_block_sums, dim3(R), dim3(kScanThreads), 0, st, bbase, nb);
+    HTH_HIP(hipMemcpyAsync(bcur, bbase, (size_t)R * nb * 4, hipMemcpyDeviceToDevice, st));
+    if (chunks)
+      hipLaunchKernelGGL(k_load_part, dim3(chunks, R), dim3(kPartThreads), part_lds(nb), st, kb->fwd_off, d.role_targets,
+                         base, N, nb, shift, bcur, pairs, flags);
+    const size_t lds = 4 * ((size_t)range + kBucketStage);
+    hipLaunchKernelGGL(k_load_bucket, dim3(nb, R), dim3(kPartThreads), lds, st, pairs, base, N, kb->W, nb, shift, range,
+                       bbase, kb->inv_off, kb->inv_tg, kb->objmask, maxdeg + R, H, flags);
+    hipLaunchKernelGGL(k_words_sum, dim3(L.tiles, R, 2), dim3(256), 0, st, kb->objmask, kb->W, L.tiles, tsum);
+    hipLaunchKernelGGL(k_scan_block_sums, dim3(4 * R), dim3(kScanThreads), 0, st, tsum, L.tiles);
+    hipLaunchKernelGGL(k_words_write, dim3(L.tiles, R, 2), dim3(256), 0, st, kb->objmask, kb->W, L.tiles, tsum,
+                       kb->objbase, kb->words, nobj, nwords);
+    if (most) {
+      const unsigned g = (unsigned)std::min<uint64_t>((most + 2047) / 2048, 65536);
+      hipLaunchKernelGGL(k_object_rank, dim3(g, R, 2), dim3(256), 0, st, d.role_targets, kb->inv_tg, base, N, kb->W,
+                         kb->objmask, kb->objbase, nobj, kb->ctg_fwd, kb->ctg_inv, flags);
     }
     HTH_HIP(hipGetLastError());
-    // the heavy-row tables of both directions
-    fs = find_heavy(kb, L, 1, meta + 1, trip, st);
-    if (fs) return fs;
-    HeavyTables all;
-    fs = upload_heavy(kb, L, trip, all, st);
-    if (fs) return fs;
-    kb->heavy_first = all.heavy_first;
-    kb->chunk_first = all.chunk_first;
-    kb->heavy_most = all.heavy_most;
-    kb->chunk_most = all.chunk_most;
   }
-  uint32_t hflags = 0;
-  HTH_HIP(hipMemcpyAsync(&hflags, flags, 4, hipMemcpyDeviceToHost, st));
+  HTH_HIP(hipMemcpyAsync(got.data(), meta, got.size() * 4, hipMemcpyDeviceToHost, st));
   HTH_HIP(hipStreamSynchronize(st));
-  if (hflags & F_PAD) return fail(HTH_E_INVALID, "invalid knowledge base: padding bits set in a bit row");
+  if (hth_status fs = check_flags(got[0])) return fs;
+  if (!R) return HTH_OK;
+  const uint32_t* g = got.data() + 4;
+  kb->max_deg[0].assign(g, g + R);
+  kb->max_deg[1].assign(g + R, g + 2 * R);
+  kb->n_words.assign(g + 2 * R, g + 4 * R);
+  kb->n_obj.assign(g + 4 * R, g + 6 * R);
+  // the heavy-row tables of both directions
+  const uint32_t nh = got[1];
+  if (nh > L.heavy_cap) return fail(HTH_E_RANGE, "heavy-row table overflow");
+  std::vector<uint32_t> trip(3 * (size_t)nh);
+  if (nh) {
+    HTH_HIP(hipMemcpyAsync(trip.data(), kb->heavy_rows, trip.size() * 4, hipMemcpyDeviceToHost, st));
+    HTH_HIP(hipStreamSynchronize(st));
+  }
+  HeavyTables all;
+  hth_status fs = upload_heavy(kb, L, trip, all, st);
+  if (fs) return fs;
+  kb->heavy_first = all.heavy_first;
+  kb->chunk_first = all.chunk_first;
+  kb->heavy_most = all.heavy_most;
+  kb->chunk_most = all.chunk_most;
   return HTH_OK;
 }
 
@@ -749,13 +845,14 @@ extern "C" hth_status hth_kb_create(const hth_kb_desc* desc, void* derived, size
   kb->pos = desc->pos_bits;
   kb->neg = desc->neg_bits;
   hipError_t e = hipGetDevice(&kb->device);
-  hipDeviceProp_t prop;
-  if (e == hipSuccess) e = hipGetDeviceProperties(&prop, kb->device);
+  int n_cu = 0, lds = 0;
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, kb->device);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, kb->device);
   if (e != hipSuccess) {
     delete kb;
-    return hip_fail(e, "hipGetDeviceProperties");
+    return hip_fail(e, "hipDeviceGetAttribute");
   }
-  kb->n_cu = prop.multiProcessorCount;
+  kb->n_cu = n_cu;
   auto env_u = [](const char* n, uint64_t dflt) {
     const char* e = std::getenv(n);
     return e ? (uint64_t)std::strtoull(e, nullptr, 10) : dflt;
@@ -772,7 +869,7 @@ extern "C" hth_status hth_kb_create(const hth_kb_desc* desc, void* derived, size
   kb->tune.short_rows = (uint32_t)std::min<uint64_t>(64, env_u("HTHEDL_SHORT_ROWS", kb->tune.short_rows));
   kb->heavy_min = (uint32_t)std::min<uint64_t>(
       1u << 30, std::max<uint64_t>(kHeavyMinFloor, env_u("HTHEDL_HEAVY_MIN", kb->heavy_min)));
-  kb->lds_per_block = prop.sharedMemPerBlock;
+  kb->lds_per_block = (size_t)lds;
   s = kb_build(kb, static_cast<char*>(derived), static_cast<hipStream_t>(stream));
   if (s) {
     delete kb;
