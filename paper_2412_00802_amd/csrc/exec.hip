@@ -1223,8 +1223,10 @@ size_t plan_t_bytes(const hth_kb_s& kb, const Plan& P) {
 size_t plan_workspace_bytes(const hth_kb_s& kb, const Plan& P) {
   size_t tables = 0;
   auto add = [&](size_t n, size_t each) { tables = align_up(tables, 256) + n * each; };
-  size_t n_reg = P.roots.size(), n_role = 0, n_grp = 0, n_mem = 0, n_fill = 0, max_groups = 0;
+  // a root covered by its pass has a region of one instruction where instances are written
+  size_t n_reg = P.roots.size(), n_cover = 0, n_role = 0, n_grp = 0, n_mem = 0, n_fill = 0, max_groups = 0;
   for (const PlanLevel& PL : P.levels) {
+    for (const GroupMember& m : PL.members) n_cover += m.cover != kNone;
     n_reg += PL.mat.size();
     n_role += PL.roles.size();
     n_grp += PL.groups.size();
@@ -1236,13 +1238,13 @@ size_t plan_workspace_bytes(const hth_kb_s& kb, const Plan& P) {
   add(P.thr.size(), sizeof(ThrGroup));
   add(P.num.size(), sizeof(NumTask));
   add(P.str.size(), sizeof(StrTask));
-  add(n_reg, sizeof(RegionTask));
+  add(n_reg + n_cover, sizeof(RegionTask));
   add(n_role, sizeof(RoleTask));
   add(n_role, sizeof(RoleTask));            // pushed role tasks (a subset of the role nodes)
   add(n_grp, sizeof(GroupTask));
   add(n_mem, sizeof(GroupMember));
   add(n_fill, sizeof(FillTask));
-  add(P.code.size(), sizeof(uint32_t));
+  add(P.code.size() + n_cover, sizeof(uint32_t));
   add(9 * n_grp + 8, sizeof(uint32_t));     // XCD slot tables: at most 8 more than groups per chunk
   return align_up(tables, 256) + (size_t)P.n_slots * kb.S * 8 + (max_groups ? plan_t_bytes(kb, P) : 0) +
          heavy_counter_bytes(kb, P) + partial_bytes(kb, P) + idset_bytes(P);
