@@ -388,15 +388,17 @@ hth_status hth_plan_destroy(hth_plan plan);
  * node is evaluated, reachable from its root or not), run level by level on
  * the executor's kernels with the kb's schedule:
  * role nodes of one (level, role, direction) share CSR passes, thresholds on
- * one property a column pass.
+ * one property a column pass.  Over large knowledge bases with few examples,
+ * what lies under no role restriction is evaluated at the examples only (the
+ * set bits of the example rows at each launch).
  *
  * hth_dplan_create runs the count pass on `stream` (validation, role-nesting
  * levels, region programs' sizes, table sizes) and waits for its counts (a few
  * bytes per role direction and property): the only data the host reads; the
  * host builds the shared passes and the table layout from them.  *ws_bytes
  * receives the workspace that hth_dplan_launch needs.  `scratch` is device
- * memory of at least hth_dplan_scratch_bytes(kb, n_nodes) (about 270 bytes per
- * node: per-node facts, the hash-consing tables, the plan's own tables),
+ * memory of at least hth_dplan_scratch_bytes(kb, n_nodes) (420 to 470 bytes
+ * per node: per-node facts, the hash-consing tables, the plan's own tables),
  * 256-byte aligned, owned by the caller and held by the plan until it is
  * destroyed.  The plan keeps the kb's set table and schedule as they were at
  * creation.  The node arrays must stay allocated and unchanged until the

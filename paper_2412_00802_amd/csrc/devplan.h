@@ -9,14 +9,18 @@
 //               region-program stack depth and program length, hash-conses
 //               the batch (each node gets a representative: the first equal
 //               node, by construct, arguments and children's representatives)
-//               and threshold leaves, numbers the rows of representative role
-//               nodes and of the compound fillers they materialise, and counts
-//               the plan's tables: role nodes per (level, role direction)
-//               bucket, distinct thresholds per property, regions, program
-//               words.  The counts are the only data the host reads back;
+//               and threshold leaves, numbers the rows of the compound fillers
+//               that representative role nodes materialise, and counts regions
+//               and program words.  The counts of these two passes are the
+//               only data the host reads back;
 //   (host)      from the counts alone: table bases, the shared CSR passes of
 //               each large bucket (ceil(count / group_k) passes), their T rows
 //               and XCD placement, threshold groups, the workspace layout;
+//   k_dp_tally  (a thread per node, after k_dp_count has marked which nodes
+//               lie under a role restriction) counts the role nodes and the
+//               thresholds, each for all individuals or for the example view
+//               (view.h), numbers their rows and lists the full rows that the
+//               view's root programs read;
 //   k_dp_emit   writes the threshold, role, fill and region tasks and the
 //               shared passes' members (and acceptance masks) of the
 //               representatives at per-table cursors, and every region program.
@@ -44,11 +48,15 @@ enum : uint32_t {
 struct DpSummary {
   unsigned long long err;       // lowest (hypothesis << 32 | node << 8 | reason); ~0 = none
   unsigned long long code;      // region-program instructions of all regions
-  uint32_t levels, mat_depth, root_depth, pad;         // maxima
-  uint32_t n_thr;               // summed per block (contiguous with the per-level array below)
+  uint32_t levels, mat_depth, root_depth;              // maxima
+  uint32_t n_vrows, n_copies;   // rows and row copies of the example view
+  uint32_t n_thr_full, n_thr_view;   // thresholds by where they are evaluated
+  uint32_t n_thr;               // distinct; summed per block (contiguous with the per-level array below)
   uint32_t n_slots;             // row counter: role and filler rows are numbered from it
   uint32_t mat[kDpLevels];
+  uint32_t pad[3];
 };
+static_assert(sizeof(DpSummary) % 16 == 0, "cleared in 16-byte units");
 constexpr int kDpSums = 2 + kDpLevels;
 
 // Role nodes are counted per bucket (level, direction 2r + dir): bk[0][L][rd]
@@ -78,18 +86,23 @@ struct DpKB {                    // what the passes read of the knowledge base
   uint32_t n_dir;                // 2 R + 1
   const uint32_t* dir;           // [3][2R+1]: non-empty words, first heavy chunk, first heavy row
   uint32_t* pk;                  // [n_data] distinct thresholds per property (count pass)
-  unsigned long long* tkey;      // threshold table: keys (kDpEmpty = free) ...
-  uint32_t* tval;                // ... and per entry: index within its property, owning node
+  unsigned long long* tkey;      // threshold table (and the fixed rows the view reads): keys (kDpEmpty = free) ...
+  uint32_t* tval;                // ... and per entry: index within its property's full and view tasks
+  uint32_t* tvrow;               // ... and its view row
   uint32_t tmask;                // entries - 1 (a power of two above twice the nodes)
-  uint32_t n_thr;                // distinct thresholds (emit pass): their rows come first
+  uint32_t n_thr;                // full thresholds (emit pass): their rows come first
   // hash-consing of the batch (count pass): canon[g] = the representative of
   // node g (the first equal node to claim the key), crep the table of
-  // representatives (same size as the threshold table), nbase[g] = the first
-  // node of g's hypothesis; per representative: rowidx (role nodes) and, for
-  // a compound filler, matclaim (the role node that materialises it) and matrow
+  // representatives (same size as the threshold table), nkey[g] the node's key
+  // in 8 words (see DpKey), nbase[g] = the first node of g's hypothesis; per
+  // representative: rowidx (role nodes), rooth (a hypothesis that it is the
+  // root of) and, for a compound filler, matclaim (the role node that
+  // materialises it) and matrow
   uint32_t* canon;                // leaves: synthetic ids from n_nodes up (see dp_leaf_id)
   uint32_t* nbase;
+  uint32_t* nkey;
   uint32_t* crep;
+  uint32_t* rooth;
   uint32_t* rowidx;
   uint32_t* matclaim;
   uint32_t* matrow;
@@ -98,8 +111,17 @@ struct DpKB {                    // what the passes read of the knowledge base
   // root of one hypothesis adds its coverage in its shared pass, without a row)
   uint32_t* ruse;
   uint32_t n_nodes;
+  // the example view: whether the plan uses it; the view rows of role nodes,
+  // per representative (those of atoms, set rows and thresholds: tvrow)
+  uint32_t view;
+  uint32_t* vrow;
+  uint32_t* pkv;                  // [n_data] view thresholds per property
+  ViewCopy* copies;               // full rows that the view's programs read
 };
-constexpr uint32_t kDpRead = 1u << 31;
+// ruse: read by some node; under a role restriction (needed for every
+// individual), or read by a root's region, in some hypothesis
+constexpr uint32_t kDpRead = 1u << 31, kDpUnder = 1u << 30, kDpAbove = 1u << 29;
+constexpr uint32_t kDpRoots = kDpAbove - 1;   // hypotheses it is the root of
 
 // The representative of a leaf is an id of its own, never a node index:
 // n_nodes + 0 (top), + 1 (bottom), + 2 + a (atom a), + 2 + C + s (set row s),
@@ -122,6 +144,10 @@ __device__ __forceinline__ unsigned long long dp_thr_key(const hth_node& x) {
   const uint32_t cmp = x.op == HTH_DATA_GE ? 0u : x.op == HTH_DATA_LE ? 1u : 2u;
   return ((unsigned long long)(x.arg * 4u + cmp) << 32) | x.q.n;
 }
+// An atom's or set row's key in the same table (a comparison that no threshold has).
+__device__ __forceinline__ unsigned long long dp_fixed_key(const DpKB& K, const hth_node& x) {
+  return (((x.op == HTH_ATOM ? 0ull : (unsigned long long)K.n_concepts) + x.arg) * 4u + 3u) << 32;
+}
 __device__ __forceinline__ uint32_t dp_hash(unsigned long long k, uint32_t mask) {
   k ^= k >> 33;
   k *= 0xFF51AFD7ED558CCDull;
@@ -133,28 +159,33 @@ __device__ __forceinline__ uint32_t dp_hash(unsigned long long k, uint32_t mask)
 
 struct DpTables {
   ThrTask* thr;
+  ThrTask* vthr;                 // the view's thresholds
   RegionTask* mat;
   RegionTask* roots;
   RoleTask* roles;
   FillTask* fills;               // fills[0]: the zero row
   uint32_t* code;
-  GroupTask* groups;             // the shared passes (copied from the plan's shells each launch)
+  GroupTask* groups;             // the shared passes, then the view's (copied from the plan's shells each launch)
   GroupMember* members;
-  const DpBucket* buckets;       // [kDpLevels][2R]
-  uint32_t* bcur;                // [kDpLevels][2R] member cursors
+  const DpBucket* buckets;       // [kDpLevels][2R], then the view's [2R]
+  uint32_t* bcur;                // as buckets: member cursors
   const uint32_t* pbase;         // [n_data] first threshold task of each property
+  const uint32_t* vpbase;        // the same of the view's tasks
 };
 
 // per-node facts of the count pass: bits 0-7 role-nesting height + 1 (0: no
 // role below), 8-15 region stack depth, 16-23 operator nesting, bit 24 a
 // row of its own (atom, set row, threshold, role node), bit 25 the complement
-// of such a row
-constexpr uint32_t kDpRow = 1u << 24, kDpNotRow = 1u << 25;
+// of such a row, bits 26 and 27 set once the whole hypothesis is known: under
+// a role restriction / read by the root's region
+constexpr uint32_t kDpRow = 1u << 24, kDpNotRow = 1u << 25, kDpDeep = 1u << 26, kDpTop = 1u << 27;
 
 __device__ __forceinline__ bool dp_role(uint8_t op) { return op >= HTH_EXISTS && op <= HTH_EXACTLY; }
 __device__ __forceinline__ bool dp_column(uint8_t op) {
   return op == HTH_DATA_GE || op == HTH_DATA_LE || op == HTH_DATA_EQ;
 }
+
+__device__ __forceinline__ bool dp_nary(uint8_t op) { return op == HTH_AND || op == HTH_OR; }
 
 __device__ __forceinline__ uint32_t dp_nwords(const DpKB& K, uint32_t rd) { return K.dir[rd]; }
 __device__ __forceinline__ uint32_t dp_chunks(const DpKB& K, uint32_t rd) {
@@ -193,45 +224,61 @@ __device__ __forceinline__ uint32_t dp_load(const uint32_t* p) {
 __device__ __forceinline__ void dp_store(uint32_t* p, uint32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// child j of node x (hypothesis at b): its representative
-__device__ __forceinline__ uint32_t dp_child_rep(const DpKB& K, const hth_node& x, const uint32_t* kids, uint32_t b,
-                                                 uint32_t j) {
-  const uint32_t c = (x.op == HTH_AND || x.op == HTH_OR) ? kids[x.child + j] : x.child;
-  return dp_load(K.canon + b + c);
-}
 __device__ __forceinline__ uint32_t dp_n_children(const hth_node& x) {
   if (x.op == HTH_AND || x.op == HTH_OR) return x.arity;
   return (x.op == HTH_NOT || dp_role(x.op)) ? 1u : 0u;
 }
 
-// The representative of node g (local index i of the hypothesis at b), whose
-// children already have theirs.  Open addressing over crep: a free slot is
-// claimed with a release compare-and-swap; an occupied one (read with
-// acquire) holds a representative whose key is compared exactly: its fields,
+// The representative of node g (of the hypothesis at b), whose children
+// already have theirs (rep(j)).  Open addressing over crep: a free slot is
+// claimed with a compare-and-swap after the key's stores have reached memory;
+// an occupied one holds a representative whose key is compared exactly: its fields
 // and its children's representatives, which its own thread stored before the
-// claim.  No thread ever waits for another.
+// claim, in one record for up to four children (one round trip to memory
+// where the fields, the base and the children's entries were three).  No
+// thread ever waits for another.
+constexpr uint32_t kDpKeyKids = 4;
+template <class Rep>
 __device__ uint32_t dp_canon(const DpKB& K, const hth_node* __restrict__ nodes, const uint32_t* __restrict__ kids,
-                             uint32_t b, uint32_t g, const hth_node& x) {
+                             uint32_t b, uint32_t g, const hth_node& x, Rep rep) {
   const DpKey k = dp_key(x);
   const uint32_t nc = dp_n_children(x);
+  uint32_t* own = K.nkey + 8 * (size_t)g;
+  uint32_t r4[kDpKeyKids];
   uint64_t h = dp_mix(dp_mix(dp_mix(0, k.head), k.arg), k.q);
-  for (uint32_t j = 0; j < nc; ++j) h = dp_mix(h, dp_child_rep(K, x, kids, b, j));
+#pragma unroll
+  for (uint32_t j = 0; j < kDpKeyKids; ++j) r4[j] = j < nc ? rep(j) : 0u;
+#pragma unroll
+  for (uint32_t j = 0; j < kDpKeyKids; ++j)
+    if (j < nc) h = dp_mix(h, r4[j]);
+  for (uint32_t j = kDpKeyKids; j < nc; ++j) h = dp_mix(h, rep(j));
   dp_store(K.nbase + g, b);
+  dp_store(own, k.head);
+  dp_store(own + 1, k.arg);
+  dp_store(own + 2, k.q);
+#pragma unroll
+  for (uint32_t j = 0; j < kDpKeyKids; ++j) dp_store(own + 4 + j, r4[j]);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the record is in memory before its claim
   for (uint32_t hs = (uint32_t)(h ^ (h >> 32)) & K.tmask;; hs = (hs + 1) & K.tmask) {
-    uint32_t r = __hip_atomic_load(K.crep + hs, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t r = dp_load(K.crep + hs);
     if (r == kNone) {
-      uint32_t expected = kNone;
-      if (__hip_atomic_compare_exchange_strong(K.crep + hs, &expected, g, __ATOMIC_ACQ_REL, __ATOMIC_ACQUIRE,
-                                               __HIP_MEMORY_SCOPE_AGENT))
-        return g;
-      r = expected;                     // the representative that claimed the slot first
+      r = atomicCAS(K.crep + hs, kNone, g);
+      if (r == kNone) return g;         // (else the representative that claimed the slot first)
     }
-    const hth_node y = nodes[r];
-    const DpKey ky = dp_key(y);
-    if (ky.head != k.head || ky.arg != k.arg || ky.q != k.q) continue;
-    const uint32_t by = dp_load(K.nbase + r);
+    asm volatile("" ::: "memory");
+    const uint32_t* o = K.nkey + 8 * (size_t)r;
+    uint32_t v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = j == 3 ? 0u : dp_load(o + j);
+    if (v[0] != k.head || v[1] != k.arg || v[2] != k.q) continue;
     bool same = true;
-    for (uint32_t j = 0; j < nc && same; ++j) same = dp_child_rep(K, y, kids, by, j) == dp_child_rep(K, x, kids, b, j);
+#pragma unroll
+    for (uint32_t j = 0; j < kDpKeyKids; ++j) same = same && v[4 + j] == r4[j];
+    if (same && nc > kDpKeyKids) {
+      const hth_node y = nodes[r];
+      const uint32_t by = dp_load(K.nbase + r);
+      for (uint32_t j = kDpKeyKids; j < nc && same; ++j) same = dp_load(K.canon + by + kids[y.child + j]) == rep(j);
+    }
     if (same) return r;
   }
 }
@@ -242,36 +289,54 @@ __device__ __forceinline__ bool dp_groupable(const hth_node& x) {
          (x.op == HTH_ATLEAST ? x.q.n <= kGroupMaxCount : x.q.n < kGroupMaxCount);
 }
 
-__global__ void __launch_bounds__(256)
-k_dp_count(const hth_node* __restrict__ nodes, const uint32_t* __restrict__ offs,
+// A hypothesis is walked by one thread, so a pass takes as long as its longest
+// hypothesis's chain of memory round trips.  Blocks are one wave of 32
+// hypotheses, so that a batch of a few thousand reaches every CU; their nodes
+// come to LDS in coalesced loads, and the per-node facts and representatives
+// that parents read back stay in LDS; a block with more nodes than its area
+// keeps them in global memory.  What is left is the probe of the tables: no
+// acquire or release at device scope there, since each writes back or drops
+// the whole L2 of its XCD (see dp_canon).  8,192 hypotheses 180 us, 65,536 438
+// (267 and 1,393 with those; 416 and 1,507 with the facts in global memory and
+// 256 threads a block too; 16 hypotheses a wave 170 and 607, 64 205 and 360).
+constexpr uint32_t kDpBlock = 64, kDpHyps = 32, kDpStage = 1024;
+__global__ void __launch_bounds__(kDpBlock)
+k_dp_count(const hth_node* __restrict__ nodes_g, const uint32_t* __restrict__ offs,
            const uint32_t* __restrict__ kids, uint32_t n_nodes, uint32_t n_kids, uint32_t n_hyps, DpKB K,
-           uint32_t* __restrict__ info, uint32_t* __restrict__ len, DpSummary* __restrict__ sum,
-           uint32_t* __restrict__ bk) {
+           uint32_t* __restrict__ info_g, uint32_t* __restrict__ len_g, DpSummary* __restrict__ sum) {
   __shared__ uint32_t s_sum[kDpSums];
   __shared__ unsigned long long s_code;
   __shared__ uint32_t s_max[3];
+  __shared__ hth_node s_node[kDpStage];
+  __shared__ uint32_t s_info[kDpStage], s_len[kDpStage], s_canon[kDpStage];
   for (uint32_t i = threadIdx.x; i < kDpSums; i += blockDim.x) s_sum[i] = 0;
   if (threadIdx.x < 3) s_max[threadIdx.x] = 0;
   if (threadIdx.x == 0) s_code = 0;
+  const uint32_t h0 = blockIdx.x * kDpHyps, h1 = min(h0 + kDpHyps, n_hyps), h = h0 + threadIdx.x;
+  const uint32_t first = offs[h0], last = offs[h1];
+  // (offsets that fall are left to the walk in global memory, which reports them)
+  const bool rising = h >= h1 || offs[h] <= offs[h + 1];
+  const bool staged = __all(rising) && last <= n_nodes && last - first <= kDpStage;
+  if (staged)
+    for (uint32_t i = threadIdx.x; i < last - first; i += kDpBlock) s_node[i] = nodes_g[first + i];
   __syncthreads();
   uint32_t* const s_thr = s_sum;
   uint32_t* const s_mat = s_sum + 2;
-  const uint32_t nbk = kDpLevels * (K.n_dir - 1);
-  const uint32_t h = blockIdx.x * blockDim.x + threadIdx.x;
-  if (h < n_hyps) {
+  // the hypothesis's nodes, facts and representatives; entry 0 is batch node n0
+  auto walk = [&](const hth_node* nodes, uint32_t* info, uint32_t* len, uint32_t* canon, uint32_t n0) {
     auto err = [&](uint32_t node, uint32_t why) {
       atomicMin(&sum->err, ((unsigned long long)h << 32) | ((unsigned long long)node << 8) | why);
     };
-    const uint32_t b = offs[h], e = offs[h + 1];
+    const uint32_t gb = offs[h], e = offs[h + 1], b = gb - n0;   // b: its first entry
     bool ok = true;
-    if (e < b || e > n_nodes) {
+    if (e < gb || e > n_nodes) {
       err(0, DP_OFFSETS);
       ok = false;
-    } else if (e == b) {
+    } else if (e == gb) {
       err(0, DP_EMPTY);
       ok = false;
     }
-    const uint32_t n = ok ? e - b : 0;
+    const uint32_t n = ok ? e - gb : 0;
     for (uint32_t i = 0; i < n && ok; ++i) {
       const hth_node x = nodes[b + i];
       uint32_t hgt = 0, dep = 1, nest = 0, flags = 0;
@@ -298,14 +363,12 @@ k_dp_count(const hth_node* __restrict__ nodes, const uint32_t* __restrict__ offs
           else if (x.q.t != x.q.t) why = DP_NAN;
           flags = kDpRow;
           if (!why) {
-            // one task and row per distinct threshold of the batch: the first
-            // node to claim a key owns it
+            // one entry per distinct threshold of the batch
             const unsigned long long key = dp_thr_key(x);
             for (uint32_t hs = dp_hash(key, K.tmask);; hs = (hs + 1) & K.tmask) {
-              const unsigned long long prev = atomicCAS(K.tkey + hs, kDpEmpty, key);
+              unsigned long long prev = __hip_atomic_load(K.tkey + hs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              if (prev == kDpEmpty) prev = atomicCAS(K.tkey + hs, kDpEmpty, key);
               if (prev == kDpEmpty) {
-                K.tval[2 * hs] = atomicAdd(K.pk + x.arg, 1u);
-                K.tval[2 * hs + 1] = b + i;
                 atomicAdd(s_thr, 1u);
                 thr_slot = hs;
                 break;
@@ -419,26 +482,28 @@ k_dp_count(const hth_node* __restrict__ nodes, const uint32_t* __restrict__ offs
       }
       info[b + i] = hgt | (min(dep, 255u) << 8) | (min(nest, 255u) << 16) | flags;
       len[b + i] = (uint32_t)L;
-      const uint32_t g = b + i;
+      len_g[gb + i] = (uint32_t)L;
+      const uint32_t g = gb + i;
+      // child j's representative
+      auto child_rep = [&](uint32_t j) { return canon[b + (dp_nary(x.op) ? kids[x.child + j] : x.child)]; };
       const bool leaf = x.op == HTH_TOP || x.op == HTH_BOT || x.op == HTH_ATOM || x.op == HTH_SET || dp_column(x.op);
-      const uint32_t rep = leaf ? dp_leaf_id(K, x, thr_slot) : dp_canon(K, nodes, kids, b, g, x);
+      const uint32_t rep = leaf ? dp_leaf_id(K, x, thr_slot) : dp_canon(K, nodes_g, kids, gb, g, x, child_rep);
+      canon[b + i] = rep;
       dp_store(K.canon + g, rep);
       if (rep == g) {   // its children are read (an equal node's are the same representatives)
         const uint32_t nc = dp_n_children(x);
         for (uint32_t j = 0; j < nc; ++j) {
-          const uint32_t cr = dp_child_rep(K, x, kids, b, j);
+          const uint32_t cr = child_rep(j);
           if (cr < K.n_nodes) atomicOr(K.ruse + cr, kDpRead);
         }
       }
       if (role_lvl != kNone && rep == g) {
-        // a representative role node: its row, its task in its bucket, and the
-        // materialisation of its compound filler unless an equal one is claimed
-        const uint32_t lvl = role_lvl, rd = 2 * x.arg + x.inv;
-        K.rowidx[g] = atomicAdd(&sum->n_slots, 1u);
-        atomicAdd(bk + (dp_groupable(x) ? 0u : nbk) + lvl * (K.n_dir - 1) + rd, 1u);
+        // a representative role node: the materialisation of its compound
+        // filler unless an equal one is claimed
+        const uint32_t lvl = role_lvl;
         atomicMax(s_max, lvl + 1);
         if (mat_c != kNone) {
-          const uint32_t cc = dp_load(K.canon + mat_c);
+          const uint32_t cc = canon[mat_c];
           if (atomicCAS(K.matclaim + cc, kNone, g) == kNone) {
             K.matrow[cc] = atomicAdd(&sum->n_slots, 1u);
             atomicAdd(s_mat + lvl, 1u);
@@ -450,13 +515,35 @@ k_dp_count(const hth_node* __restrict__ nodes, const uint32_t* __restrict__ offs
     }
     if (ok) {   // the root's region, with coverage
       const uint32_t r = b + n - 1, ri = info[r];
-      const uint32_t rr = dp_load(K.canon + r);
-      if (rr < K.n_nodes) atomicAdd(K.ruse + rr, 1u);
+      const uint32_t rr = canon[r];
+      if (rr < K.n_nodes) {
+        atomicAdd(K.ruse + rr, 1u);
+        K.rooth[rr] = h;
+      }
       if (((ri >> 8) & 255u) > (uint32_t)kStackDepth) err(n - 1, DP_DEPTH);
       else if (((ri >> 16) & 255u) > kDpNest) err(n - 1, DP_NEST);
       atomicAdd(&s_code, (unsigned long long)len[r]);
       atomicMax(s_max + 2, (ri >> 8) & 255u);
+      // from the root down: what lies under a role restriction, and what the
+      // root's region reads (a node that the root does not reach counts as
+      // under one)
+      for (uint32_t i = n; i-- > 0;) {
+        const hth_node x = nodes[b + i];
+        uint32_t f = info[b + i] & (kDpDeep | kDpTop);
+        if (i + 1 == n) f |= kDpTop;
+        if (!f) f = kDpDeep;
+        info_g[gb + i] = info[b + i] | f;
+        const uint32_t down = dp_role(x.op) ? kDpDeep : f, nk = dp_n_children(x);
+        for (uint32_t j = 0; j < nk; ++j) info[b + (dp_nary(x.op) ? kids[x.child + j] : x.child)] |= down;
+        if (dp_role(x.op)) {
+          atomicOr(K.ruse + canon[b + i], (f & kDpDeep ? kDpUnder : 0u) | (f & kDpTop ? kDpAbove : 0u));
+        }
+      }
     }
+  };
+  if (h < h1) {
+    if (staged) walk(s_node, s_info, s_len, s_canon, first);
+    else walk(nodes_g, info_g, len_g, K.canon, 0);
   }
   __syncthreads();
   uint32_t* const out = &sum->n_thr;
@@ -470,21 +557,104 @@ k_dp_count(const hth_node* __restrict__ nodes, const uint32_t* __restrict__ offs
   }
 }
 
-// The bit row a leaf-like node reads (atom, set row, or the node's own row).
-__device__ __forceinline__ uint32_t dp_leaf_row(const DpKB& K, const hth_node* nodes, const uint32_t* row,
+// A representative role node that is evaluated on the example view: nothing
+// under a role restriction reads it, and a shared pass decides it.
+__device__ __forceinline__ bool dp_viewed(const DpKB& K, const hth_node& x, uint32_t use) {
+  return K.view && !(use & kDpUnder) && dp_groupable(x);
+}
+// It is the root of one hypothesis and read by no node: its pass adds its
+// coverage and it has no row.
+__device__ __forceinline__ bool dp_root_only(uint32_t use) { return !(use & kDpRead) && (use & kDpRoots) == 1u; }
+
+// The slot of a key that the threshold table holds.
+__device__ __forceinline__ uint32_t dp_slot(const DpKB& K, unsigned long long key) {
+  uint32_t hs = dp_hash(key, K.tmask);
+  while (K.tkey[hs] != key) hs = (hs + 1) & K.tmask;
+  return hs;
+}
+
+// Claims *p (kNone: free) for this thread; the claimant then writes its index.
+__device__ __forceinline__ bool dp_claim(uint32_t* p) {
+  return dp_load(p) == kNone && atomicCAS(p, kNone, kNone - 1) == kNone;
+}
+
+// Counts and rows of the role nodes and thresholds, a thread per node of the
+// batch (nodes [offs[0], offs[n_hyps])).  bk: [2][level][direction] role nodes
+// evaluated for every individual, those a shared pass decides and the others;
+// then [direction] those of the view.
+__global__ void __launch_bounds__(256)
+k_dp_tally(const hth_node* __restrict__ nodes, const uint32_t* __restrict__ offs, uint32_t n_hyps, DpKB K,
+           const uint32_t* __restrict__ info, DpSummary* __restrict__ sum, uint32_t* __restrict__ bk) {
+  if (sum->err != ~0ull) return;
+  const uint32_t g0 = offs[0], n = offs[n_hyps] - g0, i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const uint32_t g = g0 + i, f = info[g], R2 = K.n_dir - 1, nbk = kDpLevels * R2;
+  const hth_node x = nodes[g];
+  auto copy = [&](uint32_t src) {                 // a full row of the view's programs: its view row
+    const uint32_t v = atomicAdd(&sum->n_vrows, 1u);
+    K.copies[atomicAdd(&sum->n_copies, 1u)] = ViewCopy{src, v};
+    return v;
+  };
+  const bool top = K.view && (f & kDpTop);
+  if (x.op == HTH_ATOM || x.op == HTH_SET) {
+    if (!top) return;
+    const unsigned long long key = dp_fixed_key(K, x);
+    for (uint32_t hs = dp_hash(key, K.tmask);; hs = (hs + 1) & K.tmask) {
+      unsigned long long prev = __hip_atomic_load(K.tkey + hs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (prev == kDpEmpty) prev = atomicCAS(K.tkey + hs, kDpEmpty, key);
+      if (prev == kDpEmpty) K.tvrow[hs] = copy(x.op == HTH_ATOM ? x.arg : K.n_concepts + x.arg);
+      if (prev == kDpEmpty || prev == key) break;
+    }
+  } else if (dp_column(x.op)) {
+    const uint32_t hs = dp_slot(K, dp_thr_key(x));
+    if ((!K.view || (f & kDpDeep)) && dp_claim(K.tval + 2 * hs)) {
+      K.tval[2 * hs] = atomicAdd(K.pk + x.arg, 1u);
+      atomicAdd(&sum->n_thr_full, 1u);
+    }
+    if (top && dp_claim(K.tval + 2 * hs + 1)) {
+      K.tval[2 * hs + 1] = atomicAdd(K.pkv + x.arg, 1u);
+      K.tvrow[hs] = atomicAdd(&sum->n_vrows, 1u);
+      atomicAdd(&sum->n_thr_view, 1u);
+    }
+  } else if (dp_role(x.op) && K.canon[g] == g) {
+    const uint32_t use = K.ruse[g], lvl = (f & 255u) - 1, rd = 2 * x.arg + x.inv;
+    if (dp_viewed(K, x, use)) {
+      atomicAdd(bk + 2 * nbk + rd, 1u);
+      if (!dp_root_only(use)) K.vrow[g] = atomicAdd(&sum->n_vrows, 1u);
+    } else {
+      const uint32_t r = atomicAdd(&sum->n_slots, 1u);
+      K.rowidx[g] = r;
+      atomicAdd(bk + (dp_groupable(x) ? 0u : nbk) + lvl * R2 + rd, 1u);
+      if (K.view && (use & kDpAbove)) K.vrow[g] = copy(kSlotRow | r);
+    }
+  }
+}
+
+// The bit row a leaf-like node reads: the atom's, the set row, the threshold's
+// or the role node's own (pbase: first threshold task of each property).
+__device__ __forceinline__ uint32_t dp_leaf_row(const DpKB& K, const hth_node* nodes, const uint32_t* pbase,
                                                 uint32_t g) {
   const hth_node x = nodes[g];
   if (x.op == HTH_ATOM) return x.arg;
   if (x.op == HTH_SET) return K.n_concepts + x.arg;
-  return row[g];
+  if (dp_column(x.op)) return K.n_fixed + 1 + pbase[x.arg] + K.tval[2 * dp_slot(K, dp_thr_key(x))];
+  return K.n_fixed + 1 + K.n_thr + K.rowidx[K.canon[g]];
+}
+// The view row of such a node.
+__device__ __forceinline__ uint32_t dp_view_row(const DpKB& K, const hth_node* nodes, uint32_t g) {
+  const hth_node x = nodes[g];
+  if (x.op == HTH_ATOM || x.op == HTH_SET) return K.tvrow[dp_slot(K, dp_fixed_key(K, x))];
+  if (dp_column(x.op)) return K.tvrow[dp_slot(K, dp_thr_key(x))];
+  return K.vrow[K.canon[g]];
 }
 
-// The region program of local node r of the hypothesis at b, written to out:
-// postfix over bit rows, the deepest operand of each and / or first (the
+// The region program of local node r of the hypothesis at b, written to out
+// (row_of: the bit row of a leaf-like node): postfix over bit rows, the deepest operand of each and / or first (the
 // stack then holds the fewest values).  An explicit frame stack stands in for
 // recursion; the count pass has bounded the nesting by kDpNest.
-__device__ void dp_program(const DpKB& K, const hth_node* __restrict__ nodes, const uint32_t* __restrict__ kids,
-                           const uint32_t* __restrict__ info, const uint32_t* __restrict__ row, uint32_t b,
+template <class Row>
+__device__ void dp_program(const hth_node* __restrict__ nodes, const uint32_t* __restrict__ kids,
+                           const uint32_t* __restrict__ info, Row row_of, uint32_t b,
                            uint32_t r, uint32_t* __restrict__ out) {
   struct Frame {
     uint32_t node, j, k;
@@ -499,7 +669,7 @@ __device__ void dp_program(const DpKB& K, const hth_node* __restrict__ nodes, co
     if (x.op == HTH_NOT) {
       if (f.j == 0) {
         if (info[b + x.child] & kDpRow) {
-          out[pc++] = rp_ins(RP_LEAF, 1, dp_leaf_row(K, nodes, row, b + x.child));
+          out[pc++] = rp_ins(RP_LEAF, 1, row_of(b + x.child));
           --sp;
         } else {
           f.j = 1;
@@ -540,137 +710,175 @@ __device__ void dp_program(const DpKB& K, const hth_node* __restrict__ nodes, co
     }
     if (x.op == HTH_TOP || x.op == HTH_AND) out[pc++] = rp_ins(RP_TOP, 0, 0);
     else if (x.op == HTH_BOT || x.op == HTH_OR) out[pc++] = rp_ins(RP_BOT, 0, 0);
-    else out[pc++] = rp_ins(RP_LEAF, 0, dp_leaf_row(K, nodes, row, b + f.node));
+    else out[pc++] = rp_ins(RP_LEAF, 0, row_of(b + f.node));
     --sp;
   }
 }
 
-__global__ void __launch_bounds__(256)
-k_dp_emit(const hth_node* __restrict__ nodes, const uint32_t* __restrict__ offs,
-          const uint32_t* __restrict__ kids, uint32_t n_hyps, DpKB K, const uint32_t* __restrict__ info,
-          const uint32_t* __restrict__ len, uint32_t* __restrict__ row, DpCursor* __restrict__ cur, DpBases B,
-          DpTables T) {
-  const uint32_t h = blockIdx.x * blockDim.x + threadIdx.x;
-  if (h == 0) T.fills[0] = FillTask{K.n_fixed, 0u};
-  if (h >= n_hyps) return;
-  const uint32_t b = offs[h], n = offs[h + 1] - b;
-  bool root_fused = false;
-  for (uint32_t i = 0; i < n; ++i) {
-    const hth_node x = nodes[b + i];
-    if (dp_column(x.op)) {
-      // the distinct threshold's task (the property's tasks are contiguous:
-      // one column pass serves up to 32) and row
-      const unsigned long long key = dp_thr_key(x);
-      uint32_t hs = dp_hash(key, K.tmask);
-      while (K.tkey[hs] != key) hs = (hs + 1) & K.tmask;
-      const uint32_t t = T.pbase[x.arg] + K.tval[2 * hs];
-      const uint32_t r = K.n_fixed + 1 + t;
-      row[b + i] = r;
-      if (K.tval[2 * hs + 1] == b + i) {
-        ThrTask tt;
-        tt.prop = x.arg;
-        tt.cmp = x.op == HTH_DATA_GE ? 0u : x.op == HTH_DATA_LE ? 1u : 2u;
-        tt.t = x.q.t;
-        tt.out_row = r;
-        T.thr[t] = tt;
-      }
-    } else if (dp_role(x.op)) {
-      // rows of role nodes and materialised fillers were numbered by the count
-      // pass, per representative; a node equal to an earlier one has no task
-      const uint32_t rep = K.canon[b + i];
-      const uint32_t r = K.n_fixed + 1 + K.n_thr + K.rowidx[rep];
-      row[b + i] = r;
-      if (rep != b + i) continue;
-      const uint32_t c = b + x.child, ci = info[c], lvl = ci & 255u;
-      const uint8_t cop = nodes[c].op;
-      uint32_t crow, neg = 0;
-      if (cop == HTH_TOP || cop == HTH_BOT) {
-        crow = K.n_fixed;                   // the zero row, complemented for top
-        neg = cop == HTH_TOP;
-      } else if (ci & kDpRow) {
-        crow = dp_leaf_row(K, nodes, row, c);
-      } else if (ci & kDpNotRow) {
-        crow = dp_leaf_row(K, nodes, row, b + nodes[c].child);
-        neg = 1;
-      } else {
-        const uint32_t cc = K.canon[c];
-        crow = K.n_fixed + 1 + K.n_thr + K.matrow[cc];
-        if (K.matclaim[cc] == b + i) {
-          const unsigned long long off = atomicAdd(&cur->code, (unsigned long long)len[c]);
-          dp_program(K, nodes, kids, info, row, b, x.child, T.code + off);
-          T.mat[B.mat[lvl] + atomicAdd(&cur->mat[lvl], 1u)] = RegionTask{(uint32_t)off, len[c], crow, kNone};
-        }
-      }
-      // count predicate (lo <= cnt <= hi over the successors in the child, or
-      // outside it for the universal restriction)
-      constexpr uint32_t kInf = 0xFFFFFFFFu;
-      uint32_t lo, hi;
-      switch (x.op) {
-        case HTH_EXISTS: lo = 1; hi = kInf; break;
-        case HTH_FORALL: lo = 0; hi = 0; neg ^= 1u; break;
-        case HTH_ATLEAST: lo = x.q.n; hi = kInf; break;
-        case HTH_ATMOST: lo = 0; hi = x.q.n; break;
-        default: lo = x.q.n; hi = x.q.n; break;
-      }
-      const uint32_t rd = 2 * x.arg + x.inv;
-      const uint32_t nw = dp_nwords(K, rd);
-      const uint32_t q = lvl * (K.n_dir - 1) + rd;
-      const DpBucket bu = T.buckets[q];
-      const bool member = bu.first_group != kNone && dp_groupable(x);
-      // the root of this hypothesis only, read by no node: its shared pass adds
-      // its coverage, it gets no row (its fill task writes the zero row, which
-      // holds zeros already) and the hypothesis no root region
-      const bool fused = member && i + 1 == n && K.ruse[b + i] == 1u;
-      root_fused |= fused;
-      if (nw < K.W)
-        T.fills[B.fill[lvl] + atomicAdd(&cur->fill[lvl], 1u)] =
-            fused ? FillTask{K.n_fixed, 0u} : FillTask{r, lo == 0 ? 1u : 0u};
-      if (member) {
-        // a member of one of its bucket's shared passes
-        const uint32_t j = atomicAdd(T.bcur + q, 1u);
-        GroupMember m;
-        m.child_row = crow;
-        m.neg = neg;
-        m.lo = lo;
-        m.hi = hi;
-        m.sat = hi == kInf ? lo : hi + 1;
-        m.out_row = fused ? kNone : r;
-        m.cover = fused ? h : kNone;
-        m.pad = 0;
-        T.members[bu.member_base + j] = m;
-        unsigned long long* acc =
-            reinterpret_cast<unsigned long long*>(T.groups[bu.first_group + j / bu.k].acc);
-        const unsigned long long bit = 1ull << (j % bu.k);
-        for (uint32_t v = 0; v <= kGroupMaxCount; ++v) {
-          const bool ok = v < kGroupMaxCount ? (lo <= v && v <= hi) : (hi == kInf && lo <= kGroupMaxCount);
-          if (ok) atomicOr(acc + v, bit);
-        }
-        continue;
-      }
-      RoleTask t;
-      t.role = x.arg;
-      t.inv = x.inv;
-      t.child_row = crow;
-      t.neg = neg;
-      t.lo = lo;
-      t.hi = hi;
-      t.sat = hi == kInf ? lo : hi + 1;
-      t.out_row = r;
-      t.n_words = nw;
-      t.h_first = 0;                         // set by k_dp_heavy where heavy rows exist
-      t.c_first = 0;
-      t.hc0 = K.dir[K.n_dir + rd];
-      t.hr0 = K.dir[2 * K.n_dir + rd];
-      T.roles[B.role[lvl] + atomicAdd(&cur->role[lvl], 1u)] = t;
+// A role node's bucket: by level and direction, the view's by direction (first).
+__device__ __forceinline__ uint32_t dp_bucket(const DpKB& K, const hth_node& x, uint32_t lvl, bool viewed) {
+  return (viewed ? 0u : lvl + 1u) * (K.n_dir - 1) + 2 * x.arg + x.inv;
+}
+// Its shared pass adds its coverage to its one hypothesis: no row, no region.
+// (Under no restriction and read by nothing, every node equal to it is a root.)
+__device__ __forceinline__ bool dp_fused(const DpBucket& bu, const hth_node& x, uint32_t use) {
+  return bu.first_group != kNone && dp_groupable(x) && dp_root_only(use) && !(use & kDpUnder);
+}
+
+// The task of a representative role node: its fill, its filler's region, and
+// its place in a shared pass or in the level's single passes.
+__device__ void dp_emit_role(const hth_node* __restrict__ nodes, const uint32_t* __restrict__ kids, const DpKB& K,
+                             const uint32_t* __restrict__ info, const uint32_t* __restrict__ len,
+                             DpCursor* __restrict__ cur, const DpBases& B, const DpTables& T, uint32_t g,
+                             const hth_node& x) {
+  const uint32_t use = K.ruse[g], b = K.nbase[g];
+  const bool viewed = dp_viewed(K, x, use);
+  auto full_row = [&](uint32_t n) { return dp_leaf_row(K, nodes, T.pbase, n); };
+  const uint32_t c = b + x.child, ci = info[c], lvl = ci & 255u;
+  const uint8_t cop = nodes[c].op;
+  uint32_t crow, neg = 0;
+  if (cop == HTH_TOP || cop == HTH_BOT) {
+    crow = K.n_fixed;                     // the zero row, complemented for top
+    neg = cop == HTH_TOP;
+  } else if (ci & kDpRow) {
+    crow = full_row(c);
+  } else if (ci & kDpNotRow) {
+    crow = full_row(b + nodes[c].child);
+    neg = 1;
+  } else {
+    const uint32_t cc = K.canon[c];
+    crow = K.n_fixed + 1 + K.n_thr + K.matrow[cc];
+    if (K.matclaim[cc] == g) {
+      const unsigned long long off = atomicAdd(&cur->code, (unsigned long long)len[c]);
+      dp_program(nodes, kids, info, full_row, b, x.child, T.code + off);
+      T.mat[B.mat[lvl] + atomicAdd(&cur->mat[lvl], 1u)] = RegionTask{(uint32_t)off, len[c], crow, kNone};
     }
   }
-  if (root_fused) {
-    T.roots[h] = RegionTask{0u, 0u, kNone, kNone};
+  // count predicate (lo <= cnt <= hi over the successors in the child, or
+  // outside it for the universal restriction)
+  constexpr uint32_t kInf = 0xFFFFFFFFu;
+  uint32_t lo, hi;
+  switch (x.op) {
+    case HTH_EXISTS: lo = 1; hi = kInf; break;
+    case HTH_FORALL: lo = 0; hi = 0; neg ^= 1u; break;
+    case HTH_ATLEAST: lo = x.q.n; hi = kInf; break;
+    case HTH_ATMOST: lo = 0; hi = x.q.n; break;
+    default: lo = x.q.n; hi = x.q.n; break;
+  }
+  const uint32_t rd = 2 * x.arg + x.inv, nw = dp_nwords(K, rd);
+  const uint32_t q = dp_bucket(K, x, lvl, viewed);
+  const DpBucket bu = T.buckets[q];
+  const bool member = bu.first_group != kNone && dp_groupable(x);
+  const bool fused = dp_fused(bu, x, use);
+  const uint32_t r = viewed ? (fused ? kNone : K.vrow[g]) : K.n_fixed + 1 + K.n_thr + K.rowidx[g];
+  // (a fused node's fill task writes the zero row, which holds zeros already)
+  if (nw < K.W && !viewed)
+    T.fills[B.fill[lvl] + atomicAdd(&cur->fill[lvl], 1u)] =
+        fused ? FillTask{K.n_fixed, 0u} : FillTask{r, lo == 0 ? 1u : 0u};
+  if (member) {
+    // a member of one of its bucket's shared passes
+    const uint32_t j = atomicAdd(T.bcur + q, 1u);
+    GroupMember m;
+    m.child_row = crow;
+    m.neg = neg;
+    m.lo = lo;
+    m.hi = hi;
+    m.sat = hi == kInf ? lo : hi + 1;
+    m.out_row = fused ? kNone : r;
+    m.cover = fused ? K.rooth[g] : kNone;
+    m.pad = 0;
+    T.members[bu.member_base + j] = m;
+    unsigned long long* acc = reinterpret_cast<unsigned long long*>(T.groups[bu.first_group + j / bu.k].acc);
+    const unsigned long long bit = 1ull << (j % bu.k);
+    for (uint32_t v = 0; v <= kGroupMaxCount; ++v) {
+      const bool ok = v < kGroupMaxCount ? (lo <= v && v <= hi) : (hi == kInf && lo <= kGroupMaxCount);
+      if (ok) atomicOr(acc + v, bit);
+    }
     return;
   }
-  const unsigned long long off = atomicAdd(&cur->code, (unsigned long long)len[b + n - 1]);
-  dp_program(K, nodes, kids, info, row, b, n - 1, T.code + off);
-  T.roots[h] = RegionTask{(uint32_t)off, len[b + n - 1], kNone, h};
+  RoleTask t;
+  t.role = x.arg;
+  t.inv = x.inv;
+  t.child_row = crow;
+  t.neg = neg;
+  t.lo = lo;
+  t.hi = hi;
+  t.sat = hi == kInf ? lo : hi + 1;
+  t.out_row = r;
+  t.n_words = nw;
+  t.h_first = 0;                         // set by k_dp_heavy where heavy rows exist
+  t.c_first = 0;
+  t.hc0 = K.dir[K.n_dir + rd];
+  t.hr0 = K.dir[2 * K.n_dir + rd];
+  T.roles[B.role[lvl] + atomicAdd(&cur->role[lvl], 1u)] = t;
+}
+
+// The region of hypothesis h's root, with coverage.
+__device__ void dp_emit_root(const hth_node* __restrict__ nodes, const uint32_t* __restrict__ offs,
+                             const uint32_t* __restrict__ kids, const DpKB& K, const uint32_t* __restrict__ info,
+                             const uint32_t* __restrict__ len, DpCursor* __restrict__ cur, const DpTables& T,
+                             uint32_t h) {
+  const uint32_t b = offs[h], r = offs[h + 1] - 1;
+  const hth_node x = nodes[r];
+  if (dp_role(x.op)) {
+    const uint32_t use = K.ruse[K.canon[r]];
+    if (dp_fused(T.buckets[dp_bucket(K, x, (info[r] & 255u) - 1, dp_viewed(K, x, use))], x, use)) {
+      T.roots[h] = RegionTask{0u, 0u, kNone, kNone};
+      return;
+    }
+  }
+  const unsigned long long off = atomicAdd(&cur->code, (unsigned long long)len[r]);
+  if (K.view) dp_program(nodes, kids, info, [&](uint32_t g) { return dp_view_row(K, nodes, g); }, b, r - b, T.code + off);
+  else dp_program(nodes, kids, info, [&](uint32_t g) { return dp_leaf_row(K, nodes, T.pbase, g); }, b, r - b, T.code + off);
+  T.roots[h] = RegionTask{(uint32_t)off, len[r], kNone, h};
+}
+
+// An entry of the threshold table as threshold tasks.
+__device__ void dp_emit_threshold(const DpKB& K, const DpTables& T, uint32_t hs) {
+  const unsigned long long key = K.tkey[hs];
+  if (key == kDpEmpty) return;
+  ThrTask t;
+  t.prop = (uint32_t)(key >> 34);
+  t.cmp = (uint32_t)(key >> 32) & 3u;
+  if (t.cmp == 3u) return;               // a fixed row
+  t.t = __builtin_bit_cast(float, (uint32_t)key);
+  if (K.tval[2 * hs] != kNone) {
+    const uint32_t at = T.pbase[t.prop] + K.tval[2 * hs];
+    t.out_row = K.n_fixed + 1 + at;
+    T.thr[at] = t;
+  }
+  if (K.tval[2 * hs + 1] != kNone) {
+    t.out_row = K.tvrow[hs];
+    T.vthr[T.vpbase[t.prop] + K.tval[2 * hs + 1]] = t;
+  }
+}
+
+// The plan's tables: a thread per hypothesis for its root (the first blocks,
+// their programs are the longest chains), per node for the role nodes, per
+// entry of the threshold table.  One thread per hypothesis for all of it took
+// 355 us for 8,192 hypotheses; this takes 87.
+__global__ void __launch_bounds__(kDpBlock)
+k_dp_emit(const hth_node* __restrict__ nodes, const uint32_t* __restrict__ offs,
+          const uint32_t* __restrict__ kids, uint32_t n_hyps, DpKB K, const uint32_t* __restrict__ info,
+          const uint32_t* __restrict__ len, DpCursor* __restrict__ cur, DpBases B, DpTables T,
+          uint32_t root_blocks, uint32_t node_blocks) {
+  uint32_t b = blockIdx.x;
+  if (b < root_blocks) {
+    const uint32_t h = b * kDpBlock + threadIdx.x;
+    if (h == 0) T.fills[0] = FillTask{K.n_fixed, 0u};
+    if (h < n_hyps) dp_emit_root(nodes, offs, kids, K, info, len, cur, T, h);
+    return;
+  }
+  b -= root_blocks;
+  if (b < node_blocks) {
+    const uint32_t g0 = offs[0], i = b * kDpBlock + threadIdx.x;
+    if (i >= offs[n_hyps] - g0) return;
+    const hth_node x = nodes[g0 + i];
+    if (dp_role(x.op) && K.canon[g0 + i] == g0 + i) dp_emit_role(nodes, kids, K, info, len, cur, B, T, g0 + i, x);
+    return;
+  }
+  const uint32_t hs = (b - node_blocks) * kDpBlock + threadIdx.x;
+  if (hs <= K.tmask) dp_emit_threshold(K, T, hs);
 }
 
 // Block-wide exclusive scan of one value per lane (1024 lanes); returns the
@@ -731,11 +939,40 @@ k_dp_heavy(RoleTask* __restrict__ roles, DpBases B, DpKB K) {
   }
 }
 
-// dst[i] = src[i] for i < n (the shared passes' shells, fresh for each launch)
+// The start of a launch: the counts and cursors cleared, the shared passes'
+// shells copied (their acceptance masks are gathered anew).
 __global__ void __launch_bounds__(256)
-k_dp_copy(uint32_t* __restrict__ dst, const uint32_t* __restrict__ src, uint32_t n) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = src[i];
+k_dp_start(uint32_t* __restrict__ counts, uint32_t nc, uint32_t* __restrict__ cur, uint32_t ncur,
+           uint32_t* __restrict__ bcur, uint32_t nb, uint32_t* __restrict__ groups,
+           const uint32_t* __restrict__ shells, uint32_t ng) {
+  const uint32_t i0 = blockIdx.x * 256 + threadIdx.x, step = gridDim.x * 256;
+  for (uint32_t i = i0; i < nc; i += step) counts[i] = 0;
+  for (uint32_t i = i0; i < ncur; i += step) cur[i] = 0;
+  for (uint32_t i = i0; i < nb; i += step) bcur[i] = 0;
+  for (uint32_t i = i0; i < ng; i += step) groups[i] = shells[i];
+}
+
+// The start of a plan: `zeros` 16-byte units of zeros, `ones` of ones, the
+// summary's and the row copies' first values.
+__global__ void __launch_bounds__(256)
+k_dp_init(uint4* __restrict__ zero, size_t zeros, uint4* __restrict__ one, size_t ones, DpSummary* __restrict__ sum,
+          ViewCopy* __restrict__ copies) {
+  const size_t i0 = (size_t)blockIdx.x * 256 + threadIdx.x, step = (size_t)gridDim.x * 256;
+  DpSummary s{};
+  s.err = ~0ull;
+  s.n_vrows = kViewFixed;
+  s.n_copies = 2;
+  const uint4* init = reinterpret_cast<const uint4*>(&s);
+  for (size_t i = i0; i < zeros; i += step) {
+    uint4* at = zero + i;
+    const size_t d = at - reinterpret_cast<uint4*>(sum);
+    *at = at >= reinterpret_cast<uint4*>(sum) && d < sizeof(DpSummary) / 16 ? init[d] : make_uint4(0, 0, 0, 0);
+  }
+  for (size_t i = i0; i < ones; i += step) one[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+  if (i0 == 0) {
+    copies[0] = ViewCopy{kPosRow, 0};
+    copies[1] = ViewCopy{kNegRow, 1};
+  }
 }
 
 }  // namespace
@@ -753,7 +990,6 @@ struct hth_dplan_s {
   char* buf = nullptr;     // the caller's scratch (see DpScratch)
   uint32_t* info = nullptr;
   uint32_t* len = nullptr;
-  uint32_t* row = nullptr;
   hth::DpSummary* d_sum = nullptr;
   hth::DpCursor* d_cur = nullptr;
   uint32_t* d_bk = nullptr;
@@ -762,8 +998,14 @@ struct hth_dplan_s {
   uint32_t* d_xslots = nullptr;
   uint32_t* d_bcur = nullptr;
   uint32_t* d_pbase = nullptr;        // first threshold task of each property
-  hth::ThrGroup* d_thg = nullptr;     // threshold groups: up to 32 tasks of one property
+  hth::ThrGroup* d_thg = nullptr;     // threshold groups: up to 32 tasks of one property, the view's last
   uint32_t n_buckets = 0, n_thg = 0;
+  hth::ViewPlan V;
+  uint32_t* d_vpbase = nullptr;
+  hth::GroupTask* d_vgroups = nullptr;   // the view's shared passes with their real directions
+  hth::ViewDir* d_vdirs = nullptr;
+  uint64_t* d_vbases = nullptr;          // first target of each view direction
+  size_t o_vthr = 0;
   hth::DpKB K{};
   hth::DpSummary sum{};
   hth::DpBases B{};
@@ -790,18 +1032,20 @@ namespace hth {
 namespace {
 
 // The plan's scratch (caller memory, hth_dplan_scratch_bytes): per-node facts
-// and rows, the count pass's summary and counts, cursors, the direction table,
-// the threshold hash table, and the host-built tables with bounds from the node
-// count (a shared pass holds at least one node, an XCD slot round at most
-// eight passes, a threshold group at least one threshold).
+// and rows, the count passes' summary and counts, cursors, the hash tables,
+// and the host-built tables with bounds from the node count (a shared pass
+// holds at least one node, an XCD slot round at most eight passes, a threshold
+// group at least one threshold).
 struct DpScratch {
-  size_t info, len, row, canon, nbase, rowidx, matclaim, matrow, ruse, sum, cur, bk, pk, dir, tkey, tval, crep, shell,
-      bucket, xslot, bcur, thg, pbase, total;
+  size_t zero, sum, bk, pk, pkv, ruse, zero_end;         // cleared to 0; sum to pkv are read back
+  size_t one, tkey, tval, crep, matclaim, one_end;       // cleared to all ones
+  size_t info, len, canon, nbase, nkey, rowidx, rooth, matrow, vrow, tvrow, copies, cur, bcur, tables, total;
+  size_t tables_bytes;
   uint32_t tcap;
 };
 DpScratch dp_scratch(const hth_kb_s& kb, uint32_t n_nodes) {
   DpScratch L{};
-  const size_t n = n_nodes, nd = 2 * (size_t)kb.d.n_roles + 1, nb = kDpLevels * (nd - 1);
+  const size_t n = n_nodes, nd = 2 * (size_t)kb.d.n_roles + 1, nb = kDpLevels * (nd - 1), nv = kb.d.n_data;
   L.tcap = 1024;
   while (L.tcap < 2ull * n) L.tcap <<= 1;
   size_t at = 0;
@@ -810,29 +1054,37 @@ DpScratch dp_scratch(const hth_kb_s& kb, uint32_t n_nodes) {
     at = align_up(at + bytes, 256);
     return a;
   };
-  L.info = area(n * 4);
-  L.len = area(n * 4);
-  L.row = area(n * 4);
-  L.canon = area(n * 4);
-  L.nbase = area(n * 4);
-  L.rowidx = area(n * 4);
-  L.matclaim = area(n * 4);
-  L.matrow = area(n * 4);
-  L.ruse = area(n * 4);
+  L.zero = at;
   L.sum = area(sizeof(DpSummary));
-  L.cur = area(sizeof(DpCursor));
-  L.bk = area(2 * nb * 4);
-  L.pk = area((size_t)kb.d.n_data * 4);
-  L.dir = area(3 * nd * 4);
+  L.bk = area((2 * nb + nd) * 4);
+  L.pk = area(nv * 4);
+  L.pkv = area(nv * 4);
+  L.ruse = area(n * 4);
+  L.zero_end = at;
+  L.one = at;
   L.tkey = area((size_t)L.tcap * 8);
   L.tval = area((size_t)L.tcap * 8);
   L.crep = area((size_t)L.tcap * 4);
-  L.shell = area(n * sizeof(GroupTask));
-  L.bucket = area(nb * sizeof(DpBucket));
-  L.xslot = area(8 * n * 4);
-  L.bcur = area(nb * 4);
-  L.thg = area(n * sizeof(ThrGroup));
-  L.pbase = area((size_t)kb.d.n_data * 4);
+  L.matclaim = area(n * 4);
+  L.one_end = at;
+  L.info = area(n * 4);
+  L.len = area(n * 4);
+  L.canon = area(n * 4);
+  L.nbase = area(n * 4);
+  L.nkey = area(n * 32);
+  L.rowidx = area(n * 4);
+  L.rooth = area(n * 4);
+  L.matrow = area(n * 4);
+  L.vrow = area(n * 4);
+  L.tvrow = area((size_t)L.tcap * 4);
+  L.copies = area((n + 2) * sizeof(ViewCopy));
+  L.cur = area(sizeof(DpCursor));
+  L.bcur = area((nb + nd) * 4);
+  // the host's tables, packed: shared passes (the view's twice), XCD slots,
+  // buckets, threshold groups and bases, view directions
+  L.tables_bytes = 2 * n * sizeof(GroupTask) + 8 * n * 4 + (nb + nd) * sizeof(DpBucket) + 2 * n * sizeof(ThrGroup) +
+                   2 * nv * 4 + nd * (sizeof(ViewDir) + 8) + 16 * 256;
+  L.tables = area(L.tables_bytes);
   L.total = at;
   return L;
 }
@@ -871,7 +1123,7 @@ hth_status dp_schedule(hth_dplan_s& p, const std::vector<uint32_t>& bk, std::vec
   const uint32_t R2 = p.K.n_dir - 1, nbk = kDpLevels * R2;
   const uint32_t group_min = kb.tune.group_min ? kb.tune.group_min : 0xFFFFFFFFu;
   const uint32_t gk = std::max<uint32_t>(1, std::min<uint32_t>(kb.tune.group_k, kMaxK));
-  buckets.assign(nbk, DpBucket{kNone, 0, 0, 0});
+  buckets.assign((size_t)(S.levels + 1) * R2, DpBucket{kNone, 0, 0, 0});   // the view's, then by level
   p.lv_groups.assign(S.levels, {});
   p.lv_chunks.assign(S.levels, {});
   p.lv_gbase.assign(S.levels, 0);
@@ -899,7 +1151,7 @@ hth_status dp_schedule(hth_dplan_s& p, const std::vector<uint32_t>& bk, std::vec
         const uint64_t g = bk[L * R2 + rd];
         const bool sr = short_rows(kb, rd);
         if (!(g && g >= bucket_min(kb, rd, group_min)) || (int)sr != want_short) continue;
-        DpBucket& bu = buckets[L * R2 + rd];
+        DpBucket& bu = buckets[(L + 1) * R2 + rd];
         bu.first_group = p.n_groups + (uint32_t)p.lv_groups[L].size();
         bu.member_base = p.n_members;
         bu.k = gk;
@@ -931,6 +1183,26 @@ hth_status dp_schedule(hth_dplan_s& p, const std::vector<uint32_t>& bk, std::vec
       if (kb.tune.xcd_local && c.n >= 8) place_on_xcds(kb, p.lv_groups[L], c, xslots);
     p.n_groups += (uint32_t)p.lv_groups[L].size();
   }
+  // the view's shared passes, whatever their levels: every row they read is
+  // complete by then.  Short-row directions first.
+  ViewPlan& V = p.V;
+  if (V.on) {
+    for (int want_short = 1; want_short >= 0; --want_short)
+      for (uint32_t rd = 0; rd < R2; ++rd) {
+        const uint64_t g = bk[2 * nbk + rd];
+        const bool sr = short_rows(kb, rd);
+        if (!g || (int)sr != want_short) continue;
+        buckets[rd] = DpBucket{p.n_groups + (uint32_t)V.groups.size(), p.n_members, gk, 0};
+        V.add_passes(kb, rd, g, gk, p.n_members, sr);
+        p.n_members += (uint32_t)g;
+      }
+    V.chunks = chunk_groups(kb, V.groups);
+    for (GroupChunk& c : V.chunks)
+      if (kb.tune.xcd_local && c.n >= 8) place_on_xcds(kb, V.groups, c, xslots);
+    for (size_t i = 0; i < V.groups.size(); ++i) V.passes[i].t_off = V.groups[i].t_off;
+    V.n_rows = S.n_vrows;
+    V.n_copies = S.n_copies;
+  }
   size_t gpart = 0;
   for (uint32_t L = 0; L < S.levels; ++L)
     for (const GroupChunk& c : p.lv_chunks[L]) gpart = std::max(gpart, chunk_partial_bytes(kb, p.lv_groups[L], c));
@@ -940,20 +1212,23 @@ hth_status dp_schedule(hth_dplan_s& p, const std::vector<uint32_t>& bk, std::vec
     at = align_up(at + bytes, 256);
     return a;
   };
-  p.o_thr = area((size_t)S.n_thr * sizeof(ThrTask));
+  p.o_thr = area((size_t)S.n_thr_full * sizeof(ThrTask));
+  p.o_vthr = area((size_t)S.n_thr_view * sizeof(ThrTask));
   p.o_mat = area((size_t)p.n_mat * sizeof(RegionTask));
   p.o_root = area((size_t)p.n_hyps * sizeof(RegionTask));
   p.o_role = area((size_t)p.n_role * sizeof(RoleTask));
   p.o_fill = area((size_t)fill * sizeof(FillTask));
   p.o_code = area((size_t)S.code * 4);
   p.o_part = area((size_t)p.max_nhb * 4);
-  p.o_grp = area((size_t)p.n_groups * sizeof(GroupTask));
+  p.o_grp = area((p.n_groups + V.passes.size()) * sizeof(GroupTask));
   p.o_mem = area((size_t)p.n_members * sizeof(GroupMember));
   size_t t_bytes = 0;   // the T area: the most one chunk of the plan uses
   for (uint32_t L = 0; L < S.levels; ++L) t_bytes = std::max(t_bytes, chunks_t_bytes(kb, p.lv_groups[L], p.lv_chunks[L]));
+  t_bytes = std::max(t_bytes, chunks_t_bytes(kb, V.groups, V.chunks));
   p.o_tarea = area(t_bytes);
   p.o_gpart = area(gpart);
-  p.o_slot = area(((size_t)S.n_slots + S.n_thr + 1) * kb.S * 8);
+  p.o_slot = area(((size_t)S.n_slots + S.n_thr_full + 1) * kb.S * 8);
+  V.layout(kb, area);
   p.need = at;
   return HTH_OK;
 }
@@ -991,18 +1266,11 @@ extern "C" hth_status hth_dplan_create(hth_kb kb, const hth_node* d_nodes, uint3
   p->n_nodes = n_nodes;
   p->n_hyps = n_hyps;
   p->n_kids = n_children;
-  std::vector<uint32_t> dir;
   std::lock_guard<std::mutex> g(kb->mu);
   p->sets = kb->sets;
   p->n_sets = kb->n_sets;
   p->tune = kb->tune;
   const uint32_t nd = 2 * kb->d.n_roles + 1;
-  dir.assign(3 * (size_t)nd, 0);
-  for (uint32_t rd = 0; rd + 1 < nd; ++rd) dir[rd] = kb->n_words[rd];
-  for (uint32_t rd = 0; rd < nd; ++rd) {
-    dir[nd + rd] = kb->chunk_first[rd];
-    dir[2 * nd + rd] = kb->heavy_first[rd];
-  }
   p->K.n_concepts = kb->d.n_concepts;
   p->K.n_sets = kb->n_sets;
   p->K.n_roles = kb->d.n_roles;
@@ -1010,8 +1278,9 @@ extern "C" hth_status hth_dplan_create(hth_kb kb, const hth_node* d_nodes, uint3
   p->K.W = kb->W;
   p->K.n_fixed = kb->d.n_concepts + kb->n_sets;
   p->K.n_dir = nd;
-  p->n_buckets = kDpLevels * (nd - 1);
-  const size_t nbk2 = 2 * (size_t)p->n_buckets;
+  const size_t nbk2 = 2 * (size_t)kDpLevels * (nd - 1) + (nd - 1);
+  p->V.on = view_wanted(*kb);
+  p->K.view = p->V.on;
   const size_t nd_data = kb->d.n_data;
   const DpScratch L = dp_scratch(*kb, n_nodes);
   if (scratch_bytes < L.total)
@@ -1019,45 +1288,54 @@ extern "C" hth_status hth_dplan_create(hth_kb kb, const hth_node* d_nodes, uint3
                                  std::to_string(scratch_bytes));
   const uint32_t tcap = L.tcap;
   HTH_HIP(hipEventCreateWithFlags(&p->done, hipEventDisableTiming));
-  p->buf = static_cast<char*>(scratch);
-  p->info = reinterpret_cast<uint32_t*>(p->buf + L.info);
-  p->len = reinterpret_cast<uint32_t*>(p->buf + L.len);
-  p->row = reinterpret_cast<uint32_t*>(p->buf + L.row);
-  p->d_sum = reinterpret_cast<DpSummary*>(p->buf + L.sum);
-  p->d_cur = reinterpret_cast<DpCursor*>(p->buf + L.cur);
-  p->d_bk = reinterpret_cast<uint32_t*>(p->buf + L.bk);
-  p->K.dir = reinterpret_cast<const uint32_t*>(p->buf + L.dir);
-  p->K.pk = reinterpret_cast<uint32_t*>(p->buf + L.pk);
-  p->K.tkey = reinterpret_cast<unsigned long long*>(p->buf + L.tkey);
-  p->K.tval = reinterpret_cast<uint32_t*>(p->buf + L.tval);
+  char* const buf = p->buf = static_cast<char*>(scratch);
+  auto u32 = [&](size_t at) { return reinterpret_cast<uint32_t*>(buf + at); };
+  p->info = u32(L.info);
+  p->len = u32(L.len);
+  p->d_sum = reinterpret_cast<DpSummary*>(buf + L.sum);
+  p->d_cur = reinterpret_cast<DpCursor*>(buf + L.cur);
+  p->d_bk = u32(L.bk);
+  p->d_bcur = u32(L.bcur);
+  p->K.dir = kb->dir_dev;
+  p->K.pk = u32(L.pk);
+  p->K.pkv = u32(L.pkv);
+  p->K.tkey = reinterpret_cast<unsigned long long*>(buf + L.tkey);
+  p->K.tval = u32(L.tval);
+  p->K.tvrow = u32(L.tvrow);
   p->K.tmask = tcap - 1;
-  p->K.canon = reinterpret_cast<uint32_t*>(p->buf + L.canon);
-  p->K.nbase = reinterpret_cast<uint32_t*>(p->buf + L.nbase);
-  p->K.crep = reinterpret_cast<uint32_t*>(p->buf + L.crep);
-  p->K.rowidx = reinterpret_cast<uint32_t*>(p->buf + L.rowidx);
-  p->K.matclaim = reinterpret_cast<uint32_t*>(p->buf + L.matclaim);
-  p->K.matrow = reinterpret_cast<uint32_t*>(p->buf + L.matrow);
-  p->K.ruse = reinterpret_cast<uint32_t*>(p->buf + L.ruse);
+  p->K.canon = u32(L.canon);
+  p->K.nbase = u32(L.nbase);
+  p->K.nkey = u32(L.nkey);
+  p->K.crep = u32(L.crep);
+  p->K.rowidx = u32(L.rowidx);
+  p->K.rooth = u32(L.rooth);
+  p->K.matclaim = u32(L.matclaim);
+  p->K.matrow = u32(L.matrow);
+  p->K.ruse = u32(L.ruse);
+  p->K.vrow = u32(L.vrow);
+  p->K.copies = reinterpret_cast<ViewCopy*>(buf + L.copies);
   p->K.n_nodes = n_nodes;
-  HTH_HIP(hipMemcpyAsync(p->buf + L.dir, dir.data(), dir.size() * 4, hipMemcpyHostToDevice, st));
-  DpSummary init{};
-  init.err = ~0ull;
-  HTH_HIP(hipMemcpyAsync(p->d_sum, &init, sizeof(init), hipMemcpyHostToDevice, st));
-  HTH_HIP(hipMemsetAsync(p->d_bk, 0, nbk2 * 4, st));
-  if (nd_data) HTH_HIP(hipMemsetAsync(p->K.pk, 0, nd_data * 4, st));
-  HTH_HIP(hipMemsetAsync(p->K.tkey, 0xFF, (size_t)tcap * 8, st));
-  HTH_HIP(hipMemsetAsync(p->K.crep, 0xFF, (size_t)tcap * 4, st));
-  if (n_nodes) HTH_HIP(hipMemsetAsync(p->K.matclaim, 0xFF, (size_t)n_nodes * 4, st));
-  if (n_nodes) HTH_HIP(hipMemsetAsync(p->K.ruse, 0, (size_t)n_nodes * 4, st));
-  hipLaunchKernelGGL(k_dp_count, dim3((n_hyps + 255) / 256), dim3(256), 0, st, d_nodes, d_hyp_node_offsets,
-                     d_children, n_nodes, n_children, n_hyps, p->K, p->info, p->len, p->d_sum, p->d_bk);
+  const size_t zeros = (L.zero_end - L.zero) / 16, ones = (L.one_end - L.one) / 16;
+  hipLaunchKernelGGL(k_dp_init, dim3((unsigned)std::min<size_t>((zeros + ones + 255) / 256, 4096)), dim3(256), 0, st,
+                     reinterpret_cast<uint4*>(buf + L.zero), zeros, reinterpret_cast<uint4*>(buf + L.one), ones, p->d_sum,
+                     p->K.copies);
+  hipLaunchKernelGGL(k_dp_count, dim3((n_hyps + kDpHyps - 1) / kDpHyps), dim3(kDpBlock), 0, st, d_nodes,
+                     d_hyp_node_offsets, d_children, n_nodes, n_children, n_hyps, p->K, p->info, p->len, p->d_sum);
+  if (n_nodes)
+    hipLaunchKernelGGL(k_dp_tally, dim3((n_nodes + 255) / 256), dim3(256), 0, st, d_nodes, d_hyp_node_offsets, n_hyps,
+                       p->K, p->info, p->d_sum, p->d_bk);
   HTH_HIP(hipGetLastError());
-  std::vector<uint32_t> bk(nbk2);
-  HTH_HIP(hipMemcpyAsync(&p->sum, p->d_sum, sizeof(DpSummary), hipMemcpyDeviceToHost, st));
-  HTH_HIP(hipMemcpyAsync(bk.data(), p->d_bk, nbk2 * 4, hipMemcpyDeviceToHost, st));
-  std::vector<uint32_t> pk(nd_data);
-  if (nd_data) HTH_HIP(hipMemcpyAsync(pk.data(), p->K.pk, nd_data * 4, hipMemcpyDeviceToHost, st));
+  // the summary and the counts, in one read
+  std::vector<char> back(L.ruse - L.sum);
+  HTH_HIP(hipMemcpyAsync(back.data(), p->d_sum, back.size(), hipMemcpyDeviceToHost, st));
   HTH_HIP(hipStreamSynchronize(st));
+  std::memcpy(&p->sum, back.data(), sizeof(DpSummary));
+  std::vector<uint32_t> bk(nbk2), pk(nd_data), pkv(nd_data);
+  std::memcpy(bk.data(), back.data() + (L.bk - L.sum), nbk2 * 4);
+  if (nd_data) {
+    std::memcpy(pk.data(), back.data() + (L.pk - L.sum), nd_data * 4);
+    std::memcpy(pkv.data(), back.data() + (L.pkv - L.sum), nd_data * 4);
+  }
   const DpSummary& S = p->sum;
   if (S.err != ~0ull) {
     hth_status code;
@@ -1067,43 +1345,57 @@ extern "C" hth_status hth_dplan_create(hth_kb kb, const hth_node* d_nodes, uint3
   }
   if (S.code >= (1ull << 32)) return fail(HTH_E_RANGE, "region programs exceed 2^32 instructions");
   // row ids must fit the 27-bit argument of the region bytecode
-  if ((uint64_t)p->K.n_fixed + 1 + S.n_thr + S.n_slots >= (1ull << 27)) return fail(HTH_E_RANGE, "too many bit rows");
+  if ((uint64_t)p->K.n_fixed + 1 + S.n_thr + S.n_slots >= (1ull << 27) || S.n_vrows >= (1u << 27)) return fail(HTH_E_RANGE, "too many bit rows");
   std::vector<DpBucket> buckets;
   std::vector<uint32_t> xslots;
   hth_status s = dp_schedule(*p, bk, buckets, xslots);
   if (s) return s;
+  const ViewPlan& V = p->V;
   std::vector<GroupTask> shells;
   for (const auto& lg : p->lv_groups) shells.insert(shells.end(), lg.begin(), lg.end());
+  shells.insert(shells.end(), V.passes.begin(), V.passes.end());
   // thresholds: each property's tasks together, in groups of at most kThrPerPass
-  std::vector<uint32_t> pbase(nd_data);
+  std::vector<uint32_t> pbase(nd_data), vpbase(nd_data);
   std::vector<ThrGroup> thg;
-  uint32_t tsum = 0;
-  for (uint32_t q = 0; q < nd_data; ++q) {
-    pbase[q] = tsum;
-    for (uint32_t i = 0; i < pk[q]; i += kThrPerPass)
-      thg.push_back(ThrGroup{q, tsum + i, std::min<uint32_t>(kThrPerPass, pk[q] - i), 0});
-    tsum += pk[q];
-  }
-  if (tsum != S.n_thr) return fail(HTH_E_DEVICE, "threshold counts disagree");
-  p->K.n_thr = S.n_thr;
+  auto thr_groups = [&](const std::vector<uint32_t>& count, std::vector<uint32_t>& base) {
+    uint32_t sum = 0;
+    for (uint32_t q = 0; q < nd_data; ++q) {
+      base[q] = sum;
+      for (uint32_t i = 0; i < count[q]; i += kThrPerPass)
+        thg.push_back(ThrGroup{q, sum + i, std::min<uint32_t>(kThrPerPass, count[q] - i), 0});
+      sum += count[q];
+    }
+    return sum;
+  };
+  const uint32_t tsum = thr_groups(pk, pbase);
   p->n_thg = (uint32_t)thg.size();
-  if (shells.size() > n_nodes || xslots.size() > 8ull * n_nodes || thg.size() > n_nodes)
-    return fail(HTH_E_DEVICE, "plan tables beyond their bounds");
-  p->d_shells = reinterpret_cast<GroupTask*>(p->buf + L.shell);
-  p->d_buckets = reinterpret_cast<DpBucket*>(p->buf + L.bucket);
-  p->d_xslots = reinterpret_cast<uint32_t*>(p->buf + L.xslot);
-  p->d_bcur = reinterpret_cast<uint32_t*>(p->buf + L.bcur);
-  p->d_thg = reinterpret_cast<ThrGroup*>(p->buf + L.thg);
-  p->d_pbase = reinterpret_cast<uint32_t*>(p->buf + L.pbase);
-  if (!thg.empty())
-    HTH_HIP(hipMemcpyAsync(p->d_thg, thg.data(), thg.size() * sizeof(ThrGroup), hipMemcpyHostToDevice, st));
-  if (nd_data) HTH_HIP(hipMemcpyAsync(p->d_pbase, pbase.data(), nd_data * 4, hipMemcpyHostToDevice, st));
-  if (!shells.empty())
-    HTH_HIP(hipMemcpyAsync(p->d_shells, shells.data(), shells.size() * sizeof(GroupTask), hipMemcpyHostToDevice, st));
-  HTH_HIP(hipMemcpyAsync(p->d_buckets, buckets.data(), buckets.size() * sizeof(DpBucket), hipMemcpyHostToDevice, st));
-  if (!xslots.empty())
-    HTH_HIP(hipMemcpyAsync(p->d_xslots, xslots.data(), xslots.size() * 4, hipMemcpyHostToDevice, st));
-  HTH_HIP(hipStreamSynchronize(st));   // the host vectors above end here
+  const uint32_t vsum = thr_groups(pkv, vpbase);
+  p->V.n_thg = (uint32_t)thg.size() - p->n_thg;
+  if (tsum != S.n_thr_full || vsum != S.n_thr_view) return fail(HTH_E_DEVICE, "threshold counts disagree");
+  p->K.n_thr = S.n_thr_full;
+  if (S.n_copies > n_nodes + 2ull) return fail(HTH_E_DEVICE, "plan tables beyond their bounds");
+  // the host's tables in one copy
+  std::vector<uint64_t> vbases;
+  for (const ViewDir& v : V.dirs) vbases.push_back(v.base);
+  Blob tb;
+  const size_t o_shell = tb.add(shells), o_bucket = tb.add(buckets), o_xslot = tb.add(xslots), o_thg = tb.add(thg),
+               o_pbase = tb.add(pbase), o_vpbase = tb.add(vpbase), o_vgroup = tb.add(V.groups), o_vdir = tb.add(V.dirs),
+               o_vbase = tb.add(vbases);
+  if (tb.bytes.size() > L.tables_bytes) return fail(HTH_E_DEVICE, "plan tables beyond their bounds");
+  char* const dt = buf + L.tables;
+  p->d_shells = reinterpret_cast<GroupTask*>(dt + o_shell);
+  p->d_buckets = reinterpret_cast<DpBucket*>(dt + o_bucket);
+  p->n_buckets = (uint32_t)buckets.size();
+  p->d_xslots = reinterpret_cast<uint32_t*>(dt + o_xslot);
+  p->d_thg = reinterpret_cast<ThrGroup*>(dt + o_thg);
+  p->d_pbase = reinterpret_cast<uint32_t*>(dt + o_pbase);
+  p->d_vpbase = reinterpret_cast<uint32_t*>(dt + o_vpbase);
+  p->d_vgroups = reinterpret_cast<GroupTask*>(dt + o_vgroup);
+  p->d_vdirs = reinterpret_cast<ViewDir*>(dt + o_vdir);
+  p->d_vbases = reinterpret_cast<uint64_t*>(dt + o_vbase);
+  if (!tb.bytes.empty())
+    HTH_HIP(hipMemcpyAsync(dt, tb.bytes.data(), tb.bytes.size(), hipMemcpyHostToDevice, st));
+  HTH_HIP(hipStreamSynchronize(st));   // a launch may come from another stream
   *ws_bytes = p->need;
   *out = guard.release();
   return HTH_OK;
@@ -1126,6 +1418,8 @@ extern "C" hth_status hth_dplan_launch(hth_dplan plan, void* ws, size_t ws_bytes
   char* w = static_cast<char*>(ws);
   DpTables T;
   T.thr = reinterpret_cast<ThrTask*>(w + p.o_thr);
+  T.vthr = reinterpret_cast<ThrTask*>(w + p.o_vthr);
+  T.vpbase = p.d_vpbase;
   T.mat = reinterpret_cast<RegionTask*>(w + p.o_mat);
   T.roots = reinterpret_cast<RegionTask*>(w + p.o_root);
   T.roles = reinterpret_cast<RoleTask*>(w + p.o_role);
@@ -1142,25 +1436,23 @@ extern "C" hth_status hth_dplan_launch(hth_dplan plan, void* ws, size_t ws_bytes
   d.slots = reinterpret_cast<uint64_t*>(w + p.o_slot);
   d.counts = d_counts;
   d.instances = nullptr;
-  const uint32_t nc = 2 * p.n_hyps;
-  hipLaunchKernelGGL(k_zero_u32, dim3((nc + 255) / 256), dim3(256), 0, st, d_counts, nc);
-  HTH_HIP(hipGetLastError());
-  const uint32_t ncur = (uint32_t)(sizeof(DpCursor) / 4);
-  hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(256), 0, st, reinterpret_cast<uint32_t*>(p.d_cur), ncur);
-  HTH_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_zero_u32, dim3((p.n_buckets + 255) / 256), dim3(256), 0, st, p.d_bcur, p.n_buckets);
-  HTH_HIP(hipGetLastError());
-  if (p.n_groups) {
-    const uint32_t nw = (uint32_t)(p.n_groups * sizeof(GroupTask) / 4);
-    hipLaunchKernelGGL(k_dp_copy, dim3((nw + 255) / 256), dim3(256), 0, st, reinterpret_cast<uint32_t*>(T.groups),
-                       reinterpret_cast<const uint32_t*>(p.d_shells), nw);
+  const ViewPlan& V = p.V;
+  {
+    const uint32_t nc = 2 * p.n_hyps, ncur = (uint32_t)(sizeof(DpCursor) / 4);
+    const uint32_t ng = (uint32_t)((p.n_groups + V.passes.size()) * sizeof(GroupTask) / 4);
+    const uint32_t most = std::max(std::max(nc, ncur), std::max(p.n_buckets, ng));
+    hipLaunchKernelGGL(k_dp_start, dim3(std::min(1024u, (most + 255) / 256)), dim3(256), 0, st, d_counts, nc,
+                       reinterpret_cast<uint32_t*>(p.d_cur), ncur, p.d_bcur, p.n_buckets,
+                       reinterpret_cast<uint32_t*>(T.groups), reinterpret_cast<const uint32_t*>(p.d_shells), ng);
     HTH_HIP(hipGetLastError());
   }
   const DpSummary& S = p.sum;
   Launcher Lc{kb, st};
   hth_status s = Lc.run(HTH_K_PLAN, 0.0, [&] {
-    hipLaunchKernelGGL(k_dp_emit, dim3((p.n_hyps + 255) / 256), dim3(256), 0, st, p.nodes, p.offs, p.kids,
-                       p.n_hyps, p.K, p.info, p.len, p.row, p.d_cur, p.B, T);
+    const uint32_t rb = (p.n_hyps + kDpBlock - 1) / kDpBlock, nb = (p.n_nodes + kDpBlock - 1) / kDpBlock;
+    const uint32_t tbk = p.n_thg + V.n_thg ? (p.K.tmask + 1) / kDpBlock : 0;
+    hipLaunchKernelGGL(k_dp_emit, dim3(rb + nb + tbk), dim3(kDpBlock), 0, st, p.nodes, p.offs, p.kids, p.n_hyps, p.K,
+                       p.info, p.len, p.d_cur, p.B, T, rb, nb);
   });
   if (s) return s;
   bool heavy = false;
@@ -1180,7 +1472,7 @@ extern "C" hth_status hth_dplan_launch(hth_dplan plan, void* ws, size_t ws_bytes
     const uint32_t n = p.n_thg, bpt = std::max<uint32_t>(1, (kb.W + 127) / 128);
     const double bytes = n * 4.0 * kb.N;   // the columns (model bytes; rows are an intermediate)
     s = split_launch(Lc, HTH_K_THRESHOLD, bytes, n, bpt, 256, [&](uint32_t i0, uint32_t, uint32_t blocks) {
-      hipLaunchKernelGGL(k_threshold, dim3(blocks), dim3(256), 0, st, d, p.d_thg + i0, T.thr, bpt);
+      hipLaunchKernelGGL(k_threshold<false>, dim3(blocks), dim3(256), 0, st, d, p.d_thg + i0, T.thr, bpt, nullptr);
     });
     if (s) return s;
   }
@@ -1217,6 +1509,11 @@ extern "C" hth_status hth_dplan_launch(hth_dplan plan, void* ws, size_t ws_bytes
       if (s) return s;
     }
   }
+  if (V.on) {
+    s = launch_view(Lc, d, V, w, p.d_vdirs, p.d_vbases, p.K.copies, p.K.n_fixed + 1 + p.K.n_thr, p.d_thg + p.n_thg,
+                    T.vthr, p.d_vgroups, T.groups + p.n_groups, T.members, p.d_xslots, tarea, &d);
+    if (s) return s;
+  }
   s = launch_regions_n(Lc, d, T.roots, T.code, p.n_hyps, (int)S.root_depth, 0.0);
   if (s) return s;
   HTH_HIP(hipEventRecord(p.done, st));
@@ -1229,12 +1526,12 @@ extern "C" hth_status hth_dplan_stats(hth_dplan plan, hth_dplan_info* out) {
   const hth_dplan_s& p = *plan;
   out->levels = p.sum.levels;
   out->role_nodes = p.n_role + p.n_members;
-  out->shared_passes = p.n_groups;
+  out->shared_passes = p.n_groups + (uint32_t)p.V.groups.size();
   out->thresholds = p.sum.n_thr;
   uint32_t mats = 0;
   for (uint32_t L = 0; L < kDpLevels; ++L) mats += p.sum.mat[L];
   out->materialised = mats;
-  out->rows = p.sum.n_slots + p.sum.n_thr + 1;
+  out->rows = p.sum.n_slots + p.sum.n_thr_full + 1 + (p.V.on ? p.V.n_rows : 0);
   return HTH_OK;
 }
 

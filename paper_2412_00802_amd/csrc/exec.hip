@@ -43,35 +43,58 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
 // All thresholds requested on one property in one pass over its column: one
 // lane per individual over 8 consecutive words (values loaded once, kept in
 // registers), one wave ballot per threshold and word; lanes 0..7 then store
-// the 8 words of a threshold's row together (a full 64-byte line).
+// the 8 words of a threshold's row together (a full 64-byte line).  Bound by
+// the vector unit: a compare and two lane writes per threshold and word (the
+// comparison is chosen once per threshold, and an individual past the end is a
+// missing value, so that nothing else is done per word).  VIEW: the column is
+// read at the examples (list), 64 of them a word.
+// 576 thresholds over 32M individuals 2.1 ms, where a select on the
+// comparison and on the lane per word took 7.6.
+__device__ __forceinline__ void put_lane(uint32_t& lo, uint32_t& hi, uint64_t m, int lane) {
+  // (a vector instruction may read a scalar that another one wrote two wait
+  // states later)
+  asm("s_nop 1\n\tv_writelane_b32 %0, %2, %4\n\tv_writelane_b32 %1, %3, %4"
+      : "+v"(lo), "+v"(hi)
+      : "s"((uint32_t)m), "s"((uint32_t)(m >> 32)), "n"(lane));
+}
+template <bool VIEW>
 __global__ void __launch_bounds__(256)
-k_threshold(DevKB kb, const ThrGroup* __restrict__ groups, const ThrTask* __restrict__ tasks, uint32_t bpt) {
+k_threshold(DevKB kb, const ThrGroup* __restrict__ groups, const ThrTask* __restrict__ tasks, uint32_t bpt,
+            const uint32_t* __restrict__ list) {
   const uint32_t gi = blockIdx.x / bpt, b = blockIdx.x % bpt;
   const ThrGroup G = groups[gi];
   const float* col = kb.data + (size_t)G.prop * kb.N;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const uint32_t n_blk = (kb.W + 7) / 8;
+  const uint32_t N = VIEW ? kb.view[0] : kb.N, W = VIEW ? kb.view[1] : kb.W;
+  const uint32_t n_blk = (W + 7) / 8;
   for (uint32_t blk = b * 4 + wv; blk < n_blk; blk += bpt * 4) {
     const uint32_t w0 = blk * 8;
     float f[8];
-    bool in[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const uint32_t x = (w0 + j) * 64 + lane;
-      in[j] = w0 + j < kb.W && x < kb.N;
-      f[j] = in[j] ? col[x] : 0.0f;
+      const bool in = w0 + j < W && x < N;
+      const uint32_t at = in ? x : 0u;
+      const float v = col[VIEW ? list[at] : at];
+      f[j] = in ? v : __builtin_nanf("");       // NaN (no value) compares false
     }
     for (uint32_t i = 0; i < G.n; ++i) {
       const ThrTask T = tasks[G.first + i];
-      uint64_t mine = 0;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        // NaN (no value) compares false
-        const bool pass = T.cmp == 0 ? f[j] >= T.t : T.cmp == 1 ? f[j] <= T.t : f[j] == T.t;
-        const uint64_t m = __ballot(in[j] && pass);
-        if (lane == j) mine = m;
-      }
-      if (lane < 8 && w0 + lane < kb.W) out_ptr(kb, T.out_row)[w0 + lane] = mine;
+      uint32_t lo = 0, hi = 0;
+      auto words = [&](auto pass) {
+        put_lane(lo, hi, __ballot(pass(f[0])), 0);
+        put_lane(lo, hi, __ballot(pass(f[1])), 1);
+        put_lane(lo, hi, __ballot(pass(f[2])), 2);
+        put_lane(lo, hi, __ballot(pass(f[3])), 3);
+        put_lane(lo, hi, __ballot(pass(f[4])), 4);
+        put_lane(lo, hi, __ballot(pass(f[5])), 5);
+        put_lane(lo, hi, __ballot(pass(f[6])), 6);
+        put_lane(lo, hi, __ballot(pass(f[7])), 7);
+      };
+      if (T.cmp == 0) words([&](float v) { return v >= T.t; });
+      else if (T.cmp == 1) words([&](float v) { return v <= T.t; });
+      else words([&](float v) { return v == T.t; });
+      if (lane < 8 && w0 + lane < W) out_ptr(kb, T.out_row)[w0 + lane] = ((uint64_t)hi << 32) | lo;
     }
   }
 }
@@ -258,51 +281,55 @@ k_strrole_heavy(DevKB kb, const StrTask* __restrict__ tasks, uint32_t n_tasks, u
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(kRegionThreads)
 k_region(DevKB kb, const RegionTask* __restrict__ tasks, const uint32_t* __restrict__ code,
-         uint32_t n_tasks) {
+         uint32_t n_tasks, uint32_t tiles) {
   __shared__ uint64_t stk[kStackDepth][kRegionThreads];
-  const uint32_t tile = blockIdx.x / n_tasks, task = blockIdx.x % n_tasks;
+  const uint32_t task = blockIdx.x % n_tasks;
   const RegionTask T = tasks[task];
   if (T.out_row == kNone && T.cover == kNone) return;   // a root whose coverage a shared pass adds
   const uint32_t tid = threadIdx.x;
-  const uint32_t w = tile * kRegionThreads + tid;
-  const bool live = w < kb.W;
-  uint64_t top = 0;
-  int sp = 0;
-  for (uint32_t pc = 0; pc < T.code_len; ++pc) {
-    const uint32_t ins = code[T.code_off + pc];
-    const uint32_t op = ins & 15u, arg = ins >> 5;
-    const uint64_t negm = (ins & 16u) ? ~0ull : 0ull;
-    switch (op) {
-      case RP_LEAF:
-      case RP_TOP:
-      case RP_BOT: {
-        uint64_t v;
-        if (op == RP_LEAF) v = live ? (row_ptr(kb, arg)[w] ^ negm) : 0ull;
-        else v = op == RP_TOP ? ~0ull : 0ull;
-        if (pc) stk[sp++][tid] = top;
-        top = v;
-        break;
+  const uint32_t W = span_w(kb), S = kb.view ? W : kb.S;
+  const uint64_t tail = span_tail(kb);
+  for (uint32_t tile = blockIdx.x / n_tasks; tile * kRegionThreads < S; tile += tiles) {
+    const uint32_t w = tile * kRegionThreads + tid;
+    const bool live = w < W;
+    uint64_t top = 0;
+    int sp = 0;
+    for (uint32_t pc = 0; pc < T.code_len; ++pc) {
+      const uint32_t ins = code[T.code_off + pc];
+      const uint32_t op = ins & 15u, arg = ins >> 5;
+      const uint64_t negm = (ins & 16u) ? ~0ull : 0ull;
+      switch (op) {
+        case RP_LEAF:
+        case RP_TOP:
+        case RP_BOT: {
+          uint64_t v;
+          if (op == RP_LEAF) v = live ? (row_ptr(kb, arg)[w] ^ negm) : 0ull;
+          else v = op == RP_TOP ? ~0ull : 0ull;
+          if (pc) stk[sp++][tid] = top;
+          top = v;
+          break;
+        }
+        case RP_NOT: top = ~top; break;
+        case RP_AND: top &= stk[--sp][tid]; break;
+        default: top |= stk[--sp][tid]; break;
       }
-      case RP_NOT: top = ~top; break;
-      case RP_AND: top &= stk[--sp][tid]; break;
-      default: top |= stk[--sp][tid]; break;
     }
-  }
-  if (!live) top = 0;
-  else if (w == kb.W - 1) top &= kb.tail;
-  if (T.out_row != kNone && w < kb.S) {
-    // kInstances: the caller's rows, one per covered hypothesis
-    uint64_t* o = T.out_row == kInstances ? kb.instances + (size_t)T.cover * kb.S : out_ptr(kb, T.out_row);
-    o[w] = top;
-  }
-  if (T.cover != kNone) {
-    uint32_t p = live ? (uint32_t)__popcll(top & kb.pos[w]) : 0u;
-    uint32_t q = live ? (uint32_t)__popcll(top & kb.neg[w]) : 0u;
-    p = wave_sum(p);
-    q = wave_sum(q);
-    if ((tid & 63) == 0 && (p | q)) {
-      if (p) atomicAdd(kb.counts + 2 * T.cover, p);
-      if (q) atomicAdd(kb.counts + 2 * T.cover + 1, q);
+    if (!live) top = 0;
+    else if (w == W - 1) top &= tail;
+    if (T.out_row != kNone && w < kb.S) {
+      // kInstances: the caller's rows, one per covered hypothesis
+      uint64_t* o = T.out_row == kInstances ? kb.instances + (size_t)T.cover * kb.S : out_ptr(kb, T.out_row);
+      o[w] = top;
+    }
+    if (T.cover != kNone) {
+      uint32_t p = live ? (uint32_t)__popcll(top & kb.pos[w]) : 0u;
+      uint32_t q = live ? (uint32_t)__popcll(top & kb.neg[w]) : 0u;
+      p = wave_sum(p);
+      q = wave_sum(q);
+      if ((tid & 63) == 0 && (p | q)) {
+        if (p) atomicAdd(kb.counts + 2 * T.cover, p);
+        if (q) atomicAdd(kb.counts + 2 * T.cover + 1, q);
+      }
     }
   }
 }
@@ -324,11 +351,18 @@ constexpr int kRegLeaves = 2;    // leaves whose words are loaded ahead
 template <int D, int R>
 __global__ void __launch_bounds__(256)
 k_region_reg(DevKB kb, const RegionTask* __restrict__ tasks, const uint32_t* __restrict__ code,
-             uint32_t n_tasks, uint32_t tiles, uint32_t tpb) {
+             uint32_t n_tasks, uint32_t tiles, uint32_t tpb, uint32_t runs) {
   __shared__ uint32_t s_pq[2][4];
   const uint32_t run = blockIdx.x / n_tasks, task = blockIdx.x % n_tasks;
   const RegionTask T = tasks[task];
   if (T.out_row == kNone && T.cover == kNone) return;
+  const uint32_t W = span_w(kb);
+  const uint64_t tail = span_tail(kb);
+  if (kb.view) {                // the launch's runs share the words there are
+    tiles = (W + 256 * R - 1) / (256 * R);
+    tpb = (tiles + runs - 1) / runs;
+    if (run * tpb >= tiles) return;
+  }
   const uint32_t tid = threadIdx.x;
   const uint32_t* prog = code + T.code_off;
   const uint32_t len = T.code_len;
@@ -402,7 +436,7 @@ k_region_reg(DevKB kb, const RegionTask* __restrict__ tasks, const uint32_t* __r
 #pragma unroll
               for (int r = 0; r < R; ++r) {
                 const uint32_t w = w0 + r;
-                val[r] = w < kb.W ? (row[w] ^ negm) : 0ull;
+                val[r] = w < W ? (row[w] ^ negm) : 0ull;
               }
             }
           } else {
@@ -447,8 +481,8 @@ k_region_reg(DevKB kb, const RegionTask* __restrict__ tasks, const uint32_t* __r
     for (int r = 0; r < R; ++r) {
       const uint32_t w = w0 + r;
       uint64_t v = top[r];
-      if (w >= kb.W) v = 0;
-      else if (w == kb.W - 1) v &= kb.tail;
+      if (w >= W) v = 0;
+      else if (w == W - 1) v &= tail;
       if (out && w < kb.S) out[w] = v;
       if (cover) {
         p += (uint32_t)__popcll(v & ep[r]);
@@ -868,6 +902,9 @@ DevKB dev_view(const hth_kb_s& kb) {
   return d;
 }
 
+// words of the example view as counted at load (its kernels' grids)
+inline uint32_t view_words_hint(const hth_kb_s& kb) { return (kb.ex_hint + 63) / 64 + 1; }
+
 // Kernel launches, each optionally bracketed by timing events.
 struct Launcher {
   hth_kb_s& kb;
@@ -971,9 +1008,12 @@ hth_status launch_regions_n(Launcher& L, const DevKB& d, const RegionTask* tasks
                             uint32_t n, int depth, double bytes) {
   if (!n) return HTH_OK;
   // the register kernel when every program's stack fits its shift register
+  // (the view: as many words as the load's examples fill; the kernels cover
+  // however many there are)
+  const uint32_t S = d.view ? std::min(d.S, view_words_hint(L.kb)) : d.S;
   if (depth <= kRegDepth && L.kb.tune.region_reg) {
     const uint32_t rw = L.kb.tune.region_reg;     // words per lane: 1, 2 or 4
-    const uint32_t tiles = (d.S + 256 * rw - 1) / (256 * rw);
+    const uint32_t tiles = (S + 256 * rw - 1) / (256 * rw);
     // a block walks up to kRegionTilesPerBlock tiles of its task, fewer when
     // the launch would otherwise have under kRegionMinBlocks blocks
     const uint64_t per = std::max<uint64_t>(1, (uint64_t)n * tiles / kRegionMinBlocks);
@@ -982,16 +1022,16 @@ hth_status launch_regions_n(Launcher& L, const DevKB& d, const RegionTask* tasks
     return split_launch(L, HTH_K_REGION, bytes, n, runs, 256, [&](uint32_t t0, uint32_t m, uint32_t blocks) {
       const dim3 grid(blocks), block(256);
       if (rw == 1)
-        hipLaunchKernelGGL((k_region_reg<kRegDepth, 1>), grid, block, 0, L.st, d, tasks + t0, code, m, tiles, tpb);
+        hipLaunchKernelGGL((k_region_reg<kRegDepth, 1>), grid, block, 0, L.st, d, tasks + t0, code, m, tiles, tpb, runs);
       else if (rw == 2)
-        hipLaunchKernelGGL((k_region_reg<kRegDepth, 2>), grid, block, 0, L.st, d, tasks + t0, code, m, tiles, tpb);
+        hipLaunchKernelGGL((k_region_reg<kRegDepth, 2>), grid, block, 0, L.st, d, tasks + t0, code, m, tiles, tpb, runs);
       else
-        hipLaunchKernelGGL((k_region_reg<kRegDepth, 4>), grid, block, 0, L.st, d, tasks + t0, code, m, tiles, tpb);
+        hipLaunchKernelGGL((k_region_reg<kRegDepth, 4>), grid, block, 0, L.st, d, tasks + t0, code, m, tiles, tpb, runs);
     });
   }
-  const uint32_t tiles = (d.S + kRegionThreads - 1) / kRegionThreads;
+  const uint32_t tiles = (S + kRegionThreads - 1) / kRegionThreads;
   return split_launch(L, HTH_K_REGION, bytes, n, tiles, kRegionThreads, [&](uint32_t t0, uint32_t m, uint32_t blocks) {
-    hipLaunchKernelGGL(k_region, dim3(blocks), dim3(kRegionThreads), 0, L.st, d, tasks + t0, code, m);
+    hipLaunchKernelGGL(k_region, dim3(blocks), dim3(kRegionThreads), 0, L.st, d, tasks + t0, code, m, tiles);
   });
 }
 
@@ -1040,10 +1080,13 @@ hth_status launch_roles(Launcher& L, const DevKB& d, const RoleTask* tasks,
   return launch_roles_n(L, d, tasks, (uint32_t)host.size(), bytes);
 }
 
+// vd, passes: the example view and its tasks, whose T rows are built from the
+// groups' real directions (d, groups); null: the pass runs on those too.
 template <typename TW>
 hth_status launch_group_chunk(Launcher& L, const DevKB& d, const GroupTask* groups,
                               const GroupMember* members, const std::vector<GroupTask>& host,
-                              const GroupChunk& c, const uint32_t* xslots_all, void* tarea, void* parea) {
+                              const GroupChunk& c, const uint32_t* xslots_all, void* tarea, void* parea,
+                              const DevKB* vd, const GroupTask* passes) {
   const hth_kb_s& kb = L.kb;
   const size_t g0 = c.first;
   const uint32_t n = c.n;
@@ -1054,7 +1097,9 @@ hth_status launch_group_chunk(Launcher& L, const DevKB& d, const GroupTask* grou
   for (uint32_t i = 0; i < n; ++i) {
     const GroupTask& G = host[g0 + i];
     tb += (double)G.k * kb.W * 8;
-    gb += L.csr_once(G.role, G.inv) + (double)G.k * G.n_words * 8;
+    // (the view: the examples' share of both)
+    gb += vd ? L.csr_once(G.role, G.inv) * kb.ex_hint / kb.N + (double)G.k * view_words_hint(kb) * 8
+             : L.csr_once(G.role, G.inv) + (double)G.k * G.n_words * 8;
   }
   TW* T = static_cast<TW*>(tarea);
   // 256 words per block: every word, or the object words of a compact group
@@ -1069,15 +1114,18 @@ hth_status launch_group_chunk(Launcher& L, const DevKB& d, const GroupTask* grou
   });
   if (s) return s;
   const uint32_t* xslots = c.rounds ? xslots_all + c.slot_off : nullptr;
+  const uint32_t W = vd ? std::min(kb.W, view_words_hint(kb)) : kb.W;
   uint32_t bpg, nblocks;
   if (xslots) {
-    bpg = std::min<uint32_t>(std::max<uint32_t>(1, kb.n_cu / 8 * 8), (kb.W + 3) / 4);
+    bpg = std::min<uint32_t>(std::max<uint32_t>(1, kb.n_cu / 8 * 8), (W + 3) / 4);
     nblocks = 8 * bpg * c.rounds;
   } else {
     bpg = std::max<uint32_t>(1, (8 * kb.n_cu + n - 1) / n);
-    bpg = std::min<uint32_t>(bpg, (kb.W + 3) / 4);
+    bpg = std::min<uint32_t>(bpg, (W + 3) / 4);
     nblocks = bpg * n;
   }
+  const DevKB& pd = vd ? *vd : d;
+  const GroupTask* pg = (vd ? passes : groups) + g0;
   // several list words per wave iteration where words hold few assertions
   double ew = 0, nwd = 0;
   for (uint32_t i = 0; i < n; ++i) {
@@ -1096,14 +1144,14 @@ hth_status launch_group_chunk(Launcher& L, const DevKB& d, const GroupTask* grou
     return L.run(HTH_K_GROUP_SHORT, gb, [&] {
       if (most < kGroupMaxCount)
         hipLaunchKernelGGL((k_group_short<TW, kShortWords, kShortSub, true>), dim3(nblocks), dim3(256), 0, L.st,
-                           d, groups + g0, members, T, bpg, xslots);
+                           pd, pg, members, T, bpg, xslots);
       else
         hipLaunchKernelGGL((k_group_short<TW, kShortWords, kShortSub, false>), dim3(nblocks), dim3(256), 0, L.st,
-                           d, groups + g0, members, T, bpg, xslots);
+                           pd, pg, members, T, bpg, xslots);
     });
   }
-  uint64_t seg_rows;
-  const uint32_t P = chunk_segments(kb, host, c, &seg_rows);
+  uint64_t seg_rows = 0;
+  const uint32_t P = vd ? 1 : chunk_segments(kb, host, c, &seg_rows);
   for (uint32_t sg = 0; sg < P; ++sg) {
     SegPass<TW> sp{0, 0xFFFFFFFFu, 1, 1, nullptr, (size_t)kb.W * 256};
     if (P > 1) {
@@ -1117,12 +1165,12 @@ hth_status launch_group_chunk(Launcher& L, const DevKB& d, const GroupTask* grou
       const dim3 grid(nblocks), block(256);
       const bool u16 = kb.tune.group_unroll >= 16;
       if (multi) {   // few assertions per lane: 8 in flight
-        hipLaunchKernelGGL((k_group<TW, 8, 4>), grid, block, 0, L.st, d, groups + g0, members, T, bpg, xslots, sp);
+        hipLaunchKernelGGL((k_group<TW, 8, 4>), grid, block, 0, L.st, pd, pg, members, T, bpg, xslots, sp);
       } else {
         if (u16)
-          hipLaunchKernelGGL((k_group<TW, 16, 1>), grid, block, 0, L.st, d, groups + g0, members, T, bpg, xslots, sp);
+          hipLaunchKernelGGL((k_group<TW, 16, 1>), grid, block, 0, L.st, pd, pg, members, T, bpg, xslots, sp);
         else
-          hipLaunchKernelGGL((k_group<TW, 8, 1>), grid, block, 0, L.st, d, groups + g0, members, T, bpg, xslots, sp);
+          hipLaunchKernelGGL((k_group<TW, 8, 1>), grid, block, 0, L.st, pd, pg, members, T, bpg, xslots, sp);
       }
     });
     if (s) return s;
@@ -1133,19 +1181,27 @@ hth_status launch_group_chunk(Launcher& L, const DevKB& d, const GroupTask* grou
 hth_status launch_groups(Launcher& L, const DevKB& d, const GroupTask* groups,
                          const GroupMember* members, const std::vector<GroupTask>& host,
                          const std::vector<GroupChunk>& chunks, const uint32_t* xslots, void* tarea,
-                         void* parea) {
+                         void* parea, const DevKB* vd = nullptr, const GroupTask* passes = nullptr) {
   for (const GroupChunk& c : chunks) {
     hth_status s;
     switch (c.wb) {
-      case 1: s = launch_group_chunk<uint8_t>(L, d, groups, members, host, c, xslots, tarea, parea); break;
-      case 2: s = launch_group_chunk<uint16_t>(L, d, groups, members, host, c, xslots, tarea, parea); break;
-      case 4: s = launch_group_chunk<uint32_t>(L, d, groups, members, host, c, xslots, tarea, parea); break;
-      default: s = launch_group_chunk<uint64_t>(L, d, groups, members, host, c, xslots, tarea, parea); break;
+      case 1: s = launch_group_chunk<uint8_t>(L, d, groups, members, host, c, xslots, tarea, parea, vd, passes); break;
+      case 2: s = launch_group_chunk<uint16_t>(L, d, groups, members, host, c, xslots, tarea, parea, vd, passes); break;
+      case 4: s = launch_group_chunk<uint32_t>(L, d, groups, members, host, c, xslots, tarea, parea, vd, passes); break;
+      default: s = launch_group_chunk<uint64_t>(L, d, groups, members, host, c, xslots, tarea, parea, vd, passes); break;
     }
     if (s) return s;
   }
   return HTH_OK;
 }
+
+}  // namespace
+}  // namespace hth
+
+#include "view.h"
+
+namespace hth {
+namespace {
 
 // heavy-row scratch of a plan: a partial count per (role task, chunk of its
 // direction), the largest level's worth (levels run one after the other)
@@ -1516,7 +1572,7 @@ hth_status launch_prepared(hth_kb_s& kb, const Prepared& X, char* ws, uint32_t* 
     std::sort(props.begin(), props.end());
     const double bytes = 4.0 * kb.N * (double)(std::unique(props.begin(), props.end()) - props.begin());
     hth_status s = split_launch(Lc, HTH_K_THRESHOLD, bytes, n, bpt, 256, [&](uint32_t i0, uint32_t, uint32_t blocks) {
-      hipLaunchKernelGGL(k_threshold, dim3(blocks), dim3(256), 0, st, d, thg + i0, thr, bpt);
+      hipLaunchKernelGGL(k_threshold<false>, dim3(blocks), dim3(256), 0, st, d, thg + i0, thr, bpt, nullptr);
     });
     if (s) return s;
   }

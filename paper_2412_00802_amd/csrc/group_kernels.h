@@ -36,15 +36,6 @@ __device__ __forceinline__ uint64_t uniform_row_word(const uint64_t* row, uint32
   return *(const uint64_t __attribute__((address_space(1)))*)(base + byte_off);
 }
 
-// A 32-bit word that every lane reads at the same address, through the
-// scalar cache: its wait does not also wait for the wave's vector stores.
-__device__ __forceinline__ uint32_t scalar_u32(const uint32_t* p) {
-  return *(const __attribute__((address_space(4))) uint32_t*)p;
-}
-__device__ __forceinline__ uint64_t scalar_u64(const uint64_t* p) {
-  return *(const __attribute__((address_space(4))) uint64_t*)p;
-}
-
 // T_g[y] bit j = bit(child_j, y) ^ neg_j for the groups of one launch; one lane
 // per 64-individual word, transposed in registers.  T rows are TW wide
 // (8 * sizeof(TW) >= every group's k).  A compact group keeps the rows of its
@@ -278,10 +269,11 @@ __device__ __forceinline__ void cover_word(Cover& c, const DevKB& kb, uint32_t w
 // wave `wave` of `waves`: its share of all words, then the member's atomics
 __device__ __forceinline__ void cover_finish(Cover& c, const DevKB& kb, uint32_t wave, uint32_t waves, int lane) {
   if (__ballot(c.h != kNone && c.z)) {
-    for (uint32_t w0 = wave * 64; w0 < kb.W; w0 += waves * 64) {
+    const uint32_t W = span_w(kb);
+    for (uint32_t w0 = wave * 64; w0 < W; w0 += waves * 64) {
       const uint32_t w = w0 + lane;
-      uint32_t pp = w < kb.W ? (uint32_t)__popcll(kb.pos[w]) : 0u;
-      uint32_t qq = w < kb.W ? (uint32_t)__popcll(kb.neg[w]) : 0u;
+      uint32_t pp = w < W ? (uint32_t)__popcll(kb.pos[w]) : 0u;
+      uint32_t qq = w < W ? (uint32_t)__popcll(kb.neg[w]) : 0u;
 #pragma unroll
       for (int d = 32; d >= 1; d >>= 1) {
         pp += __shfl_xor(pp, d, 64);
@@ -359,7 +351,7 @@ k_group(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember* __res
   const TW* T = tarea + G->t_off;
   const size_t roff = (size_t)G->role * (kb.N + 1);
   const uint32_t* off = (G->inv ? kb.inv_off : kb.fwd_off) + roff;
-  const uint32_t off_end = off[kb.N];
+  const uint32_t N = span_n(kb), off_end = off[N];
   // a compact group reads each assertion's object rank instead of its object
   const int32_t* tg = (G->compact ? (G->inv ? kb.ctg_inv : kb.ctg_fwd) : (G->inv ? kb.inv_tg : kb.fwd_tg)) +
                       kb.role_base[G->role];
@@ -378,8 +370,13 @@ k_group(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember* __res
   Cover cv = cover_of(G, members, k, lane);
   const uint32_t nw = blockDim.x >> 6;
   const uint32_t istep = bpg * nw;
-  const uint32_t* words = kb.words + (size_t)(2 * G->role + G->inv) * kb.W;
-  const uint32_t n_words = G->n_words;
+  // the direction's non-empty words; every word of the view
+  const uint32_t* words = kb.view ? kb.words : kb.words + (size_t)(2 * G->role + G->inv) * kb.W;
+  const uint32_t n_words = kb.view ? span_w(kb) : G->n_words;
+  if (!n_words) {
+    if (sp.last) cover_finish(cv, kb, b * nw + wv, bpg * nw, lane);
+    return;
+  }
   const uint32_t n_iter = (n_words + MW - 1) / MW;
 
   // Software pipeline over the wave's iterations: while iteration i is walked,
@@ -398,11 +395,11 @@ k_group(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember* __res
 #pragma unroll
     for (int m = 0; m < MW; ++m) {
       const bool in = it < n_iter && it * MW + m < n_words;
-      const uint32_t x = w[m] * 64 + lane, xc = min(x, kb.N - 1);
+      const uint32_t x = w[m] * 64 + lane, xc = min(x, N - 1);
       const uint32_t lo = off[xc], hi = off[xc + 1];
       q.wd[m] = in ? w[m] : kNone;   // lo and hi of an entry past the list are never read
-      q.lo[m] = x < kb.N ? lo : off_end;
-      q.hi[m] = x < kb.N ? hi : off_end;
+      q.lo[m] = x < N ? lo : off_end;
+      q.hi[m] = x < N ? hi : off_end;
     }
   };
   auto words_in = [&](uint32_t it) { return it < n_iter ? min((uint32_t)MW, n_words - it * MW) : 0u; };
@@ -576,14 +573,14 @@ k_group(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember* __res
         }
         if (sp.last) {
           TW rv = accept(p, acc);
-          if (rw.wd[m] * 64 + lane >= kb.N) rv = 0;
+          if (rw.wd[m] * 64 + lane >= N) rv = 0;
           uint64_t mine;
           if (__popcll(nzm[m]) <= kSparseWord) {
             // the subjects without assertions take the zero count, so member
             // j's word is acc[0]'s bit j at each of them; the bits of the few
             // others are read from their lanes
             const uint32_t x0 = rw.wd[m] * 64;
-            const uint64_t live = x0 + 64 <= kb.N ? ~0ull : ((1ull << (kb.N - x0)) - 1ull);
+            const uint64_t live = x0 + 64 <= N ? ~0ull : ((1ull << (N - x0)) - 1ull);
             mine = (((uint64_t)acc[0] >> lane) & 1ull) ? live : 0ull;
             for (uint64_t z = nzm[m]; z; z &= z - 1) {
               const int l = __builtin_ctzll(z);
@@ -690,8 +687,9 @@ k_group_short(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember*
   __syncthreads();
   Cover cv = cover_of(G, members, k, lane);
   const uint32_t nw = blockDim.x >> 6;
-  const uint32_t* words = kb.words + (size_t)(2 * G->role + G->inv) * kb.W;
-  const uint32_t n_words = G->n_words;
+  const uint32_t N = span_n(kb);
+  const uint32_t* words = kb.view ? kb.words : kb.words + (size_t)(2 * G->role + G->inv) * kb.W;
+  const uint32_t n_words = kb.view ? span_w(kb) : G->n_words;
   const uint32_t n_super = (n_words + SW - 1) / SW;
   uint64_t (*so)[SW + 1] = s_out[wv];
   uint32_t pw[SW];   // words staged in LDS, not yet written
@@ -725,10 +723,10 @@ k_group_short(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember*
       for (int m = 0; m < MW; ++m) wd[m] = scalar_u32(words + min(it * MW + m, n_words - 1));
 #pragma unroll
       for (int m = 0; m < MW; ++m) {
-        const uint32_t x = wd[m] * 64 + lane, xc = min(x, kb.N - 1);
+        const uint32_t x = wd[m] * 64 + lane, xc = min(x, N - 1);
         e[m] = off[xc];
         ee[m] = off[xc + 1];
-        const bool in = it * MW + m < n_words && x < kb.N;
+        const bool in = it * MW + m < n_words && x < N;
         if (!in) ee[m] = e[m];
         if (it * MW + m >= n_words) wd[m] = kNone;
       }
@@ -771,7 +769,7 @@ k_group_short(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember*
 #pragma unroll
       for (int m = 0; m < MW; ++m) {
         TW rv = accept<TW, !EXACT>(p[m], acc);
-        if (wd[m] == kNone || wd[m] * 64 + lane >= kb.N) rv = 0;
+        if (wd[m] == kNone || wd[m] * 64 + lane >= N) rv = 0;
         const uint64_t o = wave_transpose64((uint64_t)rv, lane);
         so[lane][sub * MW + m] = o;
         pw[sub * MW + m] = wd[m];

@@ -204,7 +204,28 @@ struct DevKB {
   uint32_t N, W, S;
   uint32_t heavy_min;         // rows with more assertions are heavy rows
   uint64_t tail;              // valid-bit mask of word W-1
+  // The example view (view.h): {individuals, words} on the device in place of
+  // N and W; N + 1 stays the offsets' stride, S the rows'.  Null: no view.
+  const uint32_t* view;
 };
+
+// A 32-bit word that every lane reads at the same address, through the
+// scalar cache: its wait does not also wait for the wave's vector stores.
+__device__ __forceinline__ uint32_t scalar_u32(const uint32_t* p) {
+  return *(const __attribute__((address_space(4))) uint32_t*)p;
+}
+__device__ __forceinline__ uint64_t scalar_u64(const uint64_t* p) {
+  return *(const __attribute__((address_space(4))) uint64_t*)p;
+}
+// The individuals and words that a pass covers: the knowledge base's, or the
+// example view's (counted on the device).
+__device__ __forceinline__ uint32_t span_n(const DevKB& kb) { return kb.view ? scalar_u32(kb.view) : kb.N; }
+__device__ __forceinline__ uint32_t span_w(const DevKB& kb) { return kb.view ? scalar_u32(kb.view + 1) : kb.W; }
+__device__ __forceinline__ uint64_t span_tail(const DevKB& kb) {
+  if (!kb.view) return kb.tail;
+  const uint32_t r = scalar_u32(kb.view) & 63u;
+  return r ? (1ull << r) - 1ull : ~0ull;
+}
 
 // Row ids: [0, C) concepts, [C, C + n_sets) the set table, then workspace slots.
 __device__ __forceinline__ const uint64_t* row_ptr(const DevKB& kb, uint32_t id) {

@@ -60,6 +60,17 @@ k_row_pop(const uint64_t* __restrict__ rows, uint32_t W, uint32_t S, uint32_t* _
   if (threadIdx.x == 0) out[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
 }
 
+// The number of examples, positive or negative.
+__global__ void __launch_bounds__(256)
+k_count_examples(const uint64_t* __restrict__ pos, const uint64_t* __restrict__ neg, uint32_t W,
+                 uint32_t* __restrict__ out) {
+  uint32_t c = 0;
+  for (uint32_t w = blockIdx.x * 256 + threadIdx.x; w < W; w += gridDim.x * 256) c += (uint32_t)__popcll(pos[w] | neg[w]);
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);
+  if ((threadIdx.x & 63) == 0 && c) atomicAdd(out, c);
+}
+
 // Bits past N in word W-1 and words W..S-1 of every bit row must be zero.
 __global__ void k_check_padding(const uint64_t* __restrict__ rows, uint32_t n_rows, uint32_t W,
                                 uint32_t S, uint64_t tail, uint32_t* __restrict__ flags) {
@@ -557,7 +568,7 @@ k_object_rank(const int32_t* __restrict__ fwd_tg, const int32_t* __restrict__ in
 
 struct DerivedLayout {
   size_t fwd_off, inv_off, inv_tg, cursor, tsum, base, meta, words, objmask, objbase, ctg;
-  size_t heavy, hchunk, hchunk0, cpop, total;
+  size_t heavy, hchunk, hchunk0, cpop, dir, total;
   uint32_t tiles;                // word tiles of a bit row
   size_t heavy_cap, chunk_cap;   // entries
 };
@@ -587,6 +598,7 @@ static DerivedLayout layout_for(const hth_kb_desc& d) {
   L.hchunk = at; at += align_up(L.chunk_cap * sizeof(HeavyChunk), 256);
   L.hchunk0 = at; at += align_up((L.heavy_cap + 1) * 4, 256);
   L.cpop = at; at += align_up((size_t)d.n_concepts * 4 + 4, 256);
+  L.dir = at; at += align_up(3 * (2 * R + 1) * 4, 256);
   L.total = at;
   return L;
 }
@@ -692,7 +704,7 @@ static hth_status kb_build(hth_kb_s* kb, char* derived, hipStream_t st) {
   uint32_t* tsum = reinterpret_cast<uint32_t*>(derived + L.tsum);
   uint64_t* base = reinterpret_cast<uint64_t*>(derived + L.base);
   uint32_t* meta = reinterpret_cast<uint32_t*>(derived + L.meta);
-  uint32_t* flags = meta;              // meta: flags, heavy rows, -, -, then
+  uint32_t* flags = meta;              // meta: flags, heavy rows, examples, -, then
   uint32_t* maxdeg = meta + 4;         // [2][R] largest degrees
   uint32_t* nwords = meta + 4 + 2 * R; // [R][2] non-empty words
   uint32_t* nobj = meta + 4 + 4 * R;   // [R][2] objects
@@ -713,6 +725,8 @@ static hth_status kb_build(hth_kb_s* kb, char* derived, hipStream_t st) {
                      kb->tail, flags);
   hipLaunchKernelGGL(k_check_padding, dim3(1), dim3(1), 0, st, d.neg_bits, 1u, kb->W, kb->S,
                      kb->tail, flags);
+  hipLaunchKernelGGL(k_count_examples, dim3(std::min(256u, (kb->W + 255) / 256)), dim3(256), 0, st, d.pos_bits,
+                     d.neg_bits, kb->W, meta + 2);
   kb->concept_pop.assign(d.n_concepts, 0);
   if (d.n_concepts) {
     uint32_t* cpop = reinterpret_cast<uint32_t*>(derived + L.cpop);
@@ -801,6 +815,7 @@ static hth_status kb_build(hth_kb_s* kb, char* derived, hipStream_t st) {
   HTH_HIP(hipMemcpyAsync(got.data(), meta, got.size() * 4, hipMemcpyDeviceToHost, st));
   HTH_HIP(hipStreamSynchronize(st));
   if (hth_status fs = check_flags(got[0])) return fs;
+  kb->ex_hint = got[2];
   if (!R) return HTH_OK;
   const uint32_t* g = got.data() + 4;
   kb->max_deg[0].assign(g, g + R);
@@ -822,6 +837,15 @@ static hth_status kb_build(hth_kb_s* kb, char* derived, hipStream_t st) {
   kb->chunk_first = all.chunk_first;
   kb->heavy_most = all.heavy_most;
   kb->chunk_most = all.chunk_most;
+  // each direction's non-empty words, first heavy chunk and first heavy row
+  // (device plans read them)
+  std::vector<uint32_t> dir(3 * (2 * (size_t)R + 1), 0);
+  std::copy(kb->n_words.begin(), kb->n_words.end(), dir.begin());
+  std::copy(kb->chunk_first.begin(), kb->chunk_first.end(), dir.begin() + 2 * R + 1);
+  std::copy(kb->heavy_first.begin(), kb->heavy_first.end(), dir.begin() + 2 * (2 * R + 1));
+  kb->dir_dev = reinterpret_cast<uint32_t*>(derived + L.dir);
+  HTH_HIP(hipMemcpyAsync(kb->dir_dev, dir.data(), dir.size() * 4, hipMemcpyHostToDevice, st));
+  HTH_HIP(hipStreamSynchronize(st));
   return HTH_OK;
 }
 
@@ -867,6 +891,7 @@ extern "C" hth_status hth_kb_create(const hth_kb_desc* desc, void* derived, size
   kb->tune.t_segment_kb = (uint32_t)std::min<uint64_t>(1u << 22, env_u("HTHEDL_TSEG_KB", kb->tune.t_segment_kb));
   kb->tune.push_pct = (uint32_t)std::min<uint64_t>(100, env_u("HTHEDL_PUSH_PCT", kb->tune.push_pct));
   kb->tune.short_rows = (uint32_t)std::min<uint64_t>(64, env_u("HTHEDL_SHORT_ROWS", kb->tune.short_rows));
+  kb->view_min = (uint32_t)std::min<uint64_t>(0xFFFFFFFFu, env_u("HTHEDL_VIEW_MIN", kb->view_min));
   kb->heavy_min = (uint32_t)std::min<uint64_t>(
       1u << 30, std::max<uint64_t>(kHeavyMinFloor, env_u("HTHEDL_HEAVY_MIN", kb->heavy_min)));
   kb->lds_per_block = (size_t)lds;

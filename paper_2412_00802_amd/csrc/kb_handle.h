@@ -35,9 +35,12 @@ struct hth_kb_s {
   uint32_t* heavy_chunk0 = nullptr;    // first chunk of each heavy row, then the total
   std::vector<uint32_t> heavy_first;   // [2R+1] first heavy row of direction 2r + dir
   std::vector<uint32_t> chunk_first;   // [2R+1] first chunk of direction 2r + dir
+  uint32_t* dir_dev = nullptr;         // [3][2R+1] non-empty words, first heavy chunk, first heavy row
   uint32_t heavy_most = 0;             // most heavy rows in one direction
   uint32_t chunk_most = 0;             // most heavy chunks in one direction
   std::vector<uint32_t> concept_pop;   // [C] members of each concept
+  uint32_t view_min = 65536;           // fewest individuals for the example view (HTHEDL_VIEW_MIN)
+  uint32_t ex_hint = 0;                // examples (pos | neg) at load: whether plans use the example view
   // multi-valued numeric concrete roles (hth_kb_set_numeric): caller's arrays
   uint32_t n_num = 0;
   const int64_t* num_off = nullptr;    // [n_num][N+1]

@@ -1,0 +1,413 @@
+// The example view: the part of an evaluation that only coverage needs, done
+// over the examples alone.
+//
+// A hypothesis's result is its coverage of the positive and negative examples
+// (Algorithm 15).  Only instance sets that fillers read are needed for every
+// individual; a node above every role restriction matters at the examples
+// only, which are a few percent of the individuals.  The view numbers the
+// examples (the set bits of pos | neg, in order) and holds, over them:
+//   - bit rows (64 examples a word): the examples' positive and negative bits,
+//     thresholds, the restrictions that no filler reads, and copies of the
+//     full rows that root programs read (atoms, set rows, shared restrictions);
+//   - for each role direction used there, the examples' rows of its CSR.
+// The shared passes and region programs run on it unchanged: DevKB::view
+// points at {examples, words}, counted on the device, so nothing here depends
+// on what the host believes about the example rows (they are read at each
+// launch).  The host's count of the examples at load time (ex_hint) only
+// decides whether a plan uses the view, and its grid sizes; every area has
+// room for all individuals.
+// Included by exec.hip only.
+#pragma once
+
+namespace hth {
+namespace {
+
+constexpr uint32_t kExTile = 2048;     // words per block of the example list
+constexpr uint32_t kVDirTile = 1024;   // examples per tile of a direction's copy
+constexpr uint32_t kVRows = 16;        // row copies per block
+constexpr uint32_t kPosRow = 0xFFFFFFF0u, kNegRow = 0xFFFFFFF1u;   // sources of a copy: the example rows
+constexpr uint32_t kSlotRow = 1u << 31;   // source: a workspace row, counted from the plan's first role row
+constexpr uint32_t kViewFixed = 2;     // view rows 0 and 1: the positives, the negatives
+
+// One role direction of the view: its CSR copy starts at `base` in the view's
+// target area; compact: its targets are object ranks.
+struct ViewDir {
+  uint32_t rd, compact;
+  uint64_t base;
+};
+// view row dst = the examples' bits of row src
+struct ViewCopy {
+  uint32_t src, dst;
+};
+
+// Exclusive scan of p[0 .. n) in place by one block of 1024; -> the total.
+__device__ uint32_t block_scan_row(uint32_t* __restrict__ p, uint32_t n) {
+  __shared__ uint32_t s_w[16], s_carry;
+  const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  if (threadIdx.x == 0) s_carry = 0;
+  __syncthreads();
+  for (uint32_t c = 0; c < n; c += 1024) {
+    const uint32_t i = c + threadIdx.x, v = i < n ? p[i] : 0;
+    uint32_t inc = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t u = (uint32_t)__shfl_up((int)inc, d, 64);
+      if (lane >= (uint32_t)d) inc += u;
+    }
+    if (lane == 63) s_w[wv] = inc;
+    __syncthreads();
+    uint32_t before = s_carry;
+    for (uint32_t w = 0; w < wv; ++w) before += s_w[w];
+    if (i < n) p[i] = before + inc - v;
+    __syncthreads();
+    if (threadIdx.x == 1023) s_carry = before + inc;
+    __syncthreads();
+  }
+  return s_carry;
+}
+
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {   // inclusive
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t u = (uint32_t)__shfl_up((int)v, d, 64);
+    if (lane >= d) v += u;
+  }
+  return v;
+}
+
+// The example list in three steps: words' popcounts by tile, their scan (and
+// the view's sizes), the list.  hdr: {examples, words of 64 examples}.
+__device__ __forceinline__ uint32_t ex_words(const DevKB& kb, uint64_t (&v)[8]) {
+  const uint32_t w0 = blockIdx.x * kExTile + threadIdx.x * 8;
+  uint32_t n = 0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    v[i] = w0 + i < kb.W ? kb.pos[w0 + i] | kb.neg[w0 + i] : 0ull;
+    n += (uint32_t)__popcll(v[i]);
+  }
+  return n;
+}
+__global__ void __launch_bounds__(256) k_ex_sum(DevKB kb, uint32_t* __restrict__ tsum) {
+  __shared__ uint32_t s[4];
+  uint64_t v[8];
+  const uint32_t n = wave_sum(ex_words(kb, v));
+  if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = n;
+  __syncthreads();
+  if (threadIdx.x == 0) tsum[blockIdx.x] = s[0] + s[1] + s[2] + s[3];
+}
+__global__ void __launch_bounds__(1024) k_ex_scan(uint32_t* __restrict__ tsum, uint32_t tiles, uint32_t* __restrict__ hdr) {
+  const uint32_t m = block_scan_row(tsum, tiles);
+  if (threadIdx.x == 0) {
+    hdr[0] = m;
+    hdr[1] = (m + 63) / 64;
+  }
+}
+// list[i] = example i; words[w] = w (the view's passes visit every word)
+__global__ void __launch_bounds__(256)
+k_ex_list(DevKB kb, const uint32_t* __restrict__ tsum, uint32_t* __restrict__ list, uint32_t* __restrict__ words) {
+  __shared__ uint32_t s[4];
+  uint64_t v[8];
+  const uint32_t n = ex_words(kb, v), inc = wave_scan(n), wv = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 63) s[wv] = inc;
+  __syncthreads();
+  uint32_t at = tsum[blockIdx.x] + inc - n;
+  for (uint32_t w = 0; w < wv; ++w) at += s[w];
+  const uint32_t w0 = blockIdx.x * kExTile + threadIdx.x * 8;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    if (w0 + i >= kb.W) break;
+    words[w0 + i] = w0 + i;
+    for (uint64_t m = v[i]; m; m &= m - 1) list[at++] = (w0 + i) * 64 + (uint32_t)__builtin_ctzll(m);
+  }
+}
+
+// The examples' rows of each direction: degrees by tile, their scan, then the
+// offsets and the targets (a wave copies 64 rows at a time as one run: each
+// lane finds the row of its output position among the 64 in LDS).
+__device__ __forceinline__ const uint32_t* dir_offsets(const DevKB& kb, uint32_t rd) {
+  return (rd & 1 ? kb.inv_off : kb.fwd_off) + (size_t)(rd >> 1) * (kb.N + 1);
+}
+__global__ void __launch_bounds__(256)
+k_vdir_sum(DevKB kb, const ViewDir* __restrict__ dirs, const uint32_t* __restrict__ hdr,
+           const uint32_t* __restrict__ list, uint32_t tcap, uint32_t* __restrict__ tsum) {
+  __shared__ uint32_t s[4];
+  const uint32_t m = hdr[0], tiles = (m + kVDirTile - 1) / kVDirTile;
+  const uint32_t* off = dir_offsets(kb, dirs[blockIdx.y].rd);
+  for (uint32_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+    uint32_t n = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kVDirTile / 256; ++i) {
+      const uint32_t e = t * kVDirTile + i * 256 + threadIdx.x;
+      if (e < m) {
+        const uint32_t x = list[e];
+        n += off[x + 1] - off[x];
+      }
+    }
+    n = wave_sum(n);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = n;
+    __syncthreads();
+    if (threadIdx.x == 0) tsum[(size_t)blockIdx.y * tcap + t] = s[0] + s[1] + s[2] + s[3];
+  }
+}
+__global__ void __launch_bounds__(1024)
+k_vdir_scan(const uint32_t* __restrict__ hdr, uint32_t tcap, uint32_t N, uint32_t* __restrict__ tsum,
+            uint32_t* __restrict__ voff) {
+  const uint32_t m = hdr[0];
+  const uint32_t total = block_scan_row(tsum + (size_t)blockIdx.x * tcap, (m + kVDirTile - 1) / kVDirTile);
+  if (threadIdx.x == 0) voff[(size_t)blockIdx.x * (N + 1) + m] = total;
+}
+__global__ void __launch_bounds__(256)
+k_vdir_copy(DevKB kb, const ViewDir* __restrict__ dirs, const uint32_t* __restrict__ hdr,
+            const uint32_t* __restrict__ list, uint32_t tcap, const uint32_t* __restrict__ tsum,
+            uint32_t* __restrict__ voff, int32_t* __restrict__ vtg) {
+  constexpr uint32_t kSub = kVDirTile / 256;     // rounds of 64 rows a wave
+  __shared__ uint32_t s[4], s_pre[4][64], s_lo[4][64];
+  const uint32_t m = hdr[0], tiles = (m + kVDirTile - 1) / kVDirTile;
+  const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const ViewDir D = dirs[blockIdx.y];
+  const uint32_t* off = dir_offsets(kb, D.rd);
+  const int32_t* tg = (D.compact ? (D.rd & 1 ? kb.ctg_inv : kb.ctg_fwd) : (D.rd & 1 ? kb.inv_tg : kb.fwd_tg)) +
+                      kb.role_base[D.rd >> 1];
+  uint32_t* vo = voff + (size_t)blockIdx.y * (kb.N + 1);
+  int32_t* out = vtg + D.base;
+  for (uint32_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+    uint32_t lo[kSub], inc[kSub], tot[kSub], sum = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kSub; ++i) {
+      const uint32_t e = t * kVDirTile + wv * 64 * kSub + i * 64 + lane;
+      lo[i] = inc[i] = 0;
+      if (e < m) {
+        const uint32_t x = list[e];
+        lo[i] = off[x];
+        inc[i] = off[x + 1] - lo[i];
+      }
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < kSub; ++i) {
+      inc[i] = wave_scan(inc[i]);
+      tot[i] = (uint32_t)__builtin_amdgcn_readlane((int)inc[i], 63);
+      sum += tot[i];
+    }
+    __syncthreads();
+    if (lane == 0) s[wv] = sum;
+    __syncthreads();
+    uint32_t at = tsum[(size_t)blockIdx.y * tcap + t];
+    for (uint32_t w = 0; w < wv; ++w) at += s[w];
+#pragma unroll
+    for (uint32_t i = 0; i < kSub; ++i) {
+      const uint32_t e = t * kVDirTile + wv * 64 * kSub + i * 64 + lane;
+      const uint32_t up = (uint32_t)__shfl_up((int)inc[i], 1, 64), pre = lane ? up : 0u;
+      if (e < m) vo[e] = at + pre;
+      s_pre[wv][lane] = pre;
+      s_lo[wv][lane] = lo[i];
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll 4
+      for (uint32_t p = lane; p < tot[i]; p += 64) {
+        uint32_t r = 0;                    // the last row that starts at or before p
+#pragma unroll
+        for (uint32_t d = 32; d; d >>= 1)
+          if (s_pre[wv][r + d] <= p) r += d;
+        out[at + p] = tg[s_lo[wv][r] + p - s_pre[wv][r]];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      at += tot[i];
+    }
+  }
+}
+
+// Row copies: a wave takes 8 view words, a lane one example of each, and
+// gathers the examples' bits of one full row after another; a ballot makes a
+// word.  64 consecutive examples lie in a few lines of a row, so the loads
+// read each row about once: bound by HBM and by the bit tests.
+__global__ void __launch_bounds__(256)
+k_view_rows(DevKB kb, uint64_t* __restrict__ vslots, const uint32_t* __restrict__ hdr,
+            const uint32_t* __restrict__ list, const ViewCopy* __restrict__ copies, uint32_t n_copies,
+            uint32_t slot0) {
+  const uint32_t m = hdr[0], vw = hdr[1];
+  const uint32_t lane = threadIdx.x & 63, c0 = blockIdx.y * kVRows, c1 = min(c0 + kVRows, n_copies);
+  for (uint32_t b = blockIdx.x * 4 + (threadIdx.x >> 6); b * 8 < vw; b += gridDim.x * 4) {
+    uint32_t x[8];
+    bool in[8];
+#pragma unroll
+    for (uint32_t j = 0; j < 8; ++j) {
+      const uint32_t e = (b * 8 + j) * 64 + lane;
+      in[j] = e < m;
+      x[j] = list[in[j] ? e : 0u];
+    }
+#pragma unroll 2
+    for (uint32_t c = c0; c < c1; ++c) {
+      const ViewCopy C = copies[c];
+      const uint64_t* row = C.src == kPosRow ? kb.pos : C.src == kNegRow ? kb.neg
+                            : row_ptr(kb, C.src & kSlotRow ? slot0 + (C.src & ~kSlotRow) : C.src);
+      const uint32_t* r32 = reinterpret_cast<const uint32_t*>(row);
+      uint32_t v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = r32[x[j] >> 5];
+      uint64_t mine = 0;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const uint64_t w = __ballot(in[j] && ((v[j] >> (x[j] & 31)) & 1u));
+        if (lane == (uint32_t)j) mine = w;
+      }
+      if (lane < 8 && b * 8 + lane < vw) vslots[(size_t)C.dst * kb.S + b * 8 + lane] = mine;
+    }
+  }
+}
+
+// Whether a plan uses the view: the examples are few, and the individuals so
+// many that its extra launches (about ten) are worth it.
+inline bool view_wanted(const hth_kb_s& kb) {
+  return kb.N >= kb.view_min && kb.ex_hint && (uint64_t)kb.ex_hint * 4 <= kb.N;
+}
+
+// The view of one plan: its directions, shared passes and areas (offsets into
+// the workspace, from `at`).
+struct ViewPlan {
+  bool on = false;
+  std::vector<ViewDir> dirs;            // by view direction
+  std::vector<GroupTask> groups;        // as built from: real role and direction
+  std::vector<GroupTask> passes;        // as counted over: role = view direction, inv = 0
+  std::vector<GroupChunk> chunks;
+  uint32_t n_rows = kViewFixed, n_copies = 2, n_thg = 0;
+  uint64_t targets = 0;
+  size_t o_hdr = 0, o_list = 0, o_words = 0, o_tsum = 0, o_dsum = 0, o_off = 0, o_tg = 0, o_base = 0, o_slot = 0;
+
+  // the view direction of rd (added when new)
+  uint32_t dir(const hth_kb_s& kb, uint32_t rd) {
+    for (uint32_t v = 0; v < dirs.size(); ++v)
+      if (dirs[v].rd == rd) return v;
+    dirs.push_back(ViewDir{rd, kb.tune.t_compact && 2ull * kb.n_obj[rd] <= kb.N ? 1u : 0u, targets});
+    targets += kb.role_base[rd / 2 + 1] - kb.role_base[rd / 2];
+    return (uint32_t)dirs.size() - 1;
+  }
+  // `count` role nodes of direction rd as shared passes of at most gk, their
+  // members from `first` on
+  void add_passes(const hth_kb_s& kb, uint32_t rd, uint64_t count, uint32_t gk, uint32_t first, bool short_rows) {
+    const uint32_t v = dir(kb, rd);
+    for (uint64_t i0 = 0; i0 < count; i0 += gk) {
+      GroupTask g{};
+      g.role = rd / 2;
+      g.inv = rd & 1;
+      g.k = (uint32_t)std::min<uint64_t>(gk, count - i0);
+      g.first = (uint32_t)(first + i0);
+      g.n_words = kb.n_words[rd];
+      g.n_obj_words = kb.n_words[rd ^ 1u];
+      g.compact = dirs[v].compact;
+      g.short_rows = short_rows;
+      groups.push_back(g);
+      g.role = v;
+      g.inv = 0;
+      passes.push_back(g);
+    }
+  }
+  uint32_t tiles(const hth_kb_s& kb) const { return (kb.W + kExTile - 1) / kExTile; }
+  uint32_t dir_tiles(const hth_kb_s& kb) const { return (kb.N + kVDirTile - 1) / kVDirTile; }
+  template <class Area>
+  void layout(const hth_kb_s& kb, Area&& area) {
+    if (!on) return;
+    o_hdr = area(256);
+    o_list = area((size_t)kb.N * 4);
+    o_words = area((size_t)kb.W * 4);
+    o_tsum = area((size_t)tiles(kb) * 4);
+    o_dsum = area(dirs.size() * dir_tiles(kb) * 4);
+    o_off = area(dirs.size() * ((size_t)kb.N + 1) * 4);
+    o_tg = area(targets * 4 + 4);
+    o_slot = area((size_t)n_rows * kb.S * 8);
+  }
+};
+
+// The DevKB that the view's passes and regions see.  bases: [dirs] device
+// copy of the directions' first targets.
+inline DevKB view_kb(const DevKB& d, const ViewPlan& V, char* ws, const uint64_t* bases) {
+  DevKB x = d;
+  x.view = reinterpret_cast<const uint32_t*>(ws + V.o_hdr);
+  x.slots = reinterpret_cast<uint64_t*>(ws + V.o_slot);
+  x.n_concepts = x.n_fixed = 0;
+  x.fwd_off = reinterpret_cast<const uint32_t*>(ws + V.o_off);
+  x.fwd_tg = x.ctg_fwd = reinterpret_cast<const int32_t*>(ws + V.o_tg);
+  x.role_base = bases;
+  x.words = reinterpret_cast<const uint32_t*>(ws + V.o_words);
+  x.pos = x.slots;
+  x.neg = x.slots + d.S;
+  return x;
+}
+
+// Everything of the view before its thresholds, passes and regions.
+hth_status launch_view_rows(Launcher& L, const DevKB& d, const ViewPlan& V, char* ws, const ViewDir* dirs,
+                            const ViewCopy* copies, uint32_t slot0) {
+  const hth_kb_s& kb = L.kb;
+  uint32_t* hdr = reinterpret_cast<uint32_t*>(ws + V.o_hdr);
+  uint32_t* list = reinterpret_cast<uint32_t*>(ws + V.o_list);
+  uint32_t* words = reinterpret_cast<uint32_t*>(ws + V.o_words);
+  uint32_t* tsum = reinterpret_cast<uint32_t*>(ws + V.o_tsum);
+  uint32_t* dsum = reinterpret_cast<uint32_t*>(ws + V.o_dsum);
+  uint32_t* voff = reinterpret_cast<uint32_t*>(ws + V.o_off);
+  int32_t* vtg = reinterpret_cast<int32_t*>(ws + V.o_tg);
+  uint64_t* slots = reinterpret_cast<uint64_t*>(ws + V.o_slot);
+  const uint32_t tiles = V.tiles(kb), tcap = V.dir_tiles(kb), nd = (uint32_t)V.dirs.size();
+  hth_status s = L.run(HTH_K_REGION, 2.0 * kb.W * 8, [&] {
+    hipLaunchKernelGGL(k_ex_sum, dim3(tiles), dim3(256), 0, L.st, d, tsum);
+    hipLaunchKernelGGL(k_ex_scan, dim3(1), dim3(1024), 0, L.st, tsum, tiles, hdr);
+    hipLaunchKernelGGL(k_ex_list, dim3(tiles), dim3(256), 0, L.st, d, tsum, list, words);
+  });
+  if (s) return s;
+  if (nd) {
+    // blocks for the examples expected; more of them are taken in turns
+    const uint32_t want = kb.ex_hint / kVDirTile + 1, gx = std::max(1u, std::min(want, 65536u / nd + 1));
+    s = L.run(HTH_K_GROUP, 0.0, [&] {
+      hipLaunchKernelGGL(k_vdir_sum, dim3(gx, nd), dim3(256), 0, L.st, d, dirs, hdr, list, tcap, dsum);
+      hipLaunchKernelGGL(k_vdir_scan, dim3(nd), dim3(1024), 0, L.st, hdr, tcap, kb.N, dsum, voff);
+      hipLaunchKernelGGL(k_vdir_copy, dim3(gx, nd), dim3(256), 0, L.st, d, dirs, hdr, list, tcap, dsum, voff, vtg);
+    });
+    if (s) return s;
+  }
+  const uint32_t gx = std::max(1u, std::min((view_words_hint(kb) + 31) / 32, 16384u));
+  for (uint32_t c = 0; c < V.n_copies; c += 65535 * kVRows) {
+    const uint32_t n = std::min(V.n_copies - c, 65535 * kVRows);
+    s = L.run(HTH_K_REGION, (double)n * kb.W * 8, [&] {
+      hipLaunchKernelGGL(k_view_rows, dim3(gx, (n + kVRows - 1) / kVRows), dim3(256), 0, L.st, d, slots, hdr, list,
+                         copies + c, n, slot0);
+    });
+    if (s) return s;
+  }
+  return HTH_OK;
+}
+
+// The whole view, after every full row of the plan is complete: its lists, row
+// copies, thresholds and shared passes.  *d becomes the view's DevKB for the
+// root regions.
+hth_status launch_view(Launcher& L, const DevKB& full, const ViewPlan& V, char* ws, const ViewDir* dirs,
+                       const uint64_t* bases, const ViewCopy* copies, uint32_t slot0, const ThrGroup* thg,
+                       const ThrTask* thr, const GroupTask* groups, const GroupTask* passes,
+                       const GroupMember* members, const uint32_t* xslots, void* tarea, DevKB* d) {
+  const hth_kb_s& kb = L.kb;
+  const DevKB f = full;
+  hth_status s = launch_view_rows(L, f, V, ws, dirs, copies, slot0);
+  if (s) return s;
+  const DevKB x = view_kb(f, V, ws, bases);
+  if (V.n_thg) {
+    const uint32_t* list = reinterpret_cast<const uint32_t*>(ws + V.o_list);
+    const uint32_t bpt = std::max<uint32_t>(1, (view_words_hint(kb) + 31) / 32);
+    s = split_launch(L, HTH_K_THRESHOLD, 4.0 * kb.ex_hint * V.n_thg, V.n_thg, bpt, 256,
+                     [&](uint32_t i0, uint32_t, uint32_t blocks) {
+                       hipLaunchKernelGGL(k_threshold<true>, dim3(blocks), dim3(256), 0, L.st, x, thg + i0, thr, bpt, list);
+                     });
+    if (s) return s;
+  }
+  if (!V.groups.empty()) {
+    L.csr_seen.clear();
+    s = launch_groups(L, f, groups, members, V.groups, V.chunks, xslots, tarea, nullptr, &x, passes);
+    if (s) return s;
+  }
+  *d = x;
+  return HTH_OK;
+}
+
+}  // namespace
+}  // namespace hth
