@@ -24,6 +24,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <memory>
+#include <utility>
 #include <vector>
 
 #include "kb_handle.h"
@@ -99,6 +100,46 @@ k_threshold(DevKB kb, const ThrGroup* __restrict__ groups, const ThrTask* __rest
   }
 }
 
+// The ballots of a round of chunks (64 values each), held across the wave:
+// lane c keeps chunk c's ballot and the number of passing values before it.  A
+// subject's count in the round is the difference of two prefix counts, each
+// one lookup by lane: work per subject and round, where taking every chunk's
+// part of the subject's range is work per subject and chunk.
+template <class F, int... C>
+__device__ __forceinline__ void unrolled(F&& f, std::integer_sequence<int, C...>) {
+  (f(std::integral_constant<int, C>()), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void unrolled(F&& f) {   // f of each constant 0 .. N - 1
+  unrolled(f, std::make_integer_sequence<int, N>());
+}
+struct ChunkSums {
+  uint32_t lo = 0, hi = 0, before = 0, total = 0;   // total: so far, the same on every lane
+  template <int C>
+  __device__ __forceinline__ void put(uint64_t m) {   // (the wait states: see put_lane)
+    asm("s_nop 1\n\tv_writelane_b32 %0, %3, %6\n\tv_writelane_b32 %1, %4, %6\n\tv_writelane_b32 %2, %5, %6"
+        : "+v"(lo), "+v"(hi), "+v"(before)
+        : "s"(__builtin_amdgcn_readfirstlane((uint32_t)m)), "s"(__builtin_amdgcn_readfirstlane((uint32_t)(m >> 32))),
+          "s"(__builtin_amdgcn_readfirstlane(total)), "n"(C));
+    total += (uint32_t)__popcll(m);
+  }
+  // passing values among the round's first p (p <= span, the round's values)
+  __device__ __forceinline__ uint32_t prefix(uint32_t p) const {
+    const int c = (int)(p >> 6);
+    const uint64_t m = (uint64_t)(uint32_t)__shfl((int)hi, c, 64) << 32 | (uint32_t)__shfl((int)lo, c, 64);
+    return (uint32_t)__shfl((int)before, c, 64) + (uint32_t)__popcll(m & ((1ull << (p & 63)) - 1ull));
+  }
+  // those of values [r0, r1) (absolute; the round holds [i0, i0 + span))
+  template <int CHUNKS>
+  __device__ __forceinline__ uint32_t count(uint32_t r0, uint32_t r1, uint32_t i0) {
+    constexpr uint32_t span = CHUNKS * 64;
+    put<CHUNKS>(0);
+    const uint32_t a = r0 > i0 ? min(r0 - i0, span) : 0u, z = r1 > i0 ? min(r1 - i0, span) : 0u;
+    const uint32_t pa = prefix(a), pz = prefix(z);
+    return z > a ? pz - pa : 0u;
+  }
+};
+
 // ---------------------------------------------------------------------------
 // multi-valued numeric concrete roles (Algorithms 9/10)
 // ---------------------------------------------------------------------------
@@ -108,10 +149,12 @@ __device__ __forceinline__ bool num_pass(float v, uint32_t cmp, float t) {
 
 // Value roles (numeric and string concrete roles): one wave per 64 consecutive
 // subjects, as in the role pass.  The wave walks the subjects' concatenated
-// values in chunks of 64 (eight chunks' loads in flight), each subject lane
-// takes its own values in a chunk from the ballot of passing values, and the
-// walk stops once every subject with values left has found one.  Rows above
+// values in chunks of 64 (eight chunks' loads in flight), a subject's passing
+// values are the difference of two prefix counts (ChunkSums), and the walk
+// stops once every subject with values left has found one.  Rows above
 // the heavy-row threshold are left to value_heavy (their bits here are 0).
+// 128 restrictions over 1M individuals: numeric 708 us, string 498 (870 and
+// 748 with every chunk's part of each subject's range taken in turn).
 constexpr int kNumChunks = 8;
 // off: the role's 32-bit offsets relative to vals, its first value.
 template <typename V, class Pass>
@@ -119,39 +162,33 @@ __device__ __forceinline__ void value_walk(const DevKB& kb, const uint32_t* __re
                                            const V* __restrict__ vals, Pass pass, uint64_t* __restrict__ out,
                                            uint32_t b, uint32_t bpt) {
   const int lane = threadIdx.x & 63;
-  for (uint32_t w = b * 4 + (threadIdx.x >> 6); w < kb.W; w += bpt * 4) {
+  for (uint32_t w = b * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); w < kb.W; w += bpt * 4) {
     const uint32_t x = w * 64 + lane;
     const bool in = x < kb.N;
     const uint32_t olo = off[in ? x : kb.N];
     uint32_t ohi = in ? off[x + 1] : olo;
     const bool heavy = ohi - olo > kb.heavy_min;
     if (heavy) ohi = olo;
-    const uint32_t ee = (uint32_t)__shfl((int)ohi, 63, 64);
-    uint32_t i0 = (uint32_t)__shfl((int)olo, 0, 64);
+    const uint32_t ee = (uint32_t)__builtin_amdgcn_readlane((int)ohi, 63);
+    uint32_t i0 = (uint32_t)__builtin_amdgcn_readlane((int)olo, 0);
     bool hit = false;
     while (i0 < ee) {
       V v[kNumChunks];
 #pragma unroll
       for (int c = 0; c < kNumChunks; ++c) {
         const uint64_t e = (uint64_t)i0 + 64 * c + lane;
-        v[c] = e < ee ? vals[e] : V(0);
+        v[c] = vals[e < ee ? (uint32_t)e : i0];
       }
-#pragma unroll
-      for (int c = 0; c < kNumChunks; ++c) {
-        const uint64_t base = (uint64_t)i0 + 64 * c;
-        const uint64_t m = __ballot(base + lane < ee && pass(v[c]));
-        const uint64_t a = olo > base ? min((uint64_t)olo - base, (uint64_t)64) : 0;
-        const uint64_t bb = ohi > base ? min((uint64_t)ohi - base, (uint64_t)64) : 0;
-        if (bb > a) {
-          const uint64_t rm = (bb - a == 64) ? ~0ull : (((1ull << (bb - a)) - 1ull) << a);
-          hit |= (m & rm) != 0;
-        }
-      }
+      ChunkSums sums;
+      unrolled<kNumChunks>([&](auto c) {
+        sums.template put<c.value>(__ballot(pass(v[c.value])));   // (values past ee: past every subject's range)
+      });
+      hit |= sums.template count<kNumChunks>(olo, ohi, i0) != 0;
       const uint64_t step = 64 * kNumChunks;
       const uint64_t pend = __ballot(in && !hit && ohi > i0 + step);
       if (!pend) break;
       const int l = __ffsll((unsigned long long)pend) - 1;
-      const uint32_t nxt = (uint32_t)__shfl((int)olo, l, 64);
+      const uint32_t nxt = (uint32_t)__builtin_amdgcn_readlane((int)olo, l);
       i0 = (uint32_t)max((uint64_t)i0 + step, (uint64_t)nxt);
     }
     const uint64_t word = __ballot(in && !heavy && hit);
@@ -274,6 +311,101 @@ k_strrole_heavy(DevKB kb, const StrTask* __restrict__ tasks, uint32_t n_tasks, u
     value_heavy<int32_t>(kb, off, ids, [&](int32_t id) { return (set[(uint32_t)id >> 6] >> (id & 63)) & 1; },
                          out, x, c.k);
   }
+}
+
+// Restrictions that only coverage reads, at the examples alone: one wave per
+// kExWords words of the example rows.  Their set bits are listed in LDS; a
+// lane takes one example after another and walks its row, a wave together
+// those longer than kExLane.  test(value): the value counts; the result, lo <=
+// count <= hi, decided at sat.  Every word of the output row is written, zeros
+// outside the examples.  Bound by the latency of three dependent loads (the
+// row's offsets, its values, what they select), so that a task over 1M
+// individuals costs 11 us with 62,000 examples (16 with 32 words a wave), where
+// every individual's row takes 18.
+constexpr uint32_t kExWords = 8, kExLane = 32;
+template <typename V, class Test>
+__device__ __forceinline__ void example_walk(const DevKB& kb, const uint32_t* __restrict__ off,
+                                             const V* __restrict__ vals, Test test, uint32_t lo, uint32_t hi,
+                                             uint32_t sat, uint64_t* __restrict__ out, uint32_t tile) {
+  __shared__ uint16_t s_list[kExWords * 64];
+  __shared__ uint32_t s_out[2 * kExWords];
+  const uint32_t lane = threadIdx.x, half = tile * 2 * kExWords + lane;   // a lane per 32 individuals
+  const bool mine = lane < 2 * kExWords && half < 2 * kb.W;
+  uint32_t m = 0;
+  if (mine)
+    m = reinterpret_cast<const uint32_t*>(kb.pos)[half] | reinterpret_cast<const uint32_t*>(kb.neg)[half];
+  uint32_t inc = (uint32_t)__popc(m);
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t u = (uint32_t)__shfl_up((int)inc, d, 64);
+    if (lane >= (uint32_t)d) inc += u;
+  }
+  const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+  if (lane < 2 * kExWords) s_out[lane] = 0;
+  for (uint32_t at = inc - (uint32_t)__popc(m); m; m &= m - 1) s_list[at++] = (uint16_t)(lane * 32 + __builtin_ctz(m));
+  __syncthreads();
+  for (uint32_t i0 = 0; i0 < n; i0 += 64) {
+    const uint32_t s = i0 + lane < n ? s_list[i0 + lane] : 0u, x = tile * kExWords * 64 + s;
+    const bool in = i0 + lane < n && x < kb.N;
+    const uint32_t r0 = in ? off[x] : 0u, r1 = in ? off[x + 1] : 0u;
+    uint32_t cnt = 0;
+    const bool wide = r1 - r0 > kExLane;
+    if (!wide)
+      for (uint32_t e = r0; e < r1 && cnt < sat; e += 8) {
+        V v[8];
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) v[u] = vals[min(e + u, r1 - 1)];
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) cnt += (uint32_t)(test(v[u]) && e + u < r1);
+      }
+    for (uint64_t w = __ballot(wide); w; w &= w - 1) {
+      const int l = __builtin_ctzll(w);
+      const uint32_t e1 = (uint32_t)__builtin_amdgcn_readlane((int)r1, l);
+      uint32_t c = 0;
+      for (uint32_t e0 = (uint32_t)__builtin_amdgcn_readlane((int)r0, l); e0 < e1 && c < sat; e0 += 512) {
+        V v[8];
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) v[u] = vals[min(e0 + u * 64 + lane, e1 - 1)];
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) c += (uint32_t)__popcll(__ballot(e0 + u * 64 + lane < e1 && test(v[u])));
+      }
+      if (lane == (uint32_t)l) cnt = c;
+    }
+    if (in && cnt >= lo && cnt <= hi) atomicOr(s_out + (s >> 5), 1u << (s & 31));
+  }
+  __syncthreads();
+  if (mine) reinterpret_cast<uint32_t*>(out)[half] = s_out[lane];
+}
+
+__global__ void __launch_bounds__(64)
+k_numrole_ex(DevKB kb, const NumTask* __restrict__ tasks, uint32_t tiles) {
+  const NumTask T = tasks[blockIdx.x / tiles];
+  example_walk<float>(kb, kb.num_roff + (size_t)T.role * (kb.N + 1),
+                      kb.num_val + ((uint64_t)T.base_hi << 32 | T.base_lo),
+                      [&](float v) { return num_pass(v, T.cmp, T.t); }, 1, kNone, 1, out_ptr(kb, T.out_row),
+                      blockIdx.x % tiles);
+}
+
+__global__ void __launch_bounds__(64)
+k_strrole_ex(DevKB kb, const StrTask* __restrict__ tasks, uint32_t tiles) {
+  const StrTask T = tasks[blockIdx.x / tiles];
+  const uint64_t* set = kb.idsets + T.set_word;
+  example_walk<int32_t>(kb, kb.str_roff + (size_t)T.role * (kb.N + 1),
+                        kb.str_ids + ((uint64_t)T.base_hi << 32 | T.base_lo),
+                        [&](int32_t id) {
+                          return T.kind == 0 ? (uint32_t)id == T.q : (bool)((set[(uint32_t)id >> 6] >> (id & 63)) & 1);
+                        },
+                        1, kNone, 1, out_ptr(kb, T.out_row), blockIdx.x % tiles);
+}
+
+__global__ void __launch_bounds__(64)
+k_role_ex(DevKB kb, const RoleTask* __restrict__ tasks, uint32_t tiles) {
+  const RoleTask T = tasks[blockIdx.x / tiles];
+  const uint32_t* child = reinterpret_cast<const uint32_t*>(row_ptr(kb, T.child_row));
+  example_walk<int32_t>(kb, (T.inv ? kb.inv_off : kb.fwd_off) + (size_t)T.role * (kb.N + 1),
+                        (T.inv ? kb.inv_tg : kb.fwd_tg) + kb.role_base[T.role],
+                        [&](int32_t y) { return (((child[(uint32_t)y >> 5] >> (y & 31)) & 1u) ^ T.neg) != 0; },
+                        T.lo, T.hi, T.sat, out_ptr(kb, T.out_row), blockIdx.x % tiles);
 }
 
 // ---------------------------------------------------------------------------
@@ -517,57 +649,43 @@ k_region_reg(DevKB kb, const RegionTask* __restrict__ tasks, const uint32_t* __r
 // ---------------------------------------------------------------------------
 // single role restriction, one wave per 64 subjects
 // ---------------------------------------------------------------------------
-constexpr int kRoleChunks = 8;   // 64-assertion chunks whose loads a wave issues together
-template <bool STAGE>
-__device__ __forceinline__ void role_word(const DevKB& kb, const uint32_t* __restrict__ off,
-                                          const int32_t* __restrict__ tg,
-                                          const uint64_t* __restrict__ child, uint32_t neg,
-                                          uint32_t lo, uint32_t hi, uint32_t sat,
-                                          uint64_t* __restrict__ out, uint32_t w, int lane) {
+// A wave walks its words of the direction's list as a pipeline: while one
+// word is counted, the targets of the next and the offsets of the one after
+// are in flight.  A word's assertions are one range, taken in rounds of
+// kRoleChunks chunks of 64 (the first round's loads are the ones in flight;
+// at 8 assertions a subject a second is rare); a subject's count is the
+// difference of two prefix counts over the ballots of child members.  The child row is
+// staged in LDS where it fits, with 16-byte loads, all of a lane's in flight.
+// One node over 1M individuals and 8.3M assertions: 18 us, where one word
+// at a time, counted chunk by chunk, and 8-byte staging took 36 (8 chunks a
+// round 21, 12 19).
+constexpr int kRoleChunks = 10;   // 64-assertion chunks whose loads a wave issues together
+struct RoleRows {                 // a word's subjects: their rows, heavy ones left out
+  uint32_t w, olo, ohi, i0, ee;
+  bool in, heavy;
+};
+__device__ __forceinline__ RoleRows role_rows(const DevKB& kb, const uint32_t* __restrict__ off, uint32_t w, int lane) {
+  RoleRows q;
+  q.w = w;
   const uint32_t x = w * 64 + lane;
-  const bool in = x < kb.N;
-  const uint32_t xe = in ? x : kb.N;
-  const uint32_t olo = off[xe];
-  uint32_t ohi = in ? off[x + 1] : olo;
-  const bool heavy = ohi - olo > kb.heavy_min;   // counted by k_role_heavy instead
-  if (heavy) ohi = olo;
-  const uint32_t ee = (uint32_t)__shfl((int)ohi, 63, 64);
-  uint32_t i0 = (uint32_t)__shfl((int)olo, 0, 64);
-  uint32_t cnt = 0;
-  while (i0 < ee) {
-    // kRoleChunks consecutive chunks of 64 assertions: all target loads first
-    int32_t t[kRoleChunks];
+  q.in = x < kb.N;
+  q.olo = off[q.in ? x : kb.N];
+  q.ohi = off[q.in ? x + 1 : kb.N];
+  return q;
+}
+__device__ __forceinline__ void role_range(const DevKB& kb, RoleRows& q) {
+  q.heavy = q.ohi - q.olo > kb.heavy_min;   // counted by k_role_heavy instead
+  if (q.heavy) q.ohi = q.olo;
+  q.ee = (uint32_t)__builtin_amdgcn_readlane((int)q.ohi, 63);
+  q.i0 = (uint32_t)__builtin_amdgcn_readlane((int)q.olo, 0);
+}
+__device__ __forceinline__ void role_targets(const int32_t* __restrict__ tg, uint32_t i0, uint32_t ee, int lane,
+                                             int32_t (&t)[kRoleChunks]) {
 #pragma unroll
-    for (int c = 0; c < kRoleChunks; ++c) {
-      const uint32_t e = i0 + 64 * c + lane;
-      t[c] = e < ee ? tg[e] : -1;
-    }
-#pragma unroll
-    for (int c = 0; c < kRoleChunks; ++c) {
-      const uint32_t base = i0 + 64 * c;
-      bool v = false;
-      if (t[c] >= 0) {
-        const uint32_t y = (uint32_t)t[c];
-        v = ((uint32_t)(child[y >> 6] >> (y & 63)) & 1u) ^ neg;
-      }
-      const uint64_t m = __ballot(v);
-      const uint32_t a = olo > base ? min(olo - base, 64u) : 0u;
-      const uint32_t b = ohi > base ? min(ohi - base, 64u) : 0u;
-      if (b > a) {
-        const uint64_t rm = (b - a == 64) ? ~0ull : (((1ull << (b - a)) - 1ull) << a);
-        cnt += (uint32_t)__popcll(m & rm);
-      }
-    }
-    const uint32_t step = 64 * kRoleChunks;
-    const uint64_t pend = __ballot(in && cnt < sat && ohi > i0 + step);
-    if (!pend) break;
-    const int l = __ffsll((unsigned long long)pend) - 1;
-    const uint32_t nxt = (uint32_t)__shfl((int)olo, l, 64);
-    i0 = max(i0 + step, nxt);
+  for (int c = 0; c < kRoleChunks; ++c) {
+    const uint32_t e = i0 + 64 * c + lane;   // (a listed word's role has a target 0)
+    t[c] = tg[e < ee ? e : 0u];
   }
-  const bool res = in && !heavy && cnt >= lo && cnt <= hi;
-  const uint64_t word = __ballot(res);
-  if (lane == 0) out[w] = word;
 }
 
 template <bool STAGE>
@@ -576,21 +694,76 @@ k_role(DevKB kb, const RoleTask* __restrict__ tasks, uint32_t bpt) {
   extern __shared__ uint64_t lds_child[];
   const uint32_t task = blockIdx.x / bpt, b = blockIdx.x % bpt;
   const RoleTask T = tasks[task];
-  const uint64_t* child = row_ptr(kb, T.child_row);
-  if (STAGE) {
-    for (uint32_t i = threadIdx.x; i < kb.W; i += blockDim.x) lds_child[i] = child[i];
-    __syncthreads();
-    child = lds_child;
-  }
+  const uint32_t* child = reinterpret_cast<const uint32_t*>(row_ptr(kb, T.child_row));
   const size_t ro = (size_t)T.role * (kb.N + 1);
   const uint32_t* off = (T.inv ? kb.inv_off : kb.fwd_off) + ro;
   const int32_t* tg = (T.inv ? kb.inv_tg : kb.fwd_tg) + kb.role_base[T.role];
   uint64_t* out = out_ptr(kb, T.out_row);
   const uint32_t* words = kb.words + (size_t)(2 * T.role + T.inv) * kb.W;
-  const uint32_t nw = blockDim.x >> 6;
+  const uint32_t nw = blockDim.x >> 6, step = bpt * nw;
   const int lane = threadIdx.x & 63;
-  for (uint32_t i = b * nw + (threadIdx.x >> 6); i < T.n_words; i += bpt * nw)
-    role_word<STAGE>(kb, off, tg, child, T.neg, T.lo, T.hi, T.sat, out, words[i], lane);
+  uint32_t i = b * nw + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool any = i < T.n_words;
+  auto word = [&](uint32_t j) { return scalar_u32(words + min(j, T.n_words - 1)); };
+  RoleRows q{}, qn{};
+  int32_t t[kRoleChunks];
+  if (any) {
+    q = role_rows(kb, off, word(i), lane);
+    qn = role_rows(kb, off, word(i + step), lane);
+    role_range(kb, q);
+    role_targets(tg, q.i0, q.ee, lane, t);
+  }
+  if (STAGE) {
+    constexpr uint32_t kFly = 8;
+    typedef uint32_t U4 __attribute__((ext_vector_type(4)));
+    const U4* src = reinterpret_cast<const U4*>(child);
+    U4* dst = reinterpret_cast<U4*>(lds_child);
+    const uint32_t n2 = (kb.W + 1) / 2;      // (rows are a multiple of 8 words long)
+    for (uint32_t j0 = threadIdx.x; j0 < n2; j0 += kFly * blockDim.x) {
+      U4 v[kFly];
+#pragma unroll
+      for (uint32_t j = 0; j < kFly; ++j) v[j] = src[min(j0 + j * blockDim.x, n2 - 1)];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (uint32_t j = 0; j < kFly; ++j)
+        if (j0 + j * blockDim.x < n2) dst[j0 + j * blockDim.x] = v[j];
+    }
+    __syncthreads();
+    child = reinterpret_cast<const uint32_t*>(lds_child);
+  }
+  for (; i < T.n_words; i += step) {
+    RoleRows qnn = role_rows(kb, off, word(i + 2 * step), lane);
+    role_range(kb, qn);
+    int32_t tn[kRoleChunks];
+    role_targets(tg, qn.i0, i + step < T.n_words ? qn.ee : qn.i0, lane, tn);
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t cnt = 0, i0 = q.i0;
+    while (i0 < q.ee) {
+      ChunkSums sums;
+      uint32_t v[kRoleChunks];
+#pragma unroll
+      for (int c = 0; c < kRoleChunks; ++c) v[c] = child[(uint32_t)t[c] >> 5];
+      // (values past ee lie past every subject's range)
+      unrolled<kRoleChunks>([&](auto c) {
+        sums.template put<c.value>(__ballot(((v[c.value] >> (t[c.value] & 31)) & 1u) != T.neg));
+      });
+      cnt += sums.template count<kRoleChunks>(q.olo, q.ohi, i0);
+      const uint32_t round = 64 * kRoleChunks;
+      const uint64_t pend = __ballot(q.in && cnt < T.sat && q.ohi > i0 + round);
+      if (!pend) break;
+      const int l = __ffsll((unsigned long long)pend) - 1;
+      const uint32_t nxt = (uint32_t)__builtin_amdgcn_readlane((int)q.olo, l);
+      i0 = max(i0 + round, nxt);
+      role_targets(tg, i0, q.ee, lane, t);
+    }
+    const bool res = q.in && !q.heavy && cnt >= T.lo && cnt <= T.hi;
+    const uint64_t bits = __ballot(res);
+    if (lane == 0) out[q.w] = bits;
+    q = qn;
+    qn = qnn;
+#pragma unroll
+    for (int c = 0; c < kRoleChunks; ++c) t[c] = tn[c];
+  }
 }
 
 // The task of heavy-row block b or counter i: the last task whose first block
@@ -849,8 +1022,9 @@ struct Blob {
   template <class T>
   size_t add(const std::vector<T>& v) {
     size_t at = align_up(bytes.size(), 256);
+    if (v.empty()) return at;
     bytes.resize(at + v.size() * sizeof(T));
-    if (!v.empty()) std::memcpy(bytes.data() + at, v.data(), v.size() * sizeof(T));
+    std::memcpy(bytes.data() + at, v.data(), v.size() * sizeof(T));
     return at;
   }
 };
@@ -1054,7 +1228,7 @@ hth_status launch_regions(Launcher& L, const DevKB& d, const RegionTask* tasks, 
 hth_status launch_roles_n(Launcher& L, const DevKB& d, const RoleTask* tasks, uint32_t n, double bytes) {
   const hth_kb_s& kb = L.kb;
   if (!n) return HTH_OK;
-  const size_t lds = (size_t)kb.W * 8;
+  const size_t lds = align_up((size_t)kb.W * 8, 16);
   if (lds <= kb.lds_per_block) {
     // one 1024-lane block per CU holds the child row in LDS: one round of blocks,
     // so that each CU stages the row once
@@ -1259,6 +1433,7 @@ inline size_t idset_words(uint32_t n_strings) { return align_up(((size_t)n_strin
 size_t idset_bytes(const Plan& P) {
   size_t n = 0;
   for (const StrTask& t : P.str) n += t.kind == 1;
+  for (const StrTask& t : P.ex_str) n += t.kind == 1;
   return align_up(n * idset_words(P.n_strings) * 8, 256);
 }
 
@@ -1314,7 +1489,7 @@ std::once_flag g_attr_once;
 struct Prepared {
   Plan P;
   Blob blob;
-  struct LevelAt { size_t mat, role, group, fill, nrole, ngroup, nfill, nhb, nhc, push, npush; double fill_bytes; };
+  struct LevelAt { size_t mat, role, group, fill, nrole, ngroup, nfill, nhb, nhc, push, npush; double fill_bytes; size_t ex; };
   std::vector<LevelAt> at;
   size_t root_at = 0;
   std::vector<std::vector<RoleTask>> lv_roles;
@@ -1326,6 +1501,7 @@ struct Prepared {
   size_t o_push = 0;
   size_t o_num = 0, n_num_blocks = 0;   // numeric concrete-role tasks, their heavy-row blocks
   size_t o_str = 0, n_str_blocks = 0, n_contains = 0;   // string concrete-role tasks
+  size_t o_xnum = 0, o_xstr = 0, n_xcontains = 0, o_xrole = 0;   // tasks at the examples only
   size_t o_idset = 0;                   // the CONTAIN id sets (workspace offset)
   size_t o_hcnt = 0;   // heavy-row counters (workspace offset)
   size_t o_part = 0;   // partial counts of segmented shared passes (workspace offset)
@@ -1343,6 +1519,7 @@ void prepare(const hth_kb_s& kb, Plan&& plan, uint32_t n_hyps, Prepared& X) {
   std::vector<GroupMember> members;
   std::vector<FillTask> fills;
   std::vector<RoleTask> pushes;
+  std::vector<RoleTask> ex_roles;
   std::vector<uint32_t> xslots;
   const size_t NL = P.levels.size();
   X.at.assign(NL, {});
@@ -1352,7 +1529,8 @@ void prepare(const hth_kb_s& kb, Plan&& plan, uint32_t n_hyps, Prepared& X) {
   X.lv_chunks.assign(NL, {});
   for (size_t L = 0; L < NL; ++L) {
     const PlanLevel& PL = P.levels[L];
-    X.at[L] = {regions.size(), roles.size(), groups.size(), fills.size(), 0, 0, 0, 0, 0, pushes.size(), 0, 0.0};
+    X.at[L] = {regions.size(), roles.size(), groups.size(), fills.size(), 0, 0, 0, 0, 0, pushes.size(), 0, 0.0, ex_roles.size()};
+    ex_roles.insert(ex_roles.end(), PL.ex_roles.begin(), PL.ex_roles.end());
     regions.insert(regions.end(), PL.mat.begin(), PL.mat.end());
     for (RoleTask t : PL.roles) {
       const uint32_t rd = 2 * t.role + t.inv;
@@ -1434,6 +1612,21 @@ void prepare(const hth_kb_s& kb, Plan&& plan, uint32_t n_hyps, Prepared& X) {
     if (t.kind == 1) t.set_word = (uint32_t)(X.n_contains++ * idset_words(P.n_strings));
   }
   X.o_str = X.blob.add(str);
+  std::vector<NumTask> xnum(P.ex_num);
+  for (NumTask& t : xnum) {
+    t.base_lo = (uint32_t)P.num_bounds[t.role];
+    t.base_hi = (uint32_t)(P.num_bounds[t.role] >> 32);
+  }
+  std::vector<StrTask> xstr(P.ex_str);
+  std::stable_partition(xstr.begin(), xstr.end(), [](const StrTask& t) { return t.kind == 1; });
+  for (StrTask& t : xstr) {
+    t.base_lo = (uint32_t)P.str_bounds[t.role];
+    t.base_hi = (uint32_t)(P.str_bounds[t.role] >> 32);
+    if (t.kind == 1) t.set_word = (uint32_t)((X.n_contains + X.n_xcontains++) * idset_words(P.n_strings));
+  }
+  X.o_xnum = X.blob.add(xnum);
+  X.o_xstr = X.blob.add(xstr);
+  X.o_xrole = X.blob.add(ex_roles);
   X.n_thr_groups = thr_groups.size();
   X.n_thr_tasks = thr_tasks.size();
   X.o_thr = X.blob.add(thr_tasks);
@@ -1537,17 +1730,44 @@ hth_status launch_prepared(hth_kb_s& kb, const Prepared& X, char* ws, uint32_t* 
       if (s) return s;
     }
   }
+  // the id sets: the dictionary strings holding each pattern
+  auto contains = [&](const StrTask* sk, size_t n) -> hth_status {
+    if (!n) return HTH_OK;
+    const uint32_t tiles = std::max<uint32_t>(1, (P.n_strings + 255) / 256);
+    return split_launch(Lc, HTH_K_THRESHOLD, 0.0, n, tiles, 256, [&](uint32_t i0, uint32_t, uint32_t blocks) {
+      hipLaunchKernelGGL(k_contains, dim3(blocks), dim3(256), 0, st, d, sk + i0, tiles);
+    });
+  };
+  // tasks at the examples: their rows' offsets and about as many values of each as a row has
+  const uint32_t xtiles = (kb.W + kExWords - 1) / kExWords;
+  auto ex_bytes = [&](double values) { return kb.ex_hint * (8.0 + 4.0 * values / kb.N) + 8.0 * kb.W; };
+  if (!P.ex_num.empty()) {
+    const NumTask* nt = reinterpret_cast<const NumTask*>(ws + X.o_xnum);
+    double bytes = 0;
+    for (const NumTask& t : P.ex_num) bytes += ex_bytes((double)(P.num_bounds[t.role + 1] - P.num_bounds[t.role]));
+    hth_status s = split_launch(Lc, HTH_K_THRESHOLD, bytes, P.ex_num.size(), xtiles, 64,
+                                [&](uint32_t i0, uint32_t, uint32_t blocks) {
+                                  hipLaunchKernelGGL(k_numrole_ex, dim3(blocks), dim3(64), 0, st, d, nt + i0, xtiles);
+                                });
+    if (s) return s;
+  }
+  if (!P.ex_str.empty()) {
+    const StrTask* sk = reinterpret_cast<const StrTask*>(ws + X.o_xstr);
+    hth_status s = contains(sk, X.n_xcontains);
+    if (s) return s;
+    double bytes = 0;
+    for (const StrTask& t : P.ex_str) bytes += ex_bytes((double)(P.str_bounds[t.role + 1] - P.str_bounds[t.role]));
+    s = split_launch(Lc, HTH_K_THRESHOLD, bytes, P.ex_str.size(), xtiles, 64,
+                     [&](uint32_t i0, uint32_t, uint32_t blocks) {
+                       hipLaunchKernelGGL(k_strrole_ex, dim3(blocks), dim3(64), 0, st, d, sk + i0, xtiles);
+                     });
+    if (s) return s;
+  }
   if (!P.str.empty()) {
     const uint32_t n = (uint32_t)P.str.size();
     const StrTask* sk = reinterpret_cast<const StrTask*>(ws + X.o_str);
-    hth_status s = HTH_OK;
-    if (X.n_contains) {   // the id sets: the dictionary strings holding each pattern
-      const uint32_t tiles = std::max<uint32_t>(1, (P.n_strings + 255) / 256);
-      s = split_launch(Lc, HTH_K_THRESHOLD, 0.0, X.n_contains, tiles, 256, [&](uint32_t i0, uint32_t, uint32_t blocks) {
-        hipLaunchKernelGGL(k_contains, dim3(blocks), dim3(256), 0, st, d, sk + i0, tiles);
-      });
-      if (s) return s;
-    }
+    hth_status s = contains(sk, X.n_contains);
+    if (s) return s;
     const uint32_t bpt = std::max<uint32_t>(1, std::min<uint32_t>((kb.W + 7) / 8, (32 * kb.n_cu + n - 1) / n));
     double bytes = 0;   // per task: the role's offsets and ids once, its row out
     for (const StrTask& t : P.str)
@@ -1600,6 +1820,16 @@ hth_status launch_prepared(hth_kb_s& kb, const Prepared& X, char* ws, uint32_t* 
       s = split_launch(Lc, HTH_K_ROLE, bytes, n, tiles, 256, [&](uint32_t i0, uint32_t, uint32_t blocks) {
         hipLaunchKernelGGL(k_push, dim3(blocks), dim3(256), 0, st, d, pt + i0, tiles);
       });
+      if (s) return s;
+    }
+    if (!PL.ex_roles.empty()) {
+      const RoleTask* xr = reinterpret_cast<const RoleTask*>(ws + X.o_xrole) + at.ex;
+      double bytes = 0;
+      for (const RoleTask& t : PL.ex_roles) bytes += ex_bytes((double)(kb.role_base[t.role + 1] - kb.role_base[t.role]));
+      s = split_launch(Lc, HTH_K_ROLE, bytes, PL.ex_roles.size(), xtiles, 64,
+                       [&](uint32_t i0, uint32_t, uint32_t blocks) {
+                         hipLaunchKernelGGL(k_role_ex, dim3(blocks), dim3(64), 0, st, d, xr + i0, xtiles);
+                       });
       if (s) return s;
     }
     s = launch_roles(Lc, d, rol + at.role, X.lv_roles[L]);
@@ -1660,6 +1890,7 @@ extern "C" hth_status hth_eval_one(hth_kb kb, const hth_node* nodes, uint32_t n_
   uint32_t offs[2] = {0, n_nodes};
   PlanOptions opt;
   opt.instances = d_instances != nullptr;
+  opt.examples = !opt.instances && view_wanted(*kb);
   Plan P;
   hth_status s = compile_plan(*kb, nodes, offs, 1, children, n_children, opt, P);
   if (s) return s;
@@ -1711,6 +1942,7 @@ extern "C" hth_status hth_eval_one_noalloc(hth_kb kb, const hth_node* nodes, uin
   uint32_t offs[2] = {0, n_nodes};
   PlanOptions opt;
   opt.instances = d_instances != nullptr;
+  opt.examples = !opt.instances && view_wanted(*kb);
   Plan P;
   hth_status s = compile_plan(*kb, nodes, offs, 1, children, n_children, opt, P);
   if (s) return s;

@@ -509,6 +509,20 @@ struct Compiler {
       root_uses[roots[h]]++;
       root_hyp[roots[h]] = h;
     }
+    // deep: some filler reads the node, so its row holds every individual; any
+    // other node matters at the examples only (coverage is all that is asked)
+    std::vector<uint8_t> deep(nv, opt.examples ? 0 : 1);
+    if (opt.examples)
+      for (size_t i = nv; i-- > 0;) {
+        if (!live[i]) continue;
+        const CNode& n = dag.nodes[i];
+        const uint8_t down = is_role(n.op) ? 1 : deep[i];
+        if (n.a != kNone) deep[n.a] |= down;
+        for (uint32_t j = 0; j < n.kid_n; ++j) deep[dag.kids[n.kid_off + j]] |= down;
+      }
+    // (a wave takes an example's row: long rows, whose values many blocks
+    // share, stay with the passes over every individual)
+    auto no_heavy = [](const std::vector<uint32_t>& first, uint32_t i) { return first[i] == first[i + 1]; };
     std::vector<uint8_t> covered_by_pass(roots.size(), 0);
     int32_t max_level = -1;
     for (uint32_t v = 0; v < nv; ++v) {
@@ -529,7 +543,7 @@ struct Compiler {
         t.cmp = n.op == HTH_NUM_GE ? 0 : n.op == HTH_NUM_LE ? 1 : 2;
         std::memcpy(&t.t, &n.q, 4);
         t.out_row = row[v];
-        P.num.push_back(t);
+        (!deep[v] && no_heavy(kb.num_chunk_first, n.arg) ? P.ex_num : P.num).push_back(t);
       } else if (is_string(n.op)) {
         row[v] = new_row();
         StrTask t{};
@@ -537,7 +551,7 @@ struct Compiler {
         t.kind = n.op == HTH_STR_CONTAINS ? 1 : 0;
         std::memcpy(&t.q, &n.q, 4);
         t.out_row = row[v];
-        P.str.push_back(t);
+        (!deep[v] && no_heavy(kb.str_chunk_first, n.arg) ? P.ex_str : P.str).push_back(t);
       } else if (is_role(n.op) && hit_row[v] == kNone) {
         if (!in_cache[v]) row[v] = new_row();
         max_level = std::max(max_level, height[v]);
@@ -605,9 +619,13 @@ struct Compiler {
           ++j;
         // nodes a shared pass can decide (see GroupTask) form groups when the
         // bucket is large enough; the rest run alone
-        std::vector<Pending> solo, grp;
+        std::vector<Pending> solo, ex, grp;
         for (size_t q = i; q < j; ++q) {
           const CNode& n = dag.nodes[items[q].v];
+          if (!deep[items[q].v] && no_heavy(kb.chunk_first, 2 * n.arg + n.inv)) {
+            ex.push_back(items[q]);
+            continue;
+          }
           const bool groupable = n.op == HTH_EXISTS || n.op == HTH_FORALL ||
                                  (n.op == HTH_ATLEAST ? n.q <= kGroupMaxCount : n.q < kGroupMaxCount);
           (groupable ? grp : solo).push_back(items[q]);
@@ -627,17 +645,19 @@ struct Compiler {
             default: lo = n.q; hi = n.q; break;
           }
         };
-        for (const Pending& it : solo) {
+        auto alone = [&](const Pending& it) {
           const CNode& n = dag.nodes[it.v];
-          RoleTask t;
+          RoleTask t{};
           t.role = n.arg;
           t.inv = n.inv;
           t.child_row = it.child_row;
           predicate(it, t.lo, t.hi, t.neg);
           t.sat = t.hi == kInf ? t.lo : t.hi + 1;
           t.out_row = row[it.v];
-          PL.roles.push_back(t);
-        }
+          return t;
+        };
+        for (const Pending& it : solo) PL.roles.push_back(alone(it));
+        for (const Pending& it : ex) PL.ex_roles.push_back(alone(it));
         const size_t gk = std::max<uint32_t>(1, std::min<uint32_t>(opt.group_k, kMaxK));
         for (size_t g0 = 0; g0 < grp.size(); g0 += gk) {
           const size_t g1 = std::min(grp.size(), g0 + gk);
@@ -685,7 +705,7 @@ struct Compiler {
     P.n_slots = n_slots;
     P.sets = kb.sets;
     P.n_sets = kb.n_sets;
-    if (!P.num.empty()) {
+    if (!P.num.empty() || !P.ex_num.empty()) {
       P.num_roff = kb.num_roff;
       P.num_val = kb.num_val;
       P.num_heavy_rows = kb.num_heavy_rows;
@@ -693,7 +713,7 @@ struct Compiler {
       P.num_chunk_first = kb.num_chunk_first;
       P.num_bounds = kb.num_bounds;
     }
-    if (!P.str.empty()) {
+    if (!P.str.empty() || !P.ex_str.empty()) {
       P.str_roff = kb.str_roff;
       P.str_ids = kb.str_ids;
       P.str_heavy_rows = kb.str_heavy_rows;

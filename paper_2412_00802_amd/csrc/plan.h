@@ -34,11 +34,14 @@ struct PlanOptions {
   uint32_t group_min = 0xFFFFFFFFu;  // (role, dir, level) buckets with at least this many
                                      // role nodes use a shared CSR pass; others run alone
   uint32_t group_k = 64;             // most role nodes per shared pass
+  // counts only: restrictions that no filler reads are evaluated at the examples alone
+  bool examples = false;
 };
 
 struct PlanLevel {
   std::vector<RegionTask> mat;      // children materialised before this level's role passes
   std::vector<RoleTask> roles;      // single role nodes (k = 1)
+  std::vector<RoleTask> ex_roles;   // those needed at the examples only
   std::vector<GroupTask> groups;    // shared passes (k <= 64)
   std::vector<GroupMember> members;
 };
@@ -46,6 +49,7 @@ struct PlanLevel {
 struct Plan {
   std::vector<ThrTask> thr;
   std::vector<NumTask> num;         // restrictions on numeric concrete roles
+  std::vector<NumTask> ex_num;      // those needed at the examples only
   // the numeric concrete roles the plan was compiled against
   const uint32_t* num_roff = nullptr;
   const float* num_val = nullptr;
@@ -54,6 +58,7 @@ struct Plan {
   std::vector<uint32_t> num_chunk_first;
   std::vector<uint64_t> num_bounds;        // [P+1] first value of each numeric role
   std::vector<StrTask> str;                // restrictions on string concrete roles
+  std::vector<StrTask> ex_str;             // those needed at the examples only
   const uint32_t* str_roff = nullptr;
   const int32_t* str_ids = nullptr;
   const uint32_t* str_heavy_rows = nullptr;
