@@ -1502,6 +1502,8 @@ struct Prepared {
   size_t o_num = 0, n_num_blocks = 0;   // numeric concrete-role tasks, their heavy-row blocks
   size_t o_str = 0, n_str_blocks = 0, n_contains = 0;   // string concrete-role tasks
   size_t o_xnum = 0, o_xstr = 0, n_xcontains = 0, o_xrole = 0;   // tasks at the examples only
+  ViewPlan V;                           // the example view: its tables below, its areas in V
+  size_t o_vthr = 0, o_vthg = 0, o_vgrp = 0, o_vpass = 0, o_vdir = 0, o_vbase = 0, o_vcopy = 0;
   size_t o_idset = 0;                   // the CONTAIN id sets (workspace offset)
   size_t o_hcnt = 0;   // heavy-row counters (workspace offset)
   size_t o_part = 0;   // partial counts of segmented shared passes (workspace offset)
@@ -1581,14 +1583,51 @@ void prepare(const hth_kb_s& kb, Plan&& plan, uint32_t n_hyps, Prepared& X) {
   X.root_at = regions.size();
   regions.insert(regions.end(), P.roots.begin(), P.roots.end());
   // thresholds grouped by property (at most kThrPerPass per group): one column pass each
-  std::vector<ThrTask> thr_tasks(P.thr);
-  std::stable_sort(thr_tasks.begin(), thr_tasks.end(),
-                   [](const ThrTask& a, const ThrTask& b) { return a.prop < b.prop; });
-  std::vector<ThrGroup> thr_groups;
-  for (uint32_t i = 0; i < thr_tasks.size(); ++i) {
-    if (thr_groups.empty() || thr_groups.back().prop != thr_tasks[i].prop || thr_groups.back().n == kThrPerPass)
-      thr_groups.push_back(ThrGroup{thr_tasks[i].prop, i, 0, 0});
-    thr_groups.back().n++;
+  auto by_property = [](const std::vector<ThrTask>& in, std::vector<ThrTask>& tasks) {
+    tasks = in;
+    std::stable_sort(tasks.begin(), tasks.end(), [](const ThrTask& a, const ThrTask& b) { return a.prop < b.prop; });
+    std::vector<ThrGroup> out;
+    for (uint32_t i = 0; i < tasks.size(); ++i) {
+      if (out.empty() || out.back().prop != tasks[i].prop || out.back().n == kThrPerPass)
+        out.push_back(ThrGroup{tasks[i].prop, i, 0, 0});
+      out.back().n++;
+    }
+    return out;
+  };
+  std::vector<ThrTask> thr_tasks, vthr_tasks;
+  const std::vector<ThrGroup> thr_groups = by_property(P.thr, thr_tasks), vthr_groups = by_property(P.vthr, vthr_tasks);
+  // the view's shared passes, whatever their levels (every row they read is
+  // complete by then), short-row directions first
+  ViewPlan& V = X.V;
+  V = ViewPlan();
+  V.on = P.view;
+  if (V.on) {
+    const uint32_t gk = std::max<uint32_t>(1, std::min<uint32_t>(kb.tune.group_k, kMaxK)), mbase = (uint32_t)members.size();
+    for (int want_short = 1; want_short >= 0; --want_short)
+      for (const ViewBucket& q : P.vbuckets)
+        if ((int)short_rows(kb, q.rd) == want_short) V.add_passes(kb, q.rd, q.count, gk, mbase + q.first, want_short);
+    members.insert(members.end(), P.vmembers.begin(), P.vmembers.end());
+    V.chunks = chunk_groups(kb, V.groups);
+    for (GroupChunk& c : V.chunks)
+      if (kb.tune.xcd_local && c.n >= 8) place_on_xcds(kb, V.groups, c, xslots);
+    for (size_t i = 0; i < V.groups.size(); ++i) {
+      V.passes[i].t_off = V.groups[i].t_off;
+      for (uint32_t j = 0; j < V.passes[i].k; ++j) accept_bits(V.passes[i], members[V.passes[i].first + j], j);
+    }
+    V.n_rows = P.n_vrows;
+    V.n_copies = 2 + (uint32_t)P.vcopies.size();
+    V.n_thg = (uint32_t)vthr_groups.size();
+    std::vector<ViewCopy> copies{{kPosRow, 0}, {kNegRow, 1}};
+    copies.insert(copies.end(), P.vcopies.begin(), P.vcopies.end());
+    std::vector<uint64_t> bases;
+    for (const ViewDir& v : V.dirs) bases.push_back(v.base);
+    X.o_vthr = X.blob.add(vthr_tasks);
+    X.o_vthg = X.blob.add(vthr_groups);
+    X.o_vgrp = X.blob.add(V.groups);
+    X.o_vpass = X.blob.add(V.passes);
+    X.o_vdir = X.blob.add(V.dirs);
+    X.o_vbase = X.blob.add(bases);
+    X.o_vcopy = X.blob.add(copies);
   }
   std::vector<NumTask> num(P.num);
   for (NumTask& t : num) {
@@ -1642,6 +1681,7 @@ void prepare(const hth_kb_s& kb, Plan&& plan, uint32_t n_hyps, Prepared& X) {
   X.tables = align_up(X.blob.bytes.size(), 256);
   size_t t_bytes = 0;   // the T area: the most one chunk of the plan uses
   for (size_t L = 0; L < NL; ++L) t_bytes = std::max(t_bytes, chunks_t_bytes(kb, X.lv_groups[L], X.lv_chunks[L]));
+  if (V.on) t_bytes = std::max(t_bytes, chunks_t_bytes(kb, V.groups, V.chunks));
   X.o_hcnt = X.tables + (size_t)P.n_slots * kb.S * 8 + t_bytes;
   X.o_part = X.o_hcnt + heavy_counter_bytes(kb, P);
   size_t part = 0;
@@ -1649,6 +1689,11 @@ void prepare(const hth_kb_s& kb, Plan&& plan, uint32_t n_hyps, Prepared& X) {
     for (const GroupChunk& c : X.lv_chunks[L]) part = std::max(part, chunk_partial_bytes(kb, X.lv_groups[L], c));
   X.o_idset = X.o_part + align_up(part, 256);
   X.need = X.o_idset + idset_bytes(P);
+  V.layout(kb, [&](size_t bytes) {
+    const size_t at = X.need;
+    X.need = align_up(at + bytes, 256);
+    return at;
+  });
 }
 
 hth_status check_ws(const Prepared& X, const char* ws, size_t ws_bytes) {
@@ -1850,17 +1895,38 @@ hth_status launch_prepared(hth_kb_s& kb, const Prepared& X, char* ws, uint32_t* 
                       reinterpret_cast<const uint32_t*>(ws + X.o_xslot), tarea, ws + X.o_part);
     if (s) return s;
   }
+  if (X.V.on) {   // every full row is complete: what is left is done at the examples
+    hth_status s = launch_view(Lc, d, X.V, ws, reinterpret_cast<const ViewDir*>(ws + X.o_vdir),
+                               reinterpret_cast<const uint64_t*>(ws + X.o_vbase),
+                               reinterpret_cast<const ViewCopy*>(ws + X.o_vcopy), 0,
+                               reinterpret_cast<const ThrGroup*>(ws + X.o_vthg),
+                               reinterpret_cast<const ThrTask*>(ws + X.o_vthr),
+                               reinterpret_cast<const GroupTask*>(ws + X.o_vgrp),
+                               reinterpret_cast<const GroupTask*>(ws + X.o_vpass), mem,
+                               reinterpret_cast<const uint32_t*>(ws + X.o_xslot), tarea, &d);
+    if (s) return s;
+  }
   return launch_regions(Lc, d, reg + X.root_at, code, P.roots, P.code);
+}
+
+hth_status run_prepared(hth_kb_s& kb, const Prepared& X, char* ws, size_t ws_bytes, uint32_t* counts,
+                        uint64_t* instances, hipStream_t st) {
+  hth_status s = check_ws(X, ws, ws_bytes);
+  if (s) return s;
+  HTH_HIP(hipMemcpyAsync(ws, X.blob.bytes.data(), X.blob.bytes.size(), hipMemcpyHostToDevice, st));
+  return launch_prepared(kb, X, ws, counts, instances, st);
 }
 
 hth_status run_plan(hth_kb_s& kb, Plan&& P, char* ws, size_t ws_bytes, uint32_t* counts, uint32_t n_hyps,
                     uint64_t* instances, hipStream_t st) {
   Prepared X;
   prepare(kb, std::move(P), n_hyps, X);
-  hth_status s = check_ws(X, ws, ws_bytes);
-  if (s) return s;
-  HTH_HIP(hipMemcpyAsync(ws, X.blob.bytes.data(), X.blob.bytes.size(), hipMemcpyHostToDevice, st));
-  return launch_prepared(kb, X, ws, counts, instances, st);
+  return run_prepared(kb, X, ws, ws_bytes, counts, instances, st);
+}
+
+// Whether a host-planned batch evaluates at the examples what no filler reads.
+bool batch_view(const hth_kb_s& kb, const PlanOptions& opt) {
+  return !opt.instances && opt.group_min != 0xFFFFFFFFu && view_wanted(kb);
 }
 
 }  // namespace
@@ -1975,12 +2041,20 @@ hth_status eval_batch_impl(hth_kb kb, const hth_node* nodes, const uint32_t* hyp
   opt.group_min = kb->tune.group_min ? kb->tune.group_min : 0xFFFFFFFFu;
   opt.group_k = kb->tune.group_k;
   opt.instances = d_sets != nullptr;
-  Plan P;
-  hth_status s = compile_plan(*kb, nodes, hyp_node_offsets, n_hyps, children, n_children, opt, P);
-  if (s) return s;
-  std::lock_guard<std::mutex> g(kb->mu);
-  return run_plan(*kb, std::move(P), static_cast<char*>(ws), ws_bytes, d_counts, n_hyps, d_sets,
-                  static_cast<hipStream_t>(stream));
+  opt.examples = opt.view = batch_view(*kb, opt);
+  for (;;) {
+    Plan P;
+    hth_status s = compile_plan(*kb, nodes, hyp_node_offsets, n_hyps, children, n_children, opt, P);
+    if (s) return s;
+    std::lock_guard<std::mutex> g(kb->mu);
+    Prepared X;
+    prepare(*kb, std::move(P), n_hyps, X);
+    if (X.need > ws_bytes && opt.view) {   // a workspace without room for the view: every row in full
+      opt.examples = opt.view = false;
+      continue;
+    }
+    return run_prepared(*kb, X, static_cast<char*>(ws), ws_bytes, d_counts, d_sets, static_cast<hipStream_t>(stream));
+  }
 }
 }  // namespace
 
@@ -2118,6 +2192,7 @@ extern "C" hth_status hth_plan_create(hth_kb kb, const hth_node* nodes, const ui
   PlanOptions opt;
   opt.group_min = kb->tune.group_min ? kb->tune.group_min : 0xFFFFFFFFu;
   opt.group_k = kb->tune.group_k;
+  opt.examples = opt.view = batch_view(*kb, opt);
   Plan P;
   hth_status s = compile_plan(*kb, nodes, hyp_node_offsets, n_hyps, children, n_children, opt, P);
   if (s) return s;
@@ -2169,10 +2244,17 @@ extern "C" hth_status hth_batch_workspace_bytes(hth_kb kb, const hth_node* nodes
   PlanOptions opt;
   opt.group_min = kb->tune.group_min ? kb->tune.group_min : 0xFFFFFFFFu;
   opt.group_k = kb->tune.group_k;
-  Plan P;
-  hth_status s = compile_plan(*kb, nodes, hyp_node_offsets, n_hyps, children, n_children, opt, P);
+  opt.examples = opt.view = batch_view(*kb, opt);
+  Plan P, general;
+  hth_status s = compile_plan(*kb, nodes, hyp_node_offsets, n_hyps, children, n_children, opt, P,
+                              opt.view ? &general : nullptr);
   if (s) return s;
-  *bytes = plan_workspace_bytes(*kb, P) + 4096;
+  *bytes = plan_workspace_bytes(*kb, opt.view ? general : P) + 4096;
+  if (opt.view) {
+    Prepared X;
+    prepare(*kb, std::move(P), n_hyps, X);
+    *bytes = std::max(*bytes, X.need);
+  }
   return HTH_OK;
 }
 

@@ -91,6 +91,14 @@ struct ThrGroup {
   uint32_t pad;
 };
 
+// A row of the example view: view row dst = the examples' bits of row src.
+struct ViewCopy {
+  uint32_t src, dst;
+};
+constexpr uint32_t kPosRow = 0xFFFFFFF0u, kNegRow = 0xFFFFFFF1u;   // sources of a copy: the example rows
+constexpr uint32_t kSlotRow = 1u << 31;   // source: a workspace row, counted from the plan's first role row
+constexpr uint32_t kViewFixed = 2;        // view rows 0 and 1: the positives, the negatives
+
 // One role restriction over one CSR direction, evaluated alone (k = 1).
 //   cnt(x) = #{y in succ(x) : bit(child, y) ^ neg};  result = lo <= cnt <= hi
 //   counting may stop at `sat` (every predicate is decided once cnt >= sat).
@@ -161,6 +169,14 @@ struct GroupMember {
   uint32_t cover;      // hypothesis index, or kNone
   uint32_t pad;
 };
+
+// Member j's counts among the group's acceptance masks.
+inline void accept_bits(GroupTask& g, const GroupMember& m, uint32_t j) {
+  for (uint32_t v = 0; v <= kGroupMaxCount; ++v) {
+    const bool ok = v < kGroupMaxCount ? (m.lo <= v && v <= m.hi) : (m.hi == kNone && m.lo <= kGroupMaxCount);
+    if (ok) g.acc[v] |= 1ull << j;
+  }
+}
 
 // Device view of the knowledge base and of one call's buffers (by value).
 struct DevKB {

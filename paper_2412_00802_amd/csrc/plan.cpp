@@ -264,6 +264,8 @@ struct Compiler {
   std::vector<int32_t> depth;    // stack depth of the node's region program
   uint32_t n_slots = 0;
   uint32_t zero_row = kNone;
+  std::vector<uint32_t> vrow;    // view rows of what root programs read
+  bool in_view = false;          // programs read view rows
 
   explicit Compiler(const hth_kb_s& k) : kb(k) {}
 
@@ -373,6 +375,7 @@ struct Compiler {
 
   uint32_t leaf_row(uint32_t v) const {
     const CNode& n = dag.nodes[v];
+    if (in_view) return vrow[v];
     if (n.op == HTH_ATOM) return n.arg;
     if (n.op == HTH_SET) return kb.d.n_concepts + n.arg;
     return row[v];
@@ -443,6 +446,10 @@ struct Compiler {
     live.assign(nv, 0);
     row.assign(nv, kNone);
     depth.assign(nv, -1);
+    vrow.assign(nv, kNone);
+    in_view = false;
+    n_slots = 0;
+    zero_row = kNone;
     // cross-batch cache: a role node whose subexpression holds a row is a
     // leaf of this plan (read from that row); its subtree is not evaluated
     SubexprCache* C = opt.cache;
@@ -520,6 +527,36 @@ struct Compiler {
         if (n.a != kNone) deep[n.a] |= down;
         for (uint32_t j = 0; j < n.kid_n; ++j) deep[dag.kids[n.kid_off + j]] |= down;
       }
+    // what a shared pass can decide (see GroupTask)
+    auto groupable = [](const CNode& n) {
+      return n.op == HTH_EXISTS || n.op == HTH_FORALL ||
+             (n.op == HTH_ATLEAST ? n.q <= kGroupMaxCount : n.q < kGroupMaxCount);
+    };
+    auto viewable = [&](uint32_t v) { return !deep[v] && is_role(dag.nodes[v].op) && groupable(dag.nodes[v]); };
+    // the view, and what root programs read there
+    std::vector<uint8_t> top;
+    if (opt.view) {
+      uint32_t n = 0;
+      for (uint32_t v = 0; v < nv; ++v) n += live[v] && viewable(v);
+      P.view = n >= kViewNodes;
+    }
+    const bool view = P.view;
+    if (view) {
+      top.assign(nv, 0);
+      for (uint32_t r : roots) top[r] = 1;
+      for (size_t i = nv; i-- > 0;) {
+        const CNode& n = dag.nodes[i];
+        if (!top[i] || is_role(n.op)) continue;
+        if (n.a != kNone) top[n.a] = 1;
+        for (uint32_t j = 0; j < n.kid_n; ++j) top[dag.kids[n.kid_off + j]] = 1;
+      }
+    }
+    auto copied = [&](uint32_t v) {   // a full row that a root program reads
+      if (!view || !top[v]) return;
+      vrow[v] = P.n_vrows++;
+      const CNode& n = dag.nodes[v];
+      P.vcopies.push_back(ViewCopy{n.op == HTH_ATOM ? n.arg : n.op == HTH_SET ? kb.d.n_concepts + n.arg : row[v], vrow[v]});
+    };
     // (a wave takes an example's row: long rows, whose values many blocks
     // share, stay with the passes over every individual)
     auto no_heavy = [](const std::vector<uint32_t>& first, uint32_t i) { return first[i] == first[i + 1]; };
@@ -529,13 +566,20 @@ struct Compiler {
       if (!live[v]) continue;
       const CNode& n = dag.nodes[v];
       if (is_column(n.op)) {
-        row[v] = new_row();
         ThrTask t;
         t.prop = n.arg;
         t.cmp = n.op == HTH_DATA_GE ? 0 : n.op == HTH_DATA_LE ? 1 : 2;
         std::memcpy(&t.t, &n.q, 4);
-        t.out_row = row[v];
-        P.thr.push_back(t);
+        if (!view || deep[v]) {
+          t.out_row = row[v] = new_row();
+          P.thr.push_back(t);
+        }
+        if (view && top[v]) {
+          t.out_row = vrow[v] = P.n_vrows++;
+          P.vthr.push_back(t);
+        }
+      } else if (n.op == HTH_ATOM || n.op == HTH_SET) {
+        copied(v);
       } else if (is_numeric(n.op)) {
         row[v] = new_row();
         NumTask t{};
@@ -544,6 +588,7 @@ struct Compiler {
         std::memcpy(&t.t, &n.q, 4);
         t.out_row = row[v];
         (!deep[v] && no_heavy(kb.num_chunk_first, n.arg) ? P.ex_num : P.num).push_back(t);
+        copied(v);
       } else if (is_string(n.op)) {
         row[v] = new_row();
         StrTask t{};
@@ -552,8 +597,14 @@ struct Compiler {
         std::memcpy(&t.q, &n.q, 4);
         t.out_row = row[v];
         (!deep[v] && no_heavy(kb.str_chunk_first, n.arg) ? P.ex_str : P.str).push_back(t);
+        copied(v);
       } else if (is_role(n.op) && hit_row[v] == kNone) {
-        if (!in_cache[v]) row[v] = new_row();
+        if (view && viewable(v)) {
+          if (used[v] || root_uses[v] != 1) vrow[v] = P.n_vrows++;   // (else its pass adds its coverage)
+        } else {
+          if (!in_cache[v]) row[v] = new_row();
+          copied(v);
+        }
         max_level = std::max(max_level, height[v]);
         P.n_role_nodes++;
       }
@@ -563,6 +614,7 @@ struct Compiler {
     std::vector<uint32_t> matrow(nv, kNone);
     struct Pending { uint32_t v, child_row, neg; };
     std::vector<std::vector<Pending>> per_level(max_level + 1);
+    std::vector<Pending> viewed;
     for (uint32_t v = 0; v < nv; ++v) {
       if (!live[v] || !is_role(dag.nodes[v].op) || hit_row[v] != kNone) continue;
       const CNode& n = dag.nodes[v];
@@ -599,17 +651,52 @@ struct Compiler {
         }
         crow = matrow[c];
       }
-      per_level[height[v]].push_back({v, crow, neg});
+      (view && viewable(v) ? viewed : per_level[height[v]]).push_back({v, crow, neg});
+    }
+    auto predicate = [&](const Pending& it, uint32_t& lo, uint32_t& hi, uint32_t& neg) {
+      const CNode& n = dag.nodes[it.v];
+      neg = it.neg;
+      switch (n.op) {
+        case HTH_EXISTS: lo = 1; hi = kInf; break;
+        case HTH_FORALL: lo = 0; hi = 0; neg ^= 1; break;
+        case HTH_ATLEAST: lo = n.q; hi = kInf; break;
+        case HTH_ATMOST: lo = 0; hi = n.q; break;
+        default: lo = n.q; hi = n.q; break;
+      }
+    };
+    auto by_direction = [&](const Pending& a, const Pending& b) {
+      const CNode& x = dag.nodes[a.v];
+      const CNode& y = dag.nodes[b.v];
+      return x.arg != y.arg ? x.arg < y.arg : x.inv < y.inv;
+    };
+    // the member of a shared pass; a root that nothing else reads is covered by it
+    auto member = [&](const Pending& it, uint32_t out) {
+      GroupMember m{};
+      predicate(it, m.lo, m.hi, m.neg);
+      m.sat = m.hi == kInf ? m.lo : m.hi + 1;
+      m.child_row = it.child_row;
+      m.out_row = out;
+      m.cover = kNone;
+      if (!opt.instances && !used[it.v] && root_uses[it.v] == 1 && !in_cache[it.v]) {
+        m.out_row = kNone;
+        m.cover = root_hyp[it.v];
+        covered_by_pass[root_hyp[it.v]] = 1;
+      }
+      return m;
+    };
+    std::stable_sort(viewed.begin(), viewed.end(), by_direction);
+    for (const Pending& it : viewed) {
+      const uint32_t rd = 2 * dag.nodes[it.v].arg + dag.nodes[it.v].inv;
+      if (P.vbuckets.empty() || P.vbuckets.back().rd != rd)
+        P.vbuckets.push_back(ViewBucket{rd, 0, (uint32_t)P.vmembers.size()});
+      P.vbuckets.back().count++;
+      P.vmembers.push_back(member(it, vrow[it.v]));
     }
     // role tasks, grouped per (role, direction) when the bucket is large
     for (int32_t L = 0; L <= max_level; ++L) {
       PlanLevel& PL = P.levels[L];
       auto& items = per_level[L];
-      std::stable_sort(items.begin(), items.end(), [&](const Pending& a, const Pending& b) {
-        const CNode& x = dag.nodes[a.v];
-        const CNode& y = dag.nodes[b.v];
-        return x.arg != y.arg ? x.arg < y.arg : x.inv < y.inv;
-      });
+      std::stable_sort(items.begin(), items.end(), by_direction);
       size_t i = 0;
       while (i < items.size()) {
         size_t j = i;
@@ -626,25 +713,12 @@ struct Compiler {
             ex.push_back(items[q]);
             continue;
           }
-          const bool groupable = n.op == HTH_EXISTS || n.op == HTH_FORALL ||
-                                 (n.op == HTH_ATLEAST ? n.q <= kGroupMaxCount : n.q < kGroupMaxCount);
-          (groupable ? grp : solo).push_back(items[q]);
+          (groupable(n) ? grp : solo).push_back(items[q]);
         }
         if (grp.size() < bucket_min(kb, 2 * first.arg + first.inv, opt.group_min)) {
           solo.insert(solo.end(), grp.begin(), grp.end());
           grp.clear();
         }
-        auto predicate = [&](const Pending& it, uint32_t& lo, uint32_t& hi, uint32_t& neg) {
-          const CNode& n = dag.nodes[it.v];
-          neg = it.neg;
-          switch (n.op) {
-            case HTH_EXISTS: lo = 1; hi = kInf; break;
-            case HTH_FORALL: lo = 0; hi = 0; neg ^= 1; break;
-            case HTH_ATLEAST: lo = n.q; hi = kInf; break;
-            case HTH_ATMOST: lo = 0; hi = n.q; break;
-            default: lo = n.q; hi = n.q; break;
-          }
-        };
         auto alone = [&](const Pending& it) {
           const CNode& n = dag.nodes[it.v];
           RoleTask t{};
@@ -667,24 +741,8 @@ struct Compiler {
           gt.k = (uint32_t)(g1 - g0);
           gt.first = (uint32_t)PL.members.size();
           for (size_t q = g0; q < g1; ++q) {
-            GroupMember m{};
-            predicate(grp[q], m.lo, m.hi, m.neg);
-            m.sat = m.hi == kInf ? m.lo : m.hi + 1;
-            m.child_row = grp[q].child_row;
-            const uint32_t v = grp[q].v;
-            m.out_row = row[v];
-            m.cover = kNone;
-            if (!opt.instances && !used[v] && root_uses[v] == 1 && !in_cache[v]) {
-              m.out_row = kNone;
-              m.cover = root_hyp[v];
-              covered_by_pass[root_hyp[v]] = 1;
-            }
-            const uint32_t jbit = (uint32_t)(q - g0);
-            for (uint32_t v = 0; v <= kGroupMaxCount; ++v) {
-              const bool ok = v < kGroupMaxCount ? (m.lo <= v && v <= m.hi)
-                                                 : (m.hi == kInf && m.lo <= kGroupMaxCount);
-              if (ok) gt.acc[v] |= 1ull << jbit;
-            }
+            const GroupMember m = member(grp[q], row[grp[q].v]);
+            accept_bits(gt, m, (uint32_t)(q - g0));
             PL.members.push_back(m);
           }
           PL.groups.push_back(gt);
@@ -693,6 +751,7 @@ struct Compiler {
       }
     }
     // roots with coverage
+    in_view = view;
     for (uint32_t h = 0; h < roots.size(); ++h) {
       if (covered_by_pass[h]) continue;
       RegionTask t;
@@ -735,7 +794,7 @@ struct Compiler {
 
 hth_status compile_plan(const hth_kb_s& kb, const hth_node* nodes, const uint32_t* hyp_off,
                         uint32_t n_hyps, const uint32_t* children, uint32_t n_children,
-                        const PlanOptions& opt, Plan& out) {
+                        const PlanOptions& opt, Plan& out, Plan* general) {
   out = Plan();
   Compiler c(kb);
   for (uint32_t h = 0; h < n_hyps; ++h) {
@@ -747,6 +806,13 @@ hth_status compile_plan(const hth_kb_s& kb, const hth_node* nodes, const uint32_
     // row ids (concepts < 2^26, set rows < 2^24, one slot per node) fit the
     // 27-bit argument of the region bytecode
     if (out.n_input_nodes > (1u << 24)) return fail(HTH_E_RANGE, "more than 2^24 nodes in one call");
+  }
+  if (general) {
+    PlanOptions g = opt;
+    g.examples = g.view = false;
+    *general = Plan();
+    hth_status s = c.build(g, *general);
+    if (s) return s;
   }
   return c.build(opt, out);
 }

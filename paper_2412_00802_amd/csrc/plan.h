@@ -36,7 +36,10 @@ struct PlanOptions {
   uint32_t group_k = 64;             // most role nodes per shared pass
   // counts only: restrictions that no filler reads are evaluated at the examples alone
   bool examples = false;
+  // ... and, from kViewNodes role nodes on, in shared passes over the example view
+  bool view = false;
 };
+constexpr uint32_t kViewNodes = 16;   // fewer cost less one by one than the view's launches
 
 struct PlanLevel {
   std::vector<RegionTask> mat;      // children materialised before this level's role passes
@@ -44,6 +47,10 @@ struct PlanLevel {
   std::vector<RoleTask> ex_roles;   // those needed at the examples only
   std::vector<GroupTask> groups;    // shared passes (k <= 64)
   std::vector<GroupMember> members;
+};
+
+struct ViewBucket {
+  uint32_t rd, count, first;        // direction 2 role + inv; members [first, first + count)
 };
 
 struct Plan {
@@ -73,6 +80,13 @@ struct Plan {
   std::vector<uint32_t> code;
   std::vector<PlanLevel> levels;
   std::vector<RegionTask> roots;
+  // the example view (view.h): root programs and these tasks read and write its rows
+  bool view = false;
+  std::vector<ThrTask> vthr;
+  std::vector<ViewCopy> vcopies;    // full rows that root programs read
+  std::vector<ViewBucket> vbuckets; // role nodes by direction ...
+  std::vector<GroupMember> vmembers;   // ... and these, in the same order
+  uint32_t n_vrows = kViewFixed;
   uint32_t n_slots = 0;
   const uint64_t* sets = nullptr;   // the set table the plan's HTH_SET rows refer to
   uint32_t n_sets = 0;
@@ -80,9 +94,10 @@ struct Plan {
   uint32_t n_input_nodes = 0, n_canonical = 0, n_role_nodes = 0;
 };
 
+// general: also the plan without options examples and view.
 // Compile hypotheses nodes[hyp_off[h] .. hyp_off[h+1]) (local child indices).
 hth_status compile_plan(const hth_kb_s& kb, const hth_node* nodes, const uint32_t* hyp_off,
                         uint32_t n_hyps, const uint32_t* children, uint32_t n_children,
-                        const PlanOptions& opt, Plan& out);
+                        const PlanOptions& opt, Plan& out, Plan* general = nullptr);
 
 }  // namespace hth

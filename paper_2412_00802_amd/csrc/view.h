@@ -25,9 +25,6 @@ namespace {
 constexpr uint32_t kExTile = 2048;     // words per block of the example list
 constexpr uint32_t kVDirTile = 1024;   // examples per tile of a direction's copy
 constexpr uint32_t kVRows = 16;        // row copies per block
-constexpr uint32_t kPosRow = 0xFFFFFFF0u, kNegRow = 0xFFFFFFF1u;   // sources of a copy: the example rows
-constexpr uint32_t kSlotRow = 1u << 31;   // source: a workspace row, counted from the plan's first role row
-constexpr uint32_t kViewFixed = 2;     // view rows 0 and 1: the positives, the negatives
 
 // One role direction of the view: its CSR copy starts at `base` in the view's
 // target area; compact: its targets are object ranks.
@@ -35,11 +32,6 @@ struct ViewDir {
   uint32_t rd, compact;
   uint64_t base;
 };
-// view row dst = the examples' bits of row src
-struct ViewCopy {
-  uint32_t src, dst;
-};
-
 // Exclusive scan of p[0 .. n) in place by one block of 1024; -> the total.
 __device__ uint32_t block_scan_row(uint32_t* __restrict__ p, uint32_t n) {
   __shared__ uint32_t s_w[16], s_carry;

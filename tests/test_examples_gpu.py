@@ -56,3 +56,52 @@ def test_value_roles(monkeypatch, heavy_min):
     kb = string_kb()
     check(kb, synth.make_string_hypotheses(kb, 120, seed=7) +
           [("scontains", 1, b""), ("not", ("sequal", 0, kb.strings[2])), ("exists", 0, 1, ("scontains", 0, b"a"))])
+
+
+def batches(kb, hyps):
+    """eval_batch over all of them and over a few (fewer role nodes than a view takes)."""
+    eng, want = hthedl.Engine(kb, max_hyps=len(hyps)), Oracle(kb).coverages(hyps)
+    for part in (slice(None), slice(0, 3), slice(5, 12)):
+        np.testing.assert_array_equal(eng.eval_batch(hyps[part]), want[part])
+    return eng, want
+
+
+def test_value_roles_in_batches():
+    kb, _ = numeric_kb()
+    batches(kb, synth.make_numeric_hypotheses(kb, 200, seed=6) +
+            [("exists", r % 3, r % 2, ("and", ("nge", 0, 1.0), ("atom", r))) for r in range(20)])
+    kb = string_kb()
+    batches(kb, synth.make_string_hypotheses(kb, 200, seed=8) +
+            [("and", ("scontains", 0, b"a"), ("exists", r % 2, r % 2, ("and", ("scontains", 0, b"a"), ("atom", r % 8)))) for r in range(20)])
+
+
+def test_saved_plan_and_short_workspace(monkeypatch):
+    """A compiled plan reads the example rows of the moment, and a workspace of the size that a knowledge base without
+    the example view asks for still serves the batch."""
+    import torch
+    n = 9001
+    cfg = synth.small_config(n=n, n_concepts=14, n_roles=4, cap=24, n_pos=200, n_neg=200, seed_index=1760)
+    kb = synth.make_kb(cfg)
+    hyps = synth.make_hypotheses(cfg, kb, count=200, depth=4)
+    eng, want = batches(kb, hyps)
+    nodes, offs, ch = hthedl.encode_batch(hyps)
+    counts = torch.empty((len(hyps), 2), dtype=torch.int32, device="cuda")
+    full = hthedl.hth_batch_workspace_bytes(eng.handle, nodes, offs, ch)
+    monkeypatch.setenv("HTHEDL_VIEW_MIN", str(2**31))
+    plain = hthedl.Engine(kb, max_hyps=len(hyps))
+    less = hthedl.hth_batch_workspace_bytes(plain.handle, nodes, offs, ch)
+    assert less < full
+    ws = torch.empty(full, dtype=torch.uint8, device="cuda")
+    hthedl.hth_eval_batch(eng.handle, nodes, offs, ch, ws, less, counts)
+    np.testing.assert_array_equal(counts.cpu().numpy().view(np.uint32), want)
+    plan, need = hthedl.hth_plan_create(eng.handle, nodes, offs, ch)
+    assert need <= full
+    hthedl.hth_plan_upload(plan, ws, full)
+    for ids in (np.arange(n), np.arange(0, n, 97), np.array([n - 1])):
+        kb.pos_bits, kb.neg_bits = synth.ids_to_bits(ids, n), synth.ids_to_bits(ids[::2], n)
+        rows = torch.zeros((2, eng.S), dtype=torch.int64, device="cuda")
+        rows[:, :eng.W] = torch.from_numpy(np.stack([kb.pos_bits, kb.neg_bits]).view(np.int64)).cuda()
+        hthedl.hth_kb_set_examples(eng.handle, rows[0], rows[1])
+        hthedl.hth_plan_launch(plan, ws, full, counts)
+        np.testing.assert_array_equal(counts.cpu().numpy().view(np.uint32), Oracle(kb).coverages(hyps))
+    hthedl.hth_plan_destroy(plan)
