@@ -1709,6 +1709,21 @@ __global__ void k_zero_u32(uint32_t* __restrict__ p, uint32_t n) {
   if (i < n) p[i] = 0;
 }
 
+// Small tables travel in the launch: one kernel writes them to the workspace
+// and clears the counts, where a copy and a clearing kernel were two
+// dispatches one after the other (and the copy, from pageable memory, stops
+// the host).  SETUP_A
+constexpr uint32_t kInline = 224;     // 16-byte units of a launch's arguments
+struct InlineTables {
+  uint4 v[kInline];
+};
+__global__ void __launch_bounds__(256)
+k_setup(InlineTables t, uint4* __restrict__ ws, uint32_t units, uint32_t* __restrict__ counts, uint32_t nc) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+  if (i < units) ws[i] = t.v[i];
+  if (i < nc) counts[i] = 0;
+}
+
 // k_role<true> stages the child row in up to lds_per_block bytes of LDS
 void role_attributes(const hth_kb_s& kb) {
   std::call_once(g_attr_once, [&] {
@@ -1720,7 +1735,7 @@ void role_attributes(const hth_kb_s& kb) {
 // The kernels of a prepared plan whose tables are in ws: no copies, no
 // allocation and no memset (the counts are cleared by a kernel).
 hth_status launch_prepared(hth_kb_s& kb, const Prepared& X, char* ws, uint32_t* counts, uint64_t* instances,
-                           hipStream_t st) {
+                           hipStream_t st, bool cleared = false) {
   role_attributes(kb);
   const Plan& P = X.P;
   const size_t slot_bytes = (size_t)kb.S * 8;
@@ -1746,8 +1761,10 @@ hth_status launch_prepared(hth_kb_s& kb, const Prepared& X, char* ws, uint32_t* 
   d.instances = instances;
   void* tarea = ws + X.tables + (size_t)P.n_slots * slot_bytes;
   const uint32_t nc = 2 * X.n_hyps;
-  hipLaunchKernelGGL(k_zero_u32, dim3((nc + 255) / 256), dim3(256), 0, st, counts, nc);
-  HTH_HIP(hipGetLastError());
+  if (!cleared) {
+    hipLaunchKernelGGL(k_zero_u32, dim3((nc + 255) / 256), dim3(256), 0, st, counts, nc);
+    HTH_HIP(hipGetLastError());
+  }
   const ThrTask* thr = reinterpret_cast<const ThrTask*>(ws + X.o_thr);
   const ThrGroup* thg = reinterpret_cast<const ThrGroup*>(ws + X.o_thg);
   const RegionTask* reg = reinterpret_cast<const RegionTask*>(ws + X.o_reg);
@@ -1909,12 +1926,28 @@ hth_status launch_prepared(hth_kb_s& kb, const Prepared& X, char* ws, uint32_t* 
   return launch_regions(Lc, d, reg + X.root_at, code, P.roots, P.code);
 }
 
+// A prepared plan's tables into the workspace, then its kernels.
+hth_status upload_and_launch(hth_kb_s& kb, const Prepared& X, char* ws, uint32_t* counts, uint64_t* instances,
+                             hipStream_t st) {
+  const size_t n = X.blob.bytes.size();
+  if (n > sizeof(InlineTables)) {
+    HTH_HIP(hipMemcpyAsync(ws, X.blob.bytes.data(), n, hipMemcpyHostToDevice, st));
+    return launch_prepared(kb, X, ws, counts, instances, st);
+  }
+  InlineTables t;
+  std::memcpy(t.v, X.blob.bytes.data(), n);
+  const uint32_t units = (uint32_t)((n + 15) / 16), nc = 2 * X.n_hyps;
+  hipLaunchKernelGGL(k_setup, dim3((std::max(units, nc) + 255) / 256), dim3(256), 0, st, t,
+                     reinterpret_cast<uint4*>(ws), units, counts, nc);
+  HTH_HIP(hipGetLastError());
+  return launch_prepared(kb, X, ws, counts, instances, st, true);
+}
+
 hth_status run_prepared(hth_kb_s& kb, const Prepared& X, char* ws, size_t ws_bytes, uint32_t* counts,
                         uint64_t* instances, hipStream_t st) {
   hth_status s = check_ws(X, ws, ws_bytes);
   if (s) return s;
-  HTH_HIP(hipMemcpyAsync(ws, X.blob.bytes.data(), X.blob.bytes.size(), hipMemcpyHostToDevice, st));
-  return launch_prepared(kb, X, ws, counts, instances, st);
+  return upload_and_launch(kb, X, ws, counts, instances, st);
 }
 
 hth_status run_plan(hth_kb_s& kb, Plan&& P, char* ws, size_t ws_bytes, uint32_t* counts, uint32_t n_hyps,
@@ -2024,8 +2057,7 @@ extern "C" hth_status hth_eval_one_noalloc(hth_kb kb, const hth_node* nodes, uin
                                  std::to_string((size_t)HTH_NOALLOC_SCRATCH_BYTES) +
                                  " (use hth_eval_one with a caller workspace)");
   const hipStream_t st = static_cast<hipStream_t>(stream);
-  HTH_HIP(hipMemcpyAsync(ws, X.blob.bytes.data(), X.blob.bytes.size(), hipMemcpyHostToDevice, st));
-  return launch_prepared(*kb, X, ws, d_counts, d_instances, st);
+  return upload_and_launch(*kb, X, ws, d_counts, d_instances, st);
 }
 
 namespace {
