@@ -1469,7 +1469,7 @@ extern "C" hth_status hth_dplan_launch(hth_dplan plan, void* ws, size_t ws_bytes
   });
   if (s) return s;
   if (p.n_thg) {
-    const uint32_t n = p.n_thg, bpt = std::max<uint32_t>(1, (kb.W + 127) / 128);
+    const uint32_t n = p.n_thg, bpt = threshold_blocks(kb, n, kb.W);
     const double bytes = n * 4.0 * kb.N;   // the columns (model bytes; rows are an intermediate)
     s = split_launch(Lc, HTH_K_THRESHOLD, bytes, n, bpt, 256, [&](uint32_t i0, uint32_t, uint32_t blocks) {
       hipLaunchKernelGGL(k_threshold<false>, dim3(blocks), dim3(256), 0, st, d, p.d_thg + i0, T.thr, bpt, nullptr);

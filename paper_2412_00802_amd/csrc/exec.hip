@@ -151,16 +151,19 @@ __device__ __forceinline__ bool num_pass(float v, uint32_t cmp, float t) {
 // subjects, as in the role pass.  The wave walks the subjects' concatenated
 // values in chunks of 64 (eight chunks' loads in flight), a subject's passing
 // values are the difference of two prefix counts (ChunkSums), and the walk
-// stops once every subject with values left has found one.  Rows above
-// the heavy-row threshold are left to value_heavy (their bits here are 0).
-// 128 restrictions over 1M individuals: numeric 708 us, string 498 (870 and
-// 748 with every chunk's part of each subject's range taken in turn).
+// stops once every subject with values left has found one.  Up to kValPerPass
+// tasks of one role share a walk, and a round has as many chunks as the values
+// left need (2, 4 or 8).  Rows above the heavy-row threshold are left to
+// value_heavy (their bits here are 0).  About 60 restrictions on 4 roles over
+// 1M individuals: numeric 173 us, string 167 (348 and 334 with 8 chunks in
+// every round, 437 and 372 with a walk for each task).
 constexpr int kNumChunks = 8;
+constexpr uint32_t kValPerPass = 16;
 // off: the role's 32-bit offsets relative to vals, its first value.
-template <typename V, class Pass>
+template <typename V, class Pass, class Out>
 __device__ __forceinline__ void value_walk(const DevKB& kb, const uint32_t* __restrict__ off,
-                                           const V* __restrict__ vals, Pass pass, uint64_t* __restrict__ out,
-                                           uint32_t b, uint32_t bpt) {
+                                           const V* __restrict__ vals, uint32_t n, Pass pass, Out out, uint32_t b,
+                                           uint32_t bpt) {
   const int lane = threadIdx.x & 63;
   for (uint32_t w = b * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); w < kb.W; w += bpt * 4) {
     const uint32_t x = w * 64 + lane;
@@ -171,28 +174,41 @@ __device__ __forceinline__ void value_walk(const DevKB& kb, const uint32_t* __re
     if (heavy) ohi = olo;
     const uint32_t ee = (uint32_t)__builtin_amdgcn_readlane((int)ohi, 63);
     uint32_t i0 = (uint32_t)__builtin_amdgcn_readlane((int)olo, 0);
-    bool hit = false;
-    while (i0 < ee) {
-      V v[kNumChunks];
+    uint32_t hits = 0;           // bit j: task j has a passing value
+    const uint32_t all = (1u << n) - 1u;
+    // a round of `chunks` chunks from i0 on
+    auto round = [&](auto chunks) {
+      constexpr int C = chunks.value;
+      V v[C];
 #pragma unroll
-      for (int c = 0; c < kNumChunks; ++c) {
+      for (int c = 0; c < C; ++c) {
         const uint64_t e = (uint64_t)i0 + 64 * c + lane;
         v[c] = vals[e < ee ? (uint32_t)e : i0];
       }
-      ChunkSums sums;
-      unrolled<kNumChunks>([&](auto c) {
-        sums.template put<c.value>(__ballot(pass(v[c.value])));   // (values past ee: past every subject's range)
-      });
-      hit |= sums.template count<kNumChunks>(olo, ohi, i0) != 0;
+      for (uint32_t j = 0; j < n; ++j) {
+        const auto test = pass(j);
+        ChunkSums sums;
+        unrolled<C>([&](auto c) {   // (values past ee: past every subject's range)
+          sums.template put<c.value>(__ballot(test(v[c.value])));
+        });
+        hits |= (uint32_t)(sums.template count<C>(olo, ohi, i0) != 0) << j;
+      }
+    };
+    while (i0 < ee) {
+      if (ee - i0 <= 128) round(std::integral_constant<int, 2>());
+      else if (ee - i0 <= 256) round(std::integral_constant<int, 4>());
+      else round(std::integral_constant<int, kNumChunks>());
       const uint64_t step = 64 * kNumChunks;
-      const uint64_t pend = __ballot(in && !hit && ohi > i0 + step);
+      const uint64_t pend = __ballot(in && hits != all && ohi > i0 + step);
       if (!pend) break;
       const int l = __ffsll((unsigned long long)pend) - 1;
       const uint32_t nxt = (uint32_t)__builtin_amdgcn_readlane((int)olo, l);
       i0 = (uint32_t)max((uint64_t)i0 + step, (uint64_t)nxt);
     }
-    const uint64_t word = __ballot(in && !heavy && hit);
-    if (lane == 0) out[w] = word;
+    for (uint32_t j = 0; j < n; ++j) {
+      const uint64_t word = __ballot(in && !heavy && ((hits >> j) & 1u));
+      if (lane == 0) out(j)[w] = word;
+    }
   }
 }
 
@@ -236,11 +252,17 @@ __device__ __forceinline__ uint32_t value_task(const Task* __restrict__ tasks, u
 }
 
 __global__ void __launch_bounds__(256)
-k_numrole(DevKB kb, const NumTask* __restrict__ tasks, uint32_t bpt) {
-  const NumTask T = tasks[blockIdx.x / bpt];
-  const float* vals = kb.num_val + ((uint64_t)T.base_hi << 32 | T.base_lo);
-  value_walk<float>(kb, kb.num_roff + (size_t)T.role * (kb.N + 1), vals,
-                    [&](float v) { return num_pass(v, T.cmp, T.t); }, out_ptr(kb, T.out_row), blockIdx.x % bpt, bpt);
+k_numrole(DevKB kb, const ThrGroup* __restrict__ groups, const NumTask* __restrict__ tasks, uint32_t bpt) {
+  const ThrGroup G = groups[blockIdx.x / bpt];
+  const NumTask T0 = tasks[G.first];
+  value_walk<float>(
+      kb, kb.num_roff + (size_t)G.prop * (kb.N + 1), kb.num_val + ((uint64_t)T0.base_hi << 32 | T0.base_lo), G.n,
+      [&](uint32_t j) {
+        const uint32_t cmp = tasks[G.first + j].cmp;
+        const float t = tasks[G.first + j].t;
+        return [=](float v) { return num_pass(v, cmp, t); };
+      },
+      [&](uint32_t j) { return out_ptr(kb, tasks[G.first + j].out_row); }, blockIdx.x % bpt, bpt);
 }
 
 __global__ void __launch_bounds__(256)
@@ -280,19 +302,19 @@ k_contains(DevKB kb, const StrTask* __restrict__ tasks, uint32_t tiles) {
 }
 
 __global__ void __launch_bounds__(256)
-k_strrole(DevKB kb, const StrTask* __restrict__ tasks, uint32_t bpt) {
-  const StrTask T = tasks[blockIdx.x / bpt];
-  const uint32_t* off = kb.str_roff + (size_t)T.role * (kb.N + 1);
-  const int32_t* ids = kb.str_ids + ((uint64_t)T.base_hi << 32 | T.base_lo);
-  uint64_t* out = out_ptr(kb, T.out_row);
-  if (T.kind == 0) {
-    value_walk<int32_t>(kb, off, ids, [&](int32_t id) { return (uint32_t)id == T.q; }, out,
-                        blockIdx.x % bpt, bpt);
-  } else {
-    const uint64_t* set = kb.idsets + T.set_word;
-    value_walk<int32_t>(kb, off, ids, [&](int32_t id) { return (set[(uint32_t)id >> 6] >> (id & 63)) & 1; },
-                        out, blockIdx.x % bpt, bpt);
-  }
+k_strrole(DevKB kb, const ThrGroup* __restrict__ groups, const StrTask* __restrict__ tasks, uint32_t bpt) {
+  const ThrGroup G = groups[blockIdx.x / bpt];
+  const StrTask T0 = tasks[G.first];
+  value_walk<int32_t>(
+      kb, kb.str_roff + (size_t)G.prop * (kb.N + 1), kb.str_ids + ((uint64_t)T0.base_hi << 32 | T0.base_lo), G.n,
+      [&](uint32_t j) {
+        const StrTask T = tasks[G.first + j];
+        const uint64_t* set = kb.idsets + T.set_word;
+        return [=](int32_t id) {
+          return T.kind == 0 ? (uint32_t)id == T.q : (bool)((set[(uint32_t)id >> 6] >> (id & 63)) & 1);
+        };
+      },
+      [&](uint32_t j) { return out_ptr(kb, tasks[G.first + j].out_row); }, blockIdx.x % bpt, bpt);
 }
 
 __global__ void __launch_bounds__(256)
@@ -1036,6 +1058,7 @@ size_t table_bound(uint32_t max_nodes, uint32_t max_hyps) {
   b += align_up(n * sizeof(ThrGroup), 256);
   b += align_up(n * sizeof(NumTask), 256);
   b += align_up(n * sizeof(StrTask), 256);
+  b += align_up(n * sizeof(ThrGroup), 256);                // num and string tasks by role
   b += align_up((n + max_hyps) * sizeof(RegionTask), 256);
   b += align_up(n * sizeof(RoleTask), 256);
   b += align_up(n * sizeof(RoleTask), 256);                // pushed role tasks
@@ -1176,6 +1199,18 @@ double Launcher::csr_once(uint32_t role, uint32_t inv) {
 // loads in flight while it evaluates one)
 constexpr uint32_t kRegionTilesPerBlock = 16;
 constexpr uint64_t kRegionMinBlocks = 16384;
+
+// Blocks per threshold group over W words: about 32 words per wave, enough
+// independent column loads in flight; fewer, down to the 8 a wave takes at
+// once, while the launch would leave compute units idle (7 groups over 157
+// words 18 us at 32 words a wave, THR_B at 8).
+inline uint32_t threshold_blocks(const hth_kb_s& kb, uint32_t n, uint32_t W) {
+  return std::max<uint32_t>(1, std::min((W + 31) / 32, std::max((W + 127) / 128, 4 * kb.n_cu / n)));
+}
+
+inline uint32_t value_blocks(const hth_kb_s& kb, uint32_t n) {
+  return std::max<uint32_t>(1, std::min<uint32_t>((kb.W + 7) / 8, (32 * kb.n_cu + n - 1) / n));
+}
 
 // n region tasks whose programs need at most `depth` stack entries
 hth_status launch_regions_n(Launcher& L, const DevKB& d, const RegionTask* tasks, const uint32_t* code,
@@ -1469,6 +1504,7 @@ size_t plan_workspace_bytes(const hth_kb_s& kb, const Plan& P) {
   add(P.thr.size(), sizeof(ThrGroup));
   add(P.num.size(), sizeof(NumTask));
   add(P.str.size(), sizeof(StrTask));
+  add(P.num.size() + P.str.size(), sizeof(ThrGroup));
   add(n_reg + n_cover, sizeof(RegionTask));
   add(n_role, sizeof(RoleTask));
   add(n_role, sizeof(RoleTask));            // pushed role tasks (a subset of the role nodes)
@@ -1501,6 +1537,7 @@ struct Prepared {
   size_t o_push = 0;
   size_t o_num = 0, n_num_blocks = 0;   // numeric concrete-role tasks, their heavy-row blocks
   size_t o_str = 0, n_str_blocks = 0, n_contains = 0;   // string concrete-role tasks
+  size_t o_numg = 0, n_numg = 0, o_strg = 0, n_strg = 0;   // their tasks by role (ThrGroup: prop = role)
   size_t o_xnum = 0, o_xstr = 0, n_xcontains = 0, o_xrole = 0;   // tasks at the examples only
   ViewPlan V;                           // the example view: its tables below, its areas in V
   size_t o_vthr = 0, o_vthg = 0, o_vgrp = 0, o_vpass = 0, o_vdir = 0, o_vbase = 0, o_vcopy = 0;
@@ -1629,7 +1666,19 @@ void prepare(const hth_kb_s& kb, Plan&& plan, uint32_t n_hyps, Prepared& X) {
     X.o_vbase = X.blob.add(bases);
     X.o_vcopy = X.blob.add(copies);
   }
+  // tasks of one role share a walk of its values, up to kValPerPass at a time
+  auto by_role = [](auto& tasks, auto from) {
+    std::stable_sort(tasks.begin() + from, tasks.end(), [](const auto& a, const auto& b) { return a.role < b.role; });
+    std::vector<ThrGroup> out;
+    for (uint32_t i = 0; i < tasks.size(); ++i) {
+      if (out.empty() || out.back().prop != tasks[i].role || out.back().n == kValPerPass)
+        out.push_back(ThrGroup{tasks[i].role, i, 0, 0});
+      out.back().n++;
+    }
+    return out;
+  };
   std::vector<NumTask> num(P.num);
+  const std::vector<ThrGroup> num_groups = by_role(num, 0);
   for (NumTask& t : num) {
     t.base_lo = (uint32_t)P.num_bounds[t.role];
     t.base_hi = (uint32_t)(P.num_bounds[t.role] >> 32);
@@ -1638,10 +1687,15 @@ void prepare(const hth_kb_s& kb, Plan&& plan, uint32_t n_hyps, Prepared& X) {
     X.n_num_blocks += P.num_chunk_first[t.role + 1] - P.num_chunk_first[t.role];
   }
   X.o_num = X.blob.add(num);
+  X.o_numg = X.blob.add(num_groups);
+  X.n_numg = num_groups.size();
   // string tasks: CONTAIN first (k_contains takes them as one range), each
   // with its id set; heavy-row blocks numbered in table order
   std::vector<StrTask> str(P.str);
-  std::stable_partition(str.begin(), str.end(), [](const StrTask& t) { return t.kind == 1; });
+  const ptrdiff_t first_equal =
+      std::stable_partition(str.begin(), str.end(), [](const StrTask& t) { return t.kind == 1; }) - str.begin();
+  std::stable_sort(str.begin(), str.begin() + first_equal, [](const StrTask& a, const StrTask& b) { return a.role < b.role; });
+  const std::vector<ThrGroup> str_groups = by_role(str, first_equal);
   for (StrTask& t : str) {
     t.base_lo = (uint32_t)P.str_bounds[t.role];
     t.base_hi = (uint32_t)(P.str_bounds[t.role] >> 32);
@@ -1651,6 +1705,8 @@ void prepare(const hth_kb_s& kb, Plan&& plan, uint32_t n_hyps, Prepared& X) {
     if (t.kind == 1) t.set_word = (uint32_t)(X.n_contains++ * idset_words(P.n_strings));
   }
   X.o_str = X.blob.add(str);
+  X.o_strg = X.blob.add(str_groups);
+  X.n_strg = str_groups.size();
   std::vector<NumTask> xnum(P.ex_num);
   for (NumTask& t : xnum) {
     t.base_lo = (uint32_t)P.num_bounds[t.role];
@@ -1777,12 +1833,13 @@ hth_status launch_prepared(hth_kb_s& kb, const Prepared& X, char* ws, uint32_t* 
   if (!P.num.empty()) {
     const uint32_t n = (uint32_t)P.num.size();
     const NumTask* nt = reinterpret_cast<const NumTask*>(ws + X.o_num);
-    const uint32_t bpt = std::max<uint32_t>(1, std::min<uint32_t>((kb.W + 7) / 8, (32 * kb.n_cu + n - 1) / n));
+    const uint32_t ng = (uint32_t)X.n_numg, bpt = value_blocks(kb, ng);
+    const ThrGroup* gr = reinterpret_cast<const ThrGroup*>(ws + X.o_numg);
     double bytes = 0;   // per task: the role's offsets and values once, its row out
     for (const NumTask& t : P.num)
       bytes += 4.0 * (kb.N + 1) + 4.0 * (double)(P.num_bounds[t.role + 1] - P.num_bounds[t.role]) + 8.0 * kb.W;
-    hth_status s = split_launch(Lc, HTH_K_THRESHOLD, bytes, n, bpt, 256, [&](uint32_t i0, uint32_t, uint32_t blocks) {
-      hipLaunchKernelGGL(k_numrole, dim3(blocks), dim3(256), 0, st, d, nt + i0, bpt);
+    hth_status s = split_launch(Lc, HTH_K_THRESHOLD, bytes, ng, bpt, 256, [&](uint32_t i0, uint32_t, uint32_t blocks) {
+      hipLaunchKernelGGL(k_numrole, dim3(blocks), dim3(256), 0, st, d, gr + i0, nt, bpt);
     });
     if (s) return s;
     if (X.n_num_blocks) {
@@ -1830,12 +1887,13 @@ hth_status launch_prepared(hth_kb_s& kb, const Prepared& X, char* ws, uint32_t* 
     const StrTask* sk = reinterpret_cast<const StrTask*>(ws + X.o_str);
     hth_status s = contains(sk, X.n_contains);
     if (s) return s;
-    const uint32_t bpt = std::max<uint32_t>(1, std::min<uint32_t>((kb.W + 7) / 8, (32 * kb.n_cu + n - 1) / n));
+    const uint32_t ng = (uint32_t)X.n_strg, bpt = value_blocks(kb, ng);
+    const ThrGroup* gr = reinterpret_cast<const ThrGroup*>(ws + X.o_strg);
     double bytes = 0;   // per task: the role's offsets and ids once, its row out
     for (const StrTask& t : P.str)
       bytes += 4.0 * (kb.N + 1) + 4.0 * (double)(P.str_bounds[t.role + 1] - P.str_bounds[t.role]) + 8.0 * kb.W;
-    s = split_launch(Lc, HTH_K_THRESHOLD, bytes, n, bpt, 256, [&](uint32_t i0, uint32_t, uint32_t blocks) {
-      hipLaunchKernelGGL(k_strrole, dim3(blocks), dim3(256), 0, st, d, sk + i0, bpt);
+    s = split_launch(Lc, HTH_K_THRESHOLD, bytes, ng, bpt, 256, [&](uint32_t i0, uint32_t, uint32_t blocks) {
+      hipLaunchKernelGGL(k_strrole, dim3(blocks), dim3(256), 0, st, d, gr + i0, sk, bpt);
     });
     if (s) return s;
     if (X.n_str_blocks) {
@@ -1846,9 +1904,7 @@ hth_status launch_prepared(hth_kb_s& kb, const Prepared& X, char* ws, uint32_t* 
     }
   }
   if (X.n_thr_groups) {
-    // about 32 words per wave: enough independent column loads in flight
-    const uint32_t n = (uint32_t)X.n_thr_groups;
-    const uint32_t bpt = std::max<uint32_t>(1, (kb.W + 127) / 128);
+    const uint32_t n = (uint32_t)X.n_thr_groups, bpt = threshold_blocks(kb, n, kb.W);
     std::vector<uint32_t> props;
     for (const ThrTask& t : P.thr) props.push_back(t.prop);
     std::sort(props.begin(), props.end());
