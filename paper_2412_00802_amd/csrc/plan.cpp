@@ -33,6 +33,15 @@ class Dag {
 
   Dag() { table_.assign(1 << 12, kNone); }
 
+  // room for `n` nodes and `k` children: no growth on the way
+  void reserve(size_t n, size_t k) {
+    nodes.reserve(n);
+    kids.reserve(k);
+    size_t t = table_.size();
+    while (t <= 2 * n) t <<= 1;
+    table_.assign(t, kNone);
+  }
+
   uint32_t top() { return leaf(HTH_TOP, 0, 0, 0); }
   uint32_t bot() { return leaf(HTH_BOT, 0, 0, 0); }
   uint32_t leaf(uint8_t op, uint8_t inv, uint32_t arg, uint32_t q) {
@@ -75,8 +84,8 @@ class Dag {
         tmp_.push_back(c);
       }
     }
-    std::vector<uint32_t> v;
-    v.reserve(tmp_.size());
+    std::vector<uint32_t>& v = out_;
+    v.clear();
     for (uint32_t c : tmp_) {
       uint8_t o = nodes[c].op;
       if (o == absorb) return c;
@@ -94,7 +103,7 @@ class Dag {
 
  private:
   std::vector<uint32_t> table_;
-  std::vector<uint32_t> tmp_;
+  std::vector<uint32_t> tmp_, out_;   // of mk_nary, kept between calls
 
   static uint64_t hash_of(const CNode& n, const uint32_t* k, uint32_t kn) {
     uint64_t h = mix(0x1234567ull, n.op | (uint64_t)n.inv << 8);
@@ -266,14 +275,16 @@ struct Compiler {
   uint32_t zero_row = kNone;
   std::vector<uint32_t> vrow;    // view rows of what root programs read
   bool in_view = false;          // programs read view rows
+  std::vector<uint32_t> map_, ks_;   // of add_hypothesis and emit, kept between calls
 
   explicit Compiler(const hth_kb_s& k) : kb(k) {}
 
   hth_status add_hypothesis(const hth_node* nd, uint32_t nn, const uint32_t* children,
                             uint32_t n_children, uint32_t h) {
     if (nn == 0) return fail(HTH_E_PLAN, "hypothesis " + std::to_string(h) + " has no nodes");
-    std::vector<uint32_t> map(nn);
-    std::vector<uint32_t> ks;
+    std::vector<uint32_t>& map = map_;
+    std::vector<uint32_t>& ks = ks_;
+    map.resize(nn);
     const hth_kb_desc& d = kb.d;
     for (uint32_t i = 0; i < nn; ++i) {
       const hth_node& x = nd[i];
@@ -363,11 +374,18 @@ struct Compiler {
     if (n.op == HTH_NOT) {
       r = is_leaflike(dag.nodes[n.a].op) ? 1 : region_depth(n.a);
     } else if (n.op == HTH_AND || n.op == HTH_OR) {
-      std::vector<int32_t> ds;
-      for (uint32_t j = 0; j < n.kid_n; ++j) ds.push_back(region_depth(dag.kids[n.kid_off + j]));
-      std::sort(ds.rbegin(), ds.rend());
-      r = 0;
-      for (size_t j = 0; j < ds.size(); ++j) r = std::max<int32_t>(r, ds[j] + (j ? 1 : 0));
+      // deepest child first: it needs d1 entries, every later one its own + 1
+      int32_t d1 = 0, d2 = 0;
+      for (uint32_t j = 0; j < n.kid_n; ++j) {
+        const int32_t d = region_depth(dag.kids[n.kid_off + j]);
+        if (d > d1) {
+          d2 = d1;
+          d1 = d;
+        } else if (d > d2) {
+          d2 = d;
+        }
+      }
+      r = n.kid_n > 1 ? std::max(d1, d2 + 1) : d1;
     }
     depth[v] = r;
     return r;
@@ -396,14 +414,27 @@ struct Compiler {
         return;
       case HTH_AND:
       case HTH_OR: {
-        std::vector<uint32_t> ks(dag.kids.begin() + n.kid_off, dag.kids.begin() + n.kid_off + n.kid_n);
-        std::stable_sort(ks.begin(), ks.end(),
-                         [&](uint32_t a, uint32_t b) { return region_depth(a) > region_depth(b); });
-        emit(ks[0], code);
-        for (size_t j = 1; j < ks.size(); ++j) {
-          emit(ks[j], code);
-          code.push_back(rp_ins(n.op == HTH_AND ? RP_AND : RP_OR, 0, 0));
+        // the deepest child first, the others after it in order of depth, equal
+        // ones in theirs: ks_ is a stack of the operands in progress
+        const size_t k0 = ks_.size();
+        ks_.insert(ks_.end(), dag.kids.begin() + n.kid_off, dag.kids.begin() + n.kid_off + n.kid_n);
+        if (n.kid_n <= 16) {         // an insertion sort: no buffer
+          for (size_t j = k0 + 1; j < ks_.size(); ++j) {
+            const uint32_t c = ks_[j];
+            size_t i = j;
+            for (; i > k0 && region_depth(ks_[i - 1]) < region_depth(c); --i) ks_[i] = ks_[i - 1];
+            ks_[i] = c;
+          }
+        } else {
+          std::stable_sort(ks_.begin() + k0, ks_.end(),
+                           [&](uint32_t a, uint32_t b) { return region_depth(a) > region_depth(b); });
         }
+        const uint32_t op = rp_ins(n.op == HTH_AND ? RP_AND : RP_OR, 0, 0), kn = n.kid_n;
+        for (uint32_t j = 0; j < kn; ++j) {
+          emit(ks_[k0 + j], code);
+          if (j) code.push_back(op);
+        }
+        ks_.resize(k0);
         return;
       }
       default:
@@ -416,6 +447,7 @@ struct Compiler {
     if (region_depth(v) > kStackDepth)
       return fail(HTH_E_UNSUPPORTED, "boolean region nested deeper than 16 operand levels");
     off = (uint32_t)code.size();
+    ks_.clear();
     emit(v, code);
     len = (uint32_t)code.size() - off;
     return HTH_OK;
@@ -797,6 +829,9 @@ hth_status compile_plan(const hth_kb_s& kb, const hth_node* nodes, const uint32_
                         const PlanOptions& opt, Plan& out, Plan* general) {
   out = Plan();
   Compiler c(kb);
+  // (an upper bound of the canonical nodes; offsets are checked below)
+  if (hyp_off[n_hyps] <= (1u << 24)) c.dag.reserve(hyp_off[n_hyps] + 2, n_children);
+  c.roots.reserve(n_hyps);
   for (uint32_t h = 0; h < n_hyps; ++h) {
     uint32_t b = hyp_off[h], e = hyp_off[h + 1];
     if (e < b) return fail(HTH_E_INVALID, "hyp_node_offsets decrease");
