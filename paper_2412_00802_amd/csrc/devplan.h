@@ -1463,10 +1463,9 @@ extern "C" hth_status hth_dplan_launch(hth_dplan plan, void* ws, size_t ws_bytes
     });
     if (s) return s;
   }
-  const uint32_t ftiles = fill_tiles(kb.S);
-  s = Lc.run(HTH_K_FILL, (double)kb.W * 8, [&] {   // the zero row
-    hipLaunchKernelGGL(k_fill_rows, dim3(ftiles), dim3(256), 0, st, d, T.fills, ftiles);
-  });
+  uint32_t nfill = 1;   // the zero row, then every level's
+  for (uint32_t L = 0; L < S.levels; ++L) nfill += p.fills[L];
+  s = launch_fills(Lc, d, T.fills, nfill, (double)nfill * kb.W * 8);
   if (s) return s;
   if (p.n_thg) {
     const uint32_t n = p.n_thg, bpt = threshold_blocks(kb, n, kb.W);
@@ -1481,13 +1480,6 @@ extern "C" hth_status hth_dplan_launch(hth_dplan plan, void* ws, size_t ws_bytes
     Lc.csr_seen.clear();
     s = launch_regions_n(Lc, d, T.mat + p.B.mat[L], T.code, S.mat[L], (int)S.mat_depth, 0.0);
     if (s) return s;
-    if (p.fills[L]) {
-      const uint32_t n = p.fills[L];
-      s = split_launch(Lc, HTH_K_FILL, (double)n * kb.W * 8, n, ftiles, 256, [&](uint32_t i0, uint32_t, uint32_t blocks) {
-        hipLaunchKernelGGL(k_fill_rows, dim3(blocks), dim3(256), 0, st, d, T.fills + p.B.fill[L] + i0, ftiles);
-      });
-      if (s) return s;
-    }
     const RoleTask* rol = T.roles + p.B.role[L];
     const uint32_t nt = p.B.nrole[L];
     s = launch_roles_n(Lc, d, rol, nt, 0.0);

@@ -1208,6 +1208,17 @@ inline uint32_t threshold_blocks(const hth_kb_s& kb, uint32_t n, uint32_t W) {
   return std::max<uint32_t>(1, std::min((W + 31) / 32, std::max((W + 127) / 128, 4 * kb.n_cu / n)));
 }
 
+// A plan's fills, every level's at once before the first: a launch less for
+// each further level (3 % of a round over 200,000 individuals; 3.7 GB of fills
+// over 4M individuals take the same time as level by level).
+hth_status launch_fills(Launcher& L, const DevKB& d, const FillTask* tasks, size_t n, double bytes) {
+  if (!n) return HTH_OK;
+  const uint32_t tiles = fill_tiles(L.kb.S);
+  return split_launch(L, HTH_K_FILL, bytes, n, tiles, 256, [&](uint32_t i0, uint32_t, uint32_t blocks) {
+    hipLaunchKernelGGL(k_fill_rows, dim3(blocks), dim3(256), 0, L.st, d, tasks + i0, tiles);
+  });
+}
+
 inline uint32_t value_blocks(const hth_kb_s& kb, uint32_t n) {
   return std::max<uint32_t>(1, std::min<uint32_t>((kb.W + 7) / 8, (32 * kb.n_cu + n - 1) / n));
 }
@@ -1525,14 +1536,14 @@ std::once_flag g_attr_once;
 struct Prepared {
   Plan P;
   Blob blob;
-  struct LevelAt { size_t mat, role, group, fill, nrole, ngroup, nfill, nhb, nhc, push, npush; double fill_bytes; size_t ex; };
+  struct LevelAt { size_t mat, role, group, nrole, ngroup, nhb, nhc, push, npush; double fill_bytes; size_t ex; };
   std::vector<LevelAt> at;
   size_t root_at = 0;
   std::vector<std::vector<RoleTask>> lv_roles;
   std::vector<std::vector<RoleTask>> lv_push;
   std::vector<std::vector<GroupTask>> lv_groups;
   std::vector<std::vector<GroupChunk>> lv_chunks;
-  size_t n_thr_groups = 0, n_thr_tasks = 0;
+  size_t n_thr_groups = 0, n_thr_tasks = 0, n_fills = 0;
   size_t o_thr = 0, o_thg = 0, o_reg = 0, o_role = 0, o_grp = 0, o_mem = 0, o_fill = 0, o_code = 0, o_xslot = 0;
   size_t o_push = 0;
   size_t o_num = 0, n_num_blocks = 0;   // numeric concrete-role tasks, their heavy-row blocks
@@ -1568,7 +1579,7 @@ void prepare(const hth_kb_s& kb, Plan&& plan, uint32_t n_hyps, Prepared& X) {
   X.lv_chunks.assign(NL, {});
   for (size_t L = 0; L < NL; ++L) {
     const PlanLevel& PL = P.levels[L];
-    X.at[L] = {regions.size(), roles.size(), groups.size(), fills.size(), 0, 0, 0, 0, 0, pushes.size(), 0, 0.0, ex_roles.size()};
+    X.at[L] = {regions.size(), roles.size(), groups.size(), 0, 0, 0, 0, pushes.size(), 0, 0.0, ex_roles.size()};
     ex_roles.insert(ex_roles.end(), PL.ex_roles.begin(), PL.ex_roles.end());
     regions.insert(regions.end(), PL.mat.begin(), PL.mat.end());
     for (RoleTask t : PL.roles) {
@@ -1614,7 +1625,6 @@ void prepare(const hth_kb_s& kb, Plan&& plan, uint32_t n_hyps, Prepared& X) {
     members.insert(members.end(), PL.members.begin(), PL.members.end());
     X.at[L].nrole = roles.size() - X.at[L].role;
     X.at[L].ngroup = groups.size() - X.at[L].group;
-    X.at[L].nfill = fills.size() - X.at[L].fill;
     X.at[L].npush = pushes.size() - X.at[L].push;
   }
   X.root_at = regions.size();
@@ -1731,6 +1741,7 @@ void prepare(const hth_kb_s& kb, Plan&& plan, uint32_t n_hyps, Prepared& X) {
   X.o_grp = X.blob.add(groups);
   X.o_mem = X.blob.add(members);
   X.o_fill = X.blob.add(fills);
+  X.n_fills = fills.size();
   X.o_code = X.blob.add(P.code);
   X.o_xslot = X.blob.add(xslots);
   X.o_push = X.blob.add(pushes);
@@ -1914,19 +1925,16 @@ hth_status launch_prepared(hth_kb_s& kb, const Prepared& X, char* ws, uint32_t* 
     });
     if (s) return s;
   }
+  double fill_bytes = 0;
+  for (const Prepared::LevelAt& at : X.at) fill_bytes += at.fill_bytes;
+  hth_status sf = launch_fills(Lc, d, fil, X.n_fills, fill_bytes);
+  if (sf) return sf;
   for (size_t L = 0; L < P.levels.size(); ++L) {
     const PlanLevel& PL = P.levels[L];
     const Prepared::LevelAt& at = X.at[L];
     Lc.csr_seen.clear();
     hth_status s = launch_regions(Lc, d, reg + at.mat, code, PL.mat, P.code);
     if (s) return s;
-    if (at.nfill) {
-      const uint32_t n = (uint32_t)at.nfill, tiles = fill_tiles(kb.S);
-      s = split_launch(Lc, HTH_K_FILL, at.fill_bytes, n, tiles, 256, [&](uint32_t i0, uint32_t, uint32_t blocks) {
-        hipLaunchKernelGGL(k_fill_rows, dim3(blocks), dim3(256), 0, st, d, fil + at.fill + i0, tiles);
-      });
-      if (s) return s;
-    }
     if (at.npush) {   // after the fills that set their rows to all zeros / all ones
       const uint32_t n = (uint32_t)at.npush, tiles = (kb.W + 3) / 4;
       const RoleTask* pt = reinterpret_cast<const RoleTask*>(ws + X.o_push) + at.push;
