@@ -829,8 +829,9 @@ hth_status compile_plan(const hth_kb_s& kb, const hth_node* nodes, const uint32_
                         const PlanOptions& opt, Plan& out, Plan* general) {
   out = Plan();
   Compiler c(kb);
-  // (an upper bound of the canonical nodes; offsets are checked below)
-  if (hyp_off[n_hyps] <= (1u << 24)) c.dag.reserve(hyp_off[n_hyps] + 2, n_children);
+  // room for the canonical nodes that the batch may have, up to a million (the
+  // sizes are the caller's, offsets are checked below)
+  c.dag.reserve(std::min<size_t>(hyp_off[n_hyps], 1u << 20) + 2, std::min<size_t>(n_children, 1u << 20));
   c.roots.reserve(n_hyps);
   for (uint32_t h = 0; h < n_hyps; ++h) {
     uint32_t b = hyp_off[h], e = hyp_off[h + 1];
