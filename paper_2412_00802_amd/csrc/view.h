@@ -70,13 +70,16 @@ __device__ __forceinline__ uint32_t wave_scan(uint32_t v) {   // inclusive
 
 // The example list in three steps: words' popcounts by tile, their scan (and
 // the view's sizes), the list.  hdr: {examples, words of 64 examples}.  Bound
-// by launch latency (a few microseconds each over 4M individuals).
+// by launch latency (a few microseconds each over 4M individuals).  Bits past
+// the last individual are no examples: the rows are the caller's, read at each
+// launch, and what they hold there must not become an index.
 __device__ __forceinline__ uint32_t ex_words(const DevKB& kb, uint64_t (&v)[8]) {
   const uint32_t w0 = blockIdx.x * kExTile + threadIdx.x * 8;
   uint32_t n = 0;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    v[i] = w0 + i < kb.W ? kb.pos[w0 + i] | kb.neg[w0 + i] : 0ull;
+    const uint64_t valid = w0 + i + 1 < kb.W ? ~0ull : w0 + i < kb.W ? kb.tail : 0ull;
+    v[i] = valid ? (kb.pos[w0 + i] | kb.neg[w0 + i]) & valid : 0ull;
     n += (uint32_t)__popcll(v[i]);
   }
   return n;
