@@ -158,7 +158,9 @@ k_scan_block_sums(uint32_t* __restrict__ bsum, uint32_t nb) {
 // 133M assertions of 16 roles over 1M individuals: rows 99 us, check 197,
 // partition 805, buckets 676; a load 1.9 ms where it was 17.2.
 // An invalid knowledge base sets *flags; every kernel that would index with
-// unchecked data returns when it is set.
+// unchecked data returns when it is set.  A role's assertions are those of its
+// rows (fwd_off[r][N] of them): what may lie between its last row's end and the
+// next role's first offset belongs to no subject and is not looked at.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kPartEdges = 8192;       // assertions of one chunk
 constexpr int kPartThreads = 512;
@@ -256,11 +258,12 @@ k_load_check(const uint32_t* __restrict__ fwd_off, const int32_t* __restrict__ t
   extern __shared__ uint32_t s_hist[];
   __shared__ uint32_t s_start[kPartEdges / 32], s_range[2];
   const uint32_t r = blockIdx.y, tid = threadIdx.x;
-  const uint32_t n = (uint32_t)(base[r + 1] - base[r]);
-  const uint32_t chunks = (uint32_t)(((uint64_t)n + kPartEdges - 1) / kPartEdges);
   // (only what earlier kernels set: this one's own blocks add other reasons)
-  if (blockIdx.x >= chunks || (*flags & (F_NONMONO | F_PAD))) return;
+  if (*flags & (F_NONMONO | F_PAD)) return;
   const uint32_t* fo = fwd_off + (size_t)r * (N + 1);
+  const uint32_t n = fo[N];
+  const uint32_t chunks = (uint32_t)(((uint64_t)n + kPartEdges - 1) / kPartEdges);
+  if (blockIdx.x >= chunks) return;
   const int32_t* t = tg + base[r];
   for (uint32_t i = tid; i < nb; i += kPartThreads) s_hist[i] = 0;
   uint32_t bad = 0;
@@ -325,11 +328,12 @@ k_load_part(const uint32_t* __restrict__ fwd_off, const int32_t* __restrict__ tg
   uint32_t* s_to = s_hist + nb;                                          // [nb]
   __shared__ uint32_t s_range[2], s_last[kPartThreads / 64];
   const uint32_t r = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const uint32_t n = (uint32_t)(base[r + 1] - base[r]);
-  const uint64_t c0l = (uint64_t)blockIdx.x * kPartEdges;
-  if (c0l >= n || *flags) return;
-  const uint32_t c0 = (uint32_t)c0l, cn = min(kPartEdges, n - c0);
+  if (*flags) return;
   const uint32_t* fo = fwd_off + (size_t)r * (N + 1);
+  const uint32_t n = fo[N];
+  const uint64_t c0l = (uint64_t)blockIdx.x * kPartEdges;
+  if (c0l >= n) return;
+  const uint32_t c0 = (uint32_t)c0l, cn = min(kPartEdges, n - c0);
   const int32_t* t = tg + base[r] + c0;
   uint32_t y[kOwn], row[kOwn], rank[kOwn];
 #pragma unroll
@@ -402,8 +406,8 @@ k_load_part(const uint32_t* __restrict__ fwd_off, const int32_t* __restrict__ tg
 // LDS counters goes by sub-ranges, reading its pairs once for each.
 __global__ void __launch_bounds__(kPartThreads)
 k_load_bucket(const uint2* __restrict__ pairs, const uint64_t* __restrict__ base, uint32_t N, uint32_t W, uint32_t nb,
-              uint32_t shift, uint32_t range, const uint32_t* __restrict__ bbase, uint32_t* __restrict__ inv_off,
-              int32_t* __restrict__ inv_tg, uint64_t* __restrict__ mask, uint32_t* __restrict__ maxdeg, HeavyOut H,
+              uint32_t shift, uint32_t range, const uint32_t* __restrict__ bbase, const uint32_t* __restrict__ fwd_off,
+              uint32_t* __restrict__ inv_off, int32_t* __restrict__ inv_tg, uint64_t* __restrict__ mask, uint32_t* __restrict__ maxdeg, HeavyOut H,
               const uint32_t* __restrict__ flags) {
   extern __shared__ uint32_t s_dyn[];
   __shared__ uint32_t s_wsum[kPartThreads / 64];
@@ -411,7 +415,7 @@ k_load_bucket(const uint2* __restrict__ pairs, const uint64_t* __restrict__ base
   uint32_t* s_out = s_dyn + range;         // [kBucketStage]
   if (*flags) return;
   const uint32_t r = blockIdx.y, b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const uint32_t n = (uint32_t)(base[r + 1] - base[r]);
+  const uint32_t n = fwd_off[(size_t)r * (N + 1) + N];
   const uint32_t i0 = bbase[(size_t)r * nb + b], i1 = b + 1 < nb ? bbase[(size_t)r * nb + b + 1] : n;
   const uint2* p = pairs + base[r];
   uint32_t* io = inv_off + (size_t)r * (N + 1);
@@ -550,7 +554,7 @@ k_words_write(const uint64_t* __restrict__ mask, uint32_t W, uint32_t tiles, con
 // individuals.
 __global__ void __launch_bounds__(256)
 k_object_rank(const int32_t* __restrict__ fwd_tg, const int32_t* __restrict__ inv_tg, const uint64_t* __restrict__ base,
-              uint32_t N, uint32_t W, const uint64_t* __restrict__ mask, const uint32_t* __restrict__ objbase,
+              const uint32_t* __restrict__ fwd_off, uint32_t N, uint32_t W, const uint64_t* __restrict__ mask, const uint32_t* __restrict__ objbase,
               const uint32_t* __restrict__ nobj, int32_t* __restrict__ ctg_fwd, int32_t* __restrict__ ctg_inv,
               const uint32_t* __restrict__ flags) {
   const uint32_t rd = 2 * blockIdx.y + blockIdx.z, r = rd >> 1, dir = rd & 1;
@@ -559,7 +563,7 @@ k_object_rank(const int32_t* __restrict__ fwd_tg, const int32_t* __restrict__ in
   int32_t* ctg = (dir ? ctg_inv : ctg_fwd) + base[r];
   const uint64_t* m = mask + (size_t)rd * W;
   const uint32_t* ob = objbase + (size_t)rd * (W + 1);
-  const uint64_t n = base[r + 1] - base[r];
+  const uint64_t n = fwd_off[(size_t)r * (N + 1) + N];
   for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (uint64_t)gridDim.x * 256) {
     const uint32_t y = (uint32_t)tg[i];
     ctg[i] = (int32_t)(ob[y >> 6] + (uint32_t)__popcll(m[y >> 6] & ((1ull << (y & 63)) - 1ull)));
@@ -800,14 +804,14 @@ static hth_status kb_build(hth_kb_s* kb, char* derived, hipStream_t st) {
                          base, N, nb, shift, bcur, pairs, flags);
     const size_t lds = 4 * ((size_t)range + kBucketStage);
     hipLaunchKernelGGL(k_load_bucket, dim3(nb, R), dim3(kPartThreads), lds, st, pairs, base, N, kb->W, nb, shift, range,
-                       bbase, kb->inv_off, kb->inv_tg, kb->objmask, maxdeg + R, H, flags);
+                       bbase, kb->fwd_off, kb->inv_off, kb->inv_tg, kb->objmask, maxdeg + R, H, flags);
     hipLaunchKernelGGL(k_words_sum, dim3(L.tiles, R, 2), dim3(256), 0, st, kb->objmask, kb->W, L.tiles, tsum);
     hipLaunchKernelGGL(k_scan_block_sums, dim3(4 * R), dim3(kScanThreads), 0, st, tsum, L.tiles);
     hipLaunchKernelGGL(k_words_write, dim3(L.tiles, R, 2), dim3(256), 0, st, kb->objmask, kb->W, L.tiles, tsum,
                        kb->objbase, kb->words, nobj, nwords);
     if (most) {
       const unsigned g = (unsigned)std::min<uint64_t>((most + 2047) / 2048, 65536);
-      hipLaunchKernelGGL(k_object_rank, dim3(g, R, 2), dim3(256), 0, st, d.role_targets, kb->inv_tg, base, N, kb->W,
+      hipLaunchKernelGGL(k_object_rank, dim3(g, R, 2), dim3(256), 0, st, d.role_targets, kb->inv_tg, base, kb->fwd_off, N, kb->W,
                          kb->objmask, kb->objbase, nobj, kb->ctg_fwd, kb->ctg_inv, flags);
     }
     HTH_HIP(hipGetLastError());
