@@ -62,7 +62,11 @@ template <bool VIEW>
 __global__ void __launch_bounds__(256)
 k_threshold(DevKB kb, const ThrGroup* __restrict__ groups, const ThrTask* __restrict__ tasks, uint32_t bpt,
             const uint32_t* __restrict__ list) {
-  const uint32_t gi = blockIdx.x / bpt, b = blockIdx.x % bpt;
+  uint32_t gi = blockIdx.x / bpt, b = blockIdx.x % bpt;
+  if (VIEW) {
+    const ViewBlock v = view_block(blockIdx.x, gridDim.x / bpt, bpt, (kb.view[1] + 31) / 32);
+    gi = v.item, b = v.b;
+  }
   const ThrGroup G = groups[gi];
   const float* col = kb.data + (size_t)G.prop * kb.N;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -1121,8 +1125,17 @@ DevKB dev_view(const hth_kb_s& kb) {
   return d;
 }
 
-// words of the example view as counted at load (its kernels' grids)
+// words of the example view as counted at load: its kernels' grids are sized for
+// them, and for view_fill blocks at least
 inline uint32_t view_words_hint(const hth_kb_s& kb) { return (kb.ex_hint + 63) / 64 + 1; }
+
+// Blocks for each of n items so that a launch over the view fills the chip
+// however many examples there are by then (the rows may be other ones than at
+// load, or rewritten; a block beyond the view's words leaves at once).  Loaded
+// with one example and given 25,000 of 400,000 individuals, 64 hypotheses took
+// 1,076 us with grids by the count at load, 106 with these, 106 loaded
+// with all of them.
+inline uint32_t view_fill(const hth_kb_s& kb, uint64_t n) { return (uint32_t)((4 * (uint64_t)kb.n_cu + n - 1) / n); }
 
 // Kernel launches, each optionally bracketed by timing events.
 struct Launcher {
@@ -1250,8 +1263,8 @@ hth_status launch_regions_n(Launcher& L, const DevKB& d, const RegionTask* tasks
                             uint32_t n, int depth, double bytes) {
   if (!n) return HTH_OK;
   // the register kernel when every program's stack fits its shift register
-  // (the view: as many words as the load's examples fill; the kernels cover
-  // however many there are)
+  // (the view: as many words as the load's examples fill, and blocks for the
+  // whole chip; the kernels cover however many there are)
   const uint32_t S = d.view ? std::min(d.S, view_words_hint(L.kb)) : d.S;
   if (depth <= kRegDepth && L.kb.tune.region_reg) {
     const uint32_t rw = L.kb.tune.region_reg;     // words per lane: 1, 2 or 4
@@ -1260,7 +1273,8 @@ hth_status launch_regions_n(Launcher& L, const DevKB& d, const RegionTask* tasks
     // the launch would otherwise have under kRegionMinBlocks blocks
     const uint64_t per = std::max<uint64_t>(1, (uint64_t)n * tiles / kRegionMinBlocks);
     const uint32_t tpb = (uint32_t)std::min<uint64_t>(std::min<uint64_t>(tiles, kRegionTilesPerBlock), per);
-    const uint32_t runs = (tiles + tpb - 1) / tpb;
+    const uint32_t most = (d.S + 256 * rw - 1) / (256 * rw);
+    const uint32_t runs = std::max((tiles + tpb - 1) / tpb, d.view ? std::min(most, view_fill(L.kb, n)) : 0u);
     return split_launch(L, HTH_K_REGION, bytes, n, runs, 256, [&](uint32_t t0, uint32_t m, uint32_t blocks) {
       const dim3 grid(blocks), block(256);
       if (rw == 1)
@@ -1271,7 +1285,8 @@ hth_status launch_regions_n(Launcher& L, const DevKB& d, const RegionTask* tasks
         hipLaunchKernelGGL((k_region_reg<kRegDepth, 4>), grid, block, 0, L.st, d, tasks + t0, code, m, tiles, tpb, runs);
     });
   }
-  const uint32_t tiles = (S + kRegionThreads - 1) / kRegionThreads;
+  const uint32_t most = (d.S + kRegionThreads - 1) / kRegionThreads;
+  const uint32_t tiles = std::max((S + kRegionThreads - 1) / kRegionThreads, d.view ? std::min(most, view_fill(L.kb, n)) : 0u);
   return split_launch(L, HTH_K_REGION, bytes, n, tiles, kRegionThreads, [&](uint32_t t0, uint32_t m, uint32_t blocks) {
     hipLaunchKernelGGL(k_region, dim3(blocks), dim3(kRegionThreads), 0, L.st, d, tasks + t0, code, m, tiles);
   });
@@ -1359,14 +1374,16 @@ hth_status launch_group_chunk(Launcher& L, const DevKB& d, const GroupTask* grou
     if (s) return s;
   }
   const uint32_t* xslots = c.rounds ? xslots_all + c.slot_off : nullptr;
-  const uint32_t W = vd ? std::min(kb.W, view_words_hint(kb)) : kb.W;
+  const uint32_t most_b = (kb.W + 3) / 4;       // blocks that have a word each, at most
   uint32_t bpg, nblocks;
   if (xslots) {
-    bpg = std::min<uint32_t>(std::max<uint32_t>(1, kb.n_cu / 8 * 8), (W + 3) / 4);
+    bpg = std::min<uint32_t>(std::max<uint32_t>(1, kb.n_cu / 8 * 8), most_b);
+    if (vd) bpg = std::min(bpg, std::max((view_words_hint(kb) + 3) / 4, view_fill(kb, 8ull * c.rounds)));
     nblocks = 8 * bpg * c.rounds;
   } else {
     bpg = std::max<uint32_t>(1, (8 * kb.n_cu + n - 1) / n);
-    bpg = std::min<uint32_t>(bpg, (W + 3) / 4);
+    if (vd) bpg = std::min(bpg, std::max((view_words_hint(kb) + 3) / 4, view_fill(kb, n)));
+    bpg = std::min<uint32_t>(bpg, most_b);
     nblocks = bpg * n;
   }
   const DevKB& pd = vd ? *vd : d;

@@ -308,6 +308,30 @@ struct SegPass {
   size_t stride;   // TW elements per group
 };
 
+// The group g of this block and its number b among the group's bpg blocks;
+// false: nothing is this block's.  With xslots every block of a group is kept
+// on one XCD, so that its L2 serves that group's T rows (workgroups are dealt
+// to the 8 XCDs round robin; xslots lists each XCD's groups round by round,
+// balanced on the host).  words: those of one wave's iteration.  wave: number
+// of wave wv among the group's; a block's waves take neighbouring words, or,
+// where the view leaves blocks idle, the blocks' first waves come first.
+__device__ __forceinline__ bool group_block(const DevKB& kb, uint32_t bpg, const uint32_t* __restrict__ xslots,
+                                            uint32_t words, uint32_t wv, uint32_t& g, uint32_t& b, uint32_t& wave) {
+  const uint32_t nw = blockDim.x >> 6, x = blockIdx.x & 7, j = xslots ? blockIdx.x >> 3 : blockIdx.x;
+  bool turns = false;
+  if (kb.view) {
+    const uint32_t W = span_w(kb);
+    const ViewBlock v = view_block(j, (xslots ? gridDim.x >> 3 : gridDim.x) / bpg, bpg, (W + nw * words - 1) / (nw * words));
+    g = v.item, b = v.b, turns = v.turns;
+    if (b * (turns ? 1u : nw) * words >= W) return false;
+  } else {
+    g = j / bpg, b = j % bpg;
+  }
+  wave = turns ? wv * bpg + b : b * nw + wv;
+  if (xslots) g = xslots[g * 8 + x];
+  return g != kNone;
+}
+
 // One wave per MW consecutive entries of the direction's non-empty word list
 // (64 MW subjects: one word of every member's output row per entry), all
 // members of the group at once.  Words between two list entries hold no
@@ -334,19 +358,9 @@ k_group(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember* __res
   constexpr int R = 64 * MW;          // subjects per iteration
   __shared__ uint32_t s_ro[4][R + 1];
   __shared__ TW s_pl[4][4][R];        // counters of the rows finished in this iteration
-  uint32_t g, b;
-  if (xslots) {
-    // workgroups are dealt to the 8 XCDs round robin: keep every block of a
-    // group on one XCD so that its L2 serves that group's T rows.  xslots
-    // lists each XCD's groups round by round (balanced on the host).
-    const uint32_t x = blockIdx.x & 7, j = blockIdx.x >> 3;
-    g = xslots[(j / bpg) * 8 + x];
-    b = j % bpg;
-    if (g == kNone) return;
-  } else {
-    g = blockIdx.x / bpg;
-    b = blockIdx.x % bpg;
-  }
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t g, b, wave;
+  if (!group_block(kb, bpg, xslots, MW, wv, g, b, wave)) return;
   const GroupTask* G = groups + g;
   const uint32_t k = G->k;
   TW* part = sp.first && sp.last ? nullptr : sp.part + (size_t)g * sp.stride;
@@ -357,7 +371,6 @@ k_group(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember* __res
   // a compact group reads each assertion's object rank instead of its object
   const int32_t* tg = (G->compact ? (G->inv ? kb.ctg_inv : kb.ctg_fwd) : (G->inv ? kb.inv_tg : kb.fwd_tg)) +
                       kb.role_base[G->role];
-  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t* ro = s_ro[wv];
   TW (*pl)[R] = s_pl[wv];
   TW acc[kGroupMaxCount + 1];
@@ -376,7 +389,7 @@ k_group(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember* __res
   const uint32_t* words = kb.view ? kb.words : kb.words + (size_t)(2 * G->role + G->inv) * kb.W;
   const uint32_t n_words = kb.view ? span_w(kb) : G->n_words;
   if (!n_words) {
-    if (sp.last) cover_finish(cv, kb, b * nw + wv, bpg * nw, lane);
+    if (sp.last) cover_finish(cv, kb, wave, bpg * nw, lane);
     return;
   }
   const uint32_t n_iter = (n_words + MW - 1) / MW;
@@ -428,7 +441,7 @@ k_group(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember* __res
       v[u] = (e0 + u < se && (uint32_t)t[u] - sp.lo < seg_n) ? T[(uint32_t)t[u]] : (TW)0;
   };
 
-  uint32_t it = b * nw + wv;
+  uint32_t it = wave;
   Rows rw, rn;
   fetch(it, rw);
   fetch(it + istep, rn);
@@ -634,7 +647,7 @@ k_group(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember* __res
     s = ns;
     se = nse;
   }
-  if (sp.last) cover_finish(cv, kb, b * nw + wv, bpg * nw, lane);
+  if (sp.last) cover_finish(cv, kb, wave, bpg * nw, lane);
 }
 
 // A shared pass over a role direction whose rows are all short (at most the
@@ -677,16 +690,9 @@ k_group_short(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember*
   static_assert(SW * 8 <= 128 && 64 % LPM == 0, "a member's words of one iteration lie in one 128-byte line");
   __shared__ uint64_t s_out[4][64][SW + 1];   // + 1 word: rows fall on different banks
   __shared__ uint64_t* s_dst[64];
-  uint32_t g, b;
-  if (xslots) {
-    const uint32_t x = blockIdx.x & 7, j = blockIdx.x >> 3;
-    g = xslots[(j / bpg) * 8 + x];
-    b = j % bpg;
-    if (g == kNone) return;
-  } else {
-    g = blockIdx.x / bpg;
-    b = blockIdx.x % bpg;
-  }
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t g, b, wave;
+  if (!group_block(kb, bpg, xslots, SW, wv, g, b, wave)) return;
   const GroupTask* G = groups + g;
   const uint32_t k = G->k;
   const TW* T = tarea + G->t_off;
@@ -698,7 +704,6 @@ k_group_short(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember*
   constexpr int PK = sizeof(C) / sizeof(TW);   // words per container
   constexpr int NC = MW / PK;
   static_assert(MW % PK == 0, "an iteration's words fill its containers");
-  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   C acc[kGroupMaxCount + 1];                   // in every word of a container
 #pragma unroll
   for (int v = 0; v <= (int)kGroupMaxCount; ++v) {
@@ -755,8 +760,8 @@ k_group_short(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember*
     }
   };
   Rows q, next;
-  if (b * nw + wv < n_super) fetch((b * nw + wv) * SUB, q);
-  for (uint32_t si = b * nw + wv; si < n_super; si += bpg * nw) {
+  if (wave < n_super) fetch(wave * SUB, q);
+  for (uint32_t si = wave; si < n_super; si += bpg * nw) {
     C narrow = 0;     // K = 8: the first iteration's predicates, transposed with the second's
 #pragma unroll
     for (int sub = 0; sub < SUB; ++sub) {
@@ -866,7 +871,7 @@ k_group_short(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember*
     }
   }
   flush();
-  cover_finish(cv, kb, b * nw + wv, bpg * nw, lane);
+  cover_finish(cv, kb, wave, bpg * nw, lane);
 }
 
 }  // namespace hth

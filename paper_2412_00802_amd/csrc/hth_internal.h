@@ -243,6 +243,21 @@ __device__ __forceinline__ uint64_t span_tail(const DevKB& kb) {
   return r ? (1ull << r) - 1ull : ~0ull;
 }
 
+// Block j of n items with `per` blocks each: its item and its number among the
+// item's.  An item's blocks follow one another, so that neighbours share what
+// they read, unless the view has work for less than half of them (busy) and the
+// items are few: then the items' first blocks come first, then their second
+// ones, or the busy ones meet on the same compute units (four shared passes of
+// 392 words over 256 blocks each 100 us one after the other, 14 in turns).
+struct ViewBlock {
+  uint32_t item, b;
+  bool turns;
+};
+__device__ __forceinline__ ViewBlock view_block(uint32_t j, uint32_t n, uint32_t per, uint32_t busy) {
+  if (n <= 8 && 2 * busy < per) return {j % n, j / n, true};
+  return {j / per, j % per, false};
+}
+
 // Row ids: [0, C) concepts, [C, C + n_sets) the set table, then workspace slots.
 __device__ __forceinline__ const uint64_t* row_ptr(const DevKB& kb, uint32_t id) {
   if (id < kb.n_concepts) return kb.concepts + (size_t)id * kb.S;

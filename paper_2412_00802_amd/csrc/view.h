@@ -13,9 +13,9 @@
 // The shared passes and region programs run on it unchanged: DevKB::view
 // points at {examples, words}, counted on the device, so nothing here depends
 // on what the host believes about the example rows (they are read at each
-// launch).  The host's count of the examples at load time (ex_hint) only
-// decides whether a plan uses the view, and its grid sizes; every area has
-// room for all individuals.
+// launch).  The host's count of the examples at load time (ex_hint) decides
+// whether a plan uses the view; its grids have blocks for that many examples
+// and for the whole chip, and every area has room for all individuals.
 // Included by exec.hip only.
 #pragma once
 
@@ -129,11 +129,12 @@ __device__ __forceinline__ const uint32_t* dir_offsets(const DevKB& kb, uint32_t
 }
 __global__ void __launch_bounds__(256)
 k_vdir_sum(DevKB kb, const ViewDir* __restrict__ dirs, const uint32_t* __restrict__ hdr,
-           const uint32_t* __restrict__ list, uint32_t tcap, uint32_t* __restrict__ tsum) {
+           const uint32_t* __restrict__ list, uint32_t per, uint32_t tcap, uint32_t* __restrict__ tsum) {
   __shared__ uint32_t s[4];
   const uint32_t m = hdr[0], tiles = (m + kVDirTile - 1) / kVDirTile;
-  const uint32_t* off = dir_offsets(kb, dirs[blockIdx.y].rd);
-  for (uint32_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+  const ViewBlock B = view_block(blockIdx.x, gridDim.x / per, per, tiles);
+  const uint32_t* off = dir_offsets(kb, dirs[B.item].rd);
+  for (uint32_t t = B.b; t < tiles; t += per) {
     uint32_t n = 0;
 #pragma unroll
     for (uint32_t i = 0; i < kVDirTile / 256; ++i) {
@@ -147,7 +148,7 @@ k_vdir_sum(DevKB kb, const ViewDir* __restrict__ dirs, const uint32_t* __restric
     __syncthreads();
     if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = n;
     __syncthreads();
-    if (threadIdx.x == 0) tsum[(size_t)blockIdx.y * tcap + t] = s[0] + s[1] + s[2] + s[3];
+    if (threadIdx.x == 0) tsum[(size_t)B.item * tcap + t] = s[0] + s[1] + s[2] + s[3];
   }
 }
 __global__ void __launch_bounds__(1024)
@@ -159,19 +160,20 @@ k_vdir_scan(const uint32_t* __restrict__ hdr, uint32_t tcap, uint32_t N, uint32_
 }
 __global__ void __launch_bounds__(256)
 k_vdir_copy(DevKB kb, const ViewDir* __restrict__ dirs, const uint32_t* __restrict__ hdr,
-            const uint32_t* __restrict__ list, uint32_t tcap, const uint32_t* __restrict__ tsum,
+            const uint32_t* __restrict__ list, uint32_t per, uint32_t tcap, const uint32_t* __restrict__ tsum,
             uint32_t* __restrict__ voff, int32_t* __restrict__ vtg) {
   constexpr uint32_t kSub = kVDirTile / 256;     // rounds of 64 rows a wave
   __shared__ uint32_t s[4], s_pre[4][64], s_lo[4][64];
   const uint32_t m = hdr[0], tiles = (m + kVDirTile - 1) / kVDirTile;
+  const ViewBlock B = view_block(blockIdx.x, gridDim.x / per, per, tiles);
   const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const ViewDir D = dirs[blockIdx.y];
+  const ViewDir D = dirs[B.item];
   const uint32_t* off = dir_offsets(kb, D.rd);
   const int32_t* tg = (D.compact ? (D.rd & 1 ? kb.ctg_inv : kb.ctg_fwd) : (D.rd & 1 ? kb.inv_tg : kb.fwd_tg)) +
                       kb.role_base[D.rd >> 1];
-  uint32_t* vo = voff + (size_t)blockIdx.y * (kb.N + 1);
+  uint32_t* vo = voff + (size_t)B.item * (kb.N + 1);
   int32_t* out = vtg + D.base;
-  for (uint32_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+  for (uint32_t t = B.b; t < tiles; t += per) {
     uint32_t lo[kSub], inc[kSub], tot[kSub], sum = 0;
 #pragma unroll
     for (uint32_t i = 0; i < kSub; ++i) {
@@ -192,7 +194,7 @@ k_vdir_copy(DevKB kb, const ViewDir* __restrict__ dirs, const uint32_t* __restri
     __syncthreads();
     if (lane == 0) s[wv] = sum;
     __syncthreads();
-    uint32_t at = tsum[(size_t)blockIdx.y * tcap + t];
+    uint32_t at = tsum[(size_t)B.item * tcap + t];
     for (uint32_t w = 0; w < wv; ++w) at += s[w];
 #pragma unroll
     for (uint32_t i = 0; i < kSub; ++i) {
@@ -230,8 +232,10 @@ k_view_rows(DevKB kb, uint64_t* __restrict__ vslots, const uint32_t* __restrict_
             const uint32_t* __restrict__ list, const ViewCopy* __restrict__ copies, uint32_t n_copies,
             uint32_t slot0) {
   const uint32_t m = hdr[0], vw = hdr[1];
-  const uint32_t lane = threadIdx.x & 63, c0 = blockIdx.y * kVRows, c1 = min(c0 + kVRows, n_copies);
-  for (uint32_t b = blockIdx.x * 4 + (threadIdx.x >> 6); b * 8 < vw; b += gridDim.x * 4) {
+  const uint32_t per = gridDim.x;
+  const ViewBlock B = view_block(blockIdx.y * per + blockIdx.x, gridDim.y, per, (vw + 31) / 32);
+  const uint32_t lane = threadIdx.x & 63, c0 = B.item * kVRows, c1 = min(c0 + kVRows, n_copies);
+  for (uint32_t b = B.b * 4 + (threadIdx.x >> 6); b * 8 < vw; b += per * 4) {
     uint32_t x[8];
     bool in[8];
 #pragma unroll
@@ -362,20 +366,22 @@ hth_status launch_view_rows(Launcher& L, const DevKB& d, const ViewPlan& V, char
   });
   if (s) return s;
   if (nd) {
-    // blocks for the examples expected; more of them are taken in turns
-    const uint32_t want = kb.ex_hint / kVDirTile + 1, gx = std::max(1u, std::min(want, 65536u / nd + 1));
+    // blocks for the examples expected, and for the whole chip; more examples are taken in turns
+    const uint32_t want = std::max(kb.ex_hint / kVDirTile + 1, std::min(tcap, view_fill(kb, nd)));
+    const uint32_t gx = std::max(1u, std::min(want, 65536u / nd + 1));
     s = L.run(HTH_K_GROUP, 0.0, [&] {
-      hipLaunchKernelGGL(k_vdir_sum, dim3(gx, nd), dim3(256), 0, L.st, d, dirs, hdr, list, tcap, dsum);
+      hipLaunchKernelGGL(k_vdir_sum, dim3(gx * nd), dim3(256), 0, L.st, d, dirs, hdr, list, gx, tcap, dsum);
       hipLaunchKernelGGL(k_vdir_scan, dim3(nd), dim3(1024), 0, L.st, hdr, tcap, kb.N, dsum, voff);
-      hipLaunchKernelGGL(k_vdir_copy, dim3(gx, nd), dim3(256), 0, L.st, d, dirs, hdr, list, tcap, dsum, voff, vtg);
+      hipLaunchKernelGGL(k_vdir_copy, dim3(gx * nd), dim3(256), 0, L.st, d, dirs, hdr, list, gx, tcap, dsum, voff, vtg);
     });
     if (s) return s;
   }
-  const uint32_t gx = std::max(1u, std::min((view_words_hint(kb) + 31) / 32, 16384u));
   for (uint32_t c = 0; c < V.n_copies; c += 65535 * kVRows) {
-    const uint32_t n = std::min(V.n_copies - c, 65535 * kVRows);
+    const uint32_t n = std::min(V.n_copies - c, 65535 * kVRows), gy = (n + kVRows - 1) / kVRows;
+    const uint32_t fill = std::min((kb.W + 31) / 32, view_fill(kb, gy));
+    const uint32_t gx = std::max(fill, std::min((view_words_hint(kb) + 31) / 32, 16384u));
     s = L.run(HTH_K_REGION, (double)n * kb.W * 8, [&] {
-      hipLaunchKernelGGL(k_view_rows, dim3(gx, (n + kVRows - 1) / kVRows), dim3(256), 0, L.st, d, slots, hdr, list,
+      hipLaunchKernelGGL(k_view_rows, dim3(gx, gy), dim3(256), 0, L.st, d, slots, hdr, list,
                          copies + c, n, slot0);
     });
     if (s) return s;
@@ -397,7 +403,7 @@ hth_status launch_view(Launcher& L, const DevKB& full, const ViewPlan& V, char* 
   const DevKB x = view_kb(f, V, ws, bases);
   if (V.n_thg) {
     const uint32_t* list = reinterpret_cast<const uint32_t*>(ws + V.o_list);
-    const uint32_t bpt = std::max<uint32_t>(1, (view_words_hint(kb) + 31) / 32);
+    const uint32_t bpt = std::max((view_words_hint(kb) + 31) / 32, std::min((kb.W + 31) / 32, view_fill(kb, V.n_thg)));
     s = split_launch(L, HTH_K_THRESHOLD, 4.0 * kb.ex_hint * V.n_thg, V.n_thg, bpt, 256,
                      [&](uint32_t i0, uint32_t, uint32_t blocks) {
                        hipLaunchKernelGGL(k_threshold<true>, dim3(blocks), dim3(256), 0, L.st, x, thg + i0, thr, bpt, list);
