@@ -613,25 +613,28 @@ __global__ void __launch_bounds__(64 * kScoreWaves) k_score_rows(ScoreArgs S) {
     if (i < n1[j] + n2[j]) return (S.pfeat[pb[j] + i - n1[j]] & (kFeatDim - 1)) | 0x80000000u;
     return (S.pfeat[pb[j] + i - n1[j] - n2[j]] & (kFeatDim - 1)) ^ (kFeatDim / 2);
   };
-  // the net counts of entries c0 .. c0 + 63 (mine: this lane's), each feature at
-  // its first entry of the row, as (feature, bf16 count); -> how many
-  auto merge = [&](int j, uint32_t c0, uint32_t mine) -> int {
-    const uint32_t f = mine & 0xFFFFu;
-    int net = 0;
-    bool first = c0 + lane < total[j];
-    for (uint32_t i = 0; i < total[j]; ++i) {
-      const uint32_t e = i - c0 < 64u ? (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)(i - c0)) : entry(j, i);
-      const bool same = (e & 0xFFFFu) == f;
-      net += same ? (int)(1 - 2 * (e >> 31)) : 0;
-      first = first && !(same && i < c0 + lane);
-    }
-    const bool keep = first && net != 0;
+  // the lanes' net counts of their features f as (feature, bf16 count) in the row's list; -> how many
+  auto list = [&](int j, bool keep, uint32_t f, int net) -> int {
+    keep = keep && net != 0;
     const uint64_t m = __ballot(keep);
     if (keep)
       s_list[wv][j][__popcll(m & ((1ull << lane) - 1))] =
           f | (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)(float)net) << 16;
     __builtin_amdgcn_wave_barrier();
     return __popcll(m);
+  };
+  // a row of at most 64 entries (mine: this lane's): each feature at its first entry
+  auto merge = [&](int j, uint32_t mine) -> int {
+    const uint32_t f = mine & 0xFFFFu;
+    int net = 0;
+    bool first = (uint32_t)lane < total[j];
+    for (uint32_t i = 0; i < total[j]; ++i) {
+      const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)i);
+      const bool same = (e & 0xFFFFu) == f;
+      net += same ? (int)(1 - 2 * (e >> 31)) : 0;
+      first = first && !(same && i < (uint32_t)lane);
+    }
+    return list(j, first, f, net);
   };
   auto add_rows = [&](int j, int n, float (&acc)[16]) {
     for (int i = 0; i < n; i += 4) {
@@ -660,6 +663,32 @@ __global__ void __launch_bounds__(64 * kScoreWaves) k_score_rows(ScoreArgs S) {
     }
     __builtin_amdgcn_wave_barrier();
   };
+  // a longer row: counted feature range by range in the LDS that its h1 takes
+  // afterwards, work per entry and not per pair of entries (65,536 rows of 256
+  // features 1.7 ms, of 512 entries that mostly cancel 0.54; with every entry
+  // compared with every other 5.6 and 11.9)
+  auto add_long_row = [&](int j, float (&acc)[16]) {
+    constexpr uint32_t kRange = kScoreH1 * sizeof(__bf16) / sizeof(int32_t);
+    typedef int32_t __attribute__((may_alias)) Count;
+    Count* cnt = reinterpret_cast<Count*>(&t[4 * wv + j][0]);
+    auto sync = [] {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    for (uint32_t f0 = 0; f0 < kFeatDim; f0 += kRange) {
+      for (uint32_t i = lane; i < kRange; i += 64) cnt[i] = 0;
+      sync();
+#pragma unroll 4
+      for (uint32_t i = lane; i < total[j]; i += 64) {
+        const uint32_t e = entry(j, i), d = (e & 0xFFFFu) - f0;
+        if (d < kRange) __hip_atomic_fetch_add(cnt + d, (int32_t)(1 - 2 * (e >> 31)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+      }
+      sync();
+      for (uint32_t k = lane; k < kRange; k += 64) add_rows(j, list(j, true, f0 + k, cnt[k]), acc);
+      sync();
+    }
+  };
   float b1[16];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
@@ -672,18 +701,18 @@ __global__ void __launch_bounds__(64 * kScoreWaves) k_score_rows(ScoreArgs S) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) mine[j] = (uint32_t)lane < total[j] ? entry(j, lane) : 0xFFFFu;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) n[j] = merge(j, 0, mine[j]);
+    for (int j = 0; j < 4; ++j) n[j] = merge(j, mine[j]);
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     float acc[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-    if (most <= 64) {
-      add_rows(j, n[j], acc);
+    if (total[j] > 64) {
+      add_long_row(j, acc);
     } else {
-      for (uint32_t c0 = 0; c0 < total[j]; c0 += 64)
-        add_rows(j, merge(j, c0, c0 + lane < total[j] ? entry(j, c0 + lane) : 0xFFFFu), acc);
+      if (most > 64) n[j] = merge(j, (uint32_t)lane < total[j] ? entry(j, lane) : 0xFFFFu);
+      add_rows(j, n[j], acc);
     }
     bf16x8 h[2];
 #pragma unroll

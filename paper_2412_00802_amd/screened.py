@@ -87,12 +87,39 @@ def train(scr: Screener, fb: FeatureBatch, y_dev, n: int, epochs: int, batch: in
     return losses
 
 
+# Scoring by feature lists reads a row of W1 (2 KB) for each feature and the
+# list once per range of features; the dense chain's time does not depend on
+# them.  Microseconds of the lists / of the dense chain, 8,192 rows: 63 features
+# 110 / 139, 80 160 / 139; 65,536 rows: 80 789 / 1,145, 128 1,060 / 1,152, 256
+# 1,722 / 1,163; relative to the parents with three changed subtrees, 8,192
+# rows: 258 entries 95 / 139, 514 126 / 140, 2,002 303 / 146.
+LIST_FEATURES, LIST_ENTRIES = 96, 512
+
+
+def _wide(fb: FeatureBatch, parents: FeatureBatch = None, context: int = 0) -> bool:
+    """Rows with so many features on average that the dense chain is faster."""
+    own = fb.n_nodes / max(1, fb.n_hyps)
+    if parents is None:
+        return own > LIST_FEATURES
+    par = parents.n_nodes / max(1, parents.n_hyps)
+    return (context and par > LIST_FEATURES) or own + par * (2 if context else 1) > LIST_ENTRIES
+
+
 def score(scr: Screener, fb: FeatureBatch, n: int, n_pos: int, n_neg: int, out, base=None,
           parents: FeatureBatch = None, parent_index=None, kind: int = 0, context: int = 0) -> None:
     """Predicted F1 of candidates [0, n); base (device uint32 [n][2]): the
     parents' coverage (kept shares, kind 0, or removed counts, kind 1);
     parents: features relative to the parents."""
     rel = parents is not None
+    if _wide(fb, parents, context):
+        B = scr.batch
+        for r0 in range(0, n, B):
+            m = min(B, n - r0)
+            fb.densify(r0, m, scr.x, parents, parent_index, context)
+            z = scr.logits(m)
+            hthedl.hth_head_score(z, m, float(n_pos), float(n_neg), out[r0:r0 + m],
+                                  base=None if base is None else base[r0:r0 + m], kind=kind)
+        return
     hthedl.hth_score_rows(fb.feat, fb.offsets, 0, n, parents.feat if rel else None, parents.offsets if rel else None,
                           parent_index if rel else None, scr.w1b, scr.p["b1"], scr.w2t, scr.p["b2"], scr.p["w3"],
                           scr.p["b3"], float(n_pos), float(n_neg), out, scr.score_scratch, base=base, kind=kind,

@@ -122,7 +122,7 @@ class FeatureBatch:
         import torch
         t = torch
         self.n_hyps = int(offsets.shape[0] - 1)
-        n_nodes = int(nodes.shape[0])
+        self.n_nodes = n_nodes = int(nodes.shape[0])
         self.nodes = t.from_numpy(nodes.view(np.uint8).copy()).to(device)
         self.offsets = t.from_numpy(offsets.astype(np.int32)).to(device)
         self.children = t.from_numpy(children.astype(np.int32) if children.size else np.zeros(1, np.int32)).to(device)
