@@ -95,7 +95,7 @@ class Screener:
         (device float32 [n][2]).  The summed loss accumulates in self.loss."""
         x = self.x if x is None else x
         names = ("w1", "b1", "w2", "b2", "w3", "b3")
-        t = hthedl.Train(n=n, d_in=D_IN, d_h1=D_H1, d_h2=D_H2, x=x.data_ptr(), y=None if y is None else y.data_ptr(),
+        t = hthedl.Train(n=n, d_in=D_IN, d_h1=D_H1, d_h2=D_H2, x=hthedl._ptr(x), y=hthedl._ptr(y),
                          loss_kind=self.loss_kind, step=self.step_no + 1, lr=self.lr, beta1=self.b1, beta2=self.b2,
                          eps=self.eps, wd=self.wd)
         for f in ("p", "g", "m", "v"):
