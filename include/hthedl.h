@@ -361,7 +361,9 @@ hth_status hth_cache_destroy(hth_cache cache);
  * as hth_eval_batch does (same arguments, host arrays) and reports the
  * workspace it needs; the plan keeps the kb's schedule and set table as they
  * were at creation.  hth_plan_upload copies the plan's tables into a workspace
- * (once per workspace); hth_plan_launch then runs the plan's kernels on
+ * (once per workspace; a plan that evaluates part of the batch at the examples
+ * only gives a workspace short of that but with room for every row in full
+ * tables of that form); hth_plan_launch then runs the plan's kernels on
  * `stream` with no copy, no allocation and no memset (the counts are cleared
  * by a kernel), so a caller may capture it in a HIP graph and replay it.  The
  * KB's rows (concepts, data, examples, set rows) are read at each launch.
@@ -405,7 +407,11 @@ hth_status hth_plan_destroy(hth_plan plan);
  * plan's last launch.
  * hth_dplan_launch writes the plan's tables into ws on the device and runs
  * every kernel of the evaluation on `stream`, without waiting; d_counts
- * [n_hyps][2] as hth_eval_batch.  Launches of one plan must not overlap;
+ * [n_hyps][2] as hth_eval_batch.  Where the plan evaluates part of the batch at
+ * the examples only and ws is short of that but has room for every row in
+ * full, the launch first waits for the plan's last launch and lays the plan out
+ * in that form for good (HTH_E_NOMEM once a launch of it has been captured).
+ * Launches of one plan must not overlap;
  * hth_dplan_destroy waits for the plan's last launch (the caller may then
  * free or reuse the scratch).
  * Errors (create): as hth_eval_batch, with the first failing hypothesis and

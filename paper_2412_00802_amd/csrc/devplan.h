@@ -87,7 +87,7 @@ struct DpKB {                    // what the passes read of the knowledge base
   const uint32_t* dir;           // [3][2R+1]: non-empty words, first heavy chunk, first heavy row
   uint32_t* pk;                  // [n_data] distinct thresholds per property (count pass)
   unsigned long long* tkey;      // threshold table (and the fixed rows the view reads): keys (kDpEmpty = free) ...
-  uint32_t* tval;                // ... and per entry: index within its property's full and view tasks
+  uint32_t* tval;                // ... and per entry: index within its property's full and view tasks (a fixed row: claimed)
   uint32_t* tvrow;               // ... and its view row
   uint32_t tmask;                // entries - 1 (a power of two above twice the nodes)
   uint32_t n_thr;                // full thresholds (emit pass): their rows come first
@@ -602,8 +602,9 @@ k_dp_tally(const hth_node* __restrict__ nodes, const uint32_t* __restrict__ offs
     for (uint32_t hs = dp_hash(key, K.tmask);; hs = (hs + 1) & K.tmask) {
       unsigned long long prev = __hip_atomic_load(K.tkey + hs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (prev == kDpEmpty) prev = atomicCAS(K.tkey + hs, kDpEmpty, key);
-      if (prev == kDpEmpty) K.tvrow[hs] = copy(x.op == HTH_ATOM ? x.arg : K.n_concepts + x.arg);
-      if (prev == kDpEmpty || prev == key) break;
+      if (prev != kDpEmpty && prev != key) continue;
+      if (dp_claim(K.tval + 2 * hs)) K.tvrow[hs] = copy(x.op == HTH_ATOM ? x.arg : K.n_concepts + x.arg);
+      break;
     }
   } else if (dp_column(x.op)) {
     const uint32_t hs = dp_slot(K, dp_thr_key(x));
@@ -975,6 +976,23 @@ k_dp_init(uint4* __restrict__ zero, size_t zeros, uint4* __restrict__ one, size_
   }
 }
 
+// What the tally pass counts, back to its state after the count pass: the
+// counts per bucket and property (`words` words from bk), the thresholds'
+// indices, the rows numbered after the fillers' (mats of them).
+__global__ void __launch_bounds__(256)
+k_dp_recount(uint32_t* __restrict__ bk, size_t words, uint32_t* __restrict__ tval, size_t tvals,
+             DpSummary* __restrict__ sum, uint32_t mats) {
+  const size_t i0 = (size_t)blockIdx.x * 256 + threadIdx.x, step = (size_t)gridDim.x * 256;
+  for (size_t i = i0; i < words; i += step) bk[i] = 0;
+  for (size_t i = i0; i < tvals; i += step) tval[i] = kNone;
+  if (i0 == 0) {
+    sum->n_vrows = kViewFixed;
+    sum->n_copies = 2;
+    sum->n_thr_full = sum->n_thr_view = 0;
+    sum->n_slots = mats;
+  }
+}
+
 }  // namespace
 }  // namespace hth
 
@@ -1020,6 +1038,7 @@ struct hth_dplan_s {
          o_grp = 0, o_mem = 0, o_tarea = 0, o_gpart = 0, o_slot = 0, need = 0;
   hth_kb_s::Tuning tune;              // the schedule the plan was laid out for
   hipEvent_t done = nullptr;          // recorded after each launch: destroy waits for it
+  bool captured = false;              // a graph holds launches of this layout
   ~hth_dplan_s() {
     if (done) {
       (void)hipEventSynchronize(done);
@@ -1228,9 +1247,116 @@ hth_status dp_schedule(hth_dplan_s& p, const std::vector<uint32_t>& bk, std::vec
   p.o_tarea = area(t_bytes);
   p.o_gpart = area(gpart);
   p.o_slot = area(((size_t)S.n_slots + S.n_thr_full + 1) * kb.S * 8);
+  const size_t rest = at;
   V.layout(kb, area);
+  V.bytes = at - rest;
   p.need = at;
   return HTH_OK;
+}
+
+// From the counted plan (k_dp_count has run on st) to one that can be
+// launched: the tally pass, its counts read back, the host's part and its
+// tables.  Waits for st.
+hth_status dp_layout(hth_dplan_s& p, hipStream_t st) {
+  const hth_kb_s& kb = *p.kb;
+  const DpScratch L = dp_scratch(kb, p.n_nodes);
+  const size_t nd_data = kb.d.n_data;
+  if (p.n_nodes)
+    hipLaunchKernelGGL(k_dp_tally, dim3((p.n_nodes + 255) / 256), dim3(256), 0, st, p.nodes, p.offs, p.n_hyps, p.K, p.info,
+                       p.d_sum, p.d_bk);
+  HTH_HIP(hipGetLastError());
+  // the summary and the counts, in one read
+  std::vector<char> back(L.ruse - L.sum);
+  HTH_HIP(hipMemcpyAsync(back.data(), p.d_sum, back.size(), hipMemcpyDeviceToHost, st));
+  HTH_HIP(hipStreamSynchronize(st));
+  std::memcpy(&p.sum, back.data(), sizeof(DpSummary));
+  std::vector<uint32_t> bk((2 * (size_t)kDpLevels + 1) * (p.K.n_dir - 1)), pk(nd_data), pkv(nd_data);
+  std::memcpy(bk.data(), back.data() + (L.bk - L.sum), bk.size() * 4);
+  if (nd_data) {
+    std::memcpy(pk.data(), back.data() + (L.pk - L.sum), nd_data * 4);
+    std::memcpy(pkv.data(), back.data() + (L.pkv - L.sum), nd_data * 4);
+  }
+  const DpSummary& S = p.sum;
+  if (S.err != ~0ull) {
+    hth_status code;
+    const char* why = dp_reason((uint32_t)(S.err & 255), &code);
+    return fail(code, "hypothesis " + std::to_string(S.err >> 32) + " node " +
+                          std::to_string((S.err >> 8) & 0xFFFFFF) + ": " + why);
+  }
+  if (S.code >= (1ull << 32)) return fail(HTH_E_RANGE, "region programs exceed 2^32 instructions");
+  // row ids must fit the 27-bit argument of the region bytecode
+  if ((uint64_t)p.K.n_fixed + 1 + S.n_thr + S.n_slots >= (1ull << 27) || S.n_vrows >= (1u << 27)) return fail(HTH_E_RANGE, "too many bit rows");
+  std::vector<DpBucket> buckets;
+  std::vector<uint32_t> xslots;
+  hth_status s = dp_schedule(p, bk, buckets, xslots);
+  if (s) return s;
+  const ViewPlan& V = p.V;
+  std::vector<GroupTask> shells;
+  for (const auto& lg : p.lv_groups) shells.insert(shells.end(), lg.begin(), lg.end());
+  shells.insert(shells.end(), V.passes.begin(), V.passes.end());
+  // thresholds: each property's tasks together, in groups of at most kThrPerPass
+  std::vector<uint32_t> pbase(nd_data), vpbase(nd_data);
+  std::vector<ThrGroup> thg;
+  auto thr_groups = [&](const std::vector<uint32_t>& count, std::vector<uint32_t>& base) {
+    uint32_t sum = 0;
+    for (uint32_t q = 0; q < nd_data; ++q) {
+      base[q] = sum;
+      for (uint32_t i = 0; i < count[q]; i += kThrPerPass)
+        thg.push_back(ThrGroup{q, sum + i, std::min<uint32_t>(kThrPerPass, count[q] - i), 0});
+      sum += count[q];
+    }
+    return sum;
+  };
+  const uint32_t tsum = thr_groups(pk, pbase);
+  p.n_thg = (uint32_t)thg.size();
+  const uint32_t vsum = thr_groups(pkv, vpbase);
+  p.V.n_thg = (uint32_t)thg.size() - p.n_thg;
+  if (tsum != S.n_thr_full || vsum != S.n_thr_view) return fail(HTH_E_DEVICE, "threshold counts disagree");
+  p.K.n_thr = S.n_thr_full;
+  if (S.n_copies > p.n_nodes + 2ull) return fail(HTH_E_DEVICE, "plan tables beyond their bounds");
+  // the host's tables in one copy
+  std::vector<uint64_t> vbases;
+  for (const ViewDir& v : V.dirs) vbases.push_back(v.base);
+  Blob tb;
+  const size_t o_shell = tb.add(shells), o_bucket = tb.add(buckets), o_xslot = tb.add(xslots), o_thg = tb.add(thg),
+               o_pbase = tb.add(pbase), o_vpbase = tb.add(vpbase), o_vgroup = tb.add(V.groups), o_vdir = tb.add(V.dirs),
+               o_vbase = tb.add(vbases);
+  if (tb.bytes.size() > L.tables_bytes) return fail(HTH_E_DEVICE, "plan tables beyond their bounds");
+  char* const dt = p.buf + L.tables;
+  p.d_shells = reinterpret_cast<GroupTask*>(dt + o_shell);
+  p.d_buckets = reinterpret_cast<DpBucket*>(dt + o_bucket);
+  p.n_buckets = (uint32_t)buckets.size();
+  p.d_xslots = reinterpret_cast<uint32_t*>(dt + o_xslot);
+  p.d_thg = reinterpret_cast<ThrGroup*>(dt + o_thg);
+  p.d_pbase = reinterpret_cast<uint32_t*>(dt + o_pbase);
+  p.d_vpbase = reinterpret_cast<uint32_t*>(dt + o_vpbase);
+  p.d_vgroups = reinterpret_cast<GroupTask*>(dt + o_vgroup);
+  p.d_vdirs = reinterpret_cast<ViewDir*>(dt + o_vdir);
+  p.d_vbases = reinterpret_cast<uint64_t*>(dt + o_vbase);
+  if (!tb.bytes.empty())
+    HTH_HIP(hipMemcpyAsync(dt, tb.bytes.data(), tb.bytes.size(), hipMemcpyHostToDevice, st));
+  HTH_HIP(hipStreamSynchronize(st));   // a launch may come from another stream
+  return HTH_OK;
+}
+
+// A counted plan laid out anew, with or without the example view.  Its
+// launches must have ended.
+hth_status dp_relayout(hth_dplan_s& p, bool view, hipStream_t st) {
+  const DpScratch L = dp_scratch(*p.kb, p.n_nodes);
+  const uint32_t mats = p.n_mat;
+  const size_t words = (L.ruse - L.bk) / 4, tvals = 2 * (size_t)L.tcap;
+  hipLaunchKernelGGL(k_dp_recount, dim3((unsigned)std::min<size_t>((words + tvals + 255) / 256, 4096)), dim3(256), 0, st,
+                     p.d_bk, words, p.K.tval, tvals, p.d_sum, mats);
+  HTH_HIP(hipGetLastError());
+  p.V = ViewPlan();
+  p.V.on = view;
+  p.K.view = view;
+  p.K.n_thr = 0;
+  p.B = DpBases{};
+  p.n_mat = p.n_role = p.n_groups = p.n_members = 0;
+  p.max_nhb = 0;
+  for (uint32_t L2 = 0; L2 < kDpLevels; ++L2) p.fills[L2] = 0, p.nhb[L2] = p.nhc[L2] = 0;
+  return dp_layout(p, st);
 }
 
 }  // namespace
@@ -1278,10 +1404,8 @@ extern "C" hth_status hth_dplan_create(hth_kb kb, const hth_node* d_nodes, uint3
   p->K.W = kb->W;
   p->K.n_fixed = kb->d.n_concepts + kb->n_sets;
   p->K.n_dir = nd;
-  const size_t nbk2 = 2 * (size_t)kDpLevels * (nd - 1) + (nd - 1);
   p->V.on = view_wanted(*kb);
   p->K.view = p->V.on;
-  const size_t nd_data = kb->d.n_data;
   const DpScratch L = dp_scratch(*kb, n_nodes);
   if (scratch_bytes < L.total)
     return fail(HTH_E_NOMEM, "scratch too small: need " + std::to_string(L.total) + " bytes, have " +
@@ -1321,81 +1445,10 @@ extern "C" hth_status hth_dplan_create(hth_kb kb, const hth_node* d_nodes, uint3
                      p->K.copies);
   hipLaunchKernelGGL(k_dp_count, dim3((n_hyps + kDpHyps - 1) / kDpHyps), dim3(kDpBlock), 0, st, d_nodes,
                      d_hyp_node_offsets, d_children, n_nodes, n_children, n_hyps, p->K, p->info, p->len, p->d_sum);
-  if (n_nodes)
-    hipLaunchKernelGGL(k_dp_tally, dim3((n_nodes + 255) / 256), dim3(256), 0, st, d_nodes, d_hyp_node_offsets, n_hyps,
-                       p->K, p->info, p->d_sum, p->d_bk);
   HTH_HIP(hipGetLastError());
-  // the summary and the counts, in one read
-  std::vector<char> back(L.ruse - L.sum);
-  HTH_HIP(hipMemcpyAsync(back.data(), p->d_sum, back.size(), hipMemcpyDeviceToHost, st));
-  HTH_HIP(hipStreamSynchronize(st));
-  std::memcpy(&p->sum, back.data(), sizeof(DpSummary));
-  std::vector<uint32_t> bk(nbk2), pk(nd_data), pkv(nd_data);
-  std::memcpy(bk.data(), back.data() + (L.bk - L.sum), nbk2 * 4);
-  if (nd_data) {
-    std::memcpy(pk.data(), back.data() + (L.pk - L.sum), nd_data * 4);
-    std::memcpy(pkv.data(), back.data() + (L.pkv - L.sum), nd_data * 4);
-  }
-  const DpSummary& S = p->sum;
-  if (S.err != ~0ull) {
-    hth_status code;
-    const char* why = dp_reason((uint32_t)(S.err & 255), &code);
-    return fail(code, "hypothesis " + std::to_string(S.err >> 32) + " node " +
-                          std::to_string((S.err >> 8) & 0xFFFFFF) + ": " + why);
-  }
-  if (S.code >= (1ull << 32)) return fail(HTH_E_RANGE, "region programs exceed 2^32 instructions");
-  // row ids must fit the 27-bit argument of the region bytecode
-  if ((uint64_t)p->K.n_fixed + 1 + S.n_thr + S.n_slots >= (1ull << 27) || S.n_vrows >= (1u << 27)) return fail(HTH_E_RANGE, "too many bit rows");
-  std::vector<DpBucket> buckets;
-  std::vector<uint32_t> xslots;
-  hth_status s = dp_schedule(*p, bk, buckets, xslots);
+  hth_status s = dp_layout(*p, st);
+  if (!s && p->V.too_large(*kb, p->need)) s = dp_relayout(*p, false, st);
   if (s) return s;
-  const ViewPlan& V = p->V;
-  std::vector<GroupTask> shells;
-  for (const auto& lg : p->lv_groups) shells.insert(shells.end(), lg.begin(), lg.end());
-  shells.insert(shells.end(), V.passes.begin(), V.passes.end());
-  // thresholds: each property's tasks together, in groups of at most kThrPerPass
-  std::vector<uint32_t> pbase(nd_data), vpbase(nd_data);
-  std::vector<ThrGroup> thg;
-  auto thr_groups = [&](const std::vector<uint32_t>& count, std::vector<uint32_t>& base) {
-    uint32_t sum = 0;
-    for (uint32_t q = 0; q < nd_data; ++q) {
-      base[q] = sum;
-      for (uint32_t i = 0; i < count[q]; i += kThrPerPass)
-        thg.push_back(ThrGroup{q, sum + i, std::min<uint32_t>(kThrPerPass, count[q] - i), 0});
-      sum += count[q];
-    }
-    return sum;
-  };
-  const uint32_t tsum = thr_groups(pk, pbase);
-  p->n_thg = (uint32_t)thg.size();
-  const uint32_t vsum = thr_groups(pkv, vpbase);
-  p->V.n_thg = (uint32_t)thg.size() - p->n_thg;
-  if (tsum != S.n_thr_full || vsum != S.n_thr_view) return fail(HTH_E_DEVICE, "threshold counts disagree");
-  p->K.n_thr = S.n_thr_full;
-  if (S.n_copies > n_nodes + 2ull) return fail(HTH_E_DEVICE, "plan tables beyond their bounds");
-  // the host's tables in one copy
-  std::vector<uint64_t> vbases;
-  for (const ViewDir& v : V.dirs) vbases.push_back(v.base);
-  Blob tb;
-  const size_t o_shell = tb.add(shells), o_bucket = tb.add(buckets), o_xslot = tb.add(xslots), o_thg = tb.add(thg),
-               o_pbase = tb.add(pbase), o_vpbase = tb.add(vpbase), o_vgroup = tb.add(V.groups), o_vdir = tb.add(V.dirs),
-               o_vbase = tb.add(vbases);
-  if (tb.bytes.size() > L.tables_bytes) return fail(HTH_E_DEVICE, "plan tables beyond their bounds");
-  char* const dt = buf + L.tables;
-  p->d_shells = reinterpret_cast<GroupTask*>(dt + o_shell);
-  p->d_buckets = reinterpret_cast<DpBucket*>(dt + o_bucket);
-  p->n_buckets = (uint32_t)buckets.size();
-  p->d_xslots = reinterpret_cast<uint32_t*>(dt + o_xslot);
-  p->d_thg = reinterpret_cast<ThrGroup*>(dt + o_thg);
-  p->d_pbase = reinterpret_cast<uint32_t*>(dt + o_pbase);
-  p->d_vpbase = reinterpret_cast<uint32_t*>(dt + o_vpbase);
-  p->d_vgroups = reinterpret_cast<GroupTask*>(dt + o_vgroup);
-  p->d_vdirs = reinterpret_cast<ViewDir*>(dt + o_vdir);
-  p->d_vbases = reinterpret_cast<uint64_t*>(dt + o_vbase);
-  if (!tb.bytes.empty())
-    HTH_HIP(hipMemcpyAsync(dt, tb.bytes.data(), tb.bytes.size(), hipMemcpyHostToDevice, st));
-  HTH_HIP(hipStreamSynchronize(st));   // a launch may come from another stream
   *ws_bytes = p->need;
   *out = guard.release();
   return HTH_OK;
@@ -1406,14 +1459,29 @@ extern "C" hth_status hth_dplan_launch(hth_dplan plan, void* ws, size_t ws_bytes
   using namespace hth;
   if (!plan || !ws || !d_counts) return fail(HTH_E_INVALID, "NULL argument");
   hth_dplan_s& p = *plan;
-  if (p.need > ws_bytes)
-    return fail(HTH_E_NOMEM, "workspace too small: need " + std::to_string(p.need) + " bytes, have " +
-                                 std::to_string(ws_bytes));
   if (reinterpret_cast<uintptr_t>(ws) % 256) return fail(HTH_E_INVALID, "workspace must be 256-byte aligned");
   const hipStream_t st = static_cast<hipStream_t>(stream);
   hth_kb_s& kb = *p.kb;
   std::lock_guard<std::mutex> g(kb.mu);
   TuneScope ts(kb, p.tune);
+  if (p.V.on) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();   // (another stream's capture)
+    else p.captured |= capture != hipStreamCaptureStatusNone;
+    // no room for the example view: laid out anew without it, from now on (or
+    // with it again, where that does not fit either); not once a graph holds
+    // launches of the layout there is
+    if (p.need > ws_bytes && p.need - p.V.bytes <= ws_bytes && !p.captured) {
+      HTH_HIP(hipEventSynchronize(p.done));
+      if (dp_relayout(p, false, st) || p.need > ws_bytes) {
+        hth_status s = dp_relayout(p, true, st);
+        if (s) return s;
+      }
+    }
+  }
+  if (p.need > ws_bytes)
+    return fail(HTH_E_NOMEM, "workspace too small: need " + std::to_string(p.need) + " bytes, have " +
+                                 std::to_string(ws_bytes));
   role_attributes(kb);
   char* w = static_cast<char*>(ws);
   DpTables T;

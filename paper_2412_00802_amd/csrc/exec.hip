@@ -23,7 +23,9 @@
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <memory>
+#include <set>
 #include <utility>
 #include <vector>
 
@@ -1798,11 +1800,13 @@ void prepare(const hth_kb_s& kb, Plan&& plan, uint32_t n_hyps, Prepared& X) {
     for (const GroupChunk& c : X.lv_chunks[L]) part = std::max(part, chunk_partial_bytes(kb, X.lv_groups[L], c));
   X.o_idset = X.o_part + align_up(part, 256);
   X.need = X.o_idset + idset_bytes(P);
+  const size_t rest = X.need;
   V.layout(kb, [&](size_t bytes) {
     const size_t at = X.need;
     X.need = align_up(at + bytes, 256);
     return at;
   });
+  V.bytes = X.need - rest;
 }
 
 hth_status check_ws(const Prepared& X, const char* ws, size_t ws_bytes) {
@@ -2195,7 +2199,7 @@ hth_status eval_batch_impl(hth_kb kb, const hth_node* nodes, const uint32_t* hyp
     std::lock_guard<std::mutex> g(kb->mu);
     Prepared X;
     prepare(*kb, std::move(P), n_hyps, X);
-    if (X.need > ws_bytes && opt.view) {   // a workspace without room for the view: every row in full
+    if (opt.view && (X.need > ws_bytes || X.V.too_large(*kb, X.need))) {   // no room for the view: every row in full
       opt.examples = opt.view = false;
       continue;
     }
@@ -2314,6 +2318,11 @@ struct hth_plan_s {
   hth_kb kb = nullptr;
   hth::Prepared X;
   hth_kb_s::Tuning tune;   // the schedule the tables were laid out for
+  // A workspace without room for the example view gets the plan without it,
+  // compiled when the first such workspace is uploaded: those it was uploaded to.
+  std::function<hth_status(hth::Plan&)> without_view;
+  std::unique_ptr<hth::Prepared> G;
+  std::set<const void*> general;
 };
 
 namespace hth {
@@ -2340,36 +2349,60 @@ extern "C" hth_status hth_plan_create(hth_kb kb, const hth_node* nodes, const ui
   opt.group_k = kb->tune.group_k;
   opt.examples = opt.view = batch_view(*kb, opt);
   Plan P;
-  hth_status s = compile_plan(*kb, nodes, hyp_node_offsets, n_hyps, children, n_children, opt, P);
+  std::function<hth_status(Plan&)> later;
+  hth_status s = compile_plan(*kb, nodes, hyp_node_offsets, n_hyps, children, n_children, opt, P, nullptr,
+                              opt.view ? &later : nullptr);
   if (s) return s;
-  hth_plan_s* pl = new (std::nothrow) hth_plan_s();
+  std::unique_ptr<hth_plan_s> pl(new (std::nothrow) hth_plan_s());
   if (!pl) return fail(HTH_E_NOMEM, "host allocation failed");
   pl->kb = kb;
   pl->tune = kb->tune;
   prepare(*kb, std::move(P), n_hyps, pl->X);
-  *out = pl;
+  if (pl->X.V.too_large(*kb, pl->X.need)) {
+    s = later(P);
+    if (s) return s;
+    pl->X = Prepared();
+    prepare(*kb, std::move(P), n_hyps, pl->X);
+  } else if (pl->X.V.on) {
+    pl->without_view = std::move(later);
+  }
   *ws_bytes = pl->X.need;
+  *out = pl.release();
   return HTH_OK;
 }
 
 extern "C" hth_status hth_plan_upload(hth_plan plan, void* ws, size_t ws_bytes, void* stream) {
   if (!plan || !ws) return fail(HTH_E_INVALID, "NULL argument");
-  hth_status s = check_ws(plan->X, static_cast<char*>(ws), ws_bytes);
+  std::lock_guard<std::mutex> g(plan->kb->mu);
+  const bool general = plan->X.need > ws_bytes && plan->without_view;
+  if (general && !plan->G) {
+    TuneScope ts(*plan->kb, plan->tune);
+    Plan P;
+    hth_status s = plan->without_view(P);
+    if (s) return s;
+    auto G = std::make_unique<Prepared>();
+    prepare(*plan->kb, std::move(P), plan->X.n_hyps, *G);
+    plan->G = std::move(G);
+  }
+  const Prepared& X = general ? *plan->G : plan->X;
+  hth_status s = check_ws(X, static_cast<char*>(ws), ws_bytes);
   if (s) return s;
-  HTH_HIP(hipMemcpyAsync(ws, plan->X.blob.bytes.data(), plan->X.blob.bytes.size(), hipMemcpyHostToDevice,
+  HTH_HIP(hipMemcpyAsync(ws, X.blob.bytes.data(), X.blob.bytes.size(), hipMemcpyHostToDevice,
                          static_cast<hipStream_t>(stream)));
+  if (general) plan->general.insert(ws);
+  else plan->general.erase(ws);
   return HTH_OK;
 }
 
 extern "C" hth_status hth_plan_launch(hth_plan plan, void* ws, size_t ws_bytes, uint32_t* d_counts,
                                       void* stream) {
   if (!plan || !ws || !d_counts) return fail(HTH_E_INVALID, "NULL argument");
-  hth_status s = check_ws(plan->X, static_cast<char*>(ws), ws_bytes);
-  if (s) return s;
   std::lock_guard<std::mutex> g(plan->kb->mu);
+  const Prepared& X = plan->general.count(ws) ? *plan->G : plan->X;   // as uploaded there
+  hth_status s = check_ws(X, static_cast<char*>(ws), ws_bytes);
+  if (s) return s;
   TuneScope ts(*plan->kb, plan->tune);
-  return launch_prepared(*plan->kb, plan->X, static_cast<char*>(ws), d_counts, nullptr,
-                         static_cast<hipStream_t>(stream));
+  return launch_prepared(*plan->kb, X, static_cast<char*>(ws), d_counts, nullptr, static_cast<hipStream_t>(stream));
 }
 
 extern "C" hth_status hth_plan_destroy(hth_plan plan) {
@@ -2399,7 +2432,7 @@ extern "C" hth_status hth_batch_workspace_bytes(hth_kb kb, const hth_node* nodes
   if (opt.view) {
     Prepared X;
     prepare(*kb, std::move(P), n_hyps, X);
-    *bytes = std::max(*bytes, X.need);
+    if (!X.V.too_large(*kb, X.need)) *bytes = std::max(*bytes, X.need);
   }
   return HTH_OK;
 }

@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <unordered_map>
@@ -277,7 +278,33 @@ struct Compiler {
   bool in_view = false;          // programs read view rows
   std::vector<uint32_t> map_, ks_;   // of add_hypothesis and emit, kept between calls
 
-  explicit Compiler(const hth_kb_s& k) : kb(k) {}
+  Registered reg;
+
+  explicit Compiler(const hth_kb_s& k) : kb(k) {
+    reg.sets = k.sets;
+    reg.n_sets = k.n_sets;
+    if (k.n_num) {
+      reg.num_roff = k.num_roff;
+      reg.num_val = k.num_val;
+      reg.num_heavy_rows = k.num_heavy_rows;
+      reg.num_heavy_chunks = k.num_heavy_chunks;
+      reg.num_chunk_first = k.num_chunk_first;
+      reg.num_bounds = k.num_bounds;
+    }
+    if (k.n_str) {
+      reg.str_roff = k.str_roff;
+      reg.str_ids = k.str_ids;
+      reg.str_heavy_rows = k.str_heavy_rows;
+      reg.str_heavy_chunks = k.str_heavy_chunks;
+      reg.str_chunk_first = k.str_chunk_first;
+      reg.str_bounds = k.str_bounds;
+      reg.dict_off = k.dict_off;
+      reg.dict_chars = k.dict_chars;
+      reg.pat_off = k.pat_off;
+      reg.pat_chars = k.pat_chars;
+      reg.n_strings = k.n_strings;
+    }
+  }
 
   hth_status add_hypothesis(const hth_node* nd, uint32_t nn, const uint32_t* children,
                             uint32_t n_children, uint32_t h) {
@@ -365,7 +392,7 @@ struct Compiler {
     return HTH_OK;
   }
 
-  uint32_t new_row() { return kb.d.n_concepts + kb.n_sets + n_slots++; }
+  uint32_t new_row() { return kb.d.n_concepts + reg.n_sets + n_slots++; }
 
   int32_t region_depth(uint32_t v) {
     if (depth[v] >= 0) return depth[v];
@@ -619,7 +646,7 @@ struct Compiler {
         t.cmp = n.op == HTH_NUM_GE ? 0 : n.op == HTH_NUM_LE ? 1 : 2;
         std::memcpy(&t.t, &n.q, 4);
         t.out_row = row[v];
-        (!deep[v] && no_heavy(kb.num_chunk_first, n.arg) ? P.ex_num : P.num).push_back(t);
+        (!deep[v] && no_heavy(reg.num_chunk_first, n.arg) ? P.ex_num : P.num).push_back(t);
         copied(v);
       } else if (is_string(n.op)) {
         row[v] = new_row();
@@ -628,7 +655,7 @@ struct Compiler {
         t.kind = n.op == HTH_STR_CONTAINS ? 1 : 0;
         std::memcpy(&t.q, &n.q, 4);
         t.out_row = row[v];
-        (!deep[v] && no_heavy(kb.str_chunk_first, n.arg) ? P.ex_str : P.str).push_back(t);
+        (!deep[v] && no_heavy(reg.str_chunk_first, n.arg) ? P.ex_str : P.str).push_back(t);
         copied(v);
       } else if (is_role(n.op) && hit_row[v] == kNone) {
         if (view && viewable(v)) {
@@ -794,29 +821,7 @@ struct Compiler {
       P.roots.push_back(t);
     }
     P.n_slots = n_slots;
-    P.sets = kb.sets;
-    P.n_sets = kb.n_sets;
-    if (!P.num.empty() || !P.ex_num.empty()) {
-      P.num_roff = kb.num_roff;
-      P.num_val = kb.num_val;
-      P.num_heavy_rows = kb.num_heavy_rows;
-      P.num_heavy_chunks = kb.num_heavy_chunks;
-      P.num_chunk_first = kb.num_chunk_first;
-      P.num_bounds = kb.num_bounds;
-    }
-    if (!P.str.empty() || !P.ex_str.empty()) {
-      P.str_roff = kb.str_roff;
-      P.str_ids = kb.str_ids;
-      P.str_heavy_rows = kb.str_heavy_rows;
-      P.str_heavy_chunks = kb.str_heavy_chunks;
-      P.str_chunk_first = kb.str_chunk_first;
-      P.str_bounds = kb.str_bounds;
-      P.dict_off = kb.dict_off;
-      P.dict_chars = kb.dict_chars;
-      P.pat_off = kb.pat_off;
-      P.pat_chars = kb.pat_chars;
-      P.n_strings = kb.n_strings;
-    }
+    static_cast<Registered&>(P) = reg;
     P.n_canonical = (uint32_t)nv;
     return HTH_OK;
   }
@@ -826,9 +831,11 @@ struct Compiler {
 
 hth_status compile_plan(const hth_kb_s& kb, const hth_node* nodes, const uint32_t* hyp_off,
                         uint32_t n_hyps, const uint32_t* children, uint32_t n_children,
-                        const PlanOptions& opt, Plan& out, Plan* general) {
+                        const PlanOptions& opt, Plan& out, Plan* general,
+                        std::function<hth_status(Plan&)>* later) {
   out = Plan();
-  Compiler c(kb);
+  const std::shared_ptr<Compiler> keep = std::make_shared<Compiler>(kb);
+  Compiler& c = *keep;
   // room for the canonical nodes that the batch may have, up to a million (the
   // sizes are the caller's, offsets are checked below)
   c.dag.reserve(std::min<size_t>(hyp_off[n_hyps], 1u << 20) + 2, std::min<size_t>(n_children, 1u << 20));
@@ -843,13 +850,17 @@ hth_status compile_plan(const hth_kb_s& kb, const hth_node* nodes, const uint32_
     // 27-bit argument of the region bytecode
     if (out.n_input_nodes > (1u << 24)) return fail(HTH_E_RANGE, "more than 2^24 nodes in one call");
   }
-  if (general) {
+  auto whole = [keep, opt](Plan& P) {
     PlanOptions g = opt;
     g.examples = g.view = false;
-    *general = Plan();
-    hth_status s = c.build(g, *general);
+    P = Plan();
+    return keep->build(g, P);
+  };
+  if (general) {
+    hth_status s = whole(*general);
     if (s) return s;
   }
+  if (later) *later = whole;
   return c.build(opt, out);
 }
 

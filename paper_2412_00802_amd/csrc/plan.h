@@ -5,6 +5,7 @@
 #pragma once
 
 #include <cstdint>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -56,19 +57,14 @@ struct ViewBucket {
   uint32_t rd, count, first;        // direction 2 role + inv; members [first, first + count)
 };
 
-struct Plan {
-  std::vector<ThrTask> thr;
-  std::vector<NumTask> num;         // restrictions on numeric concrete roles
-  std::vector<NumTask> ex_num;      // those needed at the examples only
-  // the numeric concrete roles the plan was compiled against
+// What the caller had registered when the plan was compiled.
+struct Registered {
   const uint32_t* num_roff = nullptr;
   const float* num_val = nullptr;
   const uint32_t* num_heavy_rows = nullptr;
   const HeavyChunk* num_heavy_chunks = nullptr;
   std::vector<uint32_t> num_chunk_first;
   std::vector<uint64_t> num_bounds;        // [P+1] first value of each numeric role
-  std::vector<StrTask> str;                // restrictions on string concrete roles
-  std::vector<StrTask> ex_str;             // those needed at the examples only
   const uint32_t* str_roff = nullptr;
   const int32_t* str_ids = nullptr;
   const uint32_t* str_heavy_rows = nullptr;
@@ -80,6 +76,16 @@ struct Plan {
   const int64_t* pat_off = nullptr;
   const uint8_t* pat_chars = nullptr;
   uint32_t n_strings = 0;
+  const uint64_t* sets = nullptr;   // the set table the plan's HTH_SET rows refer to
+  uint32_t n_sets = 0;
+};
+
+struct Plan : Registered {
+  std::vector<ThrTask> thr;
+  std::vector<NumTask> num;         // restrictions on numeric concrete roles
+  std::vector<NumTask> ex_num;      // those needed at the examples only
+  std::vector<StrTask> str;                // restrictions on string concrete roles
+  std::vector<StrTask> ex_str;             // those needed at the examples only
   std::vector<uint32_t> code;
   std::vector<PlanLevel> levels;
   std::vector<RegionTask> roots;
@@ -91,16 +97,17 @@ struct Plan {
   std::vector<GroupMember> vmembers;   // ... and these, in the same order
   uint32_t n_vrows = kViewFixed;
   uint32_t n_slots = 0;
-  const uint64_t* sets = nullptr;   // the set table the plan's HTH_SET rows refer to
-  uint32_t n_sets = 0;
   // statistics
   uint32_t n_input_nodes = 0, n_canonical = 0, n_role_nodes = 0;
 };
 
-// general: also the plan without options examples and view.
 // Compile hypotheses nodes[hyp_off[h] .. hyp_off[h+1]) (local child indices).
+// general: also the plan without options examples and view.  later: receives
+// what compiles that plan when it is asked for, from what is kept of this call
+// (by the knowledge base's schedule then).
 hth_status compile_plan(const hth_kb_s& kb, const hth_node* nodes, const uint32_t* hyp_off,
                         uint32_t n_hyps, const uint32_t* children, uint32_t n_children,
-                        const PlanOptions& opt, Plan& out, Plan* general = nullptr);
+                        const PlanOptions& opt, Plan& out, Plan* general = nullptr,
+                        std::function<hth_status(Plan&)>* later = nullptr);
 
 }  // namespace hth

@@ -284,6 +284,7 @@ struct ViewPlan {
   std::vector<GroupChunk> chunks;
   uint32_t n_rows = kViewFixed, n_copies = 2, n_thg = 0;
   uint64_t targets = 0;
+  size_t bytes = 0;                     // of its areas
   size_t o_hdr = 0, o_list = 0, o_words = 0, o_tsum = 0, o_dsum = 0, o_off = 0, o_tg = 0, o_base = 0, o_slot = 0;
 
   // the view direction of rd (added when new)
@@ -313,6 +314,15 @@ struct ViewPlan {
       g.inv = 0;
       passes.push_back(g);
     }
+  }
+  // What it adds (its areas have room for every individual, since the examples
+  // may be any by the time of a launch; less the rows that stand for full ones)
+  // would more than double the workspace, `need` with it, and by more than a
+  // gigabyte.  4,096 hypotheses over 1M individuals, 266M assertions: 4.5 GB
+  // with it, 2.6 without; 16,384 over 32M 23.5 and 16.7.
+  bool too_large(const hth_kb_s& kb, size_t need) const {
+    const size_t added = bytes - (size_t)(n_rows - n_copies) * kb.S * 8;
+    return on && added > (need - added) + (1ull << 30);
   }
   uint32_t tiles(const hth_kb_s& kb) const { return (kb.W + kExTile - 1) / kExTile; }
   uint32_t dir_tiles(const hth_kb_s& kb) const { return (kb.N + kVDirTile - 1) / kVDirTile; }
