@@ -1405,13 +1405,18 @@ hth_status launch_group_chunk(Launcher& L, const DevKB& d, const GroupTask* grou
       const GroupTask& G = host[g0 + i];
       most = std::max(most, kb.max_deg[G.inv][G.role]);
     }
-    return L.run(HTH_K_GROUP_SHORT, gb, [&] {
+    auto go = [&](auto view) {
+      constexpr bool VIEW = decltype(view)::value;
       if (most < kGroupMaxCount)
-        hipLaunchKernelGGL((k_group_short<TW, kShortWords, kShortSub, kShortFly<TW>, true>), dim3(nblocks), dim3(256), 0, L.st,
-                           pd, pg, members, T, bpg, xslots);
+        hipLaunchKernelGGL((k_group_short<TW, kShortWords, kShortSub, kShortFly<TW>, true, VIEW>), dim3(nblocks), dim3(256),
+                           0, L.st, pd, pg, members, T, bpg, xslots);
       else
-        hipLaunchKernelGGL((k_group_short<TW, kShortWords, kShortSub, kShortFly<TW>, false>), dim3(nblocks), dim3(256), 0, L.st,
-                           pd, pg, members, T, bpg, xslots);
+        hipLaunchKernelGGL((k_group_short<TW, kShortWords, kShortSub, kShortFly<TW>, false, VIEW>), dim3(nblocks), dim3(256),
+                           0, L.st, pd, pg, members, T, bpg, xslots);
+    };
+    return L.run(HTH_K_GROUP_SHORT, gb, [&] {
+      if (vd) go(std::true_type());
+      else go(std::false_type());
     });
   }
   uint64_t seg_rows = 0;
@@ -1428,14 +1433,17 @@ hth_status launch_group_chunk(Launcher& L, const DevKB& d, const GroupTask* grou
     s = L.run(HTH_K_GROUP, sg ? 0.0 : gb, [&] {
       const dim3 grid(nblocks), block(256);
       const bool u16 = kb.tune.group_unroll >= 16;
-      if (multi) {   // few assertions per lane: 8 in flight
-        hipLaunchKernelGGL((k_group<TW, 8, 4>), grid, block, 0, L.st, pd, pg, members, T, bpg, xslots, sp);
-      } else {
-        if (u16)
-          hipLaunchKernelGGL((k_group<TW, 16, 1>), grid, block, 0, L.st, pd, pg, members, T, bpg, xslots, sp);
+      auto go = [&](auto view) {
+        constexpr bool VIEW = decltype(view)::value;
+        if (multi)    // few assertions per lane: 8 in flight
+          hipLaunchKernelGGL((k_group<TW, 8, 4, VIEW>), grid, block, 0, L.st, pd, pg, members, T, bpg, xslots, sp);
+        else if (u16)
+          hipLaunchKernelGGL((k_group<TW, 16, 1, VIEW>), grid, block, 0, L.st, pd, pg, members, T, bpg, xslots, sp);
         else
-          hipLaunchKernelGGL((k_group<TW, 8, 1>), grid, block, 0, L.st, pd, pg, members, T, bpg, xslots, sp);
-      }
+          hipLaunchKernelGGL((k_group<TW, 8, 1, VIEW>), grid, block, 0, L.st, pd, pg, members, T, bpg, xslots, sp);
+      };
+      if (vd) go(std::true_type());
+      else go(std::false_type());
     });
     if (s) return s;
   }

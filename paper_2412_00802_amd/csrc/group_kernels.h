@@ -269,9 +269,10 @@ __device__ __forceinline__ void cover_word(Cover& c, const DevKB& kb, uint32_t w
   c.q += (uint32_t)__popcll(v & N) - (c.z ? (uint32_t)__popcll(N) : 0u);
 }
 // wave `wave` of `waves`: its share of all words, then the member's atomics
+template <bool VIEW>
 __device__ __forceinline__ void cover_finish(Cover& c, const DevKB& kb, uint32_t wave, uint32_t waves, int lane) {
   if (__ballot(c.h != kNone && c.z)) {
-    const uint32_t W = span_w(kb);
+    const uint32_t W = VIEW ? span_w(kb) : kb.W;
     for (uint32_t w0 = wave * 64; w0 < W; w0 += waves * 64) {
       const uint32_t w = w0 + lane;
       uint32_t pp = w < W ? (uint32_t)__popcll(kb.pos[w]) : 0u;
@@ -315,11 +316,12 @@ struct SegPass {
 // balanced on the host).  words: those of one wave's iteration.  wave: number
 // of wave wv among the group's; a block's waves take neighbouring words, or,
 // where the view leaves blocks idle, the blocks' first waves come first.
+template <bool VIEW>
 __device__ __forceinline__ bool group_block(const DevKB& kb, uint32_t bpg, const uint32_t* __restrict__ xslots,
                                             uint32_t words, uint32_t wv, uint32_t& g, uint32_t& b, uint32_t& wave) {
   const uint32_t nw = blockDim.x >> 6, x = blockIdx.x & 7, j = xslots ? blockIdx.x >> 3 : blockIdx.x;
   bool turns = false;
-  if (kb.view) {
+  if (VIEW) {
     const uint32_t W = span_w(kb);
     const ViewBlock v = view_block(j, (xslots ? gridDim.x >> 3 : gridDim.x) / bpg, bpg, (W + nw * words - 1) / (nw * words));
     g = v.item, b = v.b, turns = v.turns;
@@ -351,7 +353,8 @@ __device__ __forceinline__ bool group_block(const DevKB& kb, uint32_t bpg, const
 // member (a word with at most kSparseWord non-empty rows instead starts from
 // the zero count's predicates and takes the others' bits lane by lane).  MW > 1 serves directions with few assertions per word.
 constexpr int kSparseWord = 4;   // words with at most this many non-empty rows skip the transpose
-template <typename TW, int U, int MW>   // U: assertions in flight per lane
+// U: assertions in flight per lane; VIEW: over the example view (view.h)
+template <typename TW, int U, int MW, bool VIEW>
 __global__ void __launch_bounds__(256)
 k_group(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember* __restrict__ members,
         const TW* __restrict__ tarea, uint32_t bpg, const uint32_t* __restrict__ xslots, SegPass<TW> sp) {
@@ -360,14 +363,14 @@ k_group(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember* __res
   __shared__ TW s_pl[4][4][R];        // counters of the rows finished in this iteration
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t g, b, wave;
-  if (!group_block(kb, bpg, xslots, MW, wv, g, b, wave)) return;
+  if (!group_block<VIEW>(kb, bpg, xslots, MW, wv, g, b, wave)) return;
   const GroupTask* G = groups + g;
   const uint32_t k = G->k;
   TW* part = sp.first && sp.last ? nullptr : sp.part + (size_t)g * sp.stride;
   const TW* T = tarea + G->t_off;
   const size_t roff = (size_t)G->role * (kb.N + 1);
   const uint32_t* off = (G->inv ? kb.inv_off : kb.fwd_off) + roff;
-  const uint32_t N = span_n(kb), off_end = off[N];
+  const uint32_t N = VIEW ? span_n(kb) : kb.N, off_end = off[N];
   // a compact group reads each assertion's object rank instead of its object
   const int32_t* tg = (G->compact ? (G->inv ? kb.ctg_inv : kb.ctg_fwd) : (G->inv ? kb.inv_tg : kb.fwd_tg)) +
                       kb.role_base[G->role];
@@ -386,10 +389,10 @@ k_group(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember* __res
   const uint32_t nw = blockDim.x >> 6;
   const uint32_t istep = bpg * nw;
   // the direction's non-empty words; every word of the view
-  const uint32_t* words = kb.view ? kb.words : kb.words + (size_t)(2 * G->role + G->inv) * kb.W;
-  const uint32_t n_words = kb.view ? span_w(kb) : G->n_words;
+  const uint32_t* words = VIEW ? kb.words : kb.words + (size_t)(2 * G->role + G->inv) * kb.W;
+  const uint32_t n_words = VIEW ? span_w(kb) : G->n_words;
   if (!n_words) {
-    if (sp.last) cover_finish(cv, kb, wave, bpg * nw, lane);
+    if (sp.last) cover_finish<VIEW>(cv, kb, wave, bpg * nw, lane);
     return;
   }
   const uint32_t n_iter = (n_words + MW - 1) / MW;
@@ -647,7 +650,7 @@ k_group(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember* __res
     s = ns;
     se = nse;
   }
-  if (sp.last) cover_finish(cv, kb, wave, bpg * nw, lane);
+  if (sp.last) cover_finish<VIEW>(cv, kb, wave, bpg * nw, lane);
 }
 
 // A shared pass over a role direction whose rows are all short (at most the
@@ -680,7 +683,7 @@ template <typename TW>
 constexpr int kShortFly = sizeof(TW) <= 2 ? 2 : 1;
 // EXACT: every row of the launch's directions holds at most 7 assertions, so
 // c2 c1 c0 count exactly and the saturation plane stays empty (not kept).
-template <typename TW, int MW, int SUB, int U, bool EXACT>
+template <typename TW, int MW, int SUB, int U, bool EXACT, bool VIEW>
 __global__ void __launch_bounds__(256)
 k_group_short(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember* __restrict__ members,
               const TW* __restrict__ tarea, uint32_t bpg, const uint32_t* __restrict__ xslots) {
@@ -692,7 +695,7 @@ k_group_short(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember*
   __shared__ uint64_t* s_dst[64];
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t g, b, wave;
-  if (!group_block(kb, bpg, xslots, SW, wv, g, b, wave)) return;
+  if (!group_block<VIEW>(kb, bpg, xslots, SW, wv, g, b, wave)) return;
   const GroupTask* G = groups + g;
   const uint32_t k = G->k;
   const TW* T = tarea + G->t_off;
@@ -718,9 +721,9 @@ k_group_short(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember*
   Cover cv = cover_of(G, members, k, lane);
   const bool covers = __ballot(cv.h != kNone) != 0;
   const uint32_t nw = blockDim.x >> 6;
-  const uint32_t N = span_n(kb);
-  const uint32_t* words = kb.view ? kb.words : kb.words + (size_t)(2 * G->role + G->inv) * kb.W;
-  const uint32_t n_words = kb.view ? span_w(kb) : G->n_words;
+  const uint32_t N = VIEW ? span_n(kb) : kb.N;
+  const uint32_t* words = VIEW ? kb.words : kb.words + (size_t)(2 * G->role + G->inv) * kb.W;
+  const uint32_t n_words = VIEW ? span_w(kb) : G->n_words;
   const uint32_t n_super = (n_words + SW - 1) / SW;
   uint64_t (*so)[SW + 1] = s_out[wv];
   uint32_t pw[SW];   // words staged in LDS, not yet written
@@ -871,7 +874,7 @@ k_group_short(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember*
     }
   }
   flush();
-  cover_finish(cv, kb, wave, bpg * nw, lane);
+  cover_finish<VIEW>(cv, kb, wave, bpg * nw, lane);
 }
 
 }  // namespace hth
