@@ -1404,7 +1404,7 @@ extern "C" hth_status hth_dplan_create(hth_kb kb, const hth_node* d_nodes, uint3
   p->K.W = kb->W;
   p->K.n_fixed = kb->d.n_concepts + kb->n_sets;
   p->K.n_dir = nd;
-  p->V.on = view_wanted(*kb);
+  p->V.on = view_wanted(*kb) && kb->tune.group_min;   // (its restrictions share passes)
   p->K.view = p->V.on;
   const DpScratch L = dp_scratch(*kb, n_nodes);
   if (scratch_bytes < L.total)
