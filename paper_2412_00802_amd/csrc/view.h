@@ -287,18 +287,12 @@ struct ViewPlan {
   size_t bytes = 0;                     // of its areas
   size_t o_hdr = 0, o_list = 0, o_words = 0, o_tsum = 0, o_dsum = 0, o_off = 0, o_tg = 0, o_base = 0, o_slot = 0;
 
-  // the view direction of rd (added when new)
-  uint32_t dir(const hth_kb_s& kb, uint32_t rd) {
-    for (uint32_t v = 0; v < dirs.size(); ++v)
-      if (dirs[v].rd == rd) return v;
+  // the `count` role nodes of direction rd, each added once, as shared passes of
+  // at most gk, their members from `first` on
+  void add_passes(const hth_kb_s& kb, uint32_t rd, uint64_t count, uint32_t gk, uint32_t first, bool short_rows) {
+    const uint32_t v = (uint32_t)dirs.size();
     dirs.push_back(ViewDir{rd, kb.tune.t_compact && 2ull * kb.n_obj[rd] <= kb.N ? 1u : 0u, targets});
     targets += kb.role_base[rd / 2 + 1] - kb.role_base[rd / 2];
-    return (uint32_t)dirs.size() - 1;
-  }
-  // `count` role nodes of direction rd as shared passes of at most gk, their
-  // members from `first` on
-  void add_passes(const hth_kb_s& kb, uint32_t rd, uint64_t count, uint32_t gk, uint32_t first, bool short_rows) {
-    const uint32_t v = dir(kb, rd);
     for (uint64_t i0 = 0; i0 < count; i0 += gk) {
       GroupTask g{};
       g.role = rd / 2;
