@@ -1246,8 +1246,11 @@ inline uint32_t threshold_blocks(const hth_kb_s& kb, uint32_t n, uint32_t W) {
 }
 
 // A plan's fills, every level's at once before the first: a launch less for
-// each further level (3 % of a round over 200,000 individuals; 3.7 GB of fills
-// over 4M individuals take the same time as level by level).
+// each further level (3 % of a round over 200,000 individuals).  Far beyond the
+// last-level cache too: 13.4 GB of fills on 17 levels (65,536 hypotheses over 4M
+// individuals) take 2.78 ms at once and 2.65 level by level, which leaves part
+// of them in the cache, but the T builds next to them 10.40 and 10.71, and the
+// whole step 52.9 and 53.2.
 hth_status launch_fills(Launcher& L, const DevKB& d, const FillTask* tasks, size_t n, double bytes) {
   if (!n) return HTH_OK;
   const uint32_t tiles = fill_tiles(L.kb.S);
