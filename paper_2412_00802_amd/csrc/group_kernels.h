@@ -675,7 +675,9 @@ k_group(DevKB kb, const GroupTask* __restrict__ groups, const GroupMember* __res
 // Over 4M individuals, 13 assertions a word, 15 directions: 8 members 79 us a
 // launch (116 with a register a word and 4 words' transposes each), 16 members
 // 483 (634), 32 583 (655) of 48 directions; 64 members 24.5 us a direction as
-// before (half the rate of a copy).
+// before (half the rate of a copy): there the offsets in flight cost a wave a
+// SIMD (92 registers, 79 without) and give nothing or little: 14.8 ms of a step
+// over 65,536 hypotheses with and without, 1 % of another such batch.
 constexpr int kShortWords = 4;   // MW
 constexpr int kShortSub = 2;     // SUB
 // U: assertions of a row in flight
