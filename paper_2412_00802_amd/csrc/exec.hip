@@ -2079,11 +2079,13 @@ hth_status run_plan(hth_kb_s& kb, Plan&& P, char* ws, size_t ws_bytes, uint32_t*
 }
 
 // Whether a hypothesis evaluated alone takes its restrictions at the examples:
-// from four times the individuals on, since there is no pass to share (8
-// hypotheses over 131,072 individuals 188 us at the examples, 173 over
-// everyone; over 400,000 221 and 222; 16 over 1M 542 and 790).
+// from four times the individuals on and up to an eighth of them, since there is
+// no pass to share.  Microseconds at the examples / over everyone: 6 % examples,
+// 8 hypotheses over 131,072 individuals 188 / 173, over 400,000 221 / 222, 16 over
+// 1M 542 / 790; 16 over 400,000, 10 % 496 / 534, 20 % 549 / 530; over 1M, 10 %
+// 801 / 842, 20 % 926 / 840.
 bool one_at_examples(const hth_kb_s& kb, const PlanOptions& opt) {
-  return !opt.instances && kb.N / 4 >= kb.view_min && view_wanted(kb);
+  return !opt.instances && kb.N / 4 >= kb.view_min && (uint64_t)kb.ex_hint * 8 <= kb.N && view_wanted(kb);
 }
 
 // Whether a host-planned batch evaluates at the examples what no filler reads.

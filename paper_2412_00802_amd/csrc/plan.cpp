@@ -597,7 +597,7 @@ struct Compiler {
     if (opt.view) {
       uint32_t n = 0;
       for (uint32_t v = 0; v < nv; ++v) n += live[v] && viewable(v);
-      P.view = n >= kViewNodes;
+      P.view = n >= view_nodes(kb);
     }
     const bool view = P.view;
     if (view) {

@@ -37,13 +37,18 @@ struct PlanOptions {
   uint32_t group_k = 64;             // most role nodes per shared pass
   // counts only: restrictions that no filler reads are evaluated at the examples alone
   bool examples = false;
-  // ... and, from kViewNodes role nodes on, in shared passes over the example view
+  // ... and, from view_nodes role nodes on, in shared passes over the example view
   bool view = false;
 };
-// fewer cost less one by one than the view's launches (1M individuals, 2
-// hypotheses 42 us one by one, 74 over everyone; 16 hypotheses 495 in the view,
-// 671 over everyone)
-constexpr uint32_t kViewNodes = 16;
+// Fewer cost less one by one than the view's launches and copies: what one node
+// costs grows with the examples, the view's launches do not (16 + 2^20 / examples
+// with the default view_min).  Microseconds one
+// by one / in the view / over everyone, batches of hypotheses with one or two
+// such nodes each: 6 % of 100,000 individuals, 48 hypotheses 197 / 279 / 253, 96
+// 246 / 294 / 276; of 400,000, 32 454 / 479 / 588, 96 732 / 672 / 829; of 1M, 16
+// 855 / 881 / 1,255, 64 1,631 / 1,400 / 2,012; 25 % of 1M, 16 1,115 / 1,109 /
+// 1,253, 32 1,582 / 1,301 / 1,526.
+inline uint64_t view_nodes(const hth_kb_s& kb) { return 16 + 16ull * kb.view_min / std::max(1u, kb.ex_hint); }
 
 struct PlanLevel {
   std::vector<RegionTask> mat;      // children materialised before this level's role passes

@@ -269,7 +269,11 @@ k_view_rows(DevKB kb, uint64_t* __restrict__ vslots, const uint32_t* __restrict_
 // the view / without, 6 % examples, 8 roles of 8 assertions a subject, 256
 // hypotheses planned on the host: 16,000 individuals 346 / 283, 33,000 387 /
 // 387, 65,536 441 / 474, 400,000 1,226 / 1,333; 2,048 planned on the device:
-// 833 / 809, 926 / 980, 1,076 / 1,299, 3,023 / 3,787.
+// 833 / 809, 926 / 980, 1,076 / 1,299, 3,023 / 3,787.  By the share of examples,
+// 6 %, 25 % and 50 % with the view / without: 256 on the host over 400,000
+// 832, 932, 1,106 / 1,069, over 1M 2,084, 2,472, 2,977 / 3,457; 2,048 on the
+// device over 65,536 677, 702, 784 / 785, over 1M 6,677, 8,310, 10,481 / 12,985.
+// A quarter is where the least of them (256 on the host, 400,000) still gains.
 inline bool view_wanted(const hth_kb_s& kb) {
   return kb.N >= kb.view_min && kb.ex_hint && (uint64_t)kb.ex_hint * 4 <= kb.N;
 }

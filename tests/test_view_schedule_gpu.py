@@ -60,3 +60,12 @@ def test_many_directions(monkeypatch):
         y = (x - 1 - r) % n if inv else (x + 1 + r) % n
         assert want[h, 0] == (np.isin(y, np.arange(0, n, 2) if r % 2 == 0 else np.arange(1, n, 5))).sum()
     assert best["1"] < 4 * best["4294967295"]
+
+
+@pytest.mark.parametrize("n,n_ex", [(65_536, 4000), (70_003, 17_500)])
+def test_batches_below_the_view(n, n_ex):
+    """Enough restrictions for shared passes, too few for the example view: one by one at the examples, as roots, above
+    and under others, next to thresholds and rows that fillers read."""
+    from tests.test_view_gpu import check, kb_with, zoo
+    cfg, kb = kb_with(n, n_ex, seed=n)
+    check(hthedl.Engine(kb, max_hyps=400), kb, zoo(kb))
