@@ -959,15 +959,14 @@ __global__ void __launch_bounds__(256)
 k_dp_init(uint4* __restrict__ zero, size_t zeros, uint4* __restrict__ one, size_t ones, DpSummary* __restrict__ sum,
           ViewCopy* __restrict__ copies) {
   const size_t i0 = (size_t)blockIdx.x * 256 + threadIdx.x, step = (size_t)gridDim.x * 256;
-  DpSummary s{};
-  s.err = ~0ull;
-  s.n_vrows = kViewFixed;
-  s.n_copies = 2;
-  const uint4* init = reinterpret_cast<const uint4*>(&s);
-  for (size_t i = i0; i < zeros; i += step) {
-    uint4* at = zero + i;
-    const size_t d = at - reinterpret_cast<uint4*>(sum);
-    *at = at >= reinterpret_cast<uint4*>(sum) && d < sizeof(DpSummary) / 16 ? init[d] : make_uint4(0, 0, 0, 0);
+  const uint4* const s = reinterpret_cast<const uint4*>(sum);
+  for (size_t i = i0; i < zeros; i += step)
+    if (zero + i < s || zero + i >= s + sizeof(DpSummary) / 16) zero[i] = make_uint4(0, 0, 0, 0);
+  if (blockIdx.x == 0) {                 // the summary, by words
+    constexpr uint32_t err = offsetof(DpSummary, err) / 4, vrows = offsetof(DpSummary, n_vrows) / 4;
+    constexpr uint32_t n_copies = offsetof(DpSummary, n_copies) / 4;
+    for (uint32_t w = threadIdx.x; w < sizeof(DpSummary) / 4; w += 256)
+      reinterpret_cast<uint32_t*>(sum)[w] = w == err || w == err + 1 ? ~0u : w == vrows ? kViewFixed : w == n_copies ? 2u : 0u;
   }
   for (size_t i = i0; i < ones; i += step) one[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
   if (i0 == 0) {
