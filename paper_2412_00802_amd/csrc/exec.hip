@@ -1239,8 +1239,8 @@ constexpr uint64_t kRegionMinBlocks = 16384;
 
 // Blocks per threshold group over W words: about 32 words per wave, enough
 // independent column loads in flight; fewer, down to the 8 a wave takes at
-// once, while the launch would leave compute units idle (7 groups over 157
-// words 18 us at 32 words a wave, THR_B at 8).
+// once, while the launch would leave compute units idle (7 groups of 30
+// thresholds over 157 words 28 us at 32 words a wave, 13 at 8).
 inline uint32_t threshold_blocks(const hth_kb_s& kb, uint32_t n, uint32_t W) {
   return std::max<uint32_t>(1, std::min((W + 31) / 32, std::max((W + 127) / 128, 4 * kb.n_cu / n)));
 }
