@@ -254,13 +254,19 @@ struct Stage {
 // with the transpose as 2-byte LDS stores (weight gradients): 1024 x 1024 x 4096
 // forward 25.6 us (was 54), 4096 x 1024 x 1024 gradient 27.8 us (was 82),
 // 1024 x 256 x 1024 gradient 12.3 us (was 77).
-template <int T, int BK>
+//
+// DEEP = 0, for short k: one k-tile of loads ahead and one LDS buffer, so that
+// three blocks fit a CU and the stores of C, which bound it there, run beside
+// other blocks' products.  With DEEP = 1 the registers are held to two blocks a
+// CU; left to the compiler they were more than 256, one block a CU (65,536 x 1024 x
+// 64: 121 us; two deep blocks a CU 78, three flat ones 55).
+template <int T, int BK, int DEEP>
 struct GemmLds {
-  __bf16 a[2][T][BK + 8], b[2][T][BK + 8];
+  __bf16 a[1 + DEEP][T][BK + 8], b[1 + DEEP][T][BK + 8];
 };
 
-template <int TA, int TB, int T, int BK>
-__device__ __forceinline__ void gemm_tile(GemmLds<T, BK>& L, int bx, int by, int M, int N, int K,
+template <int TA, int TB, int T, int BK, int DEEP>
+__device__ __forceinline__ void gemm_tile(GemmLds<T, BK, DEEP>& L, int bx, int by, int M, int N, int K,
                                           const __bf16* __restrict__ A, int lda, const __bf16* __restrict__ B,
                                           int ldb, const GemmEpi& ep) {
   auto& As = L.a;
@@ -303,24 +309,41 @@ __device__ __forceinline__ void gemm_tile(GemmLds<T, BK>& L, int bx, int by, int
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
     }
   };
-  bf16x8 r0[8], r1[8];
+  bf16x8 r0[8];
   load(0, r0);
-  load(BK, r1);
-  store(0, 0, r0);
-  __syncthreads();
-  // two k-tiles a turn, the second one all zeros where their number is odd;
-  // the scheduling barriers keep the loads above the products
-  for (int k0 = 0; k0 < K; k0 += 2 * BK) {
-    load(k0 + 2 * BK, r0);
-    __builtin_amdgcn_sched_barrier(0);
-    multiply(0);
-    store(1, k0 + BK, r1);
+  if constexpr (!DEEP) {
+    store(0, 0, r0);
     __syncthreads();
-    load(k0 + 3 * BK, r1);
-    __builtin_amdgcn_sched_barrier(0);
-    multiply(1);
-    store(0, k0 + 2 * BK, r0);
+    for (int k0 = 0; k0 < K; k0 += BK) {
+      const bool more = k0 + BK < K;
+      if (more) load(k0 + BK, r0);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(0);
+      __syncthreads();
+      if (more) {
+        store(0, k0 + BK, r0);
+        __syncthreads();
+      }
+    }
+  } else {
+    bf16x8 r1[8];
+    load(BK, r1);
+    store(0, 0, r0);
     __syncthreads();
+    // two k-tiles a turn, the second one all zeros where their number is odd;
+    // the scheduling barriers keep the loads above the products
+    for (int k0 = 0; k0 < K; k0 += 2 * BK) {
+      load(k0 + 2 * BK, r0);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(0);
+      store(1, k0 + BK, r1);
+      __syncthreads();
+      load(k0 + 3 * BK, r1);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(1);
+      store(0, k0 + 2 * BK, r0);
+      __syncthreads();
+    }
   }
   // epilogue: register r of lane l holds row 8(r/4) + 4(l/32) + r%4, column l%32;
   // the bias and the mask values are loaded before the first store
@@ -354,12 +377,12 @@ __device__ __forceinline__ void gemm_tile(GemmLds<T, BK>& L, int bx, int by, int
     }
 }
 
-template <int TA, int TB, int T, int BK>
-__global__ void __launch_bounds__(256)
+template <int TA, int TB, int T, int BK, int DEEP>
+__global__ void __launch_bounds__(256, DEEP ? 2 : 3)
 k_gemm(int M, int N, int K, const __bf16* __restrict__ A, int lda, const __bf16* __restrict__ B, int ldb,
        GemmEpi ep) {
-  __shared__ GemmLds<T, BK> L;
-  gemm_tile<TA, TB, T, BK>(L, blockIdx.x, blockIdx.y, M, N, K, A, lda, B, ldb, ep);
+  __shared__ GemmLds<T, BK, DEEP> L;
+  gemm_tile<TA, TB, T, BK, DEEP>(L, blockIdx.x, blockIdx.y, M, N, K, A, lda, B, ldb, ep);
 }
 
 // Two products that do not depend on each other in one launch: the first n1
@@ -374,30 +397,36 @@ struct GemmArgs {
   GemmEpi ep;
 };
 __global__ void __launch_bounds__(256) k_gemm_pair(GemmArgs tn, GemmArgs nt, int n1) {
-  __shared__ GemmLds<64, 128> L;
+  __shared__ GemmLds<64, 128, 1> L;
   const int b = blockIdx.x;
   if (b < n1) {
     const int w = (tn.N + 63) / 64;
-    gemm_tile<1, 0, 64, 128>(L, b % w, b / w, tn.M, tn.N, tn.K, tn.A, tn.lda, tn.B, tn.ldb, tn.ep);
+    gemm_tile<1, 0, 64, 128, 1>(L, b % w, b / w, tn.M, tn.N, tn.K, tn.A, tn.lda, tn.B, tn.ldb, tn.ep);
   } else {
     const int w = (nt.N + 63) / 64;
-    gemm_tile<0, 1, 64, 128>(L, (b - n1) % w, (b - n1) / w, nt.M, nt.N, nt.K, nt.A, nt.lda, nt.B, nt.ldb, nt.ep);
+    gemm_tile<0, 1, 64, 128, 1>(L, (b - n1) % w, (b - n1) / w, nt.M, nt.N, nt.K, nt.A, nt.lda, nt.B, nt.ldb, nt.ep);
   }
 }
 
 constexpr size_t kGemmFill = 256;   // blocks: one a CU
 
 // The tile: 128 x 128 (a fragment feeds two MFMAs, half the LDS reads a flop)
-// where those tiles give every CU a block, 64 x 64 below that.
+// where those tiles give every CU a block, 64 x 64 below that.  Its flat form
+// up to 512 k's (A B^T, 65,536 x 256: 512 k's 37.2 us against 40.2, 2,048 k's
+// 118 against 109; A B at 512 and 1,024 k's 45.2 against 50.0 and 72.0 against
+// 70.9), up to 128 where A is transposed and staging costs more (27.1 against
+// 27.0 at 128, 36.7 against 33.9 at 256).
 template <int TA, int TB>
 static void launch_gemm(int M, int N, int K, const __bf16* a, int lda, const __bf16* b, int ldb, const GemmEpi& ep,
                         hipStream_t st) {
   auto tiles = [&](int t) { return dim3((N + t - 1) / t, (M + t - 1) / t); };
   const dim3 big = tiles(128);
-  if ((size_t)big.x * big.y >= kGemmFill)
-    hipLaunchKernelGGL((k_gemm<TA, TB, 128, 64>), big, dim3(256), 0, st, M, N, K, a, lda, b, ldb, ep);
+  if ((size_t)big.x * big.y < kGemmFill)
+    hipLaunchKernelGGL((k_gemm<TA, TB, 64, 128, 1>), tiles(64), dim3(256), 0, st, M, N, K, a, lda, b, ldb, ep);
+  else if (K <= (TA ? 128 : 512))
+    hipLaunchKernelGGL((k_gemm<TA, TB, 128, 64, 0>), big, dim3(256), 0, st, M, N, K, a, lda, b, ldb, ep);
   else
-    hipLaunchKernelGGL((k_gemm<TA, TB, 64, 128>), tiles(64), dim3(256), 0, st, M, N, K, a, lda, b, ldb, ep);
+    hipLaunchKernelGGL((k_gemm<TA, TB, 128, 64, 1>), big, dim3(256), 0, st, M, N, K, a, lda, b, ldb, ep);
 }
 
 // dst[c][r] = src[r][c] for a rows x cols bf16 matrix (32 x 32 tiles through LDS)
