@@ -316,12 +316,15 @@ struct ViewPlan {
   }
   // What it adds (its areas have room for every individual, since the examples
   // may be any by the time of a launch; less the rows that stand for full ones)
-  // would more than double the workspace, `need` with it, and by more than a
-  // gigabyte.  4,096 hypotheses over 1M individuals, 266M assertions: 4.5 GB
-  // with it, 2.6 without; 16,384 over 32M 23.5 and 16.7.
+  // is out of proportion: over a gigabyte, and over 128 times the rest of the
+  // workspace (need holds both).  Below that the caller chooses: a workspace
+  // without the room is served without the view.  Half a round over 32M
+  // individuals, 71 directions: 11.4 GB beside 0.4, rounds of 25.1, 24.3 and
+  // 25.9 ms with it, 28.2, 27.3 and 30.9 without; 4,096 hypotheses over 1M
+  // individuals, 266M assertions: 1.9 GB beside 2.6.
   bool too_large(const hth_kb_s& kb, size_t need) const {
     const size_t added = bytes - (size_t)(n_rows - n_copies) * kb.S * 8;
-    return on && added > (need - added) + (1ull << 30);
+    return on && added > (1ull << 30) && added / 128 > need - added;
   }
   uint32_t tiles(const hth_kb_s& kb) const { return (kb.W + kExTile - 1) / kExTile; }
   uint32_t dir_tiles(const hth_kb_s& kb) const { return (kb.N + kVDirTile - 1) / kVDirTile; }

@@ -147,3 +147,33 @@ def test_view_that_would_double_a_large_workspace(monkeypatch):
     np.testing.assert_array_equal(eng.eval_batch_device(hyps), want)
     np.testing.assert_array_equal(eng.eval_batch(hyps), want)
     eng.close()
+
+
+def test_view_beside_a_small_plan_is_kept(monkeypatch):
+    """The same directions under restrictions of their own, whose rows are a sixtieth of
+    what the view adds: its room is asked for, and less is served without it."""
+    import torch
+    n, roles = 2_000_003, 80
+    kb = synth.kb_from_edges(n, [np.arange(0, n, 3), np.arange(0, n, 7)], [[] for _ in range(roles)], pos=range(0, 4000, 2), neg=range(1, 4000, 2))
+    off = np.zeros((roles, n + 1), np.int64)
+    off[:, 9:] = 2
+    kb.role_offsets = off + 2 * np.arange(roles)[:, None]
+    kb.role_targets = np.tile(np.array([3, 8], np.int32), roles)      # subject 8 reaches itself
+    hyps = [("exists", r, inv, ("exists", r, 0, ("atom", 0))) for r in range(roles) for inv in (0, 1)]
+    eng = hthedl.Engine(kb, max_hyps=len(hyps))
+    # 8 (positive) reaches 3, of atom 0, so it holds the inner restriction; then 8 itself, and 3 (negative) over the inverse
+    want = np.zeros((len(hyps), 2), np.uint32)
+    want[:, 0] = 1
+    want[1::2, 1] = 1
+    nodes, offs, ch = eng.upload_batch(hyps)
+    eng.ensure_plan_scratch(nodes.shape[0] // 16)
+    plan, nb = hthedl.hth_dplan_create(eng.handle, nodes, nodes.shape[0] // 16, offs, len(hyps), ch, ch.shape[0], eng.dp_scratch,
+                                       eng.dp_scratch_bytes)
+    assert nb > 1 << 30
+    for room in (nb, 1 << 29):
+        ws, out = torch.empty(room, dtype=torch.uint8, device="cuda"), counts(torch, len(hyps))
+        hthedl.hth_dplan_launch(plan, ws, room, out)
+        np.testing.assert_array_equal(out.cpu().numpy().view(np.uint32), want)
+    hthedl.hth_dplan_destroy(plan)
+    np.testing.assert_array_equal(eng.eval_batch(hyps), want)
+    eng.close()
