@@ -252,14 +252,14 @@ struct Stage {
 // Bound by the LDS reads and the barrier of a k-tile.  Against one 128 x 128 x 64
 // tile per block with one k-tile of loads ahead (forward) and 128 x 128 x 32
 // with the transpose as 2-byte LDS stores (weight gradients): 1024 x 1024 x 4096
-// forward 25.6 us (was 54), 4096 x 1024 x 1024 gradient 27.8 us (was 82),
+// forward 24.9 us (was 54), 4096 x 1024 x 1024 gradient 25.6 us (was 82),
 // 1024 x 256 x 1024 gradient 12.3 us (was 77).
 //
 // DEEP = 0, for short k: one k-tile of loads ahead and one LDS buffer, so that
 // three blocks fit a CU and the stores of C, which bound it there, run beside
 // other blocks' products.  With DEEP = 1 the registers are held to two blocks a
-// CU; left to the compiler they were more than 256, one block a CU (65,536 x 1024 x
-// 64: 121 us; two deep blocks a CU 78, three flat ones 55).
+// CU; left to the compiler they were more than 256, one block a CU (65,536 x
+// 1024 x 64: 121 us; two deep blocks a CU 78, three flat ones 55).
 template <int T, int BK, int DEEP>
 struct GemmLds {
   __bf16 a[1 + DEEP][T][BK + 8], b[1 + DEEP][T][BK + 8];
@@ -593,8 +593,8 @@ __global__ void k_head_score(const float* __restrict__ z, int Bn, float n_pos, f
 // ahead; (3) the output layer and the F1.  Two blocks
 // share a CU, so one's loads overlap the other's products.
 // Bound by the latency of the lists and of the W1 rows (2 KB each, most from
-// L2).  262,157 rows: 541 us, where features apart the chain of densify, GEMMs, head and score
-// took 5.2 ms (33 batches of 8,192).
+// L2).  262,157 rows: 489 us, where features apart the chain of densify, GEMMs,
+// head and score took 5.2 ms (33 batches of 8,192).
 constexpr int kScoreRows = 32, kScoreWaves = 8, kScoreH1 = 1024, kScoreLd = kScoreH1 + 8;
 struct ScoreArgs {
   const uint16_t *feat, *pfeat;
