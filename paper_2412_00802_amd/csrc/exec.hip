@@ -157,7 +157,7 @@ __device__ __forceinline__ bool num_pass(float v, uint32_t cmp, float t) {
 // subjects, as in the role pass.  The wave walks the subjects' concatenated
 // values in chunks of 64 (eight chunks' loads in flight), a subject's passing
 // values are the difference of two prefix counts (ChunkSums), and the walk
-// stops once every subject with values left has found one.  Up to kValPerPass
+// stops once every subject with values left has found one.  Up to value_tasks()
 // tasks of one role share a walk, and a round has as many chunks as the values
 // left need (2, 4 or 8).  Rows above the heavy-row threshold are left to
 // value_heavy (their bits here are 0).  About 60 restrictions on 4 roles over
@@ -1259,6 +1259,15 @@ hth_status launch_fills(Launcher& L, const DevKB& d, const FillTask* tasks, size
   });
 }
 
+// Tasks that share a walk of a value role's values, of `tasks` in all: one while
+// all of them are at most 2^17 words, as many more as that is exceeded.  Below,
+// the chip has room for a walk each, and a shared walk is a chain of its tasks.
+// 40 numeric tasks of one role, 1 / 2 / 4 / 8 / 16 a walk, us: 5,000 individuals
+// 24.7 / 25.9 / 28.9 / 35.0 / 47.7, 65,537 34.8 / 35.6 / 38.4 / 44.7 / 46.3; 160 tasks:
+// 200,003 207.7 / 203.2 / 203.3 / 206.5 / 216.7, 1M 684 / 657 / 641 / 641 / 648.
+inline uint32_t value_tasks(const hth_kb_s& kb, size_t tasks) {
+  return (uint32_t)std::min<uint64_t>(kValPerPass, ((uint64_t)tasks * kb.W >> 17) + 1);
+}
 inline uint32_t value_blocks(const hth_kb_s& kb, uint32_t n) {
   return std::max<uint32_t>(1, std::min<uint32_t>((kb.W + 7) / 8, (32 * kb.n_cu + n - 1) / n));
 }
@@ -1731,12 +1740,13 @@ void prepare(const hth_kb_s& kb, Plan&& plan, uint32_t n_hyps, Prepared& X) {
     X.o_vbase = X.blob.add(bases);
     X.o_vcopy = X.blob.add(copies);
   }
-  // tasks of one role share a walk of its values, up to kValPerPass at a time
-  auto by_role = [](auto& tasks, auto from) {
+  // tasks of one role share a walk of its values, up to per_walk at a time
+  auto by_role = [&](auto& tasks, auto from) {
     std::stable_sort(tasks.begin() + from, tasks.end(), [](const auto& a, const auto& b) { return a.role < b.role; });
+    const uint32_t per_walk = value_tasks(kb, tasks.size());
     std::vector<ThrGroup> out;
     for (uint32_t i = 0; i < tasks.size(); ++i) {
-      if (out.empty() || out.back().prop != tasks[i].role || out.back().n == kValPerPass)
+      if (out.empty() || out.back().prop != tasks[i].role || out.back().n == per_walk)
         out.push_back(ThrGroup{tasks[i].role, i, 0, 0});
       out.back().n++;
     }
