@@ -1259,14 +1259,16 @@ hth_status launch_fills(Launcher& L, const DevKB& d, const FillTask* tasks, size
   });
 }
 
-// Tasks that share a walk of a value role's values, of `tasks` in all: one while
-// all of them are at most 2^17 words, as many more as that is exceeded.  Below,
-// the chip has room for a walk each, and a shared walk is a chain of its tasks.
-// 40 numeric tasks of one role, 1 / 2 / 4 / 8 / 16 a walk, us: 5,000 individuals
-// 24.7 / 25.9 / 28.9 / 35.0 / 47.7, 65,537 34.8 / 35.6 / 38.4 / 44.7 / 46.3; 160 tasks:
-// 200,003 207.7 / 203.2 / 203.3 / 206.5 / 216.7, 1M 684 / 657 / 641 / 641 / 648.
+// Tasks that share a walk of a value role's values, of `tasks` in all: one up to
+// 2^14 words of results, and in proportion beyond.  Few words leave the chip
+// room for a walk each, where a shared walk is a chain of its tasks; many fill
+// it, and a walk of its own is another read of the values.  Batches, 1 / 2 / 4 /
+// 8 / 16 a walk, us (words): 5,000 individuals 24.7 / 25.9 / 28.9 / 35.0 / 47.7
+// (3,160), 131,073 29.2 / 27.7 / 29.6 / 35.4 / 35.4 (31,000), 262,145 41.6 / 36.9 /
+// 36.3 / 41.1 / 40.7 (61,000), 524,289 63.3 / 57.9 / 53.9 / 52.2 / 52.9 (123,000),
+// 1M 91.1 / 81.0 / 75.9 / 73.7 / 73.4 (234,000).
 inline uint32_t value_tasks(const hth_kb_s& kb, size_t tasks) {
-  return (uint32_t)std::min<uint64_t>(kValPerPass, ((uint64_t)tasks * kb.W >> 17) + 1);
+  return (uint32_t)std::min<uint64_t>(kValPerPass, std::max<uint64_t>(1, ((uint64_t)tasks * kb.W + (1u << 13)) >> 14));
 }
 inline uint32_t value_blocks(const hth_kb_s& kb, uint32_t n) {
   return std::max<uint32_t>(1, std::min<uint32_t>((kb.W + 7) / 8, (32 * kb.n_cu + n - 1) / n));
