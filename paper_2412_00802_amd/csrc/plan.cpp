@@ -619,6 +619,13 @@ struct Compiler {
     // (a wave takes an example's row: long rows, whose values many blocks
     // share, stay with the passes over every individual)
     auto no_heavy = [](const std::vector<uint32_t>& first, uint32_t i) { return first[i] == first[i + 1]; };
+    // value roles of a batch (see values_at_examples)
+    bool values_ex = opt.examples;
+    if (opt.view) {
+      uint64_t n = 0;
+      for (uint32_t v = 0; v < nv; ++v) n += live[v] && !deep[v] && (is_numeric(dag.nodes[v].op) || is_string(dag.nodes[v].op));
+      values_ex = values_at_examples(kb, n);
+    }
     std::vector<uint8_t> covered_by_pass(roots.size(), 0);
     int32_t max_level = -1;
     for (uint32_t v = 0; v < nv; ++v) {
@@ -646,7 +653,7 @@ struct Compiler {
         t.cmp = n.op == HTH_NUM_GE ? 0 : n.op == HTH_NUM_LE ? 1 : 2;
         std::memcpy(&t.t, &n.q, 4);
         t.out_row = row[v];
-        (!deep[v] && no_heavy(reg.num_chunk_first, n.arg) ? P.ex_num : P.num).push_back(t);
+        (values_ex && !deep[v] && no_heavy(reg.num_chunk_first, n.arg) ? P.ex_num : P.num).push_back(t);
         copied(v);
       } else if (is_string(n.op)) {
         row[v] = new_row();
@@ -655,7 +662,7 @@ struct Compiler {
         t.kind = n.op == HTH_STR_CONTAINS ? 1 : 0;
         std::memcpy(&t.q, &n.q, 4);
         t.out_row = row[v];
-        (!deep[v] && no_heavy(reg.str_chunk_first, n.arg) ? P.ex_str : P.str).push_back(t);
+        (values_ex && !deep[v] && no_heavy(reg.str_chunk_first, n.arg) ? P.ex_str : P.str).push_back(t);
         copied(v);
       } else if (is_role(n.op) && hit_row[v] == kNone) {
         if (view && viewable(v)) {

@@ -50,6 +50,18 @@ struct PlanOptions {
 // 1,253, 32 1,582 / 1,301 / 1,526.
 inline uint64_t view_nodes(const hth_kb_s& kb) { return 16 + 16ull * kb.view_min / std::max(1u, kb.ex_hint); }
 
+// Whether a batch takes its n value-role restrictions that no filler reads at
+// the examples: an eighth of the individuals at most, and, below 2^19 of them,
+// enough restrictions that one more launch beside the fillers' is worth it.
+// Microseconds at the examples / over everyone: 6 % of 65,537, 4 numeric 21.3 /
+// 15.3, 8 string 32.4 / 23.4, 40 numeric roots 15.0 / 20.1; of 131,073, 8 string
+// 33.3 / 27.4, 8 numeric roots 12.3 / 13.4; of 262,145, 4 roots 12.8 / 13.1, 8 13.0 /
+// 19.2; of 524,289, 4 13.2 / 19.0; of 1M, one 12.1 / 12.6; 24 %, 40 roots: of 65,537
+// 23.9 / 20.0, of 1M 150.6 / 130.9.
+inline bool values_at_examples(const hth_kb_s& kb, uint64_t n) {
+  return (uint64_t)kb.ex_hint * 8 <= kb.N && (kb.N >= 1u << 19 || n * kb.N > 3ull << 19);
+}
+
 struct PlanLevel {
   std::vector<RegionTask> mat;      // children materialised before this level's role passes
   std::vector<RoleTask> roles;      // single role nodes (k = 1)

@@ -1,5 +1,5 @@
-"""Value-role restrictions that share a walk of a role's values, one, two, three
-and sixteen a walk with a remainder, against sets taken from the values
+"""Value-role restrictions that share a walk of a role's values, from one to sixteen
+a walk and with a remainder, against sets taken from the values
 themselves; and a time that walks of sixteen over few individuals could not
 reach."""
 import numpy as np
@@ -34,7 +34,7 @@ def want(n, off, ok):
     return [int((x % 2 == 0).sum()), int((x % 2 == 1).sum())]
 
 
-@pytest.mark.parametrize("n,tasks", [(65, 1), (4097, 40), (524289, 15), (524289, 16), (524289, 33), (524289, 100)])
+@pytest.mark.parametrize("n,tasks", [(65, 1), (4097, 40), (20001, 100), (524289, 15), (524289, 16), (524289, 33), (524289, 100)])
 def test_shared_walks(torch, n, tasks):
     kb, off, v = value_kb(n)
     eng = hthedl.Engine(kb, max_hyps=256)
@@ -65,3 +65,48 @@ def test_few_individuals_take_a_walk_each(torch):
     hthedl.hth_plan_destroy(plan)
     eng.close()
     assert best < 20, best
+
+
+@pytest.mark.parametrize("n,tasks,every", [(65537, 8, 16), (65537, 40, 16), (262145, 5, 8), (262145, 6, 8), (262145, 7, 7),
+                                           (524287, 2, 9), (524288, 1, 8), (524289, 3, 7)])
+def test_few_restrictions_at_the_examples_or_over_everyone(torch, n, tasks, every):
+    """Both sides of the rule's lines (an eighth of the individuals, 2^19 of them, their
+    product with the restrictions), also below a role restriction."""
+    kb, off, v = value_kb(n)
+    pos, neg = np.arange(0, n, 2 * every), np.arange(every, n, 2 * every)
+    kb.pos_bits[:], kb.neg_bits[:] = synth.ids_to_bits(pos, n), synth.ids_to_bits(neg, n)
+    eng = hthedl.Engine(kb, max_hyps=128)
+    hyps = [("nge", 0, float(100 - i)) for i in range(tasks)] + [("sequal", 0, b"w%02d" % i) for i in range(tasks)]
+    hyps += [("exists", 0, 0, ("nge", 0, 50.0)), ("not", ("exists", 0, 0, ("sequal", 0, b"w07")))]
+    exp = []
+    for ok in [v >= 100 - i for i in range(tasks)] + [v == i for i in range(tasks)]:
+        x = np.unique(np.repeat(np.arange(n), np.diff(off))[ok])
+        exp.append([np.isin(pos, x).sum(), np.isin(neg, x).sum()])
+    exp += [[0, 0], [len(pos), len(neg)]]      # the role has no assertions
+    np.testing.assert_array_equal(eng.eval_batch(hyps), np.array(exp, np.uint32))
+    eng.close()
+
+
+def test_few_strings_of_many_examples_take_one_launch(torch):
+    """Eight string hypotheses, some below a role, where a quarter of 65,537 individuals
+    are examples: 26 us, 40 with the others at the examples."""
+    n = 65537
+    kb = synth.make_kb(synth.small_config(seed_index=900, n=n, n_concepts=10, n_roles=4, cap=30, n_pos=n // 9, n_neg=n // 9))
+    kb = synth.with_string_roles(kb, *synth.string_roles(n, 2, 6))
+    eng = hthedl.Engine(kb, max_hyps=64)
+    enc = hthedl.encode_batch([eng.intern(h) for h in synth.make_string_hypotheses(kb, 8, 3)])
+    plan, nb = hthedl.hth_plan_create(eng.handle, *enc)
+    ws, out = torch.empty(max(nb, 256), dtype=torch.uint8, device="cuda"), torch.empty((8, 2), dtype=torch.int32, device="cuda")
+    hthedl.hth_plan_upload(plan, ws, ws.numel())
+    best = 1e9
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(20):
+            hthedl.hth_plan_launch(plan, ws, ws.numel(), out)
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 50)
+    hthedl.hth_plan_destroy(plan)
+    eng.close()
+    assert best < 33, best
