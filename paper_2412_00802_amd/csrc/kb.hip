@@ -312,7 +312,7 @@ k_load_check(const uint32_t* __restrict__ fwd_off, const int32_t* __restrict__ t
 
 // A bucket that most of a role points into is counted and placed by slices of
 // its pairs, a block each: k_load_big<false> adds a slice's counts to the
-// objects' inverse offsets (cleared by k_load_part), k_load_bucket turns them
+// objects' inverse offsets (cleared by k_load_part, which sets flags[3]), k_load_bucket turns them
 // into each object's end, and k_load_big<true> takes a slice's places off them,
 // which leaves the starts.  32M assertions to 5,000 objects: a load of 1.7 ms,
 // 17.5 with one block for the bucket; to 64 objects 1.2 and 63.  The line: a
@@ -335,7 +335,7 @@ __device__ __forceinline__ bool big_bucket(const uint32_t* __restrict__ bb, uint
 __global__ void __launch_bounds__(kPartThreads)
 k_load_part(const uint32_t* __restrict__ fwd_off, const int32_t* __restrict__ tg, const uint64_t* __restrict__ base,
             uint32_t N, uint32_t nb, uint32_t shift, const uint32_t* __restrict__ bbase, uint32_t* __restrict__ bcur,
-            uint2* __restrict__ pairs, uint32_t* __restrict__ inv_off, const uint32_t* __restrict__ flags) {
+            uint2* __restrict__ pairs, uint32_t* __restrict__ inv_off, uint32_t* __restrict__ flags) {
   constexpr uint32_t kOwn = kPartEdges / kPartThreads;
   extern __shared__ uint2 s_pair[];                       // [kPartEdges]
   uint32_t* s_row = reinterpret_cast<uint32_t*>(s_pair);  // before the pairs: [kPartEdges] row marks
@@ -418,6 +418,7 @@ k_load_part(const uint32_t* __restrict__ fwd_off, const int32_t* __restrict__ tg
   for (uint32_t b = tid; b < nb; b += kPartThreads) {
     uint32_t i0, i1;
     if (!big_bucket(bbase + (size_t)r * nb, nb, n, b, i0, i1)) continue;
+    flags[3] = 1;
     const uint64_t yend = min((uint64_t)(b + 1) << shift, (uint64_t)N);
     for (uint64_t y = (uint64_t)b << shift; y < yend; ++y) io[y] = 0;
   }
@@ -430,7 +431,7 @@ k_load_big(const uint2* __restrict__ pairs, const uint64_t* __restrict__ base, u
            uint32_t* __restrict__ inv_off, int32_t* __restrict__ inv_tg, const uint32_t* __restrict__ flags) {
   extern __shared__ uint32_t s_dyn[];      // [range]
   __shared__ uint32_t s_end[2];
-  if (*flags) return;
+  if (flags[0] || !flags[3]) return;
   const uint32_t r = blockIdx.y, tid = threadIdx.x, n = fwd_off[(size_t)r * (N + 1) + N];
   const uint64_t s0l = (uint64_t)blockIdx.x * kBigSlice;
   if (s0l >= n) return;
@@ -788,7 +789,7 @@ static hth_status kb_build(hth_kb_s* kb, char* derived, hipStream_t st) {
   uint32_t* tsum = reinterpret_cast<uint32_t*>(derived + L.tsum);
   uint64_t* base = reinterpret_cast<uint64_t*>(derived + L.base);
   uint32_t* meta = reinterpret_cast<uint32_t*>(derived + L.meta);
-  uint32_t* flags = meta;              // meta: flags, heavy rows, examples, -, then
+  uint32_t* flags = meta;              // meta: flags, heavy rows, examples, whether a bucket is big, then
   uint32_t* maxdeg = meta + 4;         // [2][R] largest degrees
   uint32_t* nwords = meta + 4 + 2 * R; // [R][2] non-empty words
   uint32_t* nobj = meta + 4 + 4 * R;   // [R][2] objects
