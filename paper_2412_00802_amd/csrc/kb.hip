@@ -316,7 +316,8 @@ k_load_check(const uint32_t* __restrict__ fwd_off, const int32_t* __restrict__ t
 // into each object's end, and k_load_big<true> takes a slice's places off them,
 // which leaves the starts.  32M assertions to 5,000 objects: a load of 1.7 ms,
 // 17.5 with one block for the bucket; to 64 objects 1.2 and 63.  The line: a
-// bucket of that size takes its one block 0.14 ms, two launches 8 us.
+// bucket of that size takes its one block 0.14 ms, the two launches 5 us where
+// none is that large.
 constexpr uint32_t kBigSlice = 65536, kBigBucket = 4 * kBigSlice;
 __device__ __forceinline__ bool big_bucket(const uint32_t* __restrict__ bb, uint32_t nb, uint32_t n, uint32_t b,
                                            uint32_t& i0, uint32_t& i1) {
